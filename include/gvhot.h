@@ -58,11 +58,13 @@ enum { GV_VERTEX = 0, GV_CONTEXT = 1 };
  *                is ever lost, reads may be slightly stale.
  *   MIXED        ATOMIC_AGENT for rows likely to be shared by concurrent samples,
  *                AGENT stores for the rest (tiled schedule only; otherwise it
- *                behaves as ATOMIC_AGENT).                                            */
+ *                behaves as ATOMIC_AGENT).  Pools so short that atomic adds keep up
+ *                with the launch use them for all rows.                               */
 enum { GV_COHERENCE_PLAIN = 0, GV_COHERENCE_AGENT = 1, GV_COHERENCE_ATOMIC_AGENT = 2, GV_COHERENCE_MIXED = 3 };
 /* Order in which an asynchronous launch walks a pool.
  *   POOL_ORDER   waves take chunks of 64 consecutive samples.
- *   TILED        workgroups take tiles of 8192 consecutive samples and sort each tile
+ *   TILED        workgroups take tiles of 8192 consecutive samples (fewer where the pool
+ *                would not fill the chip, or the graph is small) and sort each tile
  *                by the hottest row of every sample (the highest-degree one of u, v and
  *                the negatives); a wave keeps that row in registers across the run of
  *                samples sharing it, trading its change with memory every four samples
@@ -71,7 +73,9 @@ enum { GV_COHERENCE_PLAIN = 0, GV_COHERENCE_AGENT = 1, GV_COHERENCE_ATOMIC_AGENT
  *                of its position in the pool.
  *   AUTO         TILED when the graph has rows that concurrent samples are likely to share
  *                (decided by gv_build_alias from the degrees), POOL_ORDER otherwise: on a
- *                graph without such rows the tile bookkeeping buys nothing.  With
+ *                graph without such rows the tile bookkeeping buys nothing.  A pool that
+ *                is short, or of a graph so small that atomic adds are used for all rows,
+ *                is walked in pool order where that is faster than tiles.  With
  *                GV_COHERENCE_MIXED the pool-order launch then uses AGENT stores (all rows
  *                are cold).                                                            */
 enum { GV_SCHEDULE_POOL_ORDER = 0, GV_SCHEDULE_TILED = 1, GV_SCHEDULE_AUTO = 2 };
@@ -119,7 +123,8 @@ typedef struct gv_stats {
     uint64_t timed_launches;    /* launches contributing to train_kernel_ms                    */
     double h2d_ms;              /* event-timed pool copies host -> device (profile != 0)        */
     uint64_t h2d_bytes;
-    uint64_t tiled_launches;    /* asynchronous launches that took the tiled schedule            */
+    uint64_t tiled_launches;    /* asynchronous launches under the tiled schedule (short pools that
+                                   GV_SCHEDULE_AUTO walks in pool order for speed among them)    */
     uint64_t warm_rows;         /* rows that gv_build_alias classed as warm (see GV_SCHEDULE_AUTO) */
     double train_loss_sum;      /* track_loss != 0: sum over the samples trained so far of the loss (Alg. 1 with
                                    the logistic loss of negative sampling, as gv_eval_loss) each of them saw
@@ -348,7 +353,7 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
 
 /* Wait for all queued device work of the context; folds event timings into the
  * statistics; reports samples that named an id >= n (GV_EINVAL, once), and training that has
- * diverged: an embedding row holding NaN met by an asynchronous tiled launch (GV_ESTATE, once).
+ * diverged: an embedding row holding NaN met by an asynchronous launch under the tiled schedule (GV_ESTATE, once).
  * (Housekeeping, no passage.)                                                   */
 int gv_sync(gv_ctx *ctx);
 /* Counters of the context so far.  (Diagnostic hook, no passage.)               */

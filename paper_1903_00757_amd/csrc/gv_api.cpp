@@ -67,6 +67,7 @@ struct gv_ctx {
     uint16_t *dev_rank = nullptr;         // device, per node: hot rank (see gv::TrainArgs)
     uint32_t *dev_ranked = nullptr;       // device, bitmap of the nodes that have a hot rank
     uint32_t warm_ranks = 0;              // number of warm rows
+    double hottest_share = 0.0;           // share of the samples that name the hottest context row
     // orthogonal blocks (cfg.partitions > 0): partition of every node, and one alias table per partition
     std::vector<uint32_t> part;           // host, per node
     std::vector<uint64_t> part_offsets;   // host, partitions + 1: partition j owns table buckets [j] .. [j + 1] - 1
@@ -356,6 +357,9 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
     uint32_t coherence = ctx->cfg.coherence;
     if (!tiled && ctx->cfg.schedule == GV_SCHEDULE_AUTO && coherence == GV_COHERENCE_MIXED && ctx->warm_ranks == 0)
         coherence = GV_COHERENCE_AGENT;
+    const gv::AsyncPlan plan = gv::async_plan(gv::AsyncPool{count, ctx->n, ctx->cfg.dim, ctx->cfg.num_neg, coherence, tiled,
+                                                            ctx->cfg.schedule == GV_SCHEDULE_AUTO, block != nullptr,
+                                                            ctx->warm_ranks, ctx->hottest_share});
     if (tiled && fixed_records) {
         const uint64_t words = count * (ctx->cfg.num_neg + 3);
         if (words > GV_STATIC_SCRATCH_WORDS)
@@ -363,7 +367,7 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
                         "(at most %llu samples at K = %u)", (unsigned long long)count, (unsigned long long)words,
                         (unsigned long long)GV_STATIC_SCRATCH_WORDS,
                         (unsigned long long)(GV_STATIC_SCRATCH_WORDS / (ctx->cfg.num_neg + 3)), ctx->cfg.num_neg);
-    } else if (tiled) {  // before the timed span: an allocation must not count as kernel time
+    } else if (plan.tiled) {  // before the timed span: an allocation must not count as kernel time
         int rc = ensure_records(ctx, count * (ctx->cfg.num_neg + 3));
         if (rc) return rc;
     }
@@ -379,13 +383,16 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
         a.alias = ctx->dev_part_tables + ctx->part_offsets[block->partition];
         a.alias_n = (uint32_t)(ctx->part_offsets[block->partition + 1] - ctx->part_offsets[block->partition]);
     }
-    if (tiled) {
+    a.unit = plan.unit;
+    a.blocks = plan.blocks;
+    a.report_divergence = tiled ? 1u : 0u;
+    if (plan.tiled) {
         a.records = fixed_records ? fixed_records : ctx->records;
         GV_HIP(ctx, (a.loss_slots ? gv::launch_train_tiled_tracked : gv::launch_train_tiled)(
-                        a, ctx->cfg.dim, ctx->cfg.num_neg, coherence, ctx->compute));
+                        a, ctx->cfg.dim, ctx->cfg.num_neg, plan.coherence, ctx->compute));
     } else {
         GV_HIP(ctx, (a.loss_slots ? gv::launch_train_hogwild_tracked : gv::launch_train_hogwild)(
-                        a, ctx->cfg.dim, ctx->cfg.num_neg, coherence, ctx->compute));
+                        a, ctx->cfg.dim, ctx->cfg.num_neg, plan.coherence, ctx->compute));
     }
     ctx->stats.train_launches += 1;
     ctx->stats.tiled_launches += tiled ? 1 : 0;
@@ -792,12 +799,14 @@ int gv_build_alias(gv_ctx *ctx, double power) {
         std::vector<uint16_t> rank(n, (uint16_t)kRanked);
         std::vector<uint32_t> ranked_bits(((size_t)n + 31) / 32, 0u);
         uint32_t warm_ranks = 0;
+        double hottest_share = 0.0;
         for (uint32_t r = 0; r < ranked; ++r) {
             const uint32_t i = order[r];
             rank[i] = (uint16_t)r;
             ranked_bits[i >> 5] |= 1u << (i & 31u);
             const double share = (degree_sum > 0.0 ? degree_of(i) / degree_sum : 0.0) + (double)ctx->cfg.num_neg * q[i] / sum;
             if (share * kInFlight > kWarmThreshold) warm_ranks = r + 1;
+            hottest_share = std::max(hottest_share, share);
         }
         std::vector<uint4> table(n);
         for (uint32_t i = 0; i < n; ++i)  // ranks of both candidates and the bucket's node save the kernel gathers
@@ -867,6 +876,7 @@ int gv_build_alias(gv_ctx *ctx, double power) {
             ctx->part_alias = std::move(part_alias);
         }
         ctx->warm_ranks = warm_ranks;
+        ctx->hottest_share = hottest_share;
         ctx->stats.warm_rows = warm_ranks;
         ctx->alias_ready = true;
         return GV_OK;

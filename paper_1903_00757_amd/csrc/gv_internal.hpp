@@ -37,6 +37,8 @@ struct TrainArgs {
     uint64_t total;           // T of the learning-rate schedule
     uint64_t seed;            // Philox key of the negative stream
     uint32_t count;           // samples in this launch
+    uint32_t unit, blocks;    // asynchronous launches: see AsyncPlan
+    uint32_t report_divergence; // pool order: nonzero: a score that is NaN sets error_flag[1]
     uint32_t n;               // |V|
     uint32_t dim;             // d: row length in floats
     float lr0, lr_min_ratio, neg_weight;
@@ -44,7 +46,26 @@ struct TrainArgs {
 
 constexpr uint32_t kLossSlots = 64;
 
-// Launch shapes are chosen here; both return the HIP error of the launch.
+// Shape of an asynchronous launch.
+struct AsyncPool {
+    uint64_t count;           // samples
+    uint32_t n, dim, num_neg;
+    uint32_t coherence;
+    bool tiled;               // the tiled schedule applies
+    bool may_skip_tiles;      // ... and a pool that gains nothing from tiles may be walked in pool order (GV_SCHEDULE_AUTO)
+    bool part_of_pool;        // one block of a partitioned graph
+    uint32_t warm_ranks;
+    double hottest_share;     // share of the samples that name the hottest context row
+};
+struct AsyncPlan {
+    bool tiled;               // k_train_tiled, otherwise k_train_hogwild
+    uint32_t coherence;
+    uint32_t unit;            // samples of a tile, or samples a wave takes at a time
+    uint32_t blocks;          // workgroups
+};
+AsyncPlan async_plan(const AsyncPool &pool);
+
+// The launches take their shape from a.unit and a.blocks; all return the HIP error of the launch.
 hipError_t launch_train_hogwild(const TrainArgs &a, uint32_t dim, uint32_t num_neg, uint32_t coherence,
                                 hipStream_t stream);
 // Tiled stationary-row training (see k_train_tiled).

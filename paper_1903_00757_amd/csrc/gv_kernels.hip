@@ -10,6 +10,10 @@
 // nothing but the training kernels that also sum the running loss, under names ending in _tracked.
 #include "gv_internal.hpp"
 
+#include <math.h>
+
+#include <algorithm>
+
 #ifndef GV_TRACK_LOSS
 #define GV_TRACK_LOSS 0
 #endif
@@ -251,14 +255,30 @@ __device__ __forceinline__ float sigmoid(float z) { return 1.0f / (1.0f + __expf
 
 // Running training loss (kernels instantiated with kTrack only): -log sigmoid(z) = log(1 + e^-z) for either
 // sign of z; a positive's score s contributes minus_log_sigmoid(s), a negative's w * minus_log_sigmoid(-s).
-// A wave sums what its samples saw in fp32 and hands the sum over every so often as one fp64 atomic add
-// (the values are wave-uniform: lane 0 adds).
+// The scores of a chunk are laid into lanes as the wave walks it (one selection each) and the logarithms are
+// taken once per chunk, lane l for sample l: taken sample by sample, the same number on all 64 lanes, they were a
+// third of the walk (2048 samples of a wave at d = 96, K = 3: 5.0 ms with, 3.4 ms without the running loss).
+// Lanes sum in fp32; a wave hands the sum of its lanes over every so often as one fp64 atomic add.
 __device__ __forceinline__ float minus_log_sigmoid(float z) { return fmaxf(-z, 0.0f) + log1pf(__expf(-fabsf(z))); }
-__device__ __forceinline__ void hand_over_loss(double *slots, float &loss, int lane) {
+template <int kK>
+struct ChunkScores {
+    float of[kK + 1];  // lane l: the scores of sample l of the chunk
+    __device__ __forceinline__ void put(int k, uint32_t i, float score) {
+        of[k] = (threadIdx.x & (kWave - 1)) == i ? score : of[k];
+    }
+    __device__ __forceinline__ float loss(float w) const {
+        float sum = minus_log_sigmoid(of[0]);
+#pragma unroll
+        for (int k = 1; k <= kK; ++k) sum += w * minus_log_sigmoid(-of[k]);
+        return sum;
+    }
+};
+__device__ __forceinline__ void hand_over_loss(double *slots, float &lane_loss, int lane) {
+    const float total = wave_sum(lane_loss);
     if (lane == 0)
-        (void)__hip_atomic_fetch_add(slots + (blockIdx.x % kLossSlots), (double)loss, __ATOMIC_RELAXED,
+        (void)__hip_atomic_fetch_add(slots + (blockIdx.x % kLossSlots), (double)total, __ATOMIC_RELAXED,
                                      __HIP_MEMORY_SCOPE_AGENT);
-    loss = 0.0f;
+    lane_loss = 0.0f;
 }
 
 // One positive sample with its K negatives (Alg. 1, the Train calls; Sec. 2.1
@@ -268,12 +288,12 @@ __device__ __forceinline__ void hand_over_loss(double *slots, float &loss, int l
 //   context[rows_k] += coef_k * vertex[u]
 // with coef_0 = lr (1 - sigmoid(s_0)), coef_k = -lr w sigmoid(s_k).  A context
 // row named more than once in the sample is written once with the summed
-// coefficient.  u and rows[] are wave-uniform.  kTrack: the sample's loss at the rows as loaded is added
-// to `loss`.
+// coefficient.  u and rows[] are wave-uniform.  kTrack: the scores go to lane i of `scores`.
+// Returns the score of the positive.
 template <int kV, int kK, int kCoherence, bool kFull, bool kTrack>
-__device__ __forceinline__ void sgns_step(float *__restrict__ vertex, float *__restrict__ context, uint32_t u,
+__device__ __forceinline__ float sgns_step(float *__restrict__ vertex, float *__restrict__ context, uint32_t u,
                                           const uint32_t (&rows)[kK + 1], float lr, float w, int lane, uint32_t D,
-                                          float &loss) {
+                                          ChunkScores<kK> &scores, uint32_t i) {
     using Io = RowIo<kV, kCoherence, kFull>;
     float *xp = vertex + (size_t)u * D;
     float x[kV];
@@ -282,15 +302,16 @@ __device__ __forceinline__ void sgns_step(float *__restrict__ vertex, float *__r
 #pragma unroll
     for (int k = 0; k <= kK; ++k) Io::load(context + (size_t)rows[k] * D, lane, D, c[k]);
 
-    float coef[kK + 1];
+    float coef[kK + 1], positive = 0.0f;
 #pragma unroll
     for (int k = 0; k <= kK; ++k) {
         float partial = 0.0f;
 #pragma unroll
         for (int j = 0; j < kV; ++j) partial = fmaf(x[j], c[k][j], partial);
         const float score = wave_sum(partial);
+        if (k == 0) positive = score;
         coef[k] = k == 0 ? lr * (1.0f - sigmoid(score)) : -(lr * w) * sigmoid(score);
-        if constexpr (kTrack) loss += k == 0 ? minus_log_sigmoid(score) : w * minus_log_sigmoid(-score);
+        if constexpr (kTrack) scores.put(k, i, score);
     }
 
     float dx[kV];
@@ -329,6 +350,7 @@ __device__ __forceinline__ void sgns_step(float *__restrict__ vertex, float *__r
         for (int j = 0; j < kV; ++j) dx[j] += x[j];
         Io::store(xp, lane, D, dx);
     }
+    return positive;
 }
 
 // ---------------------------------------------------------------------------
@@ -341,14 +363,15 @@ __global__ __launch_bounds__(kBlock) void k_train_hogwild(TrainArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane((blockIdx.x * kBlock + threadIdx.x) / kWave);
     const uint32_t waves = gridDim.x * (kBlock / kWave);
-    const uint32_t chunks = (a.count + kWave - 1) / kWave;
+    const uint32_t chunks = (a.count + a.unit - 1) / a.unit;
     const uint2 *__restrict__ pairs = (const uint2 *)a.pairs;
-    float loss = 0.0f;
+    float lane_loss = 0.0f;
     uint32_t chunks_done = 0;
+    bool diverged = false;
 
     for (uint32_t chunk = wave; chunk < chunks; chunk += waves) {
-        const uint32_t base = chunk * kWave;
-        const uint32_t in_chunk = min((uint32_t)kWave, a.count - base);
+        const uint32_t base = chunk * a.unit;
+        const uint32_t in_chunk = min(a.unit, a.count - base);
         const bool mine = (uint32_t)lane < in_chunk;
         const uint2 p = mine ? pairs[base + lane] : make_uint2(0u, 0u);
         const uint64_t g = a.first_g + (a.order && mine ? a.order[base + lane] : base + lane);
@@ -356,7 +379,9 @@ __global__ __launch_bounds__(kBlock) void k_train_hogwild(TrainArgs a) {
 #pragma unroll
         for (int k = 0; k < kK; ++k) neg[k] = draw_negative(a.alias, a.alias_n, a.seed, g, k);
         const float lr = learning_rate(a.lr0, a.lr_min_ratio, g, a.total);
-        if (mine && (p.x >= a.n || p.y >= a.n)) *a.error_flag = 1u;
+        const bool named = mine && p.x < a.n && p.y < a.n;
+        if (mine && !named) *a.error_flag = 1u;
+        ChunkScores<kK> scores{};
 
         for (uint32_t i = 0; i < in_chunk; ++i) {
             const uint32_t u = lane_value(p.x, i);
@@ -366,12 +391,17 @@ __global__ __launch_bounds__(kBlock) void k_train_hogwild(TrainArgs a) {
 #pragma unroll
             for (int k = 0; k < kK; ++k) rows[k + 1] = lane_value(neg[k], i);
             const float lr_i = __uint_as_float(lane_value(__float_as_uint(lr), i));
-            sgns_step<kV, kK, kCoherence, kFull, kTrack>(a.vertex, a.context, u, rows, lr_i, a.neg_weight, lane, a.dim,
-                                                         loss);
+            const float score = sgns_step<kV, kK, kCoherence, kFull, kTrack>(a.vertex, a.context, u, rows, lr_i, a.neg_weight,
+                                                                             lane, a.dim, scores, i);
+            diverged |= !(score == score);
         }
-        if (kTrack && (++chunks_done & 15u) == 0u) hand_over_loss(a.loss_slots, loss, lane);
+        if constexpr (kTrack) {
+            if (named) lane_loss += scores.loss(a.neg_weight);
+            if ((++chunks_done & 15u) == 0u) hand_over_loss(a.loss_slots, lane_loss, lane);
+        }
     }
-    if constexpr (kTrack) hand_over_loss(a.loss_slots, loss, lane);
+    if (a.report_divergence && diverged) a.error_flag[1] = 1u;
+    if constexpr (kTrack) hand_over_loss(a.loss_slots, lane_loss, lane);
 }
 
 // Update of a row that is not held in registers: row += total * other.  Atomic adds keep
@@ -413,10 +443,11 @@ __device__ __forceinline__ void remote_update(float *row, int lane, uint32_t D, 
 // the pool front to back and a row's samples stay spread over time.  Every sample keeps the
 // negatives and the learning rate of its position in the pool.
 template <int kTile>
-__device__ __forceinline__ void sort_tile(uint32_t *word) {
-    for (uint32_t k = 2; k <= (uint32_t)kTile; k <<= 1) {
+__device__ __forceinline__ void sort_tile(uint32_t *word, uint32_t tile) {
+    const uint32_t size = kTile > 0 ? (uint32_t)kTile : tile;
+    for (uint32_t k = 2; k <= size; k <<= 1) {
         for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-            for (uint32_t t = threadIdx.x; t < (uint32_t)kTile / 2; t += kBlock) {
+            for (uint32_t t = threadIdx.x; t < size / 2; t += kBlock) {
                 const uint32_t lo = 2 * t - (t & (j - 1));  // partner pairs (lo, lo + j) of this bitonic step
                 const uint32_t hi = lo + j;
                 const bool ascending = (lo & k) == 0;
@@ -431,12 +462,16 @@ __device__ __forceinline__ void sort_tile(uint32_t *word) {
     }
 }
 
+constexpr uint32_t kSmallestTile = 16, kLargestTile = 8192;  // samples per workgroup of the tiled kernel
+
 // samples whose gathers a wave of the tiled kernel has in flight together (V floats of a row per lane, K negatives)
 __host__ __device__ constexpr int tiled_batch(int V, int K) { return V * (K + 1) <= 4 ? 4 : (V * (K + 1) <= 12 ? 2 : 1); }
 
 // bit of the pair of context rows j1 < j2 (rows 1 .. K + 1 of a sample) in a sample's `same` word
 __host__ __device__ constexpr int pair_bit(int j1, int j2) { return (j1 - 1) * 6 + (j2 - 1); }
 
+// kTile > 0: tiles of that size; 0: of a.unit samples, a power of two from kSmallestTile to kLargestTile, in LDS given
+// with the launch.
 template <int kV, int kK, int kCoherence, int kTile, bool kFull, bool kTrack>
 __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
     const uint32_t D = a.dim;
@@ -449,10 +484,10 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
     constexpr uint32_t kSkip = 0xFFFFFFFFu;  // word of a slot without a trainable sample (row number 7 is never used)
     constexpr uint32_t kSlotBits = 13, kGroupedRanks = 4096;
     constexpr uint32_t kRecord = kK + 3;  // words of a sample's record: u, v, K negatives, warm flags of the negatives
-    static_assert(kTile <= (1 << kSlotBits) && kTile >= 2 * kBlock, "tile size");
+    static_assert(kLargestTile <= (1u << kSlotBits) && (kTile == 0 || kTile % kBlock == 0), "tile size");
     static_assert(kK + 1 < 7, "row numbers take three bits and 7 is reserved");
-    constexpr uint32_t kPerWave = kTile / (kBlock / kWave);
-    static_assert(kPerWave % kWave == 0, "a wave walks whole 64-sample chunks");
+    const uint32_t size = kTile > 0 ? (uint32_t)kTile : a.unit;
+    const uint32_t per_wave = size / (kBlock / kWave);
     // samples whose gathers are in flight together: bounded by the registers their rows take
     constexpr int kBatch = tiled_batch(kV, kK);
     // A held row trades with memory every four samples where four samples are gathered at once, every two
@@ -469,21 +504,23 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
                        kSameShift = kClashShift + 2 * kBatch - 1;
     static_assert(kSameShift < 32, "flag word");
     using Io = RowIo<kV, kCoherence, kFull>;
-    __shared__ uint32_t s_word[kTile];
+    extern __shared__ uint32_t s_given[];
+    __shared__ uint32_t s_fixed[kTile > 0 ? kTile : 1];
+    uint32_t *const s_word = kTile > 0 ? s_fixed : s_given;  // `size` words
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave_in_group = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint2 *__restrict__ pairs = (const uint2 *)a.pairs;
-    const uint32_t tiles = (a.count + kTile - 1) / kTile;
-    float loss = 0.0f;  // kTrack: of the samples this wave has trained since it last handed its sum over
+    const uint32_t tiles = (a.count + size - 1) / size;
+    float lane_loss = 0.0f;  // kTrack: of the samples this wave has trained since it last handed its sum over
 
     for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        const uint32_t tile_base = tile * kTile;
+        const uint32_t tile_base = tile * size;
         // Every tile orders the rows through its own mask, so the order in which a tile reaches
         // the hot rows differs from tile to tile.  With one common order all workgroups, started
         // together, would reach the same rows at the same moment, and a row would receive its
         // updates of thousands of tiles in one burst, all computed from the same stale value.
         const uint32_t scramble = (tile * 0x9E3779B1u) >> 18;  // 14 bits
-        for (uint32_t t = threadIdx.x; t < (uint32_t)kTile; t += kBlock) {
+        for (uint32_t t = threadIdx.x; t < size; t += kBlock) {
             uint32_t word = kSkip;
             if (tile_base + t < a.count) {
                 const uint2 p = pairs[tile_base + t];
@@ -533,7 +570,7 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
             s_word[t] = word;
         }
         __syncthreads();
-        sort_tile<kTile>(s_word);
+        sort_tile<kTile>(s_word, size);
 
         float *held = nullptr;   // address of the row kept in y[]
         bool held_warm = true;   // its merge must not lose concurrent updates
@@ -555,11 +592,13 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
                 Io::store(held, lane, D, y);
         };
 
-        for (uint32_t base = wave_in_group * kPerWave; base < (wave_in_group + 1) * kPerWave; base += kWave) {
+        for (uint32_t base = wave_in_group * per_wave; base < (wave_in_group + 1) * per_wave; base += kWave) {
             // ---- per chunk, lane l works out everything about sample l of the chunk, so that the walk
             // below only has to fetch ready-made scalars from the owning lane (the scalar unit of a
             // compute unit is shared by its four SIMDs and is what this kernel runs out of first).
-            const uint32_t word = s_word[base + lane];
+            // a tile of fewer than 256 samples leaves a wave less than a chunk
+            const bool in_quarter = kTile > 0 || (uint32_t)lane < per_wave - (base - wave_in_group * per_wave);
+            const uint32_t word = in_quarter ? s_word[base + lane] : kSkip;
             const bool mine = word != kSkip;
             const uint32_t pos = tile_base + ((word >> 2) & ((1u << kSlotBits) - 1u));
             const uint32_t *record = a.records + (size_t)pos * kRecord;
@@ -683,7 +722,8 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
             // One sample (same arithmetic as sgns_step): switch the held row if needed, then all
             // scores and coefficients from the rows as they are before the sample, then the updates:
             // into the register copy for the held row, to memory for the others.
-            auto train_one = [&](const Sample &cur, const float (&loaded)[kRows][kV], const float (&fresh)[kV]) {
+            ChunkScores<kK> scores{};
+            auto train_one = [&](const Sample &cur, uint32_t i, const float (&loaded)[kRows][kV], const float (&fresh)[kV]) {
                 if (cur.stationary != held) {
                     flush();
 #pragma unroll
@@ -714,8 +754,7 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
                     for (int e = 0; e < kV; ++e) partial = fmaf(x[e], c[k][e], partial);
                     const float score = wave_sum(partial);
                     coef[k] = k == 0 ? cur.lr * (1.0f - sigmoid(score)) : -lrw * sigmoid(score);
-                    if constexpr (kTrack)
-                        loss += k == 0 ? minus_log_sigmoid(score) : a.neg_weight * minus_log_sigmoid(-score);
+                    if constexpr (kTrack) scores.put(k, i, score);
                 }
                 // context rows first (they take the vertex row as it was), each distinct row once
 #pragma unroll
@@ -810,10 +849,12 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
                 for (int b = 0; b < kBatch; ++b)
                     if ((uint32_t)b < taken) {
                         since_exchange = batch[b].stationary == held ? since_exchange + 1u : 1u;
-                        train_one(batch[b], loaded[b], fresh[b]);
+                        train_one(batch[b], i0 + b, loaded[b], fresh[b]);
                     }
                 i0 += taken;
             }
+            if constexpr (kTrack)
+                if ((uint32_t)lane < in_chunk) lane_loss += scores.loss(a.neg_weight);
             // what the next chunk's clash tests compare with: the row held now
             if (in_chunk > 0u) {
                 carried_id = lane_value(stationary_id, in_chunk - 1u);
@@ -824,7 +865,7 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
         // a row that is no number any more: training has diverged (reported by the next synchronising call)
         if (held && !(y[0] == y[0])) a.error_flag[1] = 1u;
         flush();
-        if constexpr (kTrack) hand_over_loss(a.loss_slots, loss, lane);
+        if constexpr (kTrack) hand_over_loss(a.loss_slots, lane_loss, lane);
         __syncthreads();  // the next tile overwrites the LDS arrays
     }
 }
@@ -847,9 +888,12 @@ __global__ __launch_bounds__(kBlock) void k_train_batch(TrainArgs a) {
 #pragma unroll
     for (int k = 0; k < kK; ++k) rows[k + 1] = a.negatives[(size_t)i * kK + k];
     const float lr = learning_rate(a.lr0, a.lr_min_ratio, a.first_g + i, a.total);
-    float loss = 0.0f;
-    sgns_step<kV, kK, kPlain, kFull, kTrack>(a.vertex, a.context, u, rows, lr, a.neg_weight, lane, a.dim, loss);
-    if constexpr (kTrack) hand_over_loss(a.loss_slots, loss, lane);
+    ChunkScores<kK> scores{};
+    (void)sgns_step<kV, kK, kPlain, kFull, kTrack>(a.vertex, a.context, u, rows, lr, a.neg_weight, lane, a.dim, scores, 0u);
+    if constexpr (kTrack) {
+        float lane_loss = lane == 0 ? scores.loss(a.neg_weight) : 0.0f;
+        hand_over_loss(a.loss_slots, lane_loss, lane);
+    }
 }
 
 #if !GV_TRACK_LOSS
@@ -1088,21 +1132,6 @@ __global__ __launch_bounds__(kWalkBlock) void k_augment(AugmentArgs a) {
 
 #endif  // !GV_TRACK_LOSS
 
-// Persistent-style grid: enough workgroups to fill all 256 CUs at full occupancy; each
-// wave strides over the chunks.  The number of samples in flight is also kept below
-// |V|/32: every in-flight sample works on values that miss the updates of the others
-// (Def. 1, Sec. 3.2: the order of updates stops mattering only while concurrent samples
-// rarely share rows), and a small graph gains nothing from thousands of waves.
-uint32_t hogwild_blocks(uint32_t count, uint32_t n) {
-    constexpr uint32_t max_blocks = 256u * 8u;
-    const uint32_t chunks = (count + kWave - 1) / kWave;
-    const uint32_t wanted = (chunks + (kBlock / kWave) - 1) / (kBlock / kWave);
-    const uint32_t by_rows = (n / 32u) / (kBlock / kWave);
-    uint32_t blocks = wanted < max_blocks ? wanted : max_blocks;
-    if (blocks > by_rows) blocks = by_rows > 64u ? by_rows : (blocks < 64u ? blocks : 64u);
-    return blocks;
-}
-
 // A row that fills its lanes exactly (d = 64, 128, 256, 512) takes the kernels without per-lane bounds tests.
 template <int kV, int kK, bool kFull, bool kTrack>
 hipError_t launch_hogwild_vkft(const TrainArgs &a, uint32_t coherence, uint32_t blocks, hipStream_t stream) {
@@ -1130,42 +1159,42 @@ hipError_t launch_hogwild_vkf(const TrainArgs &a, uint32_t coherence, uint32_t b
 
 template <int kV, int kK>
 hipError_t launch_hogwild_vk(const TrainArgs &a, uint32_t coherence, hipStream_t stream) {
-    const uint32_t blocks = hogwild_blocks(a.count, a.n);
-    if (blocks == 0) return hipSuccess;
-    return a.dim == (uint32_t)(kWave * kV) ? launch_hogwild_vkf<kV, kK, true>(a, coherence, blocks, stream)
-                                           : launch_hogwild_vkf<kV, kK, false>(a, coherence, blocks, stream);
+    if (a.count == 0) return hipSuccess;
+    if (a.unit == 0 || a.unit > (uint32_t)kWave || a.blocks == 0) return hipErrorInvalidValue;
+    return a.dim == (uint32_t)(kWave * kV) ? launch_hogwild_vkf<kV, kK, true>(a, coherence, a.blocks, stream)
+                                           : launch_hogwild_vkf<kV, kK, false>(a, coherence, a.blocks, stream);
 }
 
-template <int kV, int kK, int kTile, bool kFull, bool kTrack>
-hipError_t launch_tiled_vktt(const TrainArgs &a, uint32_t coherence, uint32_t blocks, hipStream_t stream) {
-    if (coherence == kAgent)
-        hipLaunchKernelGGL((k_train_tiled<kV, kK, kAgent, kTile, kFull, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
-    else if (coherence == kMixed)
-        hipLaunchKernelGGL((k_train_tiled<kV, kK, kMixed, kTile, kFull, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
-    else
-        hipLaunchKernelGGL((k_train_tiled<kV, kK, kAtomicAgent, kTile, kFull, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
+template <int kV, int kK, bool kFull, bool kTrack>
+hipError_t launch_tiled_vkft(const TrainArgs &a, uint32_t coherence, uint32_t blocks, hipStream_t stream) {
+    constexpr int tile = (int)kLargestTile;
+    if (a.unit != kLargestTile) {  // smaller tiles come with atomic adds for all rows
+        if (coherence != kAtomicAgent) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_train_tiled<kV, kK, kAtomicAgent, 0, kFull, kTrack>), dim3(blocks), dim3(kBlock),
+                           a.unit * sizeof(uint32_t), stream, a);
+    } else if (coherence == kAgent) {
+        hipLaunchKernelGGL((k_train_tiled<kV, kK, kAgent, tile, kFull, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
+    } else if (coherence == kMixed) {
+        hipLaunchKernelGGL((k_train_tiled<kV, kK, kMixed, tile, kFull, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
+    } else {
+        hipLaunchKernelGGL((k_train_tiled<kV, kK, kAtomicAgent, tile, kFull, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
+    }
     return hipGetLastError();
 }
 
-template <int kV, int kK, int kTile, bool kFull>
-hipError_t launch_tiled_vkt(const TrainArgs &a, uint32_t coherence, uint32_t blocks, hipStream_t stream) {
+template <int kV, int kK, bool kFull>
+hipError_t launch_tiled_vkf(const TrainArgs &a, uint32_t coherence, uint32_t blocks, hipStream_t stream) {
     if ((a.loss_slots != nullptr) != (GV_TRACK_LOSS != 0)) return hipErrorInvalidValue;
-    return launch_tiled_vktt<kV, kK, kTile, kFull, GV_TRACK_LOSS != 0>(a, coherence, blocks, stream);
+    return launch_tiled_vkft<kV, kK, kFull, GV_TRACK_LOSS != 0>(a, coherence, blocks, stream);
 }
 
 template <int kV, int kK>
 hipError_t launch_tiled_vk(const TrainArgs &a, uint32_t coherence, hipStream_t stream) {
     if (a.count == 0) return hipSuccess;
-    if (a.rank == nullptr || a.records == nullptr) return hipErrorInvalidValue;
-    constexpr uint32_t tile = 8192;  // samples per workgroup (2048 and 4096 were 10 % and 5 % slower on the power-law graph)
-    // One workgroup per tile, started by the hardware in tile order as earlier ones end, unless the
-    // graph is so small that fewer samples must be in flight: then a fixed number of workgroups
-    // strides over the tiles.
-    const uint32_t limit = hogwild_blocks(a.count, a.n);
-    const uint32_t tiles = (a.count + tile - 1) / tile;
-    const uint32_t blocks = limit >= 2048u || limit > tiles ? tiles : limit;
-    return a.dim == (uint32_t)(kWave * kV) ? launch_tiled_vkt<kV, kK, (int)tile, true>(a, coherence, blocks, stream)
-                                           : launch_tiled_vkt<kV, kK, (int)tile, false>(a, coherence, blocks, stream);
+    if (a.rank == nullptr || a.records == nullptr || a.blocks == 0) return hipErrorInvalidValue;
+    if (a.unit < kSmallestTile || a.unit > kLargestTile || (a.unit & (a.unit - 1u))) return hipErrorInvalidValue;
+    return a.dim == (uint32_t)(kWave * kV) ? launch_tiled_vkf<kV, kK, true>(a, coherence, a.blocks, stream)
+                                           : launch_tiled_vkf<kV, kK, false>(a, coherence, a.blocks, stream);
 }
 
 template <int kV, int kK>
@@ -1184,9 +1213,75 @@ hipError_t launch_batch_vk(const TrainArgs &a, hipStream_t stream) {
 }  // namespace
 
 #if !GV_TRACK_LOSS
-uint32_t samples_per_batch(uint32_t dim, uint32_t num_neg) {
-    const int V = dim <= 64 ? 1 : (dim <= 128 ? 2 : (dim <= 256 ? 4 : 8));  // as GV_DISPATCH below
-    return (uint32_t)tiled_batch(V, (int)num_neg);
+namespace {
+int floats_per_lane(uint32_t dim) { return dim <= 64 ? 1 : (dim <= 128 ? 2 : (dim <= 256 ? 4 : 8)); }  // as GV_DISPATCH below
+}  // namespace
+
+uint32_t samples_per_batch(uint32_t dim, uint32_t num_neg) { return (uint32_t)tiled_batch(floats_per_lane(dim), (int)num_neg); }
+
+// Shape of an asynchronous launch.
+//
+// A pool that fills the chip with tiles of 8192 is bound by the rows that it moves (2^24 samples, d = 128, K = 1, a
+// million nodes: 9.8 ms, 5.3 TB/s; tiles of 4096 and 2048 10.1 and 10.7 ms, since fewer samples of a tile share their
+// hottest row).  A shorter one is bound by the walk of one wave over its quarter of a tile, 1.8 ms for any pool of up
+// to 10^6 samples at d = 128, K = 1.  Smaller tiles spread it over the chip, but then more samples are in flight and
+// the mixed policy's stores to cold rows lose more updates; so where it is short enough for that to be the faster
+// way, all its rows are updated with atomic adds, which lose none.  They move 1.1 TB/s of rows, which about 1000 waves
+// in pool order reach; more of them only put more samples in flight.  Rows that a percent of the samples name are
+// what pool order is slow at: then tiles small enough for 1024 workgroups combine their updates.  (4096 samples,
+// d = 128, K = 1: 1.82 -> 0.02 ms; 10^6 samples, d = 96, K = 3: 3.5 -> 1.7 ms; 10^6 samples, d = 64, K = 2, a million
+// nodes: 2.0 -> 1.0 ms with tiles of 1024, 1.45 in pool order; distance from sequential training 3 to 30 times
+// smaller.  2.2*10^6 samples at d = 128, K = 1: 2.2 ms with the mixed policy, 2.8 with atomic adds.)  The same holds
+// for any pool of a graph whose rows are all warm, where the mixed policy is atomic adds with the bookkeeping of the
+// store policies (2*10^6 samples on 10^4 nodes: 7.7 -> 2.9 ms).
+AsyncPlan async_plan(const AsyncPool &p) {
+    constexpr uint32_t kWaves = kBlock / kWave;
+    auto pieces = [&](uint32_t size) { return (uint32_t)((p.count + size - 1) / size); };
+    // Every sample in flight works on values that miss the updates of the others (Def. 1, Sec. 3.2: the order of
+    // updates stops mattering only while concurrent samples rarely share rows), and a small graph gains nothing from
+    // thousands of waves: n / 32 of them, and at least 256.
+    constexpr uint32_t kFullGrid = 2048;  // workgroups that fill the chip
+    const uint32_t by_rows = std::max(p.n / 32u / kWaves, 64u), limit = std::min(by_rows, kFullGrid);
+    auto tiled = [&](uint32_t coherence, uint32_t tile) {
+        // one workgroup per tile, started by the hardware in tile order as earlier ones end, unless the graph is so
+        // small that a fixed number of workgroups has to stride over the tiles
+        return AsyncPlan{true, coherence, tile, limit == kFullGrid ? pieces(tile) : std::min(pieces(tile), limit)};
+    };
+    auto pool_order = [&](uint32_t coherence, uint32_t chunk, uint32_t blocks) {
+        return AsyncPlan{false, coherence, chunk, std::min((pieces(chunk) + kWaves - 1) / kWaves, blocks)};
+    };
+    if (!p.tiled) return pool_order(p.coherence, kWave, limit);
+    const AsyncPlan full = tiled(p.coherence, kLargestTile);
+    // One block of a partitioned graph keeps tiles of 8192: it names its rows `partitions` times as often as a pool
+    // does, and more samples in flight show in the loss (10^4 nodes, 8 x 8 blocks: +2.3 %).
+    if (p.part_of_pool || p.coherence == kAgent) return full;
+
+    // Microseconds.  A sample of a wave that walks a tile takes 0.2 + 0.33 K + 0.18 V (measured, d = 64 .. 512, K = 1
+    // .. 5, one wave per SIMD), a little less in pool order; one row takes 16 million additions a second, of
+    // which tiles combine four into one.
+    const double V = floats_per_lane(p.dim), K = p.num_neg, sample_us = 0.2 + 0.33 * K + 0.18 * V;
+    auto walk_us = [&](const AsyncPlan &t) {
+        return (double)((pieces(t.unit) + t.blocks - 1) / t.blocks) * std::max(t.unit / kWaves, 1u) * sample_us;
+    };
+    const double add_us = (double)p.count * (K + 2.0) * p.dim * sizeof(float) / 1.1e6;
+    const double hot_us = (double)p.count * p.hottest_share * 0.06;
+    const double full_us = p.warm_ranks >= p.n ? HUGE_VAL : walk_us(full);
+
+    uint32_t tile = kSmallestTile;
+    while (tile < kLargestTile && (uint64_t)tile * 2048u <= p.count) tile *= 2;  // 1024 .. 2047 tiles
+    const AsyncPlan small = tiled(kAtomicAgent, tile);
+    const double small_us = std::max({add_us, 0.25 * hot_us, walk_us(small)});
+
+    // in pool order a wave has one sample in flight instead of a batch: n / 16 waves are half of what tiles have
+    const uint32_t waves = std::min(std::max(p.n / 16u, 256u), 1024u);
+    uint32_t chunk = 4;  // as few samples to a wave as keep the waves busy, up to 16
+    while (chunk < 16u && pieces(chunk) > waves) chunk *= 2;
+    const AsyncPlan short_pool = pool_order(kAtomicAgent, chunk, waves / kWaves);
+    const double short_us = std::max({add_us + 0.5 * hot_us, hot_us, (double)p.count / (short_pool.blocks * kWaves) * sample_us});
+
+    if (p.coherence == kMixed && p.may_skip_tiles && short_us < 1.25 * small_us && short_us < full_us) return short_pool;
+    if (p.coherence == kAtomicAgent || small_us < full_us) return small;
+    return full;
 }
 
 bool supported_shape(uint32_t dim, uint32_t num_neg) {

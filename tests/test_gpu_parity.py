@@ -392,6 +392,40 @@ def test_tiled_pools_of_changing_size(gv, policy):
     assert np.array_equal(got_c[cc == 0], context[cc == 0])
 
 
+@pytest.mark.parametrize("policy", [(TILED, MIXED), (TILED, ATOMIC), (TILED, AGENT)])
+@pytest.mark.parametrize("n,d,K,count", [
+    (200_000, 64, 1, 1), (200_000, 64, 1, 15), (200_000, 64, 1, 16), (200_000, 96, 2, 17), (200_000, 128, 1, 65),
+    (200_000, 128, 1, 32_767), (200_000, 128, 1, 32_768), (200_000, 32, 5, 131_073),  # tiles of 16, 32, 64, 128 samples
+    (3_000, 64, 1, 50_001),       # every row is warm, and a few workgroups stride over the tiles
+    (100_000, 64, 1, 6_500_001),  # the same with tiles of 2048 under a store policy
+])
+def test_tile_sizes_and_their_edges(gv, policy, n, d, K, count):
+    """Samples planted at the edges of the pool and of every tile size, on nodes that nothing else names (they have no
+    degree, so they are never drawn as negatives): context[v] ends up one step from its initial value, whatever the
+    tile, the number of workgroups and the policy, and rows that nobody names keep their bits."""
+    w, seed, T = 5.0 / K, 31, 20 * count
+    rng = np.random.default_rng(count)
+    lone = n // 4  # nodes n - lone .. n - 1 have no degree
+    deg = rng.integers(1, 50, size=n).astype(np.uint32)
+    deg[n - lone:] = 0
+    pool = rng.integers(n - lone, size=(count, 2)).astype(np.uint32)
+    edges = {0, count - 1} | {t * m + e for t in (16, 32, 64, 128, 256, 2048, 8192) for m in (1, 3) for e in (-1, 0)}
+    at = np.array(sorted(e for e in edges if 0 <= e < count))
+    u, v = n - lone + np.arange(at.size), n - 1 - np.arange(at.size)
+    pool[at, 0], pool[at, 1] = u, v
+    vertex, context = random_embeddings(n, d, seed=7)
+    got_v, got_c = hogwild_run(gv, n, deg, d, K, w, [pool], vertex, context, T, seed, policy)
+    x, c = vertex[u].astype(np.float64), context[v].astype(np.float64)
+    lr = np.float32(LR0) * (1.0 - at / T)
+    step = (lr / (1.0 + np.exp((x * c).sum(1))))[:, None] * x
+    # fp32: a score of size about one is good to d 2^-24, the row to 2^-24 of itself
+    assert np.abs(got_c[v] - (c + step)).max() <= 1e-6 * np.abs(c).max() + 1e-5 * np.abs(step).max()
+    assert np.abs(step).max(1).min() > 1e-4 and not np.array_equal(got_v[u], vertex[u])
+    rest = np.arange(n - lone + at.size, n - at.size)
+    assert np.array_equal(got_v[rest], vertex[rest]) and np.array_equal(got_c[rest], context[rest])
+    assert np.isfinite(got_v).all() and np.isfinite(got_c).all()
+
+
 @pytest.mark.parametrize("policy", [(TILED, AGENT), (TILED, ATOMIC), (TILED, MIXED)])
 def test_tiled_run_on_one_hub_row_is_sequential(gv, policy):
     """60 samples that all name one high-degree node u: the tiled schedule keeps vertex[u] in registers
