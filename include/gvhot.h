@@ -42,8 +42,8 @@ enum { GV_OK = 0, GV_EINVAL = -1, GV_ENOMEM = -2, GV_ESTATE = -3, GV_EHIP = -4 }
 /* HOGWILD: asynchronous SGD (Sec. 4.3), thousands of samples in flight; it relies on concurrent samples rarely
  *   sharing rows (Def. 1, Sec. 3.2) and is not meant for graphs on which a single node takes part in a large
  *   share of all samples (a star): those train in DETERMINISTIC mode.
- * DETERMINISTIC: samples in pool order, cut into batches without shared rows; equals sequential SGD up to
- *   fp32 rounding inside a sample.                                                                       */
+ * DETERMINISTIC: samples sorted into batches without shared rows, those that share a row in pool order; equals
+ *   sequential SGD up to fp32 rounding inside a sample.                                                  */
 enum { GV_MODE_HOGWILD = 0, GV_MODE_DETERMINISTIC = 1 };
 enum { GV_VERTEX = 0, GV_CONTEXT = 1 };
 /* How embedding rows travel between compute units and memory while an
@@ -116,8 +116,8 @@ typedef struct gv_config {
 typedef struct gv_stats {
     uint64_t samples_trained;   /* positive samples consumed so far = next global position g   */
     uint64_t pools_trained;
-    uint64_t train_launches;    /* training kernel launches (deterministic mode: one per batch) */
-    uint64_t batches;           /* deterministic mode: conflict-free batches cut so far         */
+    uint64_t train_launches;    /* training kernel launches (deterministic mode: at most one per batch) */
+    uint64_t batches;           /* deterministic mode: conflict-free batches so far             */
     double train_kernel_ms;     /* sum of event-timed launch durations (profile != 0), resolved
                                    by gv_sync                                                   */
     uint64_t timed_launches;    /* launches contributing to train_kernel_ms                    */

@@ -16,7 +16,8 @@ struct TrainArgs {
                               // the table of one partition of the nodes (orthogonal blocks)
     uint32_t alias_n;         // buckets in that table
     const uint32_t *pairs;    // count x (u, v)
-    const uint32_t *negatives;// deterministic mode: count x K precomputed draws (else unused)
+    const uint32_t *level_starts; // deterministic mode, narrow levels: first record of every level, levels + 1 entries
+    uint32_t levels;          // deterministic mode: number of narrow levels, or 0: the records are one level
     const uint32_t *order;    // null, or per sample its index in the pool it was redistributed from: sample i then has
                               // global position first_g + order[i] (its negatives and learning rate) instead of
                               // first_g + i
@@ -28,12 +29,13 @@ struct TrainArgs {
     uint32_t warm_ranks;      // rows of hot rank below this are warm: their updates must not be lost
                               // (see gv_build_alias)
     uint32_t *records;        // tiled schedule: scratch of count x (K + 3) words, written and read by the launch
-                              // (u, v, the K negatives, warm flags of the negatives)
+                              // (u, v, the K negatives, warm flags of the negatives); deterministic mode: the
+                              // samples of the launch in the order of their levels (u, v, the K negatives, place)
     uint32_t *error_flag;     // two words: [0] set to 1 when a sample names a node id >= n (sample skipped), [1] set
                               // to 1 when the tiled kernel meets a row that holds NaN (training has diverged)
     double *loss_slots;       // null, or kLossSlots sums: every wave adds the losses its samples saw before their
                               // steps to slot (workgroup number mod kLossSlots)
-    uint64_t first_g;         // global position of pairs[0]
+    uint64_t first_g;         // global position of pairs[0] (deterministic mode: of the sample of place 0)
     uint64_t total;           // T of the learning-rate schedule
     uint64_t seed;            // Philox key of the negative stream
     uint32_t count;           // samples in this launch
@@ -71,16 +73,20 @@ hipError_t launch_train_hogwild(const TrainArgs &a, uint32_t dim, uint32_t num_n
 // Tiled stationary-row training (see k_train_tiled).
 hipError_t launch_train_tiled(const TrainArgs &a, uint32_t dim, uint32_t num_neg, uint32_t coherence,
                               hipStream_t stream);
-// One wave per sample over samples [0, a.count): the caller guarantees that no
-// two of them share a vertex row or a context row (negatives included).
-hipError_t launch_train_batch(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
+// Deterministic mode: a.count records of one level, or of a.levels consecutive narrow ones; the caller guarantees
+// that no two samples of a level share a vertex row or a context row (negatives included).
+hipError_t launch_train_levels(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
+constexpr uint32_t kNarrowLevel = 48;  // samples: three rounds of the one workgroup (see k_train_levels)
+// records[i] = sample order[i] of the pool, as launch_train_levels takes it.
+hipError_t launch_level_records(const uint32_t *pairs, const uint32_t *negatives, const uint32_t *order, uint32_t count,
+                                uint32_t num_neg, uint32_t *records, hipStream_t stream);
 // The same three launches with kernels that also sum the running loss into a.loss_slots (which must be set for
 // these and null for the ones above).
 hipError_t launch_train_hogwild_tracked(const TrainArgs &a, uint32_t dim, uint32_t num_neg, uint32_t coherence,
                                         hipStream_t stream);
 hipError_t launch_train_tiled_tracked(const TrainArgs &a, uint32_t dim, uint32_t num_neg, uint32_t coherence,
                                       hipStream_t stream);
-hipError_t launch_train_batch_tracked(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
+hipError_t launch_train_levels_tracked(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
 // out[i*K + k] = negative k of positive sample first_g + i.
 hipError_t launch_draw_negatives(const uint4 *alias, uint32_t n, uint64_t seed, uint64_t first_g, uint64_t count,
                                  uint32_t num_neg, uint32_t *out, hipStream_t stream);

@@ -870,30 +870,71 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
     }
 }
 
-// Deterministic mode: wave i trains sample i of a batch whose samples share no
-// vertex row and no context row (Def. 1, Sec. 3.2: such samples commute), so the
-// result equals the sequential order up to fp32 rounding inside a sample.
+// Deterministic mode.  The samples of a pool are sorted into levels (gv_api.cpp): those of one level share no vertex
+// row and no context row (Def. 1, Sec. 3.2: such samples commute), and samples that share a row keep their order from
+// level to level, so the result equals the sequential order up to fp32 rounding inside a sample.  A record holds
+// what a wave needs of its sample: u, v, the K negatives, and its place in the pool.
+template <int kK>
+struct LevelSample {
+    uint32_t u, rows[kK + 1], place;
+};
+template <int kK>
+__device__ __forceinline__ LevelSample<kK> level_sample(const uint32_t *__restrict__ records, uint32_t i) {
+    const uint32_t *record = records + (size_t)i * (kK + 3);
+    LevelSample<kK> s;
+    s.u = record[0];
+#pragma unroll
+    for (int k = 0; k <= kK; ++k) s.rows[k] = record[1 + k];
+    s.place = record[kK + 2];
+    return s;
+}
+
+// A level too wide for one workgroup: wave i trains sample i.
 template <int kV, int kK, bool kFull, bool kTrack>
-__global__ __launch_bounds__(kBlock) void k_train_batch(TrainArgs a) {
+__global__ __launch_bounds__(kBlock) void k_train_level(TrainArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t i = __builtin_amdgcn_readfirstlane((blockIdx.x * kBlock + threadIdx.x) / kWave);
     if (i >= a.count) return;
-    const uint32_t u = a.pairs[2 * (size_t)i];
-    uint32_t rows[kK + 1];
-    rows[0] = a.pairs[2 * (size_t)i + 1];
-    if (u >= a.n || rows[0] >= a.n) {
-        *a.error_flag = 1u;
-        return;
-    }
-#pragma unroll
-    for (int k = 0; k < kK; ++k) rows[k + 1] = a.negatives[(size_t)i * kK + k];
-    const float lr = learning_rate(a.lr0, a.lr_min_ratio, a.first_g + i, a.total);
+    const LevelSample<kK> s = level_sample<kK>(a.records, i);
+    const float lr = learning_rate(a.lr0, a.lr_min_ratio, a.first_g + s.place, a.total);
     ChunkScores<kK> scores{};
-    (void)sgns_step<kV, kK, kPlain, kFull, kTrack>(a.vertex, a.context, u, rows, lr, a.neg_weight, lane, a.dim, scores, 0u);
+    (void)sgns_step<kV, kK, kPlain, kFull, kTrack>(a.vertex, a.context, s.u, s.rows, lr, a.neg_weight, lane, a.dim, scores, 0u);
     if constexpr (kTrack) {
         float lane_loss = lane == 0 ? scores.loss(a.neg_weight) : 0.0f;
         hand_over_loss(a.loss_slots, lane_loss, lane);
     }
+}
+
+// Consecutive narrow levels in one launch: one workgroup of 16 waves walks level after level, a barrier between them (its
+// waves share their L1 cache, so rows stored before the barrier are read after it).  A level costs the latency of
+// gathering, storing and the barrier, 1.3 us, where a launch of its own takes 3.5 us; the record of a wave's first
+// sample of the next level is on its way meanwhile.
+constexpr int kLevelBlock = 1024;
+template <int kV, int kK, bool kFull, bool kTrack>
+__global__ __launch_bounds__(kLevelBlock) void k_train_levels(TrainArgs a) {
+    constexpr uint32_t kWaves = kLevelBlock / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    float lane_loss = 0.0f;
+    uint32_t end = a.level_starts[0], i = end + wave;
+    const uint32_t last = a.level_starts[a.levels] - 1u;  // a record to read where a wave has no sample left
+    LevelSample<kK> s = level_sample<kK>(a.records, min(i, last));
+    for (uint32_t level = 0; level < a.levels; ++level) {
+        const uint32_t start = end;
+        end = a.level_starts[level + 1];
+        for (i = start + wave; i < end; i += kWaves) {
+            const float lr = learning_rate(a.lr0, a.lr_min_ratio, a.first_g + s.place, a.total);
+            const LevelSample<kK> now = s;
+            s = level_sample<kK>(a.records, min(i + kWaves < end ? i + kWaves : end + wave, last));
+            ChunkScores<kK> scores{};
+            (void)sgns_step<kV, kK, kPlain, kFull, kTrack>(a.vertex, a.context, now.u, now.rows, lr, a.neg_weight, lane,
+                                                           a.dim, scores, 0u);
+            if constexpr (kTrack) lane_loss += lane == 0 ? scores.loss(a.neg_weight) : 0.0f;
+        }
+        if (start + wave >= end) s = level_sample<kK>(a.records, min(end + wave, last));  // nothing here: the next level's
+        __syncthreads();
+    }
+    if constexpr (kTrack) hand_over_loss(a.loss_slots, lane_loss, lane);
 }
 
 #if !GV_TRACK_LOSS
@@ -989,6 +1030,22 @@ __global__ __launch_bounds__(kBlock) void k_draw_negatives(const uint4 *__restri
         const uint64_t i = t / num_neg;
         const uint32_t k = (uint32_t)(t - i * num_neg);
         out[t] = draw_negative(alias, n, seed, first_g + i, k);
+    }
+}
+
+// The records of a deterministic launch (see k_train_level): record i is sample order[i] of the pool.
+__global__ __launch_bounds__(kBlock) void k_level_records(const uint2 *__restrict__ pairs,
+                                                          const uint32_t *__restrict__ negatives,
+                                                          const uint32_t *__restrict__ order, uint32_t count,
+                                                          uint32_t num_neg, uint32_t *__restrict__ records) {
+    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (uint64_t)gridDim.x * kBlock) {
+        const uint32_t place = order[i];
+        const uint2 p = pairs[place];
+        uint32_t *record = records + i * (num_neg + 3);
+        record[0] = p.x;
+        record[1] = p.y;
+        for (uint32_t k = 0; k < num_neg; ++k) record[2 + k] = negatives[(size_t)place * num_neg + k];
+        record[2 + num_neg] = place;
     }
 }
 
@@ -1198,15 +1255,23 @@ hipError_t launch_tiled_vk(const TrainArgs &a, uint32_t coherence, hipStream_t s
 }
 
 template <int kV, int kK>
-hipError_t launch_batch_vk(const TrainArgs &a, hipStream_t stream) {
+hipError_t launch_levels_vk(const TrainArgs &a, hipStream_t stream) {
     if (a.count == 0) return hipSuccess;
-    const uint32_t blocks = (a.count + (kBlock / kWave) - 1) / (kBlock / kWave);
-    if ((a.loss_slots != nullptr) != (GV_TRACK_LOSS != 0)) return hipErrorInvalidValue;
+    if ((a.loss_slots != nullptr) != (GV_TRACK_LOSS != 0) || a.records == nullptr) return hipErrorInvalidValue;
     constexpr bool kTrack = GV_TRACK_LOSS != 0;
-    if (a.dim == (uint32_t)(kWave * kV))
-        hipLaunchKernelGGL((k_train_batch<kV, kK, true, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
+    const bool full = a.dim == (uint32_t)(kWave * kV);
+    if (a.levels > 0) {
+        if (full)
+            hipLaunchKernelGGL((k_train_levels<kV, kK, true, kTrack>), dim3(1), dim3(kLevelBlock), 0, stream, a);
+        else
+            hipLaunchKernelGGL((k_train_levels<kV, kK, false, kTrack>), dim3(1), dim3(kLevelBlock), 0, stream, a);
+        return hipGetLastError();
+    }
+    const uint32_t blocks = (a.count + (kBlock / kWave) - 1) / (kBlock / kWave);
+    if (full)
+        hipLaunchKernelGGL((k_train_level<kV, kK, true, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
     else
-        hipLaunchKernelGGL((k_train_batch<kV, kK, false, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
+        hipLaunchKernelGGL((k_train_level<kV, kK, false, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -1320,8 +1385,8 @@ hipError_t GV_TRAIN_NAME(launch_train_tiled)(const TrainArgs &a, uint32_t dim, u
 #undef GV_CALL
 }
 
-hipError_t GV_TRAIN_NAME(launch_train_batch)(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t stream) {
-#define GV_CALL(V, K) launch_batch_vk<V, K>(a, stream)
+hipError_t GV_TRAIN_NAME(launch_train_levels)(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t stream) {
+#define GV_CALL(V, K) launch_levels_vk<V, K>(a, stream)
     GV_DISPATCH(GV_CALL)
 #undef GV_CALL
 }
@@ -1366,6 +1431,15 @@ hipError_t launch_draw_negatives(const uint4 *alias, uint32_t n, uint64_t seed, 
     const uint32_t blocks = (uint32_t)(wanted < 65536 ? wanted : 65536);
     hipLaunchKernelGGL(k_draw_negatives, dim3(blocks), dim3(kBlock), 0, stream, alias, n, seed, first_g, count,
                        num_neg, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_level_records(const uint32_t *pairs, const uint32_t *negatives, const uint32_t *order, uint32_t count,
+                                uint32_t num_neg, uint32_t *records, hipStream_t stream) {
+    if (count == 0) return hipSuccess;
+    const uint32_t wanted = (uint32_t)(((uint64_t)count + kBlock - 1) / kBlock);
+    hipLaunchKernelGGL(k_level_records, dim3(std::min(wanted, 65536u)), dim3(kBlock), 0, stream, (const uint2 *)pairs,
+                       negatives, order, count, num_neg, records);
     return hipGetLastError();
 }
 

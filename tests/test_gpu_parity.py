@@ -177,6 +177,40 @@ def test_deterministic_full_tiny_configuration(gv, tiny_graph):
         assert fro <= 1e-5 and mx <= 1e-4, (name, fro, mx)
 
 
+@pytest.mark.parametrize("track", [0, 1])
+@pytest.mark.parametrize("d,K", [(128, 1), (96, 5), (512, 2)])
+@pytest.mark.parametrize("widths", [[1] * 40, [15, 16, 17, 1, 48, 49, 47, 200, 3], [49] * 5, [48] * 7 + [500] + [2] * 3])
+def test_deterministic_levels_of_every_width(gv, widths, d, K, track):
+    """Pools whose conflict-free levels have chosen widths (the samples of level l use the vertex rows 0 .. width - 1,
+    so each follows the one of the level before; the few that meet through a negative come later): one workgroup walks
+    the levels of up to 48 samples, wider ones are launches of their own.  Twice in a row, the second pool shuffled."""
+    n, w, seed = 300_000, 5.0 / K, 41
+    rng = np.random.default_rng(len(widths) + d)
+    deg = rng.integers(1, 50, size=n).astype(np.uint32)
+    u = np.concatenate([np.arange(width) for width in widths]).astype(np.uint32)
+    pool = np.stack([u, rng.permutation(n)[:u.size].astype(np.uint32)], axis=1)
+    pools = [pool, pool[rng.permutation(u.size)]]
+    vertex, context = random_embeddings(n, d, seed=13)
+    T = 20 * u.size
+    with context_for(gv, dim=d, num_neg=K, neg_weight=w, mode=gv.GV_MODE_DETERMINISTIC, total_samples=T, seed=seed,
+                     pool_capacity=u.size, lr0=LR0, track_loss=track) as ctx:
+        gv.gv_set_degrees(ctx, deg)
+        gv.gv_build_alias(ctx, 0.75)
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+        for p in pools:
+            gv.gv_push_pool(ctx, p)
+            gv.gv_train_pool(ctx)
+        got_v = gv.gv_read_embeddings(ctx, gv.GV_VERTEX, n, d)
+        got_c = gv.gv_read_embeddings(ctx, gv.GV_CONTEXT, n, d)
+        stats = gv.gv_get_stats(ctx)
+    ref_v, ref_c = run_oracle(deg, K, w, pools, vertex, context, T, seed)
+    for got, ref, start in ((got_v, ref_v, vertex), (got_c, ref_c, context)):
+        step = np.abs(ref - start).max()
+        assert np.abs(got - ref).max() <= 1e-5 * step + 1e-6 * np.abs(ref).max() and step > 1e-4
+    assert stats["samples_trained"] == 2 * u.size and stats["batches"] >= 2 * len(widths) - 1
+
+
 @pytest.mark.parametrize("d,K,w", [(128, 1, 5.0), (96, 3, 2.0), (512, 5, 1.0)])
 def test_running_loss_of_deterministic_mode_matches_oracle(gv, tiny_graph, d, K, w):
     """gv_config.track_loss: the sum of the losses the samples saw before their steps equals the sequential
