@@ -1287,19 +1287,22 @@ int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64
         if (count == 0 || count > (1ull << 32) - 1) return fail(ctx, GV_EINVAL, "count must be in 1 .. 2^32-1");
         rc = sync_all(ctx);
         if (rc) return rc;
-        // scratch layout: the running total (a double, 256 bytes reserved), then the pairs
-        rc = ensure_eval_scratch(ctx, 256 + count * 2 * sizeof(uint32_t));
+        // scratch layout: the partial sums, then the pairs
+        constexpr uint64_t kSums = gv::kEvalBlocks * sizeof(double);
+        rc = ensure_eval_scratch(ctx, kSums + count * 2 * sizeof(uint32_t));
         if (rc) return rc;
-        double *dev_total = (double *)ctx->eval_scratch;
-        uint32_t *dev_pairs = (uint32_t *)((char *)ctx->eval_scratch + 256);
+        double *dev_partial = (double *)ctx->eval_scratch;
+        uint32_t *dev_pairs = (uint32_t *)((char *)ctx->eval_scratch + kSums);
         GV_HIP(ctx, hipMemcpyAsync(dev_pairs, host_pairs, count * 2 * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
-        GV_HIP(ctx, hipMemsetAsync(dev_total, 0, sizeof(double), ctx->compute));
         gv::TrainArgs a = train_args(ctx, dev_pairs, 0, (uint32_t)count);
         a.seed = eval_seed;
-        GV_HIP(ctx, gv::launch_eval_loss(a, ctx->cfg.dim, ctx->cfg.num_neg, dev_total, ctx->compute));
-        double total = 0.0;
-        GV_HIP(ctx, hipMemcpyAsync(&total, dev_total, sizeof(double), hipMemcpyDeviceToHost, ctx->compute));
+        uint32_t blocks = 0;
+        GV_HIP(ctx, gv::launch_eval_loss(a, ctx->cfg.dim, ctx->cfg.num_neg, dev_partial, &blocks, ctx->compute));
+        double partial[gv::kEvalBlocks];
+        GV_HIP(ctx, hipMemcpyAsync(partial, dev_partial, blocks * sizeof(double), hipMemcpyDeviceToHost, ctx->compute));
         GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
+        double total = 0.0;
+        for (uint32_t b = 0; b < blocks; ++b) total += partial[b];
         *mean_loss = total / (double)count;
         return sync_all(ctx);  // reports ids >= n
     });
@@ -1362,16 +1365,39 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
             return fail(ctx, GV_EINVAL, "both pair sets must be non-empty and hold at most 2^31 pairs together");
         rc = sync_all(ctx);
         if (rc) return rc;
-        std::vector<float> scores(num_edges + num_others);
-        rc = cosine_scores(ctx, host_edge_first, host_edge_second, num_edges, scores.data());
+        // scratch: the partial sums and flags, what sorting needs, the ends of the pairs, the scores
+        const uint64_t count = num_edges + num_others;
+        constexpr uint64_t kSums = 2 * gv::kRankBlocks * sizeof(unsigned long long);
+        const uint64_t sorting = (gv::rank_scratch_words((uint32_t)num_others) + 3u) & ~3ull;
+        rc = ensure_eval_scratch(ctx, kSums + (sorting + 3 * count) * sizeof(uint32_t));
         if (rc) return rc;
-        rc = cosine_scores(ctx, host_other_first, host_other_second, num_others, scores.data() + num_edges);
-        if (rc) return rc;
+        unsigned long long *dev_sums = (unsigned long long *)ctx->eval_scratch;
+        uint32_t *dev_sorting = (uint32_t *)((char *)ctx->eval_scratch + kSums);
+        uint32_t *dev_first = dev_sorting + sorting, *dev_second = dev_first + count;
+        float *dev_scores = (float *)(dev_second + count);
+        auto upload = [&](uint32_t *to, const uint32_t *from, uint64_t ids) {
+            return hipMemcpyAsync(to, from, ids * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute);
+        };
+        GV_HIP(ctx, upload(dev_first, host_edge_first, num_edges));
+        GV_HIP(ctx, upload(dev_first + num_edges, host_other_first, num_others));
+        GV_HIP(ctx, upload(dev_second, host_edge_second, num_edges));
+        GV_HIP(ctx, upload(dev_second + num_edges, host_other_second, num_others));
+        GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, dev_first, dev_second, (uint32_t)count, dev_scores,
+                                      ctx->error_flag, ctx->compute));
+        GV_HIP(ctx, gv::launch_rank_statistic((uint32_t *)dev_scores, (uint32_t)num_edges, (uint32_t)num_others, dev_sorting,
+                                              dev_sums, dev_sums + gv::kRankBlocks, ctx->compute));
+        unsigned long long sums[2 * gv::kRankBlocks];
+        GV_HIP(ctx, hipMemcpyAsync(sums, dev_sums, sizeof sums, hipMemcpyDeviceToHost, ctx->compute));
+        GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
         rc = sync_all(ctx);  // ids >= n
         if (rc) return rc;
-        for (float x : scores)
-            if (!isfinite(x)) return fail(ctx, GV_EINVAL, "an embedding row is not finite");
-        *auc = rank_auc(scores.data(), num_edges, scores.data() + num_edges, num_others);
+        unsigned long long twice = 0, not_finite = 0;
+        for (uint32_t b = 0; b < gv::kRankBlocks; ++b) {
+            twice += sums[b];
+            not_finite |= sums[gv::kRankBlocks + b];
+        }
+        if (not_finite) return fail(ctx, GV_EINVAL, "an embedding row is not finite");
+        *auc = 0.5 * (double)twice / ((double)num_edges * (double)num_others);
         return GV_OK;
     });
 }

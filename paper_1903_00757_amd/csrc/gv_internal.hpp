@@ -99,10 +99,21 @@ hipError_t launch_draw_negatives_partitioned(const uint4 *tables, const uint64_t
 // vertex ~ U(-0.5/d, 0.5/d) from Philox stream 1 (context is cleared by the caller).
 hipError_t launch_init_vertex(float *vertex, uint64_t rows, uint32_t dim, uint64_t seed, hipStream_t stream);
 
-// *total += sum of the per-sample losses of a.pairs[0 .. a.count) (a.seed = evaluation seed).
-hipError_t launch_eval_loss(const TrainArgs &a, uint32_t dim, uint32_t num_neg, double *total, hipStream_t stream);
+// Sum of the per-sample losses of a.pairs[0 .. a.count) (a.seed = evaluation seed), in *blocks partial sums (at most
+// kEvalBlocks).
+constexpr uint32_t kEvalBlocks = 2048;
+hipError_t launch_eval_loss(TrainArgs a, uint32_t dim, uint32_t num_neg, double *partial, uint32_t *blocks, hipStream_t stream);
 hipError_t launch_cosine(const float *vertex, uint32_t n, uint32_t dim, const uint32_t *first, const uint32_t *second,
                          uint32_t count, float *out, uint32_t *error_flag, hipStream_t stream);
+
+// The sum of twice[0 .. kRankBlocks) is 2 (pairs of a positive above a negative) + (pairs of equal score) of scores[0 ..
+// num_pos) against the num_neg scores behind them, num_pos + num_neg <= 2^31 (all are overwritten); not_finite[0 ..
+// kRankBlocks) holds a nonzero where a score is no number.  scratch: rank_scratch_words(num_neg) words at a multiple of
+// 16 bytes.
+constexpr uint32_t kRankBlocks = 512;
+uint64_t rank_scratch_words(uint32_t num_neg);
+hipError_t launch_rank_statistic(uint32_t *scores, uint32_t num_pos, uint32_t num_neg, uint32_t *scratch,
+                                 unsigned long long *twice, unsigned long long *not_finite, hipStream_t stream);
 
 // One pool of walk samples written on the device (see k_augment).
 struct AugmentArgs {

@@ -1007,6 +1007,47 @@ def test_link_prediction_auc_matches_oracle(gv, tiny_graph):
     assert abs(got - oracle.auc(pos, neg)) <= 1e-5
 
 
+@pytest.mark.parametrize("edges,others", [(1, 1), (1, 1000), (1000, 1), (1023, 1025), (4095, 4096), (4097, 12_289),
+                                          (70_000, 130_001), (3, 4_300_001)])  # the last: over 1024 segments of 4096
+def test_link_prediction_auc_is_the_rank_statistic_of_the_cosines(gv, edges, others):
+    """Bit for bit the host's rank statistic of the same scores: negative and equal ones, both zeros, repeated pairs."""
+    n, d = 500, 64
+    rng = np.random.default_rng(edges + others)
+    vertex = rng.standard_normal((n, d)).astype(np.float32)
+    vertex[:50] = 0.0
+    vertex[50:60, 1:] = 0.0  # cosines of exactly 1 and -1, and zeros of either sign against the rows below
+    vertex[60:70, 0] = 0.0
+    with context_for(gv, dim=d, num_neg=1, total_samples=1000, pool_capacity=8) as ctx:
+        gv.gv_set_degrees(ctx, np.ones(n, dtype=np.uint32))
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        a, b, c, e = (rng.integers(n, size=k).astype(np.uint32) for k in (edges, edges, others, others))
+        got = gv.gv_link_prediction_auc(ctx, a, b, c, e)
+        pos, neg = gv.gv_cosine(ctx, a, b), gv.gv_cosine(ctx, c, e)
+    assert got == gv.gv_auc(pos, neg)
+
+
+@pytest.mark.parametrize("count", [1, 3, 4, 5, 63, 65, 8192 * 4 - 1, 8192 * 4 + 1, 8192 * 64 + 65])
+@pytest.mark.parametrize("d,K", [(128, 1), (96, 3), (512, 5)])  # rows of 4, 2 and 1 samples gathered together
+def test_evaluation_loss_of_every_chunk_size(gv, tiny_graph, tiny_alias, count, d, K):
+    """Remainders of a chunk and of a batch, and chunks of 4 to 64 samples, against the oracle."""
+    g, w, seed = tiny_graph, 5.0 / K, 77
+    rng = np.random.default_rng(count)
+    pairs = rng.integers(g["n"], size=(count, 2)).astype(np.uint32)
+    vertex, context = random_embeddings(g["n"], d, seed=3)
+    with context_for(gv, dim=d, num_neg=K, neg_weight=w, total_samples=1000, pool_capacity=8) as ctx:
+        gv.gv_set_degrees(ctx, g["deg"])
+        gv.gv_build_alias(ctx, 0.75)
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+        got = gv.gv_eval_loss(ctx, pairs, seed)
+        assert got == gv.gv_eval_loss(ctx, pairs, seed)
+        with pytest.raises(gv.GvError):
+            gv.gv_eval_loss(ctx, np.concatenate([pairs, np.array([[0, g["n"]]], dtype=np.uint32)]), seed)
+    thresh, alias = tiny_alias
+    ref = oracle.loss(vertex, context, pairs, K=K, w=w, seed=seed, thresh=thresh, alias=alias)
+    assert abs(got - ref) <= 1e-5 * abs(ref)
+
+
 def test_errors_are_reported_not_fatal(gv, tiny_graph):
     g = tiny_graph
     n = g["n"]
