@@ -36,6 +36,17 @@ struct PoolSlot {
     SlotState state = kFree;
 };
 
+// What the host waits for at the end of a call, in pinned memory: copied there on the compute stream, so that one wait
+// for that stream is all (a blocking copy of a few bytes takes 20 us on top of it).
+struct HostResults {
+    uint32_t flag[2];
+    double loss_slots[gv::kLossSlots];
+    union {
+        double partial[gv::kEvalBlocks];                          // gv_eval_loss
+        unsigned long long sums[2 * gv::kRankBlocks];             // gv_link_prediction_auc
+    };
+};
+
 struct TimedSpan {
     hipEvent_t start, stop;
     int kind;  // 0 training launch, 1 host-to-device copy
@@ -80,6 +91,7 @@ struct gv_ctx {
     uint32_t *dev_adj = nullptr;
     uint64_t half_edges = 0;
     uint32_t *error_flag = nullptr;       // device
+    HostResults *results = nullptr;       // pinned
     double *dev_loss = nullptr;           // device, cfg.track_loss: gv::kLossSlots running sums of the training loss
     uint32_t *negatives = nullptr;        // device scratch, deterministic mode / gv_draw_negatives
     uint64_t negatives_capacity = 0;      // in uint32 elements
@@ -175,20 +187,21 @@ void fold_spans(gv_ctx *ctx) {
 }
 
 int sync_all(gv_ctx *ctx) {
+    HostResults &r = *ctx->results;
+    if (ctx->dev_loss)
+        GV_HIP(ctx, hipMemcpyAsync(r.loss_slots, ctx->dev_loss, sizeof r.loss_slots, hipMemcpyDeviceToHost, ctx->compute));
+    GV_HIP(ctx, hipMemcpyAsync(r.flag, ctx->error_flag, sizeof r.flag, hipMemcpyDeviceToHost, ctx->compute));
     GV_HIP(ctx, hipStreamSynchronize(ctx->copy));
     GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
     fold_spans(ctx);
     for (PoolSlot &s : ctx->slot)
         if (s.state == kTraining) s.state = kFree;
     if (ctx->dev_loss) {
-        double slots[gv::kLossSlots];
-        GV_HIP(ctx, hipMemcpy(slots, ctx->dev_loss, sizeof slots, hipMemcpyDeviceToHost));
         double total = 0.0;
-        for (double x : slots) total += x;
+        for (double x : r.loss_slots) total += x;
         ctx->stats.train_loss_sum = total;
     }
-    uint32_t flag[2] = {0, 0};
-    GV_HIP(ctx, hipMemcpy(flag, ctx->error_flag, sizeof flag, hipMemcpyDeviceToHost));
+    const uint32_t flag[2] = {r.flag[0], r.flag[1]};
     if (flag[0] || flag[1]) {
         GV_HIP(ctx, hipMemset(ctx->error_flag, 0, sizeof flag));
         if (flag[0])
@@ -638,6 +651,7 @@ int gv_create(const gv_config *cfg, gv_ctx **out) {
         }
         GV_TRY(hipStreamCreateWithFlags(&ctx->compute, hipStreamNonBlocking));
         GV_TRY(hipStreamCreateWithFlags(&ctx->copy, hipStreamNonBlocking));
+        GV_TRY(hipHostMalloc((void **)&ctx->results, sizeof(HostResults), hipHostMallocDefault));
         GV_TRY(hipMalloc((void **)&ctx->error_flag, 2 * sizeof(uint32_t)));
         GV_TRY(hipMemset(ctx->error_flag, 0, 2 * sizeof(uint32_t)));
         if (cfg->track_loss) {
@@ -682,6 +696,7 @@ void gv_destroy(gv_ctx *ctx) {
     if (ctx->records) (void)hipFree(ctx->records);
     if (ctx->eval_scratch) (void)hipFree(ctx->eval_scratch);
     if (ctx->error_flag) (void)hipFree(ctx->error_flag);
+    if (ctx->results) (void)hipHostFree(ctx->results);
     if (ctx->dev_loss) (void)hipFree(ctx->dev_loss);
     if (ctx->copy) (void)hipStreamDestroy(ctx->copy);
     if (ctx->compute) (void)hipStreamDestroy(ctx->compute);
@@ -1285,8 +1300,8 @@ int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64
         if (rc) return rc;
         if (!mean_loss || (count > 0 && !host_pairs)) return fail(ctx, GV_EINVAL, "null argument");
         if (count == 0 || count > (1ull << 32) - 1) return fail(ctx, GV_EINVAL, "count must be in 1 .. 2^32-1");
-        rc = sync_all(ctx);
-        if (rc) return rc;
+        // everything below is ordered behind the training on the compute stream; what that has to report is read at
+        // the end, together with the result
         // scratch layout: the partial sums, then the pairs
         constexpr uint64_t kSums = gv::kEvalBlocks * sizeof(double);
         rc = ensure_eval_scratch(ctx, kSums + count * 2 * sizeof(uint32_t));
@@ -1298,13 +1313,14 @@ int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64
         a.seed = eval_seed;
         uint32_t blocks = 0;
         GV_HIP(ctx, gv::launch_eval_loss(a, ctx->cfg.dim, ctx->cfg.num_neg, dev_partial, &blocks, ctx->compute));
-        double partial[gv::kEvalBlocks];
-        GV_HIP(ctx, hipMemcpyAsync(partial, dev_partial, blocks * sizeof(double), hipMemcpyDeviceToHost, ctx->compute));
-        GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
+        const double *partial = ctx->results->partial;
+        GV_HIP(ctx, hipMemcpyAsync(ctx->results->partial, dev_partial, blocks * sizeof(double), hipMemcpyDeviceToHost, ctx->compute));
+        rc = sync_all(ctx);  // also reports ids >= n
+        if (rc) return rc;
         double total = 0.0;
         for (uint32_t b = 0; b < blocks; ++b) total += partial[b];
         *mean_loss = total / (double)count;
-        return sync_all(ctx);  // reports ids >= n
+        return GV_OK;
     });
 }
 
@@ -1363,8 +1379,6 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
             return fail(ctx, GV_EINVAL, "null argument");
         if (num_edges == 0 || num_others == 0 || num_edges + num_others > (1ull << 31))
             return fail(ctx, GV_EINVAL, "both pair sets must be non-empty and hold at most 2^31 pairs together");
-        rc = sync_all(ctx);
-        if (rc) return rc;
         // scratch: the partial sums and flags, what sorting needs, the ends of the pairs, the scores
         const uint64_t count = num_edges + num_others;
         constexpr uint64_t kSums = 2 * gv::kRankBlocks * sizeof(unsigned long long);
@@ -1386,10 +1400,9 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
                                       ctx->error_flag, ctx->compute));
         GV_HIP(ctx, gv::launch_rank_statistic((uint32_t *)dev_scores, (uint32_t)num_edges, (uint32_t)num_others, dev_sorting,
                                               dev_sums, dev_sums + gv::kRankBlocks, ctx->compute));
-        unsigned long long sums[2 * gv::kRankBlocks];
-        GV_HIP(ctx, hipMemcpyAsync(sums, dev_sums, sizeof sums, hipMemcpyDeviceToHost, ctx->compute));
-        GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
-        rc = sync_all(ctx);  // ids >= n
+        const unsigned long long *sums = ctx->results->sums;
+        GV_HIP(ctx, hipMemcpyAsync(ctx->results->sums, dev_sums, sizeof ctx->results->sums, hipMemcpyDeviceToHost, ctx->compute));
+        rc = sync_all(ctx);  // also reports ids >= n, and what training before had to report
         if (rc) return rc;
         unsigned long long twice = 0, not_finite = 0;
         for (uint32_t b = 0; b < gv::kRankBlocks; ++b) {
