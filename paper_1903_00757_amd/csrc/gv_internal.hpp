@@ -118,7 +118,10 @@ hipError_t launch_rank_statistic(uint32_t *scores, uint32_t num_pos, uint32_t nu
 // One pool of walk samples written on the device (see k_augment).
 struct AugmentArgs {
     const uint64_t *offsets;  // CSR row starts, n + 1 entries
-    const uint32_t *adj;      // neighbours, both directions of every edge
+    const uint32_t *adj;      // neighbours, both directions of every edge (unless steps is given)
+    const uint4 *steps;       // null, or per adjacency entry {neighbour, its degree, its first half-edge (64 bits)}
+    const uint32_t *guide;    // unweighted graph: owners of the half-edges j << guide_shift, see launch_departure_guide
+    uint32_t guide_shift;
     const uint2 *node_table;  // weighted graph: alias table of the departure nodes {threshold, alias node}; else null
     const uint2 *nbr_table;   // weighted graph: per adjacency entry {threshold, alias entry of the same row}; else null
     uint2 *pairs;             // output, count x (u, v)
@@ -126,6 +129,13 @@ struct AugmentArgs {
     uint64_t seed, first_walk, walks, count, per_walk;
     uint32_t n, length, window, pseudo_shuffle;
 };
+// steps[e] = {adj[e], degree and first half-edge of that node}.
+hipError_t launch_pack_steps(const uint64_t *offsets, const uint32_t *adj, uint64_t half_edges, uint4 *steps, hipStream_t stream);
+// owners[j] = node that half-edge j << guide_shift(half_edges) belongs to, (half_edges >> shift) + 2 entries, at most
+// kGuideEntries; the owner of half-edge e lies between owners[e >> shift] and owners[(e >> shift) + 1].
+constexpr uint32_t kGuideEntries = 65536 + 2;
+uint32_t guide_shift(uint64_t half_edges);
+hipError_t launch_departure_guide(const uint64_t *offsets, uint32_t n, uint64_t half_edges, uint32_t *owners, hipStream_t stream);
 // walk length at most 64
 hipError_t launch_augment(const AugmentArgs &a, hipStream_t stream);
 

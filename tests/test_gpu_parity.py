@@ -1440,6 +1440,49 @@ def test_device_producer_writes_the_oracle_pool(gv, tiny_graph, L, s, count, fir
     assert (got[count:] == 0xFFFFFFFF).all()  # nothing written past the pool
 
 
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("graph", ["two nodes", "star", "gaps", "many"])
+@pytest.mark.parametrize("L,s,count,shuffle", [(1, 1, 1, 1), (1, 5, 1000, 1), (64, 1, 64 * 128 + 3, 1), (64, 70, 300_001, 1),
+                                               (7, 3, 4099, 0), (40, 5, 190 * 128 * 3, 1), (40, 5, 190 * 128 + 1, 1),
+                                               (9, 10, 7, 1), (13, 4, 46 * 128 - 1, 1)])
+def test_device_producer_at_its_edges(gv, graph, weighted, L, s, count, shuffle):
+    """The pools of the host producer, bit for bit: nodes without edges before, between and after the others, a hub,
+    more half-edges than the departure guide has entries; one pair a walk, windows beyond the walk, pools that end
+    inside a walk, inside a workgroup's walks and at their edge."""
+    rng = np.random.default_rng(5)
+    if graph == "two nodes":
+        n, src, dst = 2, np.array([0]), np.array([1])
+    elif graph == "star":
+        n, src, dst = 1000, np.zeros(999, dtype=np.int64), np.arange(1, 1000)
+    elif graph == "gaps":
+        n = 3000
+        ends = np.arange(500, 2500)[rng.random(2000) < 0.3]
+        src, dst = ends[:-1], ends[1:]
+    else:
+        n = 40_000
+        src = rng.integers(n, size=90_000)
+        dst = (src + 1 + rng.integers(n - 1, size=src.size)) % n
+    src, dst = src.astype(np.uint32), dst.astype(np.uint32)
+    offsets, adj = W.csr_from_edges(n, src, dst)
+    import torch
+
+    out = torch.empty((count, 2), dtype=torch.int32, device="cuda")
+    first = (1 << 33) + 17
+    with context_for(gv, dim=32, num_neg=1, total_samples=1000, pool_capacity=8) as ctx:
+        kw = dict(seed=11, walk_length=L, window=s, first_walk=first, count=count, shuffle=shuffle)
+        if weighted:
+            weights = W.csr_edge_weights(src, dst, seed=4)
+            gv.gv_set_weighted_graph(ctx, offsets, adj, weights)
+            ref, walks = gv.gv_augment_weighted(offsets, adj, gv.gv_build_walk_tables(offsets, weights)[1:], **kw)
+        else:
+            gv.gv_set_degrees(ctx, W.degrees(n, src, dst))
+            gv.gv_set_adjacency(ctx, offsets, adj)
+            ref, walks = gv.gv_augment(offsets, adj, **kw)
+        assert gv.gv_augment_device(ctx, out.data_ptr(), **kw) == walks
+        gv.gv_sync(ctx)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), ref)
+
+
 def test_device_producer_feeds_training_like_the_host_producer(gv, tiny_graph):
     """A pool produced on the device and trained from there gives the same embeddings as the same pool
     produced by the host producer and pushed (deterministic mode: bit-identical)."""
