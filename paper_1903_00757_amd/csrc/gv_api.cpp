@@ -271,17 +271,22 @@ int adopt_degrees(gv_ctx *ctx, uint32_t n, std::vector<uint32_t> &&deg) {
 }
 
 // What the device producer reads, from the adjacency just uploaded: the guide of its departures, and the adjacency
-// with degree and first half-edge of every neighbour beside it, 16 bytes an entry, which saves a walk one of two
-// dependent loads a step (k_pack_steps).  Up to 2^28 entries (4 GiB); larger adjacencies, and one that finds no
-// memory for it, are walked as they are.
+// with degree and first half-edge of every neighbour beside it, 16 bytes an entry (32 on a weighted graph, for both
+// outcomes of the alias draw), which leaves a walk one dependent load a step instead of two or three (k_pack_steps,
+// k_pack_weighted_steps).  Up to 4 GiB of it; larger adjacencies, and one that finds no memory for it, are walked as
+// they are.
 int prepare_walks(gv_ctx *ctx) {
-    constexpr uint64_t kMostPacked = 1ull << 28;
+    const bool weighted = ctx->dev_nbr_table != nullptr;
+    const uint64_t bytes = ctx->half_edges * (weighted ? 2 : 1) * sizeof(uint4);
     GV_HIP(ctx, hipMalloc((void **)&ctx->dev_guide, gv::kGuideEntries * sizeof(uint32_t)));
     GV_HIP(ctx, gv::launch_departure_guide(ctx->dev_offsets, ctx->n, ctx->half_edges, ctx->dev_guide, ctx->compute));
-    if (ctx->half_edges <= kMostPacked) {
-        if (hipMalloc((void **)&ctx->dev_steps, ctx->half_edges * sizeof(uint4)) != hipSuccess) {
+    if (bytes <= 1ull << 32) {
+        if (hipMalloc((void **)&ctx->dev_steps, bytes) != hipSuccess) {
             (void)hipGetLastError();  // not an error: the walk does without
             ctx->dev_steps = nullptr;
+        } else if (weighted) {
+            GV_HIP(ctx, gv::launch_pack_weighted_steps(ctx->dev_offsets, ctx->dev_adj, ctx->dev_nbr_table, ctx->n, ctx->dev_steps,
+                                                       ctx->compute));
         } else {
             GV_HIP(ctx, gv::launch_pack_steps(ctx->dev_offsets, ctx->dev_adj, ctx->half_edges, ctx->dev_steps, ctx->compute));
         }
@@ -289,7 +294,9 @@ int prepare_walks(gv_ctx *ctx) {
     GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
     if (ctx->dev_steps) {
         (void)hipFree(ctx->dev_adj);
+        if (weighted) (void)hipFree(ctx->dev_nbr_table);
         ctx->dev_adj = nullptr;
+        ctx->dev_nbr_table = nullptr;
     }
     return GV_OK;
 }
@@ -1294,7 +1301,9 @@ int gv_augment_device(gv_ctx *ctx, uint64_t seed, uint32_t walk_length, uint32_t
         gv::AugmentArgs a{};
         a.offsets = ctx->dev_offsets;
         a.adj = ctx->dev_adj;
-        a.steps = ctx->dev_steps;
+        const bool weighted = ctx->dev_node_table != nullptr;
+        a.steps = weighted ? nullptr : ctx->dev_steps;
+        a.weighted_steps = weighted ? ctx->dev_steps : nullptr;
         a.guide = ctx->dev_guide;
         a.guide_shift = gv::guide_shift(ctx->half_edges);
         a.pairs = (uint2 *)dev_pairs;

@@ -120,6 +120,7 @@ struct AugmentArgs {
     const uint64_t *offsets;  // CSR row starts, n + 1 entries
     const uint32_t *adj;      // neighbours, both directions of every edge (unless steps is given)
     const uint4 *steps;       // null, or per adjacency entry {neighbour, its degree, its first half-edge (64 bits)}
+    const uint4 *weighted_steps; // null, or, of a weighted graph, the same for both outcomes of an entry's alias draw
     const uint32_t *guide;    // unweighted graph: owners of the half-edges j << guide_shift, see launch_departure_guide
     uint32_t guide_shift;
     const uint2 *node_table;  // weighted graph: alias table of the departure nodes {threshold, alias node}; else null
@@ -131,6 +132,9 @@ struct AugmentArgs {
 };
 // steps[e] = {adj[e], degree and first half-edge of that node}.
 hipError_t launch_pack_steps(const uint64_t *offsets, const uint32_t *adj, uint64_t half_edges, uint4 *steps, hipStream_t stream);
+// steps[2e], steps[2e + 1]: see k_pack_weighted_steps; fewer than 2^32 half-edges.
+hipError_t launch_pack_weighted_steps(const uint64_t *offsets, const uint32_t *adj, const uint2 *nbr_table, uint32_t n,
+                                      uint4 *steps, hipStream_t stream);
 // owners[j] = node that half-edge j << guide_shift(half_edges) belongs to, (half_edges >> shift) + 2 entries, at most
 // kGuideEntries; the owner of half-edge e lies between owners[e >> shift] and owners[(e >> shift) + 1].
 constexpr uint32_t kGuideEntries = 65536 + 2;
