@@ -273,14 +273,17 @@ int adopt_degrees(gv_ctx *ctx, uint32_t n, std::vector<uint32_t> &&deg) {
 // What the device producer reads, from the adjacency just uploaded: the guide of its departures, and the adjacency
 // with degree and first half-edge of every neighbour beside it, 16 bytes an entry (32 on a weighted graph, for both
 // outcomes of the alias draw), which leaves a walk one dependent load a step instead of two or three (k_pack_steps,
-// k_pack_weighted_steps).  Up to 4 GiB of it; larger adjacencies, and one that finds no memory for it, are walked as
-// they are.
+// k_pack_weighted_steps).  Not where that takes the walk out of an L2 cache (4 MiB a die) that holds the plain arrays
+// (3.1*10^5 entries, pools of 10^7 pairs: 28 us plain, 36 us packed), and up to 4 GiB of it; larger adjacencies, and one
+// that finds no memory for it, are walked as they are.
 int prepare_walks(gv_ctx *ctx) {
     const bool weighted = ctx->dev_nbr_table != nullptr;
     const uint64_t bytes = ctx->half_edges * (weighted ? 2 : 1) * sizeof(uint4);
     GV_HIP(ctx, hipMalloc((void **)&ctx->dev_guide, gv::kGuideEntries * sizeof(uint32_t)));
     GV_HIP(ctx, gv::launch_departure_guide(ctx->dev_offsets, ctx->n, ctx->half_edges, ctx->dev_guide, ctx->compute));
-    if (bytes <= 1ull << 32) {
+    const uint64_t plain = ctx->half_edges * (sizeof(uint32_t) + (weighted ? sizeof(uint2) : 0)) + (uint64_t)ctx->n * sizeof(uint64_t);
+    constexpr uint64_t kCached = 3ull << 20;
+    if (bytes <= 1ull << 32 && (bytes <= kCached || plain > kCached)) {
         if (hipMalloc((void **)&ctx->dev_steps, bytes) != hipSuccess) {
             (void)hipGetLastError();  // not an error: the walk does without
             ctx->dev_steps = nullptr;
@@ -858,10 +861,8 @@ int gv_build_alias(gv_ctx *ctx, double power) {
         // Under the orthogonal-block schedule the samples in flight all come from one block, where a
         // row's share is `partitions` times its share of the pool.
         const uint32_t B = ctx->cfg.partitions;
-        // Where rows are so long that a wave gathers fewer than four samples at once, a sample's rows stay between
-        // their load and their store for longer (it moves several times the bytes): half the threshold.
-        const uint32_t per_batch = gv::samples_per_batch(ctx->cfg.dim, ctx->cfg.num_neg);
-        const double kInFlight = 2048.0 * per_batch * (B > 0 ? (double)B : 1.0), kWarmThreshold = per_batch >= 4 ? 0.1 : 0.05;
+        const double kInFlight = 2048.0 * gv::samples_per_batch(ctx->cfg.dim, ctx->cfg.num_neg) * (B > 0 ? (double)B : 1.0);
+        const double kWarmThreshold = 0.05;
         const uint32_t kRanked = 0xFFFFu;
         auto hotter = [&](uint32_t x, uint32_t y) {
             const double dx = degree_of(x), dy = degree_of(y);

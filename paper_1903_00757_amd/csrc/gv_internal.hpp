@@ -144,7 +144,7 @@ hipError_t launch_departure_guide(const uint64_t *offsets, uint32_t n, uint64_t 
 hipError_t launch_augment(const AugmentArgs &a, hipStream_t stream);
 
 bool supported_shape(uint32_t dim, uint32_t num_neg);
-// samples whose rows one wave of the tiled kernel gathers together (4, or fewer where rows are long)
+// samples whose rows one wave of the tiled kernel gathers together (2, or 1 where rows are long)
 uint32_t samples_per_batch(uint32_t dim, uint32_t num_neg);
 
 }  // namespace gv

@@ -463,8 +463,12 @@ __device__ __forceinline__ void sort_tile(uint32_t *word, uint32_t tile) {
 
 constexpr uint32_t kSmallestTile = 16, kLargestTile = 8192;  // samples per workgroup of the tiled kernel
 
-// samples whose gathers a wave of the tiled kernel has in flight together (V floats of a row per lane, K negatives)
-__host__ __device__ constexpr int tiled_batch(int V, int K) { return V * (K + 1) <= 4 ? 4 : (V * (K + 1) <= 12 ? 2 : 1); }
+// samples whose gathers a wave of the tiled kernel has in flight together (V floats of a row per lane, K negatives).
+// Four of short rows fit the registers, but twice the workgroups with two each keep the same number in flight and wait
+// less between a gather and its use (2.2*10^6 samples, d = 128, K = 1: 2.29 ms with four in tiles of 8192, 1.73 with two
+// in tiles of 4096; 2^24: 9.80 and 9.67 ms in tiles of 8192).
+__host__ __device__ constexpr bool short_rows(int V, int K) { return V * (K + 1) <= 4; }
+__host__ __device__ constexpr int tiled_batch(int V, int K) { return V * (K + 1) <= 12 ? 2 : 1; }
 
 // bit of the pair of context rows j1 < j2 (rows 1 .. K + 1 of a sample) in a sample's `same` word
 __host__ __device__ constexpr int pair_bit(int j1, int j2) { return (j1 - 1) * 6 + (j2 - 1); }
@@ -489,12 +493,13 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
     const uint32_t per_wave = size / (kBlock / kWave);
     // samples whose gathers are in flight together: bounded by the registers their rows take
     constexpr int kBatch = tiled_batch(kV, kK);
-    // A held row trades with memory every four samples where four samples are gathered at once, every two
-    // where rows are so long that one or two samples fill the registers: there an exchange is a small part of
-    // a sample's traffic, and the shorter interval halves how far the run's scores lag behind the other
+    // A held row trades with memory every four samples, or every two where rows are so long that an exchange is a
+    // small part of a sample's traffic: the shorter interval halves how far the run's scores lag behind the other
     // holders of the row (measured on d = 512, K = 5: distance to the sequential trajectory after 4 pools
     // -0.33 % -> -0.10 % in loss at 3 % more time).
-    constexpr uint32_t kExchangeEvery = kBatch >= 4 ? 4u : 2u;
+    // A block of a partitioned graph, whose hottest row several percent of its samples name, is at the limit of what
+    // is stable with four (one long run in six of 8 x 8 blocks on a million nodes ran away): two there as well.
+    const uint32_t exchange_every = short_rows(kV, kK) && !a.order ? 4u : 2u;
     constexpr int kRows = kK + 2;  // rows of a sample: 0 = vertex[u], 1 = context[v], 2 + k = context[negative k]
     constexpr uint32_t kNoRow = 0xFFFFFFFFu;  // never a node id (ids are below n <= 2^31)
     // layout of a sample's flag word in the walk: 3 bits stationary row number, kRows warm bits, kRows
@@ -806,12 +811,12 @@ __global__ __launch_bounds__(kBlock) void k_train_tiled(TrainArgs a) {
                 Sample batch[kBatch];
                 float loaded[kBatch][kRows][kV], fresh[kBatch][kV];
                 batch[0] = decode(i0);
-                // A run that goes on trades with memory before its staleness would pass kExchangeEvery
+                // A run that goes on trades with memory before its staleness would pass exchange_every
                 // samples: its change so far is added and the register copy takes in what other waves
                 // added meanwhile, so a held row is never more than that many samples behind the other
                 // holders of that row.
                 if (held && held == batch[0].stationary && since_exchange > 0u &&
-                    since_exchange + kBatch > kExchangeEvery &&
+                    since_exchange + kBatch > exchange_every &&
                     (kCoherence == kAtomicAgent || (kCoherence == kMixed && held_warm))) {
                     Io::exchange(held, lane, D, moved, y);
                     since_exchange = 0;
@@ -1477,11 +1482,22 @@ hipError_t launch_hogwild_vk(const TrainArgs &a, uint32_t coherence, hipStream_t
 template <int kV, int kK, bool kFull, bool kTrack>
 hipError_t launch_tiled_vkft(const TrainArgs &a, uint32_t coherence, uint32_t blocks, hipStream_t stream) {
     constexpr int tile = (int)kLargestTile;
-    if (a.unit != kLargestTile) {  // smaller tiles come with atomic adds for all rows
-        if (coherence != kAtomicAgent) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_train_tiled<kV, kK, kAtomicAgent, 0, kFull, kTrack>), dim3(blocks), dim3(kBlock),
-                           a.unit * sizeof(uint32_t), stream, a);
-    } else if (coherence == kAgent) {
+    if (a.unit != kLargestTile) {  // smaller tiles come with atomic adds for all rows, or with the mixed policy on short ones
+        if (coherence == kAtomicAgent) {
+            hipLaunchKernelGGL((k_train_tiled<kV, kK, kAtomicAgent, 0, kFull, kTrack>), dim3(blocks), dim3(kBlock),
+                               a.unit * sizeof(uint32_t), stream, a);
+            return hipGetLastError();
+        }
+        if constexpr (short_rows(kV, kK)) {
+            if (coherence == kMixed) {
+                hipLaunchKernelGGL((k_train_tiled<kV, kK, kMixed, 0, kFull, kTrack>), dim3(blocks), dim3(kBlock),
+                                   a.unit * sizeof(uint32_t), stream, a);
+                return hipGetLastError();
+            }
+        }
+        return hipErrorInvalidValue;
+    }
+    if (coherence == kAgent) {
         hipLaunchKernelGGL((k_train_tiled<kV, kK, kAgent, tile, kFull, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
     } else if (coherence == kMixed) {
         hipLaunchKernelGGL((k_train_tiled<kV, kK, kMixed, tile, kFull, kTrack>), dim3(blocks), dim3(kBlock), 0, stream, a);
@@ -1559,10 +1575,13 @@ AsyncPlan async_plan(const AsyncPool &p) {
     // thousands of waves: n / 32 of them, and at least 256.
     constexpr uint32_t kFullGrid = 2048;  // workgroups that fill the chip
     const uint32_t by_rows = std::max(p.n / 32u / kWaves, 64u), limit = std::min(by_rows, kFullGrid);
+    const bool shorts = short_rows(floats_per_lane(p.dim), (int)p.num_neg);
     auto tiled = [&](uint32_t coherence, uint32_t tile) {
         // one workgroup per tile, started by the hardware in tile order as earlier ones end, unless the graph is so
-        // small that a fixed number of workgroups has to stride over the tiles
-        return AsyncPlan{true, coherence, tile, limit == kFullGrid ? pieces(tile) : std::min(pieces(tile), limit)};
+        // small that a fixed number of workgroups has to stride over the tiles (n / 8 samples in flight where rows are
+        // short, else n / 16)
+        const uint32_t most = std::min(shorts ? 2u * by_rows : by_rows, kFullGrid);
+        return AsyncPlan{true, coherence, tile, most == kFullGrid ? pieces(tile) : std::min(pieces(tile), most)};
     };
     auto pool_order = [&](uint32_t coherence, uint32_t chunk, uint32_t blocks) {
         return AsyncPlan{false, coherence, chunk, std::min((pieces(chunk) + kWaves - 1) / kWaves, blocks)};
@@ -1598,6 +1617,10 @@ AsyncPlan async_plan(const AsyncPool &p) {
 
     if (p.coherence == kMixed && p.may_skip_tiles && short_us < 1.25 * small_us && short_us < full_us) return short_pool;
     if (p.coherence == kAtomicAgent || small_us < full_us) return small;
+    // Short rows take tiles of 4096 with the mixed policy as long as that puts no more samples in flight than four to a
+    // wave of an 8192-sample tile would: where these are too few to fill the chip, and up to d = 64 always (2^24
+    // samples, d = 64, K = 1: 6.6 -> 5.9 ms).
+    if (p.coherence == kMixed && shorts && (V == 1.0 || pieces(kLargestTile) < 640u)) return tiled(kMixed, kLargestTile / 2u);
     return full;
 }
 
