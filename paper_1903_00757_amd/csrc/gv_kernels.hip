@@ -1555,7 +1555,7 @@ uint32_t samples_per_batch(uint32_t dim, uint32_t num_neg) { return (uint32_t)ti
 // Shape of an asynchronous launch.
 //
 // A pool that fills the chip with tiles of 8192 is bound by the rows that it moves (2^24 samples, d = 128, K = 1, a
-// million nodes: 9.8 ms, 5.3 TB/s; tiles of 4096 and 2048 10.1 and 10.7 ms, since fewer samples of a tile share their
+// million nodes: 9.7 ms, 5.3 TB/s; tiles of 4096 and 2048 9.9 and 10.4 ms, since fewer samples of a tile share their
 // hottest row).  A shorter one is bound by the walk of one wave over its quarter of a tile, 1.8 ms for any pool of up
 // to 10^6 samples at d = 128, K = 1.  Smaller tiles spread it over the chip, but then more samples are in flight and
 // the mixed policy's stores to cold rows lose more updates; so where it is short enough for that to be the faster
@@ -1564,7 +1564,7 @@ uint32_t samples_per_batch(uint32_t dim, uint32_t num_neg) { return (uint32_t)ti
 // what pool order is slow at: then tiles small enough for 1024 workgroups combine their updates.  (4096 samples,
 // d = 128, K = 1: 1.82 -> 0.02 ms; 10^6 samples, d = 96, K = 3: 3.5 -> 1.7 ms; 10^6 samples, d = 64, K = 2, a million
 // nodes: 2.0 -> 1.0 ms with tiles of 1024, 1.45 in pool order; distance from sequential training 3 to 30 times
-// smaller.  2.2*10^6 samples at d = 128, K = 1: 2.2 ms with the mixed policy, 2.8 with atomic adds.)  The same holds
+// smaller.  2.2*10^6 samples at d = 128, K = 1: 1.7 ms with the mixed policy, 2.8 with atomic adds.)  The same holds
 // for any pool of a graph whose rows are all warm, where the mixed policy is atomic adds with the bookkeeping of the
 // store policies (2*10^6 samples on 10^4 nodes: 7.7 -> 2.9 ms).
 AsyncPlan async_plan(const AsyncPool &p) {
