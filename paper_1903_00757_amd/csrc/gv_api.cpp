@@ -470,34 +470,44 @@ int train_deterministic(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *
     if (rc) return rc;
     GV_HIP(ctx, gv::launch_draw_negatives(ctx->alias, ctx->n, ctx->cfg.seed, ctx->next_g, count, K, ctx->negatives,
                                           ctx->compute));
-    std::unique_ptr<uint32_t[]> neg(new uint32_t[count * K]), pairs_copy;
+    std::unique_ptr<uint32_t[]> neg(new uint32_t[count * K]), pairs_copy(host_pairs ? nullptr : new uint32_t[count * 2]);
+    std::unique_ptr<uint32_t[]> level(new uint32_t[count]), order(new uint32_t[count]);
+    std::vector<uint32_t> starts;  // samples of every level, then the first of every level
+    // Whatever ends the call before the pool's levels are complete and on the device (also an exception of a container
+    // that cannot grow) leaves rows with levels of samples that were not trained, and copies in flight to the arrays
+    // above: the next call starts from cleared rows, and the arrays outlive the copies.
+    struct Levelling {
+        gv_ctx *ctx;
+        bool complete;
+        ~Levelling() {
+            if (complete) return;
+            (void)hipStreamSynchronize(ctx->compute);
+            ctx->level_vertex.clear();
+            ctx->level_context.clear();
+        }
+    } levelling{ctx, false};
     GV_HIP(ctx, hipMemcpyAsync(neg.get(), ctx->negatives, count * K * sizeof(uint32_t), hipMemcpyDeviceToHost,
                                ctx->compute));
     if (!host_pairs) {
-        pairs_copy.reset(new uint32_t[count * 2]);
         GV_HIP(ctx, hipMemcpyAsync(pairs_copy.get(), dev_pairs, count * 2 * sizeof(uint32_t), hipMemcpyDeviceToHost,
                                    ctx->compute));
         host_pairs = pairs_copy.get();
     }
-    std::unique_ptr<uint32_t[]> level(new uint32_t[count]), order(new uint32_t[count]);
     GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
 
     // level_vertex / level_context: per row, ctx->level_base + the lowest level that the next sample naming it may
     // have; an entry of an earlier pool is at most level_base
-    if (ctx->level_vertex.size() != ctx->n || ctx->level_base > UINT32_MAX - count) {
+    if (ctx->level_vertex.size() != ctx->n || ctx->level_context.size() != ctx->n || ctx->level_base > UINT32_MAX - count) {
         ctx->level_vertex.assign(ctx->n, 0);
         ctx->level_context.assign(ctx->n, 0);
         ctx->level_base = 0;
     }
     const uint32_t base = ctx->level_base;
     uint32_t *const row_u = ctx->level_vertex.data(), *const row_c = ctx->level_context.data();
-    std::vector<uint32_t> starts;  // samples of every level, then the first of every level
     for (uint64_t i = 0; i < count; ++i) {
         const uint32_t u = host_pairs[2 * i], v = host_pairs[2 * i + 1];
-        if (u >= ctx->n || v >= ctx->n) {
-            ctx->level_base = base + (uint32_t)starts.size();
+        if (u >= ctx->n || v >= ctx->n)
             return fail(ctx, GV_EINVAL, "sample %llu names node id >= n (%u)", (unsigned long long)i, ctx->n);
-        }
         uint32_t at = std::max(std::max(base, row_u[u]), row_c[v]);
         for (uint32_t k = 0; k < K; ++k) at = std::max(at, row_c[neg[i * K + k]]);
         level[i] = at - base;
@@ -521,6 +531,7 @@ int train_deterministic(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *
     GV_HIP(ctx, hipMemcpyAsync(dev_starts, starts.data(), starts.size() * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
     GV_HIP(ctx, gv::launch_level_records(dev_pairs, ctx->negatives, dev_order, (uint32_t)count, K, ctx->records, ctx->compute));
     GV_HIP(ctx, hipStreamSynchronize(ctx->compute));  // the host arrays go out of scope
+    levelling.complete = true;
 
     TimedSpan span{};
     const bool timed = ctx->cfg.profile != 0;

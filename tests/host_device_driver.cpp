@@ -1,0 +1,325 @@
+// The runtime behind the C boundary (gv_api.cpp) on a device made of host memory, so that what it does when memory
+// runs out, and the arguments it hands to the kernels, can be checked without a GPU.  The HIP calls that it makes are
+// defined here (they take precedence over the runtime's), and so are the launches: each of them reads and writes what
+// its kernel would, so that AddressSanitizer sees an array that is too short, and checks what its kernel relies on.
+// One argument: the name of the check.  Exit code 0 = it passed.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <algorithm>
+#include <map>
+#include <new>
+#include <vector>
+
+#include "gv_internal.hpp"
+#include "gvhot.h"
+
+#define CHECK(cond)                                                                  \
+    do {                                                                             \
+        if (!(cond)) {                                                               \
+            fprintf(stderr, "%s:%d: check failed: %s\n", __FILE__, __LINE__, #cond); \
+            exit(1);                                                                 \
+        }                                                                            \
+    } while (0)
+
+// ---------------------------------------------------------------------------------------------------- memory
+namespace {
+long host_allocations_left = -1;    // this many more, then one fails; negative: no limit
+long device_allocations_left = -1;  // the same of hipMalloc
+}  // namespace
+
+void *operator new(size_t size) {
+    if (host_allocations_left == 0) {
+        host_allocations_left = -1;
+        throw std::bad_alloc();
+    }
+    if (host_allocations_left > 0) --host_allocations_left;
+    void *p = malloc(size);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void *operator new[](size_t size) { return operator new(size); }
+void *operator new(size_t size, const std::nothrow_t &) noexcept { return malloc(size); }
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+void operator delete[](void *p) noexcept { free(p); }
+void operator delete[](void *p, size_t) noexcept { free(p); }
+
+extern "C" {
+hipError_t hipMalloc(void **p, size_t size) {
+    if (device_allocations_left == 0) {
+        device_allocations_left = -1;
+        *p = nullptr;
+        return hipErrorOutOfMemory;
+    }
+    if (device_allocations_left > 0) --device_allocations_left;
+    *p = malloc(size);
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipFree(void *p) {
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t size, unsigned) {
+    *p = malloc(size);
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipHostFree(void *p) { return hipFree(p); }
+hipError_t hipMemcpy(void *to, const void *from, size_t size, hipMemcpyKind) {
+    memcpy(to, from, size);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *to, const void *from, size_t size, hipMemcpyKind kind, hipStream_t) {
+    return hipMemcpy(to, from, size, kind);
+}
+hipError_t hipMemset(void *p, int value, size_t size) {
+    memset(p, value, size);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void *p, int value, size_t size, hipStream_t) { return hipMemset(p, value, size); }
+static int handle;  // streams and events: everything is done in the order of the calls
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
+    *s = (hipStream_t)&handle;
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) {
+    *e = (hipEvent_t)&handle;
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) {
+    *ms = 0.0f;
+    return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDeviceCount(int *count) {
+    *count = 1;
+    return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "as told"; }
+hipError_t hipGetSymbolAddress(void **p, const void *) {
+    static std::vector<uint32_t> scratch(GV_STATIC_SCRATCH_WORDS);
+    *p = scratch.data();
+    return hipSuccess;
+}
+}  // extern "C"
+
+// ---------------------------------------------------------------------------------------------------- launches
+namespace {
+struct Trained {  // of deterministic mode, in the order of training
+    uint32_t level;
+    std::vector<uint32_t> rows;  // u, then n + every context row
+    uint64_t place;
+};
+std::vector<Trained> trained;
+uint32_t levels_trained = 0;
+uint64_t touched = 0;  // of the arrays that a kernel would read
+
+uint32_t draw(uint64_t g, uint32_t k, uint32_t n) { return (uint32_t)((g * 0x9E3779B97F4A7C15ull + k * 0xD1B54A32D192ED03ull) >> 40) % n; }
+
+template <class T>
+void read_all(const T *array, uint64_t count) {
+    const unsigned char *bytes = (const unsigned char *)array;
+    for (uint64_t i = 0; i < count * sizeof(T); ++i) touched += bytes[i];
+}
+}  // namespace
+
+namespace gv {
+AsyncPlan async_plan(const AsyncPool &p) { return AsyncPlan{p.tiled, p.coherence, p.tiled ? 8192u : 64u, 1u}; }
+hipError_t launch_train_hogwild(const TrainArgs &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_train_tiled(const TrainArgs &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_train_hogwild_tracked(const TrainArgs &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_train_tiled_tracked(const TrainArgs &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_train_levels(const TrainArgs &a, uint32_t, uint32_t num_neg, hipStream_t) {
+    const long left = host_allocations_left;  // what this function allocates is not the library's
+    host_allocations_left = -1;
+    const uint32_t levels = a.levels ? a.levels : 1u;
+    for (uint32_t l = 0; l < levels; ++l) {
+        const uint32_t begin = a.levels ? a.level_starts[l] : 0u, end = a.levels ? a.level_starts[l + 1] : a.count;
+        CHECK(begin < end);
+        for (uint32_t i = begin; i < end; ++i) {
+            const uint32_t *record = a.records + (size_t)i * (num_neg + 3);
+            Trained t{levels_trained, {record[0]}, a.first_g + record[num_neg + 2]};
+            for (uint32_t k = 0; k <= num_neg; ++k) t.rows.push_back(a.n + record[1 + k]);
+            trained.push_back(t);
+        }
+        ++levels_trained;
+    }
+    host_allocations_left = left;
+    return hipSuccess;
+}
+hipError_t launch_train_levels_tracked(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t s) {
+    return launch_train_levels(a, dim, num_neg, s);
+}
+hipError_t launch_level_records(const uint32_t *pairs, const uint32_t *negatives, const uint32_t *order, uint32_t count,
+                                uint32_t num_neg, uint32_t *records, hipStream_t) {
+    for (uint32_t i = 0; i < count; ++i) {
+        uint32_t *record = records + (size_t)i * (num_neg + 3);
+        record[0] = pairs[2 * (size_t)order[i]];
+        record[1] = pairs[2 * (size_t)order[i] + 1];
+        for (uint32_t k = 0; k < num_neg; ++k) record[2 + k] = negatives[(size_t)order[i] * num_neg + k];
+        record[2 + num_neg] = order[i];
+    }
+    return hipSuccess;
+}
+hipError_t launch_draw_negatives(const uint4 *, uint32_t n, uint64_t, uint64_t first_g, uint64_t count, uint32_t num_neg,
+                                 uint32_t *out, hipStream_t) {
+    for (uint64_t i = 0; i < count; ++i)
+        for (uint32_t k = 0; k < num_neg; ++k) out[i * num_neg + k] = draw(first_g + i, k, n);
+    return hipSuccess;
+}
+hipError_t launch_draw_negatives_partitioned(const uint4 *, const uint64_t *, const uint8_t *, const uint32_t *, uint64_t,
+                                             uint64_t, uint64_t, uint32_t, uint32_t *, hipStream_t) {
+    return hipSuccess;
+}
+hipError_t launch_init_vertex(float *, uint64_t, uint32_t, uint64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_eval_loss(TrainArgs, uint32_t, uint32_t, double *partial, uint32_t *blocks, hipStream_t) {
+    *blocks = 1;
+    partial[0] = 0.0;
+    return hipSuccess;
+}
+hipError_t launch_cosine(const float *, uint32_t, uint32_t, const uint32_t *first, const uint32_t *second, uint32_t count,
+                         float *out, uint32_t *, hipStream_t) {
+    for (uint32_t i = 0; i < count; ++i) out[i] = (float)first[i] - (float)second[i];
+    return hipSuccess;
+}
+uint64_t rank_scratch_words(uint32_t num_neg) { return num_neg; }
+hipError_t launch_rank_statistic(uint32_t *, uint32_t, uint32_t, uint32_t *, unsigned long long *twice,
+                                 unsigned long long *not_finite, hipStream_t) {
+    memset(twice, 0, kRankBlocks * sizeof *twice);
+    memset(not_finite, 0, kRankBlocks * sizeof *not_finite);
+    return hipSuccess;
+}
+hipError_t launch_pack_steps(const uint64_t *offsets, const uint32_t *adj, uint64_t half_edges, uint4 *steps, hipStream_t) {
+    for (uint64_t e = 0; e < half_edges; ++e) {
+        const uint64_t begin = offsets[adj[e]];
+        steps[e] = make_uint4(adj[e], (uint32_t)(offsets[adj[e] + 1] - begin), (uint32_t)begin, (uint32_t)(begin >> 32));
+    }
+    return hipSuccess;
+}
+hipError_t launch_pack_weighted_steps(const uint64_t *offsets, const uint32_t *adj, const uint2 *nbr_table, uint32_t n,
+                                      uint4 *steps, hipStream_t) {
+    for (uint64_t e = 0; e < offsets[n]; ++e) {
+        steps[2 * e] = make_uint4(nbr_table[e].x, adj[e], 0u, 0u);
+        steps[2 * e + 1] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    return hipSuccess;
+}
+uint32_t guide_shift(uint64_t) { return 0; }
+hipError_t launch_departure_guide(const uint64_t *, uint32_t, uint64_t, uint32_t *owners, hipStream_t) {
+    memset(owners, 0, kGuideEntries * sizeof *owners);
+    return hipSuccess;
+}
+hipError_t launch_augment(const AugmentArgs &a, hipStream_t) {
+    read_all(a.offsets, (uint64_t)a.n + 1);
+    CHECK(!(a.steps && a.weighted_steps));
+    if (a.node_table) {
+        read_all(a.node_table, a.n);
+        CHECK(!a.steps && (a.weighted_steps || a.nbr_table));
+    } else {
+        CHECK(!a.weighted_steps && !a.nbr_table);
+        if (a.guide) read_all(a.guide, kGuideEntries);
+    }
+    if (a.weighted_steps) read_all(a.weighted_steps, 2 * a.half_edges);
+    if (a.steps) read_all(a.steps, a.half_edges);
+    if (!a.steps && !a.weighted_steps) read_all(a.adj, a.half_edges);
+    if (a.nbr_table) read_all(a.nbr_table, a.half_edges);
+    return hipSuccess;
+}
+bool supported_shape(uint32_t dim, uint32_t num_neg) { return dim % 32 == 0 && dim <= 512 && num_neg >= 1 && num_neg <= 5; }
+uint32_t samples_per_batch(uint32_t, uint32_t) { return 2; }
+}  // namespace gv
+
+// ---------------------------------------------------------------------------------------------------- checks
+namespace {
+gv_ctx *context(uint32_t mode, uint32_t num_neg) {
+    gv_config cfg{};
+    cfg.dim = 32;
+    cfg.num_neg = num_neg;
+    cfg.lr0 = 0.025f;
+    cfg.neg_weight = GV_NEG_WEIGHT_DEFAULT;
+    cfg.mode = mode;
+    cfg.total_samples = 1000000;
+    cfg.pool_capacity = 8;
+    cfg.coherence = GV_COHERENCE_MIXED;
+    cfg.schedule = GV_SCHEDULE_AUTO;
+    gv_ctx *ctx = nullptr;
+    CHECK(gv_create(&cfg, &ctx) == GV_OK);
+    return ctx;
+}
+
+std::vector<uint32_t> random_pool(uint32_t n, uint32_t count, uint32_t seed) {
+    std::vector<uint32_t> pool(2 * (size_t)count);
+    for (size_t i = 0; i < pool.size(); ++i) pool[i] = draw(i + 1, seed, n);
+    return pool;
+}
+
+// `count` samples from position g were trained in conflict-free levels that keep the order of samples sharing a row.
+void check_levels(const std::vector<uint32_t> &pool, uint64_t g, uint32_t n, uint32_t num_neg) {
+    const uint64_t count = pool.size() / 2;
+    CHECK(trained.size() == count);
+    std::vector<bool> seen(count, false);
+    std::map<uint32_t, const Trained *> last;
+    for (const Trained &t : trained) {
+        const uint64_t i = t.place - g;
+        CHECK(i < count && !seen[i]);
+        seen[i] = true;
+        CHECK(t.rows[0] == pool[2 * i] && t.rows[1] == n + pool[2 * i + 1]);
+        for (uint32_t k = 0; k < num_neg; ++k) CHECK(t.rows[2 + k] == n + draw(t.place, k, n));
+        for (uint32_t row : t.rows) {
+            const Trained *before = last.count(row) ? last[row] : nullptr;
+            CHECK(!before || before == &t || (before->level < t.level && before->place < t.place));
+            last[row] = &t;
+        }
+    }
+    trained.clear();
+}
+
+// Deterministic mode: a call that runs out of host memory, wherever it does, reports it and leaves nothing behind.
+void levels_after_failed_allocations() {
+    const uint32_t n = 200, K = 2, count = 300;
+    const std::vector<uint32_t> degrees(n, 3), first = random_pool(n, count, 1), second = random_pool(n, count, 2);
+    int failures = 0;
+    for (long at = 0;; ++at) {
+        gv_ctx *ctx = context(GV_MODE_DETERMINISTIC, K);
+        CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+        host_allocations_left = at;
+        const int rc = gv_train_device_pool(ctx, first.data(), count);
+        const bool done = host_allocations_left >= 0;  // nothing was left to fail
+        host_allocations_left = -1;
+        CHECK(rc == GV_OK || rc == GV_ENOMEM);
+        uint64_t g = 0;
+        if (rc == GV_OK) {
+            check_levels(first, 0, n, K);
+            g = count;
+        }
+        failures += rc != GV_OK;
+        CHECK(trained.empty());
+        CHECK(gv_train_device_pool(ctx, second.data(), count) == GV_OK);
+        check_levels(second, g, n, K);
+        CHECK(gv_train_device_pool(ctx, first.data(), count) == GV_OK);
+        check_levels(first, g + count, n, K);
+        gv_destroy(ctx);
+        if (done) break;
+    }
+    CHECK(failures >= 6);  // host arrays, rows, and the list of levels as it grows
+}
+}  // namespace
+
+int main(int argc, char **argv) {
+    const std::map<std::string, void (*)()> checks = {
+        {"levels after failed allocations", levels_after_failed_allocations},
+    };
+    if (argc != 2 || !checks.count(argv[1])) return 2;
+    checks.at(argv[1])();
+    printf("host device driver: all checks passed\n");
+    return 0;
+}
