@@ -214,6 +214,23 @@ int sync_all(gv_ctx *ctx) {
     return GV_OK;
 }
 
+// The adjacency on the device, in whichever form it is there, and the walk tables of a weighted graph.
+void free_adjacency(gv_ctx *ctx) {
+    if (ctx->dev_offsets) (void)hipFree(ctx->dev_offsets);
+    if (ctx->dev_adj) (void)hipFree(ctx->dev_adj);
+    if (ctx->dev_steps) (void)hipFree(ctx->dev_steps);
+    if (ctx->dev_guide) (void)hipFree(ctx->dev_guide);
+    if (ctx->dev_node_table) (void)hipFree(ctx->dev_node_table);
+    if (ctx->dev_nbr_table) (void)hipFree(ctx->dev_nbr_table);
+    ctx->dev_offsets = nullptr;
+    ctx->dev_adj = nullptr;
+    ctx->dev_steps = nullptr;
+    ctx->dev_guide = nullptr;
+    ctx->dev_node_table = nullptr;
+    ctx->dev_nbr_table = nullptr;
+    ctx->half_edges = 0;
+}
+
 void free_matrices(gv_ctx *ctx) {
     if (ctx->vertex) (void)hipFree(ctx->vertex);
     if (ctx->context) (void)hipFree(ctx->context);
@@ -221,25 +238,13 @@ void free_matrices(gv_ctx *ctx) {
     if (ctx->dev_rank) (void)hipFree(ctx->dev_rank);
     if (ctx->dev_ranked) (void)hipFree(ctx->dev_ranked);
     ctx->dev_ranked = nullptr;
-    if (ctx->dev_offsets) (void)hipFree(ctx->dev_offsets);
-    if (ctx->dev_adj) (void)hipFree(ctx->dev_adj);
-    if (ctx->dev_steps) (void)hipFree(ctx->dev_steps);
-    if (ctx->dev_guide) (void)hipFree(ctx->dev_guide);
-    ctx->dev_steps = nullptr;
-    ctx->dev_guide = nullptr;
-    if (ctx->dev_node_table) (void)hipFree(ctx->dev_node_table);
-    if (ctx->dev_nbr_table) (void)hipFree(ctx->dev_nbr_table);
-    ctx->dev_node_table = nullptr;
-    ctx->dev_nbr_table = nullptr;
+    free_adjacency(ctx);
     if (ctx->dev_part_tables) (void)hipFree(ctx->dev_part_tables);
     if (ctx->dev_part_offsets) (void)hipFree(ctx->dev_part_offsets);
     if (ctx->dev_part) (void)hipFree(ctx->dev_part);
     ctx->dev_part_tables = nullptr;
     ctx->dev_part_offsets = nullptr;
     ctx->dev_part = nullptr;
-    ctx->dev_offsets = nullptr;
-    ctx->dev_adj = nullptr;
-    ctx->half_edges = 0;
     ctx->vertex = ctx->context = nullptr;
     ctx->alias = nullptr;
     ctx->dev_rank = nullptr;
@@ -816,19 +821,25 @@ int gv_set_weighted_graph(gv_ctx *ctx, uint32_t n, const uint64_t *host_offsets,
         std::vector<uint2> node_table(n), nbr_table(half_edges);
         for (uint32_t i = 0; i < n; ++i) node_table[i] = make_uint2(node_thresh[i], node_alias[i]);
         for (uint64_t e = 0; e < half_edges; ++e) nbr_table[e] = make_uint2(nbr_thresh[e], nbr_alias[e]);
-        GV_HIP(ctx, hipMalloc((void **)&ctx->dev_offsets, ((size_t)n + 1) * sizeof(uint64_t)));
-        GV_HIP(ctx, hipMalloc((void **)&ctx->dev_adj, (size_t)half_edges * sizeof(uint32_t)));
-        GV_HIP(ctx, hipMalloc((void **)&ctx->dev_node_table, (size_t)n * sizeof(uint2)));
-        GV_HIP(ctx, hipMalloc((void **)&ctx->dev_nbr_table, (size_t)half_edges * sizeof(uint2)));
-        GV_HIP(ctx, hipMemcpy(ctx->dev_offsets, host_offsets, ((size_t)n + 1) * sizeof(uint64_t), hipMemcpyHostToDevice));
-        GV_HIP(ctx, hipMemcpy(ctx->dev_adj, host_adj, (size_t)half_edges * sizeof(uint32_t), hipMemcpyHostToDevice));
-        GV_HIP(ctx, hipMemcpy(ctx->dev_node_table, node_table.data(), (size_t)n * sizeof(uint2), hipMemcpyHostToDevice));
-        GV_HIP(ctx, hipMemcpy(ctx->dev_nbr_table, nbr_table.data(), (size_t)half_edges * sizeof(uint2), hipMemcpyHostToDevice));
-        ctx->half_edges = half_edges;
+        auto upload = [&]() -> int {
+            GV_HIP(ctx, hipMalloc((void **)&ctx->dev_offsets, ((size_t)n + 1) * sizeof(uint64_t)));
+            GV_HIP(ctx, hipMalloc((void **)&ctx->dev_adj, (size_t)half_edges * sizeof(uint32_t)));
+            GV_HIP(ctx, hipMalloc((void **)&ctx->dev_node_table, (size_t)n * sizeof(uint2)));
+            GV_HIP(ctx, hipMalloc((void **)&ctx->dev_nbr_table, (size_t)half_edges * sizeof(uint2)));
+            GV_HIP(ctx, hipMemcpy(ctx->dev_offsets, host_offsets, ((size_t)n + 1) * sizeof(uint64_t), hipMemcpyHostToDevice));
+            GV_HIP(ctx, hipMemcpy(ctx->dev_adj, host_adj, (size_t)half_edges * sizeof(uint32_t), hipMemcpyHostToDevice));
+            GV_HIP(ctx, hipMemcpy(ctx->dev_node_table, node_table.data(), (size_t)n * sizeof(uint2), hipMemcpyHostToDevice));
+            GV_HIP(ctx, hipMemcpy(ctx->dev_nbr_table, nbr_table.data(), (size_t)half_edges * sizeof(uint2), hipMemcpyHostToDevice));
+            ctx->half_edges = half_edges;
+            return prepare_walks(ctx);
+        };
+        rc = upload();
+        if (rc) {
+            free_adjacency(ctx);  // a part of it would be taken for the walk tables of the next adjacency
+            return rc;
+        }
         ctx->wdegree = std::move(wdeg);
-        rc = prepare_walks(ctx);
-        if (rc) ctx->half_edges = 0;  // no adjacency
-        return rc;
+        return GV_OK;
     });
 }
 
@@ -1278,22 +1289,17 @@ int gv_set_adjacency(gv_ctx *ctx, const uint64_t *host_offsets, const uint32_t *
         if (rc != GV_OK && rc != GV_EINVAL && rc != GV_ESTATE) return rc;  // reports about pools already trained do not stop this call
         if (ctx->wdegree.size() == n)
             return fail(ctx, GV_ESTATE, "the graph is weighted: gv_set_weighted_graph has uploaded its adjacency already");
-        if (ctx->dev_offsets) (void)hipFree(ctx->dev_offsets);
-        if (ctx->dev_adj) (void)hipFree(ctx->dev_adj);
-        if (ctx->dev_steps) (void)hipFree(ctx->dev_steps);
-        if (ctx->dev_guide) (void)hipFree(ctx->dev_guide);
-        ctx->dev_offsets = nullptr;
-        ctx->dev_adj = nullptr;
-        ctx->dev_steps = nullptr;
-        ctx->dev_guide = nullptr;
-        ctx->half_edges = 0;
-        GV_HIP(ctx, hipMalloc((void **)&ctx->dev_offsets, ((size_t)n + 1) * sizeof(uint64_t)));
-        GV_HIP(ctx, hipMalloc((void **)&ctx->dev_adj, (size_t)half_edges * sizeof(uint32_t)));
-        GV_HIP(ctx, hipMemcpy(ctx->dev_offsets, host_offsets, ((size_t)n + 1) * sizeof(uint64_t), hipMemcpyHostToDevice));
-        GV_HIP(ctx, hipMemcpy(ctx->dev_adj, host_adj, (size_t)half_edges * sizeof(uint32_t), hipMemcpyHostToDevice));
-        ctx->half_edges = half_edges;
-        rc = prepare_walks(ctx);
-        if (rc) ctx->half_edges = 0;  // no adjacency
+        free_adjacency(ctx);
+        auto upload = [&]() -> int {
+            GV_HIP(ctx, hipMalloc((void **)&ctx->dev_offsets, ((size_t)n + 1) * sizeof(uint64_t)));
+            GV_HIP(ctx, hipMalloc((void **)&ctx->dev_adj, (size_t)half_edges * sizeof(uint32_t)));
+            GV_HIP(ctx, hipMemcpy(ctx->dev_offsets, host_offsets, ((size_t)n + 1) * sizeof(uint64_t), hipMemcpyHostToDevice));
+            GV_HIP(ctx, hipMemcpy(ctx->dev_adj, host_adj, (size_t)half_edges * sizeof(uint32_t), hipMemcpyHostToDevice));
+            ctx->half_edges = half_edges;
+            return prepare_walks(ctx);
+        };
+        rc = upload();
+        if (rc) free_adjacency(ctx);
         return rc;
     });
 }
@@ -1304,8 +1310,7 @@ int gv_augment_device(gv_ctx *ctx, uint64_t seed, uint32_t walk_length, uint32_t
     return guarded(ctx, [&]() -> int {
         int rc = need_graph(ctx);
         if (rc) return rc;
-        if (!ctx->dev_offsets || ctx->half_edges == 0)
-            return fail(ctx, GV_ESTATE, "no adjacency: call gv_set_adjacency first");
+        if (!ctx->dev_offsets) return fail(ctx, GV_ESTATE, "no adjacency: call gv_set_adjacency first");
         if (walk_length == 0 || walk_length > 64 || window == 0 || window > GV_MAX_WINDOW || shuffle > GV_SHUFFLE_PSEUDO)
             return fail(ctx, GV_EINVAL, "walk_length must be in 1..64, window in 1..GV_MAX_WINDOW, shuffle GV_SHUFFLE_*");
         if (count == 0) return GV_OK;

@@ -121,6 +121,7 @@ struct Trained {  // of deterministic mode, in the order of training
 };
 std::vector<Trained> trained;
 uint32_t levels_trained = 0;
+bool walked_weighted = false;  // by the device producer
 uint64_t touched = 0;  // of the arrays that a kernel would read
 
 uint32_t draw(uint64_t g, uint32_t k, uint32_t n) { return (uint32_t)((g * 0x9E3779B97F4A7C15ull + k * 0xD1B54A32D192ED03ull) >> 40) % n; }
@@ -219,6 +220,7 @@ hipError_t launch_departure_guide(const uint64_t *, uint32_t, uint64_t, uint32_t
     return hipSuccess;
 }
 hipError_t launch_augment(const AugmentArgs &a, hipStream_t) {
+    walked_weighted = a.node_table != nullptr;
     read_all(a.offsets, (uint64_t)a.n + 1);
     CHECK(!(a.steps && a.weighted_steps));
     if (a.node_table) {
@@ -312,11 +314,79 @@ void levels_after_failed_allocations() {
     }
     CHECK(failures >= 6);  // host arrays, rows, and the list of levels as it grows
 }
+
+// A graph of a ring with chords: every node has its two neighbours and the nodes two steps away.
+struct Ring {
+    static constexpr uint32_t n = 50;
+    std::vector<uint64_t> offsets;
+    std::vector<uint32_t> degrees, adj;
+    std::vector<float> weights;
+    Ring() : degrees(n, 4) {
+        for (uint32_t i = 0; i <= n; ++i) offsets.push_back(4ull * i);
+        for (uint32_t i = 0; i < n; ++i)
+            for (uint32_t step : {1u, 2u, n - 1u, n - 2u}) {
+                adj.push_back((i + step) % n);
+                weights.push_back(1.0f + (float)(step % 3u));
+            }
+    }
+};
+
+// A weighted graph that runs out of device memory, wherever it does, leaves nothing that a later graph without weights
+// would be walked by; the device producer reads the tables of the graph that was taken last, whole.
+void walks_after_failed_allocations() {
+    const Ring ring;
+    std::vector<uint32_t> pairs(2 * 1000);
+    uint64_t walks = 0;
+    auto walk = [&](gv_ctx *ctx) {
+        return gv_augment_device(ctx, 1, 5, 2, 0, 1000, GV_SHUFFLE_NONE, pairs.data(), &walks);
+    };
+    int refused = 0, taken = 0;
+    for (long at = 0;; ++at) {
+        gv_ctx *ctx = context(GV_MODE_HOGWILD, 1);
+        device_allocations_left = at;
+        const int rc = gv_set_weighted_graph(ctx, ring.n, ring.offsets.data(), ring.adj.data(), ring.weights.data());
+        const bool done = device_allocations_left >= 0;
+        device_allocations_left = -1;
+        CHECK(rc == GV_OK || rc == GV_ENOMEM);
+        refused += rc != GV_OK;
+        if (rc == GV_OK) {
+            CHECK(walk(ctx) == GV_OK && walked_weighted);
+        } else {
+            CHECK(walk(ctx) == GV_ESTATE);
+            const int next = gv_set_adjacency(ctx, ring.offsets.data(), ring.adj.data());
+            CHECK(next == GV_OK || next == GV_ESTATE);  // no graph yet, or one that knows its degrees
+            taken += next == GV_OK;
+            if (next == GV_OK) CHECK(walk(ctx) == GV_OK && !walked_weighted);
+            CHECK(gv_set_weighted_graph(ctx, ring.n, ring.offsets.data(), ring.adj.data(), ring.weights.data()) == GV_OK);
+            CHECK(walk(ctx) == GV_OK && walked_weighted);
+        }
+        CHECK(gv_set_degrees(ctx, ring.n, ring.degrees.data()) == GV_OK && walk(ctx) == GV_ESTATE);
+        CHECK(gv_set_adjacency(ctx, ring.offsets.data(), ring.adj.data()) == GV_OK && walk(ctx) == GV_OK && !walked_weighted);
+        gv_destroy(ctx);
+        if (done) break;
+    }
+    CHECK(refused >= 9 && taken >= 4);
+    // the same of a graph without weights
+    for (long at = 0;; ++at) {
+        gv_ctx *ctx = context(GV_MODE_HOGWILD, 1);
+        CHECK(gv_set_degrees(ctx, ring.n, ring.degrees.data()) == GV_OK);
+        device_allocations_left = at;
+        const int rc = gv_set_adjacency(ctx, ring.offsets.data(), ring.adj.data());
+        const bool done = device_allocations_left >= 0;
+        device_allocations_left = -1;
+        CHECK(rc == GV_OK || rc == GV_ENOMEM);
+        CHECK(walk(ctx) == (rc == GV_OK ? GV_OK : GV_ESTATE));
+        CHECK(gv_set_adjacency(ctx, ring.offsets.data(), ring.adj.data()) == GV_OK && walk(ctx) == GV_OK && !walked_weighted);
+        gv_destroy(ctx);
+        if (done) break;
+    }
+}
 }  // namespace
 
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"levels after failed allocations", levels_after_failed_allocations},
+        {"walks after failed allocations", walks_after_failed_allocations},
     };
     if (argc != 2 || !checks.count(argv[1])) return 2;
     checks.at(argv[1])();
