@@ -284,8 +284,15 @@ int adopt_degrees(gv_ctx *ctx, uint32_t n, std::vector<uint32_t> &&deg) {
 int prepare_walks(gv_ctx *ctx) {
     const bool weighted = ctx->dev_nbr_table != nullptr;
     const uint64_t bytes = ctx->half_edges * (weighted ? 2 : 1) * sizeof(uint4);
-    GV_HIP(ctx, hipMalloc((void **)&ctx->dev_guide, gv::kGuideEntries * sizeof(uint32_t)));
-    GV_HIP(ctx, gv::launch_departure_guide(ctx->dev_offsets, ctx->n, ctx->half_edges, ctx->dev_guide, ctx->compute));
+    // departures of a weighted graph come from its alias table; among 16 nodes the search is as short without a guide
+    if (!weighted && ctx->n > 16) {
+        if (hipMalloc((void **)&ctx->dev_guide, gv::kGuideEntries * sizeof(uint32_t)) != hipSuccess) {
+            (void)hipGetLastError();  // not an error: the search starts from all nodes
+            ctx->dev_guide = nullptr;
+        } else {
+            GV_HIP(ctx, gv::launch_departure_guide(ctx->dev_offsets, ctx->n, ctx->half_edges, ctx->dev_guide, ctx->compute));
+        }
+    }
     const uint64_t plain = ctx->half_edges * (sizeof(uint32_t) + (weighted ? sizeof(uint2) : 0)) + (uint64_t)ctx->n * sizeof(uint64_t);
     constexpr uint64_t kCached = 3ull << 20;
     if (bytes <= 1ull << 32 && (bytes <= kCached || plain > kCached)) {

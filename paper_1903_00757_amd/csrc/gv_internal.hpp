@@ -121,7 +121,7 @@ struct AugmentArgs {
     const uint32_t *adj;      // neighbours, both directions of every edge (unless steps is given)
     const uint4 *steps;       // null, or per adjacency entry {neighbour, its degree, its first half-edge (64 bits)}
     const uint4 *weighted_steps; // null, or, of a weighted graph, the same for both outcomes of an entry's alias draw
-    const uint32_t *guide;    // unweighted graph: owners of the half-edges j << guide_shift, see launch_departure_guide
+    const uint32_t *guide;    // null, or owners of the half-edges j << guide_shift, see launch_departure_guide
     uint32_t guide_shift;
     const uint2 *node_table;  // weighted graph: alias table of the departure nodes {threshold, alias node}; else null
     const uint2 *nbr_table;   // weighted graph: per adjacency entry {threshold, alias entry of the same row}; else null

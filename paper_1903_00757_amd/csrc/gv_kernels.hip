@@ -1370,7 +1370,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_augment(AugmentArgs a) {
             // departure: last node whose first half-edge is at or before the chosen one
             const uint64_t e = pick_below(r0, a.half_edges);
             const uint32_t bucket = (uint32_t)(e >> a.guide_shift);
-            x = owner_of(a.offsets, e, a.guide[bucket], a.guide[bucket + 1] + 1u);
+            x = a.guide ? owner_of(a.offsets, e, a.guide[bucket], a.guide[bucket + 1] + 1u) : owner_of(a.offsets, e, 0u, a.n);
         }
         s_path[threadIdx.x][0] = x;
         uint64_t begin = a.offsets[x];
@@ -1803,7 +1803,6 @@ hipError_t launch_departure_guide(const uint64_t *offsets, uint32_t n, uint64_t 
 
 hipError_t launch_augment(const AugmentArgs &a, hipStream_t stream) {
     if (a.walks == 0) return hipSuccess;
-    if (!a.node_table && !a.guide) return hipErrorInvalidValue;
     if (a.length == 0 || a.length > (uint32_t)kMaxWalkLength || a.window == 0) return hipErrorInvalidValue;
     const uint64_t blocks = (a.walks + kWalkBlock - 1) / kWalkBlock;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;

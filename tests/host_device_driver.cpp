@@ -225,7 +225,7 @@ hipError_t launch_augment(const AugmentArgs &a, hipStream_t) {
     CHECK(!(a.steps && a.weighted_steps));
     if (a.node_table) {
         read_all(a.node_table, a.n);
-        CHECK(!a.steps && (a.weighted_steps || a.nbr_table));
+        CHECK(!a.steps && !a.guide && (a.weighted_steps || a.nbr_table));
     } else {
         CHECK(!a.weighted_steps && !a.nbr_table);
         if (a.guide) read_all(a.guide, kGuideEntries);
@@ -365,8 +365,9 @@ void walks_after_failed_allocations() {
         gv_destroy(ctx);
         if (done) break;
     }
-    CHECK(refused >= 9 && taken >= 4);
-    // the same of a graph without weights
+    CHECK(refused == 9 && taken >= 4);  // for want of the matrices and node tables (5) and the adjacency with its tables (4)
+    // the same of a graph without weights: all but the adjacency itself can be done without
+    refused = 0;
     for (long at = 0;; ++at) {
         gv_ctx *ctx = context(GV_MODE_HOGWILD, 1);
         CHECK(gv_set_degrees(ctx, ring.n, ring.degrees.data()) == GV_OK);
@@ -375,11 +376,13 @@ void walks_after_failed_allocations() {
         const bool done = device_allocations_left >= 0;
         device_allocations_left = -1;
         CHECK(rc == GV_OK || rc == GV_ENOMEM);
+        refused += rc != GV_OK;
         CHECK(walk(ctx) == (rc == GV_OK ? GV_OK : GV_ESTATE));
         CHECK(gv_set_adjacency(ctx, ring.offsets.data(), ring.adj.data()) == GV_OK && walk(ctx) == GV_OK && !walked_weighted);
         gv_destroy(ctx);
         if (done) break;
     }
+    CHECK(refused == 2);
 }
 }  // namespace
 

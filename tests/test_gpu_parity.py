@@ -1441,7 +1441,7 @@ def test_device_producer_writes_the_oracle_pool(gv, tiny_graph, L, s, count, fir
 
 
 @pytest.mark.parametrize("weighted", [False, True])
-@pytest.mark.parametrize("graph", ["two nodes", "star", "gaps", "many"])
+@pytest.mark.parametrize("graph", ["two nodes", "sixteen nodes", "star", "gaps", "many"])
 @pytest.mark.parametrize("L,s,count,shuffle", [(1, 1, 1, 1), (1, 5, 1000, 1), (64, 1, 64 * 128 + 3, 1), (64, 70, 300_001, 1),
                                                (7, 3, 4099, 0), (40, 5, 190 * 128 * 3, 1), (40, 5, 190 * 128 + 1, 1),
                                                (9, 10, 7, 1), (13, 4, 46 * 128 - 1, 1)])
@@ -1452,6 +1452,8 @@ def test_device_producer_at_its_edges(gv, graph, weighted, L, s, count, shuffle)
     rng = np.random.default_rng(5)
     if graph == "two nodes":
         n, src, dst = 2, np.array([0]), np.array([1])
+    elif graph == "sixteen nodes":  # the most that are searched for a departure without a guide
+        n, src, dst = 16, np.array([3, 3, 3, 5, 7, 7, 13]), np.array([5, 7, 13, 13, 5, 12, 12])
     elif graph == "star":
         n, src, dst = 1000, np.zeros(999, dtype=np.int64), np.arange(1, 1000)
     elif graph == "gaps":
