@@ -39,7 +39,7 @@ struct PoolSlot {
 // What the host waits for at the end of a call, in pinned memory: copied there on the compute stream, so that one wait
 // for that stream is all (a blocking copy of a few bytes takes 20 us on top of it).
 struct HostResults {
-    uint32_t flag[2];
+    uint32_t flag[3];
     double loss_slots[gv::kLossSlots];
     union {
         double partial[gv::kEvalBlocks];                          // gv_eval_loss
@@ -92,7 +92,7 @@ struct gv_ctx {
     uint4 *dev_steps = nullptr;           // the adjacency as the producer reads it (then dev_adj is null), see prepare_walks
     uint32_t *dev_guide = nullptr;        // where the producer's search for a departure starts
     uint64_t half_edges = 0;
-    uint32_t *error_flag = nullptr;       // device
+    uint32_t *error_flag = nullptr;       // device: two words of training (see gv::TrainArgs), then one of evaluation
     HostResults *results = nullptr;       // pinned
     double *dev_loss = nullptr;           // device, cfg.track_loss: gv::kLossSlots running sums of the training loss
     uint32_t *negatives = nullptr;        // device scratch, deterministic mode / gv_draw_negatives
@@ -188,7 +188,8 @@ void fold_spans(gv_ctx *ctx) {
     ctx->spans.clear();
 }
 
-int sync_all(gv_ctx *ctx) {
+// *evaluation_ids (may be null): set where the report is that the evaluation just queued names ids that are no nodes.
+int sync_all(gv_ctx *ctx, bool *evaluation_ids = nullptr) {
     HostResults &r = *ctx->results;
     if (ctx->dev_loss)
         GV_HIP(ctx, hipMemcpyAsync(r.loss_slots, ctx->dev_loss, sizeof r.loss_slots, hipMemcpyDeviceToHost, ctx->compute));
@@ -203,13 +204,16 @@ int sync_all(gv_ctx *ctx) {
         for (double x : r.loss_slots) total += x;
         ctx->stats.train_loss_sum = total;
     }
-    const uint32_t flag[2] = {r.flag[0], r.flag[1]};
-    if (flag[0] || flag[1]) {
+    const uint32_t flag[3] = {r.flag[0], r.flag[1], r.flag[2]};
+    if (flag[0] || flag[1] || flag[2]) {
         GV_HIP(ctx, hipMemset(ctx->error_flag, 0, sizeof flag));
         if (flag[0])
             return fail(ctx, GV_EINVAL, "a trained pool named a node id >= n (%u); those samples were skipped", ctx->n);
-        return fail(ctx, GV_ESTATE, "training has diverged: an embedding row holds NaN (asynchronous mode on a graph "
-                    "where one node takes part in a large share of all samples? see GV_MODE_HOGWILD)");
+        if (flag[1])
+            return fail(ctx, GV_ESTATE, "training has diverged: an embedding row holds NaN (asynchronous mode on a graph "
+                        "where one node takes part in a large share of all samples? see GV_MODE_HOGWILD)");
+        if (evaluation_ids) *evaluation_ids = true;
+        return fail(ctx, GV_EINVAL, "a pair to evaluate names a node id >= n (%u)", ctx->n);
     }
     return GV_OK;
 }
@@ -715,8 +719,8 @@ int gv_create(const gv_config *cfg, gv_ctx **out) {
         GV_TRY(hipStreamCreateWithFlags(&ctx->compute, hipStreamNonBlocking));
         GV_TRY(hipStreamCreateWithFlags(&ctx->copy, hipStreamNonBlocking));
         GV_TRY(hipHostMalloc((void **)&ctx->results, sizeof(HostResults), hipHostMallocDefault));
-        GV_TRY(hipMalloc((void **)&ctx->error_flag, 2 * sizeof(uint32_t)));
-        GV_TRY(hipMemset(ctx->error_flag, 0, 2 * sizeof(uint32_t)));
+        GV_TRY(hipMalloc((void **)&ctx->error_flag, 3 * sizeof(uint32_t)));
+        GV_TRY(hipMemset(ctx->error_flag, 0, 3 * sizeof(uint32_t)));
         if (cfg->track_loss) {
             GV_TRY(hipMalloc((void **)&ctx->dev_loss, gv::kLossSlots * sizeof(double)));
             GV_TRY(hipMemset(ctx->dev_loss, 0, gv::kLossSlots * sizeof(double)));
@@ -1386,16 +1390,18 @@ int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64
         GV_HIP(ctx, hipMemcpyAsync(dev_pairs, host_pairs, count * 2 * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
         gv::TrainArgs a = train_args(ctx, dev_pairs, 0, (uint32_t)count);
         a.seed = eval_seed;
+        a.error_flag = ctx->error_flag + 2;
         uint32_t blocks = 0;
         GV_HIP(ctx, gv::launch_eval_loss(a, ctx->cfg.dim, ctx->cfg.num_neg, dev_partial, &blocks, ctx->compute));
         const double *partial = ctx->results->partial;
         GV_HIP(ctx, hipMemcpyAsync(ctx->results->partial, dev_partial, blocks * sizeof(double), hipMemcpyDeviceToHost, ctx->compute));
-        rc = sync_all(ctx);  // also reports ids >= n
-        if (rc) return rc;
+        bool bad_ids = false;  // then the result covers the other pairs
+        rc = sync_all(ctx, &bad_ids);
+        if (rc && !bad_ids) return rc;
         double total = 0.0;
         for (uint32_t b = 0; b < blocks; ++b) total += partial[b];
         *mean_loss = total / (double)count;
-        return GV_OK;
+        return rc;
     });
 }
 
@@ -1409,7 +1415,7 @@ static int cosine_scores(gv_ctx *ctx, const uint32_t *host_first, const uint32_t
     GV_HIP(ctx, hipMemcpyAsync(dev_ids, host_first, count * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
     GV_HIP(ctx, hipMemcpyAsync(dev_ids + count, host_second, count * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
     GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, dev_ids, dev_ids + count, (uint32_t)count, dev_out,
-                                  ctx->error_flag, ctx->compute));
+                                  ctx->error_flag + 2, ctx->compute));
     GV_HIP(ctx, hipMemcpyAsync(host_out, dev_out, count * sizeof(float), hipMemcpyDeviceToHost, ctx->compute));
     GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
     return GV_OK;
@@ -1472,7 +1478,7 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
         GV_HIP(ctx, upload(dev_second, host_edge_second, num_edges));
         GV_HIP(ctx, upload(dev_second + num_edges, host_other_second, num_others));
         GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, dev_first, dev_second, (uint32_t)count, dev_scores,
-                                      ctx->error_flag, ctx->compute));
+                                      ctx->error_flag + 2, ctx->compute));
         GV_HIP(ctx, gv::launch_rank_statistic((uint32_t *)dev_scores, (uint32_t)num_edges, (uint32_t)num_others, dev_sorting,
                                               dev_sums, dev_sums + gv::kRankBlocks, ctx->compute));
         const unsigned long long *sums = ctx->results->sums;

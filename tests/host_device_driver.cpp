@@ -121,6 +121,7 @@ struct Trained {  // of deterministic mode, in the order of training
 };
 std::vector<Trained> trained;
 uint32_t levels_trained = 0;
+int training_reports = -1;  // word of the error flag that asynchronous training sets, if any
 bool walked_weighted = false;  // by the device producer
 uint64_t touched = 0;  // of the arrays that a kernel would read
 
@@ -135,8 +136,14 @@ void read_all(const T *array, uint64_t count) {
 
 namespace gv {
 AsyncPlan async_plan(const AsyncPool &p) { return AsyncPlan{p.tiled, p.coherence, p.tiled ? 8192u : 64u, 1u}; }
-hipError_t launch_train_hogwild(const TrainArgs &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_train_tiled(const TrainArgs &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_train_hogwild(const TrainArgs &a, uint32_t, uint32_t, uint32_t, hipStream_t) {
+    if (training_reports >= 0) a.error_flag[training_reports] = 1u;
+    return hipSuccess;
+}
+hipError_t launch_train_tiled(const TrainArgs &a, uint32_t, uint32_t, uint32_t, hipStream_t) {
+    if (training_reports >= 0) a.error_flag[training_reports] = 1u;
+    return hipSuccess;
+}
 hipError_t launch_train_hogwild_tracked(const TrainArgs &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_train_tiled_tracked(const TrainArgs &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_train_levels(const TrainArgs &a, uint32_t, uint32_t num_neg, hipStream_t) {
@@ -182,14 +189,21 @@ hipError_t launch_draw_negatives_partitioned(const uint4 *, const uint64_t *, co
     return hipSuccess;
 }
 hipError_t launch_init_vertex(float *, uint64_t, uint32_t, uint64_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_eval_loss(TrainArgs, uint32_t, uint32_t, double *partial, uint32_t *blocks, hipStream_t) {
+hipError_t launch_eval_loss(TrainArgs a, uint32_t, uint32_t, double *partial, uint32_t *blocks, hipStream_t) {
     *blocks = 1;
     partial[0] = 0.0;
+    for (uint32_t i = 0; i < a.count; ++i) {
+        if (a.pairs[2 * i] < a.n && a.pairs[2 * i + 1] < a.n) partial[0] += 0.5;
+        else *a.error_flag = 1u;
+    }
     return hipSuccess;
 }
-hipError_t launch_cosine(const float *, uint32_t, uint32_t, const uint32_t *first, const uint32_t *second, uint32_t count,
-                         float *out, uint32_t *, hipStream_t) {
-    for (uint32_t i = 0; i < count; ++i) out[i] = (float)first[i] - (float)second[i];
+hipError_t launch_cosine(const float *, uint32_t n, uint32_t, const uint32_t *first, const uint32_t *second, uint32_t count,
+                         float *out, uint32_t *error_flag, hipStream_t) {
+    for (uint32_t i = 0; i < count; ++i) {
+        out[i] = (float)first[i] - (float)second[i];
+        if (first[i] >= n || second[i] >= n) *error_flag = 1u;
+    }
     return hipSuccess;
 }
 uint64_t rank_scratch_words(uint32_t num_neg) { return num_neg; }
@@ -384,12 +398,52 @@ void walks_after_failed_allocations() {
     }
     CHECK(refused == 2);
 }
+
+// What training has to report comes first, whatever the evaluation call that waits for it was given, and the call's own
+// bad ids are reported by the next call that names them.
+void reports_of_evaluation() {
+    const std::vector<uint32_t> degrees(10, 3), good = {0, 1, 2, 3}, bad = {0, 1, 2, 10}, other = {4, 5};
+    gv_ctx *ctx = context(GV_MODE_HOGWILD, 1);
+    CHECK(gv_set_degrees(ctx, 10, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+    double result = 0.0;
+    auto loss = [&](const std::vector<uint32_t> &pairs) {
+        result = -1.0;
+        return gv_eval_loss(ctx, pairs.data(), 2, 1, &result);
+    };
+    auto auc = [&](const std::vector<uint32_t> &pairs) {
+        result = -1.0;
+        return gv_link_prediction_auc(ctx, pairs.data(), pairs.data() + 2, 2, other.data(), other.data() + 1, 1, &result);
+    };
+    for (int word : {0, 1}) {
+        const int code = word == 0 ? GV_EINVAL : GV_ESTATE;
+        auto train = [&] {
+            training_reports = word;
+            CHECK(gv_train_device_pool(ctx, good.data(), 2) == GV_OK);
+        };
+        train();
+        CHECK(loss(bad) == code && result == -1.0);
+        CHECK(loss(bad) == GV_EINVAL && result == 0.25);  // of the pairs whose ids are nodes
+        CHECK(loss(good) == GV_OK && result == 0.5);
+        train();
+        CHECK(loss(good) == code && result == -1.0 && loss(good) == GV_OK);
+        train();
+        CHECK(auc(bad) == code && auc(bad) == GV_EINVAL && result == -1.0 && auc(good) == GV_OK);
+        train();
+        CHECK(auc(good) == code && auc(good) == GV_OK && gv_sync(ctx) == GV_OK);
+        float scores[2];
+        train();
+        CHECK(gv_cosine(ctx, bad.data(), bad.data() + 2, 2, scores) == code);
+        CHECK(gv_cosine(ctx, bad.data(), bad.data() + 2, 2, scores) == GV_EINVAL && gv_sync(ctx) == GV_OK);
+    }
+    gv_destroy(ctx);
+}
 }  // namespace
 
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"levels after failed allocations", levels_after_failed_allocations},
         {"walks after failed allocations", walks_after_failed_allocations},
+        {"reports of evaluation", reports_of_evaluation},
     };
     if (argc != 2 || !checks.count(argv[1])) return 2;
     checks.at(argv[1])();
