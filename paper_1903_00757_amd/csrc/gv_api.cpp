@@ -454,6 +454,7 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
     }
     a.unit = plan.unit;
     a.blocks = plan.blocks;
+    a.exchange_every = plan.exchange_every;
     a.report_divergence = tiled ? 1u : 0u;
     if (plan.tiled) {
         a.records = fixed_records ? fixed_records : ctx->records;

@@ -7,6 +7,23 @@
 
 namespace gv {
 
+constexpr int kWave = 64;
+constexpr int kBlock = 256;  // 4 waves per workgroup
+// Row traffic policies (gv_config.coherence).
+constexpr int kPlain = 0;        // cached loads and stores
+constexpr int kAgent = 1;        // device-scope loads and stores
+constexpr int kAtomicAgent = 2;  // device-scope loads, updates as device-scope fp32 atomic adds
+constexpr int kMixed = 3;        // as kAtomicAgent for rows flagged warm, plain device-scope store otherwise
+
+constexpr uint32_t kSmallestTile = 16, kLargestTile = 8192;  // samples per workgroup of the tiled kernel
+
+// samples whose gathers a wave of the tiled kernel has in flight together (V floats of a row per lane, K negatives).
+// Four of short rows fit the registers, but twice the workgroups with two each keep the same number in flight and wait
+// less between a gather and its use (2.2*10^6 samples, d = 128, K = 1: 2.29 ms with four in tiles of 8192, 1.73 with two
+// in tiles of 4096; 2^24: 9.80 and 9.67 ms in tiles of 8192).
+__host__ __device__ constexpr bool short_rows(int V, int K) { return V * (K + 1) <= 4; }
+__host__ __device__ constexpr int tiled_batch(int V, int K) { return V * (K + 1) <= 12 ? 2 : 1; }
+
 // Everything a training launch needs; passed by value as the kernel argument.
 struct TrainArgs {
     float *vertex;            // |V| x d, row-major
@@ -39,7 +56,7 @@ struct TrainArgs {
     uint64_t total;           // T of the learning-rate schedule
     uint64_t seed;            // Philox key of the negative stream
     uint32_t count;           // samples in this launch
-    uint32_t unit, blocks;    // asynchronous launches: see AsyncPlan
+    uint32_t unit, blocks, exchange_every; // asynchronous launches: see AsyncPlan
     uint32_t report_divergence; // pool order: nonzero: a score that is NaN sets error_flag[1]
     uint32_t n;               // |V|
     uint32_t dim;             // d: row length in floats
@@ -64,10 +81,11 @@ struct AsyncPlan {
     uint32_t coherence;
     uint32_t unit;            // samples of a tile, or samples a wave takes at a time
     uint32_t blocks;          // workgroups
+    uint32_t exchange_every;  // samples after which a held row trades its change with memory (tiles only)
 };
-AsyncPlan async_plan(const AsyncPool &pool);
+AsyncPlan async_plan(const AsyncPool &pool);  // gv_plan.cpp
 
-// The launches take their shape from a.unit and a.blocks; all return the HIP error of the launch.
+// The launches take their shape from a.unit, a.blocks and a.exchange_every; all return the HIP error of the launch.
 hipError_t launch_train_hogwild(const TrainArgs &a, uint32_t dim, uint32_t num_neg, uint32_t coherence,
                                 hipStream_t stream);
 // Tiled stationary-row training (see k_train_tiled).
@@ -144,6 +162,7 @@ hipError_t launch_departure_guide(const uint64_t *offsets, uint32_t n, uint64_t 
 hipError_t launch_augment(const AugmentArgs &a, hipStream_t stream);
 
 bool supported_shape(uint32_t dim, uint32_t num_neg);
+int floats_per_lane(uint32_t dim);
 // samples whose rows one wave of the tiled kernel gathers together (2, or 1 where rows are long)
 uint32_t samples_per_batch(uint32_t dim, uint32_t num_neg);
 

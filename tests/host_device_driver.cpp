@@ -135,7 +135,6 @@ void read_all(const T *array, uint64_t count) {
 }  // namespace
 
 namespace gv {
-AsyncPlan async_plan(const AsyncPool &p) { return AsyncPlan{p.tiled, p.coherence, p.tiled ? 8192u : 64u, 1u}; }
 hipError_t launch_train_hogwild(const TrainArgs &a, uint32_t, uint32_t, uint32_t, hipStream_t) {
     if (training_reports >= 0) a.error_flag[training_reports] = 1u;
     return hipSuccess;
@@ -250,8 +249,6 @@ hipError_t launch_augment(const AugmentArgs &a, hipStream_t) {
     if (a.nbr_table) read_all(a.nbr_table, a.half_edges);
     return hipSuccess;
 }
-bool supported_shape(uint32_t dim, uint32_t num_neg) { return dim % 32 == 0 && dim <= 512 && num_neg >= 1 && num_neg <= 5; }
-uint32_t samples_per_batch(uint32_t, uint32_t) { return 2; }
 }  // namespace gv
 
 // ---------------------------------------------------------------------------------------------------- checks
@@ -437,6 +434,67 @@ void reports_of_evaluation() {
     }
     gv_destroy(ctx);
 }
+
+// Every kind of pool against the plan that it is meant to get, and what the launches rely on for pools of all sizes.
+void plans_of_pools() {
+    using gv::AsyncPlan;
+    using gv::AsyncPool;
+    constexpr uint32_t agent = gv::kAgent, atomic = gv::kAtomicAgent, mixed = gv::kMixed;
+    struct Expected {
+        const char *what;
+        AsyncPool pool;  // samples, n, dim, K, policy, tiled schedule, may skip tiles, block, warm rows, hottest share
+        AsyncPlan plan;  // tiles, policy, samples to a tile or wave, workgroups, exchange every
+    };
+    const Expected all[] = {
+        {"a pool that fills the chip", {1 << 24, 1000000, 128, 1, mixed, true, true, false, 15000, 0.011}, {true, mixed, 8192, 2048, 4}},
+        {"long rows", {1 << 22, 1000000, 512, 5, mixed, true, true, false, 8000, 0.011}, {true, mixed, 8192, 512, 2}},
+        {"rows of 64 floats", {1 << 24, 1000000, 64, 1, mixed, true, true, false, 15000, 0.011}, {true, mixed, 4096, 4096, 4}},
+        {"too few tiles of 8192 to fill the chip", {3000000, 1000000, 128, 1, mixed, true, true, false, 15000, 0.011}, {true, mixed, 4096, 733, 4}},
+        {"short enough for atomic adds, hubs", {1 << 20, 1000000, 64, 2, mixed, true, true, false, 15000, 0.011}, {true, atomic, 1024, 1024, 4}},
+        {"the same, few hubs", {1000003, 200003, 96, 3, mixed, true, true, false, 30000, 0.01}, {false, atomic, 16, 256, 0}},
+        {"a few thousand samples", {4096, 100000, 128, 1, mixed, true, true, false, 20000, 0.005}, {false, atomic, 4, 256, 0}},
+        {"a small graph, all rows warm", {2000000, 10000, 128, 1, mixed, true, true, false, 10000, 0.006}, {false, atomic, 16, 156, 0}},
+        {"short pool, hubs", {65536, 100000, 64, 1, mixed, true, true, false, 20000, 0.035}, {true, atomic, 64, 1024, 4}},
+        {"tiles asked for", {4099, 200000, 128, 1, mixed, true, false, false, 60000, 0.0001}, {true, atomic, 16, 257, 4}},
+        {"tiles and stores asked for", {100000, 100000, 128, 1, agent, true, false, false, 20000, 0.01}, {true, agent, 8192, 13, 4}},
+        {"tiles and atomic adds asked for", {1 << 24, 1000000, 128, 1, atomic, true, false, false, 15000, 0.011}, {true, atomic, 8192, 2048, 4}},
+        {"one block of a partitioned graph", {1 << 18, 1000000, 128, 1, mixed, true, true, true, 65535, 0.011}, {true, mixed, 8192, 32, 2}},
+        {"no warm row", {1 << 22, 4000000, 128, 1, agent, false, true, false, 0, 0.0}, {false, agent, 64, 2048, 0}},
+        {"pool order and atomic adds asked for", {1 << 24, 1000000, 128, 1, atomic, false, false, false, 15000, 0.011}, {false, atomic, 64, 2048, 0}},
+    };
+    for (const Expected &e : all) {
+        const AsyncPlan got = gv::async_plan(e.pool), &want = e.plan;
+        const bool same = got.tiled == want.tiled && got.coherence == want.coherence && got.unit == want.unit &&
+                          got.blocks == want.blocks && got.exchange_every == want.exchange_every;
+        if (!same)
+            fprintf(stderr, "%s: {%d, %u, %u, %u, %u}\n", e.what, got.tiled, got.coherence, got.unit, got.blocks, got.exchange_every);
+        CHECK(same);
+    }
+    for (uint32_t n : {2u, 100u, 10000u, 65535u, 65536u, 300000u, 1000000u, 66000000u, 0x80000000u})
+        for (uint32_t dim : {32u, 64u, 128u, 160u, 512u})
+            for (uint32_t K : {1u, 2u, 5u})
+                for (uint64_t count : {1ull, 15ull, 4096ull, 100003ull, 1000000ull, 3000000ull, 1ull << 24, 1ull << 31})
+                    for (uint32_t policy : {(uint32_t)gv::kPlain, agent, atomic, mixed})
+                        for (int flags = 0; flags < 8; ++flags)
+                            for (double share : {0.0, 0.01, 1.0}) {
+                                const bool tiled = flags & 1, skip = flags & 2, block = flags & 4;
+                                const AsyncPlan p = gv::async_plan(AsyncPool{count, n, dim, K, policy, tiled, skip, block,
+                                                                            std::min(n, 65535u) / 2u, share});
+                                CHECK(p.blocks >= 1 && p.blocks <= (count + p.unit - 1) / p.unit);
+                                CHECK(tiled || !p.tiled);                       // pool order is never left
+                                CHECK(p.tiled || !tiled || (skip && policy == mixed));  // tiles only where they may be
+                                CHECK(p.coherence == policy || p.coherence == atomic);  // no update is lost that was kept
+                                if (p.tiled) {
+                                    CHECK(p.unit >= gv::kSmallestTile && p.unit <= gv::kLargestTile && !(p.unit & (p.unit - 1)));
+                                    CHECK(p.unit == gv::kLargestTile || p.coherence == atomic ||  // the instantiations there are
+                                          (p.coherence == mixed && gv::short_rows(gv::floats_per_lane(dim), (int)K)));
+                                    CHECK(p.exchange_every == 2 || p.exchange_every == 4);
+                                } else {
+                                    CHECK(p.unit >= 1 && p.unit <= 64);
+                                    CHECK(policy != agent || p.coherence == agent);
+                                }
+                            }
+}
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -444,6 +502,7 @@ int main(int argc, char **argv) {
         {"levels after failed allocations", levels_after_failed_allocations},
         {"walks after failed allocations", walks_after_failed_allocations},
         {"reports of evaluation", reports_of_evaluation},
+        {"plans of pools", plans_of_pools},
     };
     if (argc != 2 || !checks.count(argv[1])) return 2;
     checks.at(argv[1])();

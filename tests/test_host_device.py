@@ -1,5 +1,5 @@
 """The runtime behind the C boundary on a device made of host memory (no GPU): tests/host_device_driver.cpp defines the
-HIP calls and the launches, is built with gv_api.cpp under AddressSanitizer and UndefinedBehaviorSanitizer, and checks
+HIP calls and the launches, is built with the host sources under AddressSanitizer and UndefinedBehaviorSanitizer, and checks
 what happens when memory runs out and what the kernels are handed."""
 import os
 import subprocess
@@ -22,7 +22,7 @@ def driver(tmp_path_factory):
     common = [HIPCC, "-std=c++17", "-O1", "-g", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
               "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
     objects = []
-    for src in (os.path.join(CSRC, "gv_api.cpp"), os.path.join(CSRC, "gv_augment.cpp"), DRIVER):
+    for src in [os.path.join(CSRC, f) for f in ("gv_api.cpp", "gv_plan.cpp", "gv_augment.cpp")] + [DRIVER]:
         obj = str(out / (os.path.basename(src) + ".o"))
         subprocess.run([*common, "-x", "hip", *sanitizers, "-c", src, "-o", obj], check=True, capture_output=True, text=True)
         objects.append(obj)
@@ -32,7 +32,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["levels after failed allocations", "walks after failed allocations", "reports of evaluation"])
+@pytest.mark.parametrize("check", ["levels after failed allocations", "walks after failed allocations", "reports of evaluation",
+                                   "plans of pools"])
 def test_host_runtime(driver, check):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1:alloc_dealloc_mismatch=0",
                UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1")

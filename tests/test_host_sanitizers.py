@@ -53,7 +53,8 @@ def test_host_runtime_under_address_and_undefined_behaviour_sanitizers(tmp_path)
     common = [HIPCC, "-std=c++17", "-O1", "-g", "--offload-arch=gfx950", "-munsafe-fp-atomics", "-Xclang", "-target-feature",
               "-Xclang", "-packed-fp32-ops", *INCLUDES]
     objects = []
-    sources = [("gv_api.cpp", ["-x", "hip", *host_flags], "gv_api.o"), ("gv_augment.cpp", host_flags, "gv_augment.o")]
+    sources = [("gv_api.cpp", ["-x", "hip", *host_flags], "gv_api.o"), ("gv_plan.cpp", ["-x", "hip", *host_flags], "gv_plan.o"),
+               ("gv_augment.cpp", host_flags, "gv_augment.o")]
     # the kernels (two objects, see the head of gv_kernels.hip) are only linked, never launched: the objects of the
     # regular build will do when they are up to date
     kernel_sources = [os.path.join(CSRC, f) for f in ("gv_kernels.hip", "gv_internal.hpp")]
