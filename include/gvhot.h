@@ -123,8 +123,8 @@ typedef struct gv_stats {
     uint64_t timed_launches;    /* launches contributing to train_kernel_ms                    */
     double h2d_ms;              /* event-timed pool copies host -> device (profile != 0)        */
     uint64_t h2d_bytes;
-    uint64_t tiled_launches;    /* asynchronous launches under the tiled schedule (short pools that
-                                   GV_SCHEDULE_AUTO walks in pool order for speed among them)    */
+    uint64_t tiled_launches;    /* asynchronous launches that walked their pool in tiles (not the short pools
+                                   that GV_SCHEDULE_AUTO takes in pool order)                    */
     uint64_t warm_rows;         /* rows that gv_build_alias classed as warm (see GV_SCHEDULE_AUTO) */
     double train_loss_sum;      /* track_loss != 0: sum over the samples trained so far of the loss (Alg. 1 with
                                    the logistic loss of negative sampling, as gv_eval_loss) each of them saw

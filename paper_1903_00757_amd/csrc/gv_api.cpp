@@ -465,7 +465,7 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
                         a, ctx->cfg.dim, ctx->cfg.num_neg, plan.coherence, ctx->compute));
     }
     ctx->stats.train_launches += 1;
-    ctx->stats.tiled_launches += tiled ? 1 : 0;
+    ctx->stats.tiled_launches += plan.tiled ? 1 : 0;
     if (ctx->dev_loss) ctx->stats.train_loss_samples += count;
     if (timed) return end_span(ctx, ctx->compute, span);
     return GV_OK;

@@ -122,6 +122,7 @@ struct Trained {  // of deterministic mode, in the order of training
 std::vector<Trained> trained;
 uint32_t levels_trained = 0;
 int training_reports = -1;  // word of the error flag that asynchronous training sets, if any
+bool tiled_launched = false;
 bool walked_weighted = false;  // by the device producer
 uint64_t touched = 0;  // of the arrays that a kernel would read
 
@@ -140,6 +141,7 @@ hipError_t launch_train_hogwild(const TrainArgs &a, uint32_t, uint32_t, uint32_t
     return hipSuccess;
 }
 hipError_t launch_train_tiled(const TrainArgs &a, uint32_t, uint32_t, uint32_t, hipStream_t) {
+    tiled_launched = true;
     if (training_reports >= 0) a.error_flag[training_reports] = 1u;
     return hipSuccess;
 }
@@ -253,7 +255,7 @@ hipError_t launch_augment(const AugmentArgs &a, hipStream_t) {
 
 // ---------------------------------------------------------------------------------------------------- checks
 namespace {
-gv_ctx *context(uint32_t mode, uint32_t num_neg) {
+gv_ctx *context(uint32_t mode, uint32_t num_neg, uint32_t schedule = GV_SCHEDULE_AUTO) {
     gv_config cfg{};
     cfg.dim = 32;
     cfg.num_neg = num_neg;
@@ -263,7 +265,7 @@ gv_ctx *context(uint32_t mode, uint32_t num_neg) {
     cfg.total_samples = 1000000;
     cfg.pool_capacity = 8;
     cfg.coherence = GV_COHERENCE_MIXED;
-    cfg.schedule = GV_SCHEDULE_AUTO;
+    cfg.schedule = schedule;
     gv_ctx *ctx = nullptr;
     CHECK(gv_create(&cfg, &ctx) == GV_OK);
     return ctx;
@@ -495,6 +497,32 @@ void plans_of_pools() {
                                 }
                             }
 }
+
+// gv_stats.tiled_launches counts the launches of the tiled kernel, whatever the schedule of the graph.
+void counted_launches() {
+    const uint32_t n = 20000;
+    std::vector<uint32_t> degrees(n, 3), pool = random_pool(n, 400000, 3);
+    degrees[7] = 3000;  // a few percent of the samples name it
+    struct Expected {
+        uint32_t schedule, hub;
+        uint64_t count;
+        bool tiled;
+    };
+    for (const Expected &e : {Expected{GV_SCHEDULE_AUTO, 3000, 400000, true}, Expected{GV_SCHEDULE_AUTO, 3, 400000, false},
+                              Expected{GV_SCHEDULE_AUTO, 3000, 100, false}, Expected{GV_SCHEDULE_TILED, 3, 100, true},
+                              Expected{GV_SCHEDULE_POOL_ORDER, 3000, 400000, false}}) {
+        degrees[7] = e.hub;
+        gv_ctx *ctx = context(GV_MODE_HOGWILD, 1, e.schedule);
+        CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+        training_reports = -1;
+        tiled_launched = false;
+        CHECK(gv_train_device_pool(ctx, pool.data(), e.count) == GV_OK);
+        gv_stats stats;
+        CHECK(gv_get_stats(ctx, &stats) == GV_OK && stats.train_launches == 1);
+        CHECK(tiled_launched == e.tiled && stats.tiled_launches == (e.tiled ? 1u : 0u));
+        gv_destroy(ctx);
+    }
+}
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -503,6 +531,7 @@ int main(int argc, char **argv) {
         {"walks after failed allocations", walks_after_failed_allocations},
         {"reports of evaluation", reports_of_evaluation},
         {"plans of pools", plans_of_pools},
+        {"counted launches", counted_launches},
     };
     if (argc != 2 || !checks.count(argv[1])) return 2;
     checks.at(argv[1])();

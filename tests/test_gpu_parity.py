@@ -666,16 +666,20 @@ def test_random_sharing_of_a_few_rows_is_exact(gv, policy, d, K, trial, samples,
 
 
 def test_schedule_is_chosen_from_the_graph(gv, tiny_graph):
-    """GV_SCHEDULE_AUTO: a graph with rows that concurrent samples share is trained with the tiled schedule, one
-    without (4*10^5 nodes of equal degree: each is named by 2 of 8192 samples in flight with probability 0.04) in
-    pool order."""
+    """GV_SCHEDULE_AUTO: a graph with rows that concurrent samples share is trained in tiles where the pool is long
+    enough for them to pay (2*10^6 samples on 10^6 nodes with a hub), in pool order where it is not; one without such
+    rows (4*10^5 nodes of equal degree: each is named by 2 of 8192 samples in flight with probability 0.04) in pool
+    order."""
     g = tiny_graph
     rng = np.random.default_rng(1)
-    flat_n = 400_000
-    cases = ((g["deg"], np.stack([g["src"][:5000], g["dst"][:5000]], axis=1), True),
-             (np.full(flat_n, 3, dtype=np.uint32), rng.integers(flat_n, size=(5000, 2)).astype(np.uint32), False))
-    for deg, pool, tiled in cases:
-        with context_for(gv, dim=32, num_neg=1, total_samples=10_000, pool_capacity=5000) as ctx:
+    flat_n, hub_n = 400_000, 1_000_000
+    hub = rng.integers(1, 10, size=hub_n).astype(np.uint32)
+    hub[:100] = 50_000
+    cases = ((hub, rng.integers(hub_n, size=(2_000_000, 2)).astype(np.uint32), True, True),
+             (g["deg"], np.stack([g["src"][:5000], g["dst"][:5000]], axis=1), True, False),
+             (np.full(flat_n, 3, dtype=np.uint32), rng.integers(flat_n, size=(5000, 2)).astype(np.uint32), False, False))
+    for deg, pool, shared, tiled in cases:
+        with context_for(gv, dim=32, num_neg=1, total_samples=10 * pool.shape[0], pool_capacity=pool.shape[0]) as ctx:
             gv.gv_set_degrees(ctx, deg)
             gv.gv_build_alias(ctx, 0.75)
             gv.gv_init_embeddings(ctx, 1)
@@ -683,7 +687,7 @@ def test_schedule_is_chosen_from_the_graph(gv, tiny_graph):
             gv.gv_train_pool(ctx)
             gv.gv_sync(ctx)
             stats = gv.gv_get_stats(ctx)
-            assert (stats["tiled_launches"] == 1) == tiled and (stats["warm_rows"] > 0) == tiled
+            assert (stats["tiled_launches"] == 1) == tiled and (stats["warm_rows"] > 0) == shared
             assert np.abs(gv.gv_read_embeddings(ctx, gv.GV_CONTEXT, deg.size, 32)).max() > 0
 
 

@@ -32,8 +32,13 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["levels after failed allocations", "walks after failed allocations", "reports of evaluation",
-                                   "plans of pools"])
+@pytest.mark.parametrize("check", [
+    "levels after failed allocations",
+    "walks after failed allocations",
+    "reports of evaluation",
+    "plans of pools",
+    "counted launches",
+])
 def test_host_runtime(driver, check):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1:alloc_dealloc_mismatch=0",
                UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1")
