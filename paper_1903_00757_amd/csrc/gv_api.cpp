@@ -428,7 +428,8 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
         coherence = GV_COHERENCE_AGENT;
     const gv::AsyncPlan plan = gv::async_plan(gv::AsyncPool{count, ctx->n, ctx->cfg.dim, ctx->cfg.num_neg, coherence, tiled,
                                                             ctx->cfg.schedule == GV_SCHEDULE_AUTO, block != nullptr,
-                                                            ctx->warm_ranks, ctx->hottest_share});
+                                                            ctx->warm_ranks,
+                                                            ctx->hottest_share * (block ? ctx->cfg.partitions : 1u)});
     if (tiled && fixed_records) {
         const uint64_t words = count * (ctx->cfg.num_neg + 3);
         if (words > GV_STATIC_SCRATCH_WORDS)

@@ -74,7 +74,7 @@ struct AsyncPool {
     bool may_skip_tiles;      // ... and a pool that gains nothing from tiles may be walked in pool order (GV_SCHEDULE_AUTO)
     bool part_of_pool;        // one block of a partitioned graph
     uint32_t warm_ranks;
-    double hottest_share;     // share of the samples that name the hottest context row
+    double hottest_share;     // share of these samples that name the hottest context row
 };
 struct AsyncPlan {
     bool tiled;               // k_train_tiled, otherwise k_train_hogwild

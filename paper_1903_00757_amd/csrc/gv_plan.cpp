@@ -45,16 +45,25 @@ AsyncPlan async_plan(const AsyncPool &p) {
     // small part of a sample's traffic: the shorter interval halves how far the run's scores lag behind the other
     // holders of the row (measured on d = 512, K = 5: distance to the sequential trajectory after 4 pools
     // -0.33 % -> -0.10 % in loss at 3 % more time).
-    // A block of a partitioned graph, whose hottest row several percent of its samples name, is at the limit of what
-    // is stable with four (one long run in six of 8 x 8 blocks on a million nodes ran away): two there as well.
-    const uint32_t exchange_every = shorts && !p.part_of_pool ? 4u : 2u;
+    // The samples of a block of a partitioned graph name its rows `partitions` times as often as those of a pool, and with
+    // an interval of four its hottest rows run away once some 300 of the samples in flight name one of them: a million
+    // nodes, exponent 2.1, pools of 2^24 in 4 x 4 blocks (600 such samples) and 8 x 8 (300): every long run diverged, 2 x 2
+    // (590 of a share half as large): ends 0.5 % higher in loss than with two.  Where at most 128 do, four is as good as
+    // two to the fourth digit of the loss, and faster (exponent 2.5: 2 x 2, 115 samples, 2.42 against 2.33*10^9 samples/s;
+    // 8 x 8, 57 samples, 5.9 against 5.5*10^8; 200000 nodes in 2 x 2, 49 samples: 1.10*10^9 against 0.98); at 190 it
+    // ends 0.2 % higher.
+    auto exchange_every = [&](uint32_t blocks) {
+        if (!shorts) return 2u;
+        const double in_flight = (double)std::min(blocks, kFullGrid) * kWaves * tiled_batch(floats_per_lane(p.dim), (int)p.num_neg);
+        return p.part_of_pool && in_flight * p.hottest_share > 128.0 ? 2u : 4u;
+    };
     auto tiled = [&](uint32_t coherence, uint32_t tile) {
         // one workgroup per tile, started by the hardware in tile order as earlier ones end, unless the graph is so
         // small that a fixed number of workgroups has to stride over the tiles (n / 8 samples in flight where rows are
         // short, else n / 16)
         const uint32_t most = std::min(shorts ? 2u * by_rows : by_rows, kFullGrid);
-        return AsyncPlan{true, coherence, tile, most == kFullGrid ? pieces(tile) : std::min(pieces(tile), most),
-                         exchange_every};
+        const uint32_t blocks = most == kFullGrid ? pieces(tile) : std::min(pieces(tile), most);
+        return AsyncPlan{true, coherence, tile, blocks, exchange_every(blocks)};
     };
     auto pool_order = [&](uint32_t coherence, uint32_t chunk, uint32_t blocks) {
         return AsyncPlan{false, coherence, chunk, std::min((pieces(chunk) + kWaves - 1) / kWaves, blocks), 0u};

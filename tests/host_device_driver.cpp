@@ -460,7 +460,11 @@ void plans_of_pools() {
         {"tiles asked for", {4099, 200000, 128, 1, mixed, true, false, false, 60000, 0.0001}, {true, atomic, 16, 257, 4}},
         {"tiles and stores asked for", {100000, 100000, 128, 1, agent, true, false, false, 20000, 0.01}, {true, agent, 8192, 13, 4}},
         {"tiles and atomic adds asked for", {1 << 24, 1000000, 128, 1, atomic, true, false, false, 15000, 0.011}, {true, atomic, 8192, 2048, 4}},
-        {"one block of a partitioned graph", {1 << 18, 1000000, 128, 1, mixed, true, true, true, 65535, 0.011}, {true, mixed, 8192, 32, 2}},
+        {"one of 8 x 8 blocks, hubs", {1 << 21, 1000000, 128, 1, mixed, true, true, true, 65535, 0.145}, {true, mixed, 8192, 256, 2}},
+        {"one of 2 x 2 blocks, hubs", {1 << 25, 1000000, 128, 1, mixed, true, true, true, 65535, 0.036}, {true, mixed, 8192, 4096, 2}},
+        {"one of 8 x 8 blocks, few hubs", {1 << 21, 1000000, 64, 1, mixed, true, true, true, 65535, 0.028}, {true, mixed, 8192, 256, 4}},
+        {"one of 2 x 2 blocks, few hubs", {1 << 25, 1000000, 64, 1, mixed, true, true, true, 65535, 0.007}, {true, mixed, 8192, 4096, 4}},
+        {"a block with long rows", {1 << 18, 1000000, 256, 1, mixed, true, true, true, 65535, 0.007}, {true, mixed, 8192, 32, 2}},
         {"no warm row", {1 << 22, 4000000, 128, 1, agent, false, true, false, 0, 0.0}, {false, agent, 64, 2048, 0}},
         {"pool order and atomic adds asked for", {1 << 24, 1000000, 128, 1, atomic, false, false, false, 15000, 0.011}, {false, atomic, 64, 2048, 0}},
     };
