@@ -41,6 +41,7 @@ AsyncPlan async_plan(const AsyncPool &p) {
     constexpr uint32_t kFullGrid = 2048;  // workgroups that fill the chip
     const uint32_t by_rows = std::max(p.n / 32u / kWaves, 64u), limit = std::min(by_rows, kFullGrid);
     const bool shorts = short_rows(floats_per_lane(p.dim), (int)p.num_neg);
+    const uint32_t batch = samples_per_batch(p.dim, p.num_neg);
     // A held row trades with memory every four samples, or every two where rows are so long that an exchange is a
     // small part of a sample's traffic: the shorter interval halves how far the run's scores lag behind the other
     // holders of the row (measured on d = 512, K = 5: distance to the sequential trajectory after 4 pools
@@ -54,13 +55,13 @@ AsyncPlan async_plan(const AsyncPool &p) {
     // ends 0.2 % higher.
     auto exchange_every = [&](uint32_t blocks) {
         if (!shorts) return 2u;
-        const double in_flight = (double)std::min(blocks, kFullGrid) * kWaves * tiled_batch(floats_per_lane(p.dim), (int)p.num_neg);
+        const double in_flight = (double)std::min(blocks, kFullGrid) * kWaves * batch;
         return p.part_of_pool && in_flight * p.hottest_share > 128.0 ? 2u : 4u;
     };
     auto tiled = [&](uint32_t coherence, uint32_t tile) {
         // one workgroup per tile, started by the hardware in tile order as earlier ones end, unless the graph is so
         // small that a fixed number of workgroups has to stride over the tiles (n / 8 samples in flight where rows are
-        // short, else n / 16)
+        // short, else n / 16 or n / 32)
         const uint32_t most = std::min(shorts ? 2u * by_rows : by_rows, kFullGrid);
         const uint32_t blocks = most == kFullGrid ? pieces(tile) : std::min(pieces(tile), most);
         return AsyncPlan{true, coherence, tile, blocks, exchange_every(blocks)};
@@ -87,7 +88,12 @@ AsyncPlan async_plan(const AsyncPool &p) {
 
     uint32_t tile = kSmallestTile;
     while (tile < kLargestTile && (uint64_t)tile * 2048u <= p.count) tile *= 2;  // 1024 .. 2047 tiles
-    const AsyncPlan small = tiled(kAtomicAgent, tile);
+    // n / 32 samples in flight (at least 256 workgroups): the hottest rows set the pace, and four times as many took as
+    // long and left training further behind (10^5 nodes, exponent 2.1, d = 64, K = 1, whole runs from a learning rate of
+    // 0.025, final loss against the sequential one: pools of 500000, 65536 and 8192 samples +1.5, +0.9 and +0.3 % at n / 8,
+    // +0.4, +0.3 and +0.2 % at n / 32; 490 -> 500, 96 -> 98 and 16 -> 20 us a pool).
+    AsyncPlan small = tiled(kAtomicAgent, tile);
+    if (tile < kLargestTile) small.blocks = std::min(small.blocks, std::max(p.n / 32u / (kWaves * batch), 256u));
     const double small_us = std::max({add_us, 0.25 * hot_us, walk_us(small)});
 
     // in pool order a wave has one sample in flight instead of a batch: n / 16 waves are half of what tiles have

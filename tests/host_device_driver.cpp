@@ -456,8 +456,10 @@ void plans_of_pools() {
         {"the same, few hubs", {1000003, 200003, 96, 3, mixed, true, true, false, 30000, 0.01}, {false, atomic, 16, 256, 0}},
         {"a few thousand samples", {4096, 100000, 128, 1, mixed, true, true, false, 20000, 0.005}, {false, atomic, 4, 256, 0}},
         {"a small graph, all rows warm", {2000000, 10000, 128, 1, mixed, true, true, false, 10000, 0.006}, {false, atomic, 16, 156, 0}},
-        {"short pool, hubs", {65536, 100000, 64, 1, mixed, true, true, false, 20000, 0.035}, {true, atomic, 64, 1024, 4}},
-        {"tiles asked for", {4099, 200000, 128, 1, mixed, true, false, false, 60000, 0.0001}, {true, atomic, 16, 257, 4}},
+        {"short pool, hubs", {65536, 100000, 64, 1, mixed, true, true, false, 20000, 0.035}, {true, atomic, 64, 390, 4}},
+        {"shorter pool, hubs", {8192, 100000, 64, 1, mixed, true, true, false, 20000, 0.035}, {true, atomic, 16, 390, 4}},
+        {"short pool, hubs, fewer nodes", {65536, 30000, 64, 2, mixed, true, true, false, 20000, 0.03}, {true, atomic, 64, 256, 4}},
+        {"tiles asked for", {4099, 300000, 128, 1, mixed, true, false, false, 60000, 0.0001}, {true, atomic, 16, 257, 4}},
         {"tiles and stores asked for", {100000, 100000, 128, 1, agent, true, false, false, 20000, 0.01}, {true, agent, 8192, 13, 4}},
         {"tiles and atomic adds asked for", {1 << 24, 1000000, 128, 1, atomic, true, false, false, 15000, 0.011}, {true, atomic, 8192, 2048, 4}},
         {"one of 8 x 8 blocks, hubs", {1 << 21, 1000000, 128, 1, mixed, true, true, true, 65535, 0.145}, {true, mixed, 8192, 256, 2}},
