@@ -36,6 +36,11 @@ struct PoolSlot {
     SlotState state = kFree;
 };
 
+// Pairs that gv_link_prediction_auc ranks on the host: a sort of a few thousand there is over before the fourteen launches
+// of the device's sort are (a call of one pair against one: 103 us with the sort on the device, 37 on the host; 1000 against 1000:
+// 101 and 48).
+constexpr uint64_t kHostRanked = 4096;
+
 // What the host waits for at the end of a call, in pinned memory: copied there on the compute stream, so that one wait
 // for that stream is all (a blocking copy of a few bytes takes 20 us on top of it).
 struct HostResults {
@@ -44,6 +49,7 @@ struct HostResults {
     union {
         double partial[gv::kEvalBlocks];                          // gv_eval_loss
         unsigned long long sums[2 * gv::kRankBlocks];             // gv_link_prediction_auc
+        float scores[kHostRanked];                                // gv_link_prediction_auc of few pairs
     };
 };
 
@@ -1462,14 +1468,34 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
             return fail(ctx, GV_EINVAL, "null argument");
         if (num_edges == 0 || num_others == 0 || num_edges + num_others > (1ull << 31))
             return fail(ctx, GV_EINVAL, "both pair sets must be non-empty and hold at most 2^31 pairs together");
-        // scratch: the partial sums and flags, what sorting needs, the ends of the pairs, the scores
         const uint64_t count = num_edges + num_others;
-        constexpr uint64_t kSums = 2 * gv::kRankBlocks * sizeof(unsigned long long);
-        const uint64_t sorting = (gv::rank_scratch_words((uint32_t)num_others) + 3u) & ~3ull;
-        rc = ensure_eval_scratch(ctx, kSums + (sorting + 3 * count) * sizeof(uint32_t));
+        auto rank_on_host = [&](const float *scores) -> int {
+            for (uint64_t i = 0; i < count; ++i)
+                if (!isfinite(scores[i])) return fail(ctx, GV_EINVAL, "an embedding row is not finite");
+            *auc = rank_auc(scores, num_edges, scores + num_edges, num_others);
+            return GV_OK;
+        };
+        // scratch: what ranking on the device needs (the partial sums and flags, then the sort), the ends of the pairs, the
+        // scores
+        const bool few = count <= kHostRanked;
+        const uint64_t sums = few ? 0 : 2 * gv::kRankBlocks * sizeof(unsigned long long);
+        const uint64_t sorting = few ? 0 : (gv::rank_scratch_words((uint32_t)num_others) + 3u) & ~3ull;
+        rc = ensure_eval_scratch(ctx, sums + (sorting + 3 * count) * sizeof(uint32_t));
+        if (rc == GV_ENOMEM && !few) {  // the cosines of one set after the other take less
+            (void)hipGetLastError();
+            rc = sync_all(ctx);
+            if (rc) return rc;
+            std::vector<float> scores(count);
+            rc = cosine_scores(ctx, host_edge_first, host_edge_second, num_edges, scores.data());
+            if (rc) return rc;
+            rc = cosine_scores(ctx, host_other_first, host_other_second, num_others, scores.data() + num_edges);
+            if (rc) return rc;
+            rc = sync_all(ctx);  // ids >= n
+            return rc ? rc : rank_on_host(scores.data());
+        }
         if (rc) return rc;
         unsigned long long *dev_sums = (unsigned long long *)ctx->eval_scratch;
-        uint32_t *dev_sorting = (uint32_t *)((char *)ctx->eval_scratch + kSums);
+        uint32_t *dev_sorting = (uint32_t *)((char *)ctx->eval_scratch + sums);
         uint32_t *dev_first = dev_sorting + sorting, *dev_second = dev_first + count;
         float *dev_scores = (float *)(dev_second + count);
         auto upload = [&](uint32_t *to, const uint32_t *from, uint64_t ids) {
@@ -1481,16 +1507,21 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
         GV_HIP(ctx, upload(dev_second + num_edges, host_other_second, num_others));
         GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, dev_first, dev_second, (uint32_t)count, dev_scores,
                                       ctx->error_flag + 2, ctx->compute));
-        GV_HIP(ctx, gv::launch_rank_statistic((uint32_t *)dev_scores, (uint32_t)num_edges, (uint32_t)num_others, dev_sorting,
-                                              dev_sums, dev_sums + gv::kRankBlocks, ctx->compute));
-        const unsigned long long *sums = ctx->results->sums;
-        GV_HIP(ctx, hipMemcpyAsync(ctx->results->sums, dev_sums, sizeof ctx->results->sums, hipMemcpyDeviceToHost, ctx->compute));
+        HostResults &r = *ctx->results;
+        if (few) {
+            GV_HIP(ctx, hipMemcpyAsync(r.scores, dev_scores, count * sizeof(float), hipMemcpyDeviceToHost, ctx->compute));
+        } else {
+            GV_HIP(ctx, gv::launch_rank_statistic((uint32_t *)dev_scores, (uint32_t)num_edges, (uint32_t)num_others, dev_sorting,
+                                                  dev_sums, dev_sums + gv::kRankBlocks, ctx->compute));
+            GV_HIP(ctx, hipMemcpyAsync(r.sums, dev_sums, sizeof r.sums, hipMemcpyDeviceToHost, ctx->compute));
+        }
         rc = sync_all(ctx);  // also reports ids >= n, and what training before had to report
         if (rc) return rc;
+        if (few) return rank_on_host(r.scores);
         unsigned long long twice = 0, not_finite = 0;
         for (uint32_t b = 0; b < gv::kRankBlocks; ++b) {
-            twice += sums[b];
-            not_finite |= sums[gv::kRankBlocks + b];
+            twice += r.sums[b];
+            not_finite |= r.sums[gv::kRankBlocks + b];
         }
         if (not_finite) return fail(ctx, GV_EINVAL, "an embedding row is not finite");
         *auc = 0.5 * (double)twice / ((double)num_edges * (double)num_others);

@@ -27,6 +27,7 @@
 namespace {
 long host_allocations_left = -1;    // this many more, then one fails; negative: no limit
 long device_allocations_left = -1;  // the same of hipMalloc
+size_t device_largest = SIZE_MAX;   // bytes that a hipMalloc may ask for
 }  // namespace
 
 void *operator new(size_t size) {
@@ -47,15 +48,16 @@ void operator delete[](void *p) noexcept { free(p); }
 void operator delete[](void *p, size_t) noexcept { free(p); }
 
 extern "C" {
+static hipError_t last_error = hipSuccess;
 hipError_t hipMalloc(void **p, size_t size) {
     if (device_allocations_left == 0) {
         device_allocations_left = -1;
         *p = nullptr;
-        return hipErrorOutOfMemory;
+        return last_error = hipErrorOutOfMemory;
     }
     if (device_allocations_left > 0) --device_allocations_left;
-    *p = malloc(size);
-    return *p ? hipSuccess : hipErrorOutOfMemory;
+    *p = size <= device_largest ? malloc(size) : nullptr;
+    return *p ? hipSuccess : last_error = hipErrorOutOfMemory;
 }
 hipError_t hipFree(void *p) {
     free(p);
@@ -103,7 +105,11 @@ hipError_t hipGetDeviceCount(int *count) {
     *count = 1;
     return hipSuccess;
 }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {  // what a launch after a failed allocation would return for its own
+    const hipError_t error = last_error;
+    last_error = hipSuccess;
+    return error;
+}
 const char *hipGetErrorString(hipError_t) { return "as told"; }
 hipError_t hipGetSymbolAddress(void **p, const void *) {
     static std::vector<uint32_t> scratch(GV_STATIC_SCRATCH_WORDS);
@@ -123,6 +129,7 @@ std::vector<Trained> trained;
 uint32_t levels_trained = 0;
 int training_reports = -1;  // word of the error flag that asynchronous training sets, if any
 bool tiled_launched = false;
+bool ranked_on_device = false;
 bool walked_weighted = false;  // by the device producer
 uint64_t touched = 0;  // of the arrays that a kernel would read
 
@@ -205,13 +212,17 @@ hipError_t launch_cosine(const float *, uint32_t n, uint32_t, const uint32_t *fi
         out[i] = (float)first[i] - (float)second[i];
         if (first[i] >= n || second[i] >= n) *error_flag = 1u;
     }
-    return hipSuccess;
+    return hipGetLastError();
 }
 uint64_t rank_scratch_words(uint32_t num_neg) { return num_neg; }
-hipError_t launch_rank_statistic(uint32_t *, uint32_t, uint32_t, uint32_t *, unsigned long long *twice,
+hipError_t launch_rank_statistic(uint32_t *scores, uint32_t num_pos, uint32_t num_neg, uint32_t *, unsigned long long *twice,
                                  unsigned long long *not_finite, hipStream_t) {
+    ranked_on_device = true;
     memset(twice, 0, kRankBlocks * sizeof *twice);
     memset(not_finite, 0, kRankBlocks * sizeof *not_finite);
+    const float *positive = (const float *)scores, *negative = positive + num_pos;
+    for (uint32_t i = 0; i < num_pos; ++i)
+        for (uint32_t j = 0; j < num_neg; ++j) twice[0] += positive[i] > negative[j] ? 2u : positive[i] == negative[j] ? 1u : 0u;
     return hipSuccess;
 }
 hipError_t launch_pack_steps(const uint64_t *offsets, const uint32_t *adj, uint64_t half_edges, uint4 *steps, hipStream_t) {
@@ -529,6 +540,49 @@ void counted_launches() {
         gv_destroy(ctx);
     }
 }
+
+// Link prediction ranks few pairs on the host, more on the device, and more on the host where the device has no memory
+// left for it: the same result all ways.
+void ranking_where_it_can_be_done() {
+    const uint32_t n = 100;
+    const std::vector<uint32_t> degrees(n, 3);
+    struct Expected {
+        uint32_t edges, others;
+        size_t largest;
+        bool on_device;
+    };
+    for (const Expected &e : {Expected{1, 1, SIZE_MAX, false}, Expected{2048, 2048, SIZE_MAX, false},
+                              Expected{2049, 2048, SIZE_MAX, true}, Expected{3000, 4000, SIZE_MAX, true},
+                              Expected{3000, 4000, 60000, false}, Expected{4000, 3000, 50000, false}}) {
+        gv_ctx *ctx = context(GV_MODE_HOGWILD, 1);
+        CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK);
+        const std::vector<uint32_t> edges = random_pool(n, e.edges, 5), others = random_pool(n, e.others, 6);
+        std::vector<uint32_t> ends[4];
+        for (uint32_t i = 0; i < e.edges; ++i) ends[0].push_back(edges[2 * i]), ends[1].push_back(edges[2 * i + 1]);
+        for (uint32_t i = 0; i < e.others; ++i) ends[2].push_back(others[2 * i]), ends[3].push_back(others[2 * i + 1]);
+        double wins = 0.0, got = -1.0;
+        for (uint32_t i = 0; i < e.edges; ++i)
+            for (uint32_t j = 0; j < e.others; ++j) {
+                const float a = (float)ends[0][i] - (float)ends[1][i], b = (float)ends[2][j] - (float)ends[3][j];
+                wins += a > b ? 1.0 : a == b ? 0.5 : 0.0;
+            }
+        ranked_on_device = false;
+        device_largest = e.largest;
+        const int rc = gv_link_prediction_auc(ctx, ends[0].data(), ends[1].data(), e.edges, ends[2].data(), ends[3].data(),
+                                              e.others, &got);
+        device_largest = SIZE_MAX;
+        CHECK(rc == GV_OK && got == wins / ((double)e.edges * e.others) && ranked_on_device == e.on_device);
+        gv_ctx *full = context(GV_MODE_HOGWILD, 1);
+        CHECK(gv_set_degrees(full, n, degrees.data()) == GV_OK);
+        device_largest = 12 * std::max(e.edges, e.others) - 1;  // not even for the cosines of the larger set
+        CHECK(gv_link_prediction_auc(full, ends[0].data(), ends[1].data(), e.edges, ends[2].data(), ends[3].data(), e.others,
+                                     &got) == GV_ENOMEM);
+        device_largest = SIZE_MAX;
+        CHECK(hipGetLastError() == hipErrorOutOfMemory);
+        gv_destroy(full);
+        gv_destroy(ctx);
+    }
+}
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -538,6 +592,7 @@ int main(int argc, char **argv) {
         {"reports of evaluation", reports_of_evaluation},
         {"plans of pools", plans_of_pools},
         {"counted launches", counted_launches},
+        {"ranking where it can be done", ranking_where_it_can_be_done},
     };
     if (argc != 2 || !checks.count(argv[1])) return 2;
     checks.at(argv[1])();

@@ -38,6 +38,7 @@ def driver(tmp_path_factory):
     "reports of evaluation",
     "plans of pools",
     "counted launches",
+    "ranking where it can be done",
 ])
 def test_host_runtime(driver, check):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1:alloc_dealloc_mismatch=0",
