@@ -40,6 +40,7 @@ struct PoolSlot {
 // of the device's sort are (a call of one pair against one: 103 us with the sort on the device, 37 on the host; 1000 against 1000:
 // 101 and 48).
 constexpr uint64_t kHostRanked = 4096;
+constexpr uint64_t kDeterministicPart = 1u << 20;  // see train_deterministic
 
 // What the host waits for at the end of a call, in pinned memory: copied there on the compute stream, so that one wait
 // for that stream is all (a blocking copy of a few bytes takes 20 us on top of it).
@@ -485,21 +486,25 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
 // rounding inside a sample.  The number of levels is close to the number of samples that name the hottest row, however
 // far apart they stand in the pool: 1051 for 2*10^5 samples on 10^4 nodes, where maximal runs of consecutive samples
 // without a shared row number 32046 (6 samples each, one launch each: 112 ms; levels: 5 ms).
+//
+// A pool is taken in parts of at most kDeterministicPart samples, one after the other, which bounds what the host and the
+// device hold of it beside the pairs.
 int train_deterministic(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *host_pairs, uint64_t count) {
     const uint32_t K = ctx->cfg.num_neg;
-    // device scratch: the draws, then the order of the samples and the starts of the levels (at most count of them)
-    int rc = ensure_negatives(ctx, count * K + 2 * count + 1);
+    const uint64_t part = std::min(count, kDeterministicPart);
+    // device scratch: the draws, then the order of the samples and the starts of the levels (at most one per sample)
+    int rc = ensure_negatives(ctx, part * K + 2 * part + 1);
     if (rc) return rc;
-    rc = ensure_records(ctx, count * (K + 3));
+    rc = ensure_records(ctx, part * (K + 3));
     if (rc) return rc;
-    GV_HIP(ctx, gv::launch_draw_negatives(ctx->alias, ctx->n, ctx->cfg.seed, ctx->next_g, count, K, ctx->negatives,
-                                          ctx->compute));
-    std::unique_ptr<uint32_t[]> neg(new uint32_t[count * K]), pairs_copy(host_pairs ? nullptr : new uint32_t[count * 2]);
-    std::unique_ptr<uint32_t[]> level(new uint32_t[count]), order(new uint32_t[count]);
-    std::vector<uint32_t> starts;  // samples of every level, then the first of every level
-    // Whatever ends the call before the pool's levels are complete and on the device (also an exception of a container
-    // that cannot grow) leaves rows with levels of samples that were not trained, and copies in flight to the arrays
-    // above: the next call starts from cleared rows, and the arrays outlive the copies.
+    uint32_t *const dev_order = ctx->negatives + part * K, *const dev_starts = dev_order + part;
+    // the same on the host, the level of every sample, and the pairs if they are on the device only
+    const uint64_t words = part * K + 3 * part + 1 + (host_pairs ? 0 : 2 * count);
+    std::unique_ptr<uint32_t[]> arrays(new uint32_t[words]);
+    uint32_t *const neg = arrays.get(), *const order = neg + part * K, *const starts = order + part,
+                    *const level = starts + part + 1, *const pairs_copy = level + part;
+    // Whatever ends the call early leaves rows with levels of samples that were not trained, and copies in flight to the
+    // arrays above: the next call starts from cleared rows, and the arrays outlive the copies.
     struct Levelling {
         gv_ctx *ctx;
         bool complete;
@@ -510,77 +515,95 @@ int train_deterministic(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *
             ctx->level_context.clear();
         }
     } levelling{ctx, false};
-    GV_HIP(ctx, hipMemcpyAsync(neg.get(), ctx->negatives, count * K * sizeof(uint32_t), hipMemcpyDeviceToHost,
-                               ctx->compute));
-    if (!host_pairs) {
-        GV_HIP(ctx, hipMemcpyAsync(pairs_copy.get(), dev_pairs, count * 2 * sizeof(uint32_t), hipMemcpyDeviceToHost,
-                                   ctx->compute));
-        host_pairs = pairs_copy.get();
-    }
-    GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
-
     // level_vertex / level_context: per row, ctx->level_base + the lowest level that the next sample naming it may
-    // have; an entry of an earlier pool is at most level_base
-    if (ctx->level_vertex.size() != ctx->n || ctx->level_context.size() != ctx->n || ctx->level_base > UINT32_MAX - count) {
+    // have; an entry of an earlier part is at most level_base
+    if (ctx->level_vertex.size() != ctx->n || ctx->level_context.size() != ctx->n) {
         ctx->level_vertex.assign(ctx->n, 0);
         ctx->level_context.assign(ctx->n, 0);
         ctx->level_base = 0;
     }
-    const uint32_t base = ctx->level_base;
     uint32_t *const row_u = ctx->level_vertex.data(), *const row_c = ctx->level_context.data();
-    for (uint64_t i = 0; i < count; ++i) {
-        const uint32_t u = host_pairs[2 * i], v = host_pairs[2 * i + 1];
-        if (u >= ctx->n || v >= ctx->n)
-            return fail(ctx, GV_EINVAL, "sample %llu names node id >= n (%u)", (unsigned long long)i, ctx->n);
-        uint32_t at = std::max(std::max(base, row_u[u]), row_c[v]);
-        for (uint32_t k = 0; k < K; ++k) at = std::max(at, row_c[neg[i * K + k]]);
-        level[i] = at - base;
-        if (level[i] == starts.size()) starts.push_back(0);
-        starts[level[i]] += 1;
-        row_u[u] = row_c[v] = at + 1;
-        for (uint32_t k = 0; k < K; ++k) row_c[neg[i * K + k]] = at + 1;
-    }
-    const uint32_t levels = (uint32_t)starts.size();
-    ctx->level_base = base + levels;
-    uint32_t before = 0;
-    for (uint32_t &s : starts) {
-        const uint32_t width = s;
-        s = before;
-        before += width;
-    }
-    for (uint64_t i = 0; i < count; ++i) order[starts[level[i]]++] = (uint32_t)i;  // leaves every start at its level's end
-    starts.insert(starts.begin(), 0u);
-    uint32_t *const dev_order = ctx->negatives + count * K, *const dev_starts = dev_order + count;
-    GV_HIP(ctx, hipMemcpyAsync(dev_order, order.get(), count * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
-    GV_HIP(ctx, hipMemcpyAsync(dev_starts, starts.data(), starts.size() * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
-    GV_HIP(ctx, gv::launch_level_records(dev_pairs, ctx->negatives, dev_order, (uint32_t)count, K, ctx->records, ctx->compute));
-    GV_HIP(ctx, hipStreamSynchronize(ctx->compute));  // the host arrays go out of scope
-    levelling.complete = true;
-
-    TimedSpan span{};
-    const bool timed = ctx->cfg.profile != 0;
-    if (timed) {
-        rc = begin_span(ctx, 0, ctx->compute, &span);
-        if (rc) return rc;
-    }
-    auto narrow = [&](uint32_t l) { return starts[l + 1] - starts[l] <= gv::kNarrowLevel; };
-    gv::TrainArgs a = train_args(ctx, dev_pairs, ctx->next_g, 0);
+    const uint32_t *const pairs = host_pairs ? host_pairs : pairs_copy;
     const auto launch = ctx->dev_loss ? gv::launch_train_levels_tracked : gv::launch_train_levels;
-    for (uint32_t l = 0; l < levels;) {
-        uint32_t end = l + 1;
-        while (narrow(l) && end < levels && narrow(end)) ++end;
-        a.count = starts[end] - starts[l];
-        // a run of narrow levels reads its records by their place among all of them, a wide level from its first
-        a.levels = narrow(l) ? end - l : 0u;
-        a.level_starts = dev_starts + l;
-        a.records = ctx->records + (narrow(l) ? 0 : (size_t)starts[l] * (K + 3));
-        GV_HIP(ctx, launch(a, ctx->cfg.dim, K, ctx->compute));
-        ctx->stats.train_launches += 1;
-        l = end;
+
+    for (uint64_t first = 0; first < count; first += part) {
+        const uint64_t here = std::min(part, count - first);
+        const uint32_t *const part_pairs = dev_pairs + 2 * first;
+        GV_HIP(ctx, gv::launch_draw_negatives(ctx->alias, ctx->n, ctx->cfg.seed, ctx->next_g + first, here, K, ctx->negatives,
+                                              ctx->compute));
+        if (first == 0 && !host_pairs)
+            GV_HIP(ctx, hipMemcpyAsync(pairs_copy, dev_pairs, count * 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->compute));
+        GV_HIP(ctx, hipMemcpyAsync(neg, ctx->negatives, here * K * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->compute));
+        GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
+        if (first == 0) {  // the whole pool is looked at before any of it is trained
+            uint32_t largest = 0;
+            for (uint64_t i = 0; i < 2 * count; ++i) largest = std::max(largest, pairs[i]);
+            if (largest >= ctx->n) {
+                uint64_t i = 0;
+                while (pairs[i] < ctx->n) ++i;
+                return fail(ctx, GV_EINVAL, "sample %llu names node id >= n (%u)", (unsigned long long)(i / 2), ctx->n);
+            }
+        }
+        if (ctx->level_base > UINT32_MAX - here) {
+            std::fill(ctx->level_vertex.begin(), ctx->level_vertex.end(), 0u);
+            std::fill(ctx->level_context.begin(), ctx->level_context.end(), 0u);
+            ctx->level_base = 0;
+        }
+        const uint32_t base = ctx->level_base;
+        uint32_t levels = 0;
+        starts[0] = 0;
+        for (uint64_t i = 0; i < here; ++i) {  // starts[l + 1]: samples of level l
+            const uint32_t u = pairs[2 * (first + i)], v = pairs[2 * (first + i) + 1];
+            uint32_t at = std::max(std::max(base, row_u[u]), row_c[v]);
+            for (uint32_t k = 0; k < K; ++k) at = std::max(at, row_c[neg[i * K + k]]);
+            level[i] = at - base;
+            if (level[i] == levels) starts[++levels] = 0;
+            starts[level[i] + 1] += 1;
+            row_u[u] = row_c[v] = at + 1;
+            for (uint32_t k = 0; k < K; ++k) row_c[neg[i * K + k]] = at + 1;
+        }
+        ctx->level_base = base + levels;
+        for (uint32_t l = 0; l < levels; ++l) starts[l + 1] += starts[l];
+        for (uint64_t i = 0; i < here; ++i) order[starts[level[i]]++] = (uint32_t)i;  // leaves starts[l] at the end of level l
+        memmove(starts + 1, starts, levels * sizeof(uint32_t));
+        starts[0] = 0;
+        if (here == part) {
+            GV_HIP(ctx, hipMemcpyAsync(dev_order, order, (part + levels + 1) * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
+        } else {  // the last part of several
+            GV_HIP(ctx, hipMemcpyAsync(dev_order, order, here * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
+            GV_HIP(ctx, hipMemcpyAsync(dev_starts, starts, (levels + 1) * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
+        }
+        GV_HIP(ctx, gv::launch_level_records(part_pairs, ctx->negatives, dev_order, (uint32_t)here, K, ctx->records, ctx->compute));
+        GV_HIP(ctx, hipStreamSynchronize(ctx->compute));  // the arrays are written again, or go out of scope
+
+        TimedSpan span{};
+        const bool timed = ctx->cfg.profile != 0;
+        if (timed) {
+            rc = begin_span(ctx, 0, ctx->compute, &span);
+            if (rc) return rc;
+        }
+        auto narrow = [&](uint32_t l) { return starts[l + 1] - starts[l] <= gv::kNarrowLevel; };
+        gv::TrainArgs a = train_args(ctx, part_pairs, ctx->next_g + first, 0);
+        for (uint32_t l = 0; l < levels;) {
+            uint32_t end = l + 1;
+            while (narrow(l) && end < levels && narrow(end)) ++end;
+            a.count = starts[end] - starts[l];
+            // a run of narrow levels reads its records by their place among all of them, a wide level from its first
+            a.levels = narrow(l) ? end - l : 0u;
+            a.level_starts = dev_starts + l;
+            a.records = ctx->records + (narrow(l) ? 0 : (size_t)starts[l] * (K + 3));
+            GV_HIP(ctx, launch(a, ctx->cfg.dim, K, ctx->compute));
+            ctx->stats.train_launches += 1;
+            l = end;
+        }
+        ctx->stats.batches += levels;
+        if (ctx->dev_loss) ctx->stats.train_loss_samples += here;
+        if (timed) {
+            rc = end_span(ctx, ctx->compute, span);
+            if (rc) return rc;
+        }
     }
-    ctx->stats.batches += levels;
-    if (ctx->dev_loss) ctx->stats.train_loss_samples += count;
-    if (timed) return end_span(ctx, ctx->compute, span);
+    levelling.complete = true;
     return GV_OK;
 }
 

@@ -310,8 +310,8 @@ void check_levels(const std::vector<uint32_t> &pool, uint64_t g, uint32_t n, uin
 }
 
 // Deterministic mode: a call that runs out of host memory, wherever it does, reports it and leaves nothing behind.
-void levels_after_failed_allocations() {
-    const uint32_t n = 200, K = 2, count = 300;
+void levels_after_failed_allocations(uint32_t count, int at_least) {
+    const uint32_t n = 200, K = 2;
     const std::vector<uint32_t> degrees(n, 3), first = random_pool(n, count, 1), second = random_pool(n, count, 2);
     int failures = 0;
     for (long at = 0;; ++at) {
@@ -336,7 +336,33 @@ void levels_after_failed_allocations() {
         gv_destroy(ctx);
         if (done) break;
     }
-    CHECK(failures >= 6);  // host arrays, rows, and the list of levels as it grows
+    CHECK(failures >= at_least);
+}
+void levels_after_failed_allocations() {
+    levels_after_failed_allocations(300, 3);  // the call's arrays, the levels of either matrix
+    levels_after_failed_allocations(4000, 3);
+}
+
+// A pool of more than one part is trained in order, with no more scratch than one part has, and a bad id at its end is
+// found before any of it is trained.
+void pools_in_parts() {
+    const uint32_t n = 100000, K = 2, part = 1u << 20;
+    const std::vector<uint32_t> degrees(n, 3);
+    gv_ctx *ctx = context(GV_MODE_DETERMINISTIC, K);
+    CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+    device_largest = (size_t)part * (K + 3) * sizeof(uint32_t);
+    uint64_t g = 0;
+    for (uint32_t count : {part + 12345u, 1000u, part, part + 1u}) {
+        std::vector<uint32_t> pool = random_pool(n, count, count);
+        pool[2 * count - 1] = n;
+        CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_EINVAL && trained.empty());
+        pool[2 * count - 1] = 0;
+        CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK);
+        check_levels(pool, g, n, K);
+        g += count;
+    }
+    device_largest = SIZE_MAX;
+    gv_destroy(ctx);
 }
 
 // A graph of a ring with chords: every node has its two neighbours and the nodes two steps away.
@@ -588,6 +614,7 @@ void ranking_where_it_can_be_done() {
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"levels after failed allocations", levels_after_failed_allocations},
+        {"pools in parts", pools_in_parts},
         {"walks after failed allocations", walks_after_failed_allocations},
         {"reports of evaluation", reports_of_evaluation},
         {"plans of pools", plans_of_pools},

@@ -211,6 +211,42 @@ def test_deterministic_levels_of_every_width(gv, widths, d, K, track):
     assert stats["samples_trained"] == 2 * u.size and stats["batches"] >= 2 * len(widths) - 1
 
 
+@pytest.mark.parametrize("resident", [False, True])
+def test_deterministic_pool_of_several_parts(gv, resident):
+    """A pool of more than the 2^20 samples that are sorted into levels at a time, pushed and resident, then
+    shorter ones."""
+    import torch
+
+    n, d, K, w, seed = 50_000, 32, 2, 2.5, 43
+    rng = np.random.default_rng(12)
+    deg = rng.integers(1, 50, size=n).astype(np.uint32)
+    sizes = [(1 << 20) + 777, 1, 3277, 5]
+    pools = [rng.integers(n, size=(size, 2)).astype(np.uint32) for size in sizes]
+    vertex, context = random_embeddings(n, d, seed=14)
+    T = 2 * sum(sizes)
+    with context_for(gv, dim=d, num_neg=K, neg_weight=w, mode=gv.GV_MODE_DETERMINISTIC, total_samples=T, seed=seed,
+                     pool_capacity=max(sizes), lr0=LR0, profile=1) as ctx:
+        gv.gv_set_degrees(ctx, deg)
+        gv.gv_build_alias(ctx, 0.75)
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+        held = [torch.from_numpy(p.view(np.int32)).cuda() for p in pools]
+        torch.cuda.synchronize()
+        for p, q in zip(pools, held):
+            if resident:
+                gv.gv_train_device_pool(ctx, q.data_ptr(), p.shape[0])
+            else:
+                gv.gv_push_pool(ctx, p)
+                gv.gv_train_pool(ctx)
+        got_v = gv.gv_read_embeddings(ctx, gv.GV_VERTEX, n, d)
+        got_c = gv.gv_read_embeddings(ctx, gv.GV_CONTEXT, n, d)
+        assert gv.gv_get_stats(ctx)["samples_trained"] == sum(sizes)
+    ref_v, ref_c = run_oracle(deg, K, w, pools, vertex, context, T, seed)
+    for got, ref in ((got_v, ref_v), (got_c, ref_c)):
+        fro, mx = rel_errors(got, ref)
+        assert fro <= 1e-5 and mx <= 1e-4, (fro, mx)
+
+
 @pytest.mark.parametrize("d,K,w", [(128, 1, 5.0), (96, 3, 2.0), (512, 5, 1.0)])
 def test_running_loss_of_deterministic_mode_matches_oracle(gv, tiny_graph, d, K, w):
     """gv_config.track_loss: the sum of the losses the samples saw before their steps equals the sequential

@@ -34,6 +34,7 @@ def driver(tmp_path_factory):
 
 @pytest.mark.parametrize("check", [
     "levels after failed allocations",
+    "pools in parts",
     "walks after failed allocations",
     "reports of evaluation",
     "plans of pools",
