@@ -40,12 +40,13 @@ struct PoolSlot {
 // of the device's sort are (a call of one pair against one: 103 us with the sort on the device, 37 on the host; 1000 against 1000:
 // 101 and 48).
 constexpr uint64_t kHostRanked = 4096;
-constexpr uint64_t kDeterministicPart = 1u << 20;  // see train_deterministic
+constexpr uint64_t kStageWords = 16384, kDeterministicPart = 1u << 20;  // see train_deterministic
 
-// What the host waits for at the end of a call, in pinned memory: copied there on the compute stream, so that one wait
+// What the host waits for at the end of a call, and short pools of deterministic mode, in pinned memory: copied there on the compute stream, so that one wait
 // for that stream is all (a blocking copy of a few bytes takes 20 us on top of it).
 struct HostResults {
     uint32_t flag[3];
+    uint32_t stage[kStageWords];                                  // deterministic mode
     double loss_slots[gv::kLossSlots];
     union {
         double partial[gv::kEvalBlocks];                          // gv_eval_loss
@@ -488,7 +489,8 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
 // without a shared row number 32046 (6 samples each, one launch each: 112 ms; levels: 5 ms).
 //
 // A pool is taken in parts of at most kDeterministicPart samples, one after the other, which bounds what the host and the
-// device hold of it beside the pairs.
+// device hold of it beside the pairs.  Pools whose arrays fit the pinned stage use that: copies to and from pageable
+// memory wait for each other (30 samples, K = 1: 56 us a call from pageable arrays, 28 staged).
 int train_deterministic(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *host_pairs, uint64_t count) {
     const uint32_t K = ctx->cfg.num_neg;
     const uint64_t part = std::min(count, kDeterministicPart);
@@ -500,8 +502,9 @@ int train_deterministic(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *
     uint32_t *const dev_order = ctx->negatives + part * K, *const dev_starts = dev_order + part;
     // the same on the host, the level of every sample, and the pairs if they are on the device only
     const uint64_t words = part * K + 3 * part + 1 + (host_pairs ? 0 : 2 * count);
-    std::unique_ptr<uint32_t[]> arrays(new uint32_t[words]);
-    uint32_t *const neg = arrays.get(), *const order = neg + part * K, *const starts = order + part,
+    const bool staged = words <= kStageWords;
+    std::unique_ptr<uint32_t[]> arrays(staged ? nullptr : new uint32_t[words]);
+    uint32_t *const neg = staged ? ctx->results->stage : arrays.get(), *const order = neg + part * K, *const starts = order + part,
                     *const level = starts + part + 1, *const pairs_copy = level + part;
     // Whatever ends the call early leaves rows with levels of samples that were not trained, and copies in flight to the
     // arrays above: the next call starts from cleared rows, and the arrays outlive the copies.
@@ -574,7 +577,8 @@ int train_deterministic(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *
             GV_HIP(ctx, hipMemcpyAsync(dev_starts, starts, (levels + 1) * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
         }
         GV_HIP(ctx, gv::launch_level_records(part_pairs, ctx->negatives, dev_order, (uint32_t)here, K, ctx->records, ctx->compute));
-        GV_HIP(ctx, hipStreamSynchronize(ctx->compute));  // the arrays are written again, or go out of scope
+        // the arrays go out of scope; the stage stays, and is written again only behind the wait above
+        if (!staged) GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
 
         TimedSpan span{};
         const bool timed = ctx->cfg.profile != 0;

@@ -339,8 +339,8 @@ void levels_after_failed_allocations(uint32_t count, int at_least) {
     CHECK(failures >= at_least);
 }
 void levels_after_failed_allocations() {
-    levels_after_failed_allocations(300, 3);  // the call's arrays, the levels of either matrix
-    levels_after_failed_allocations(4000, 3);
+    levels_after_failed_allocations(300, 2);   // through the pinned stage: the levels of either matrix
+    levels_after_failed_allocations(4000, 3);  // through arrays of its own
 }
 
 // A pool of more than one part is trained in order, with no more scratch than one part has, and a bad id at its end is

@@ -213,14 +213,15 @@ def test_deterministic_levels_of_every_width(gv, widths, d, K, track):
 
 @pytest.mark.parametrize("resident", [False, True])
 def test_deterministic_pool_of_several_parts(gv, resident):
-    """A pool of more than the 2^20 samples that are sorted into levels at a time, pushed and resident, then
-    shorter ones."""
+    """A pool of more than the 2^20 samples that are sorted into levels at a time, pushed and resident; then
+    pools at either side of what goes through the pinned stage (16384 words: at K = 2, 5 a sample of a pushed pool and 7 of
+    a resident one, and one over)."""
     import torch
 
     n, d, K, w, seed = 50_000, 32, 2, 2.5, 43
     rng = np.random.default_rng(12)
     deg = rng.integers(1, 50, size=n).astype(np.uint32)
-    sizes = [(1 << 20) + 777, 1, 3277, 5]
+    sizes = [(1 << 20) + 777, 1, 2340, 2341, 3276, 3277, 5]
     pools = [rng.integers(n, size=(size, 2)).astype(np.uint32) for size in sizes]
     vertex, context = random_embeddings(n, d, seed=14)
     T = 2 * sum(sizes)
