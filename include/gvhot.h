@@ -283,7 +283,8 @@ int gv_augment(uint32_t n, const uint64_t *host_offsets, const uint32_t *host_ad
  * gv_set_degrees: host_offsets[n + 1] (offsets[0] = 0, row i has degree(i) entries),
  * host_adj[offsets[n]] with both directions of every edge; both are copied, the caller keeps
  * its arrays; a later gv_set_graph / gv_set_degrees discards the copy.  (On the device an entry
- * takes 4 bytes, or 16 where that speeds walks up and is at most 4 GiB.)  Errors: GV_ESTATE
+ * takes 4 bytes, or 16 where that speeds walks up and is at most 4 GiB and an eighth of the memory
+ * that is left; on a weighted graph 12, or 32.)  Errors: GV_ESTATE
  * without a graph, GV_EINVAL when a row length differs from the node's degree, an entry is
  * >= n or the graph has no edge.
  * gv_augment_device writes the pool that gv_augment would write for the same arguments

@@ -291,8 +291,9 @@ int adopt_degrees(gv_ctx *ctx, uint32_t n, std::vector<uint32_t> &&deg) {
 // with degree and first half-edge of every neighbour beside it, 16 bytes an entry (32 on a weighted graph, for both
 // outcomes of the alias draw), which leaves a walk one dependent load a step instead of two or three (k_pack_steps,
 // k_pack_weighted_steps).  Not where that takes the walk out of an L2 cache (4 MiB a die) that holds the plain arrays
-// (3.1*10^5 entries, pools of 10^7 pairs: 28 us plain, 36 us packed), and up to 4 GiB of it; larger adjacencies, and one
-// that finds no memory for it, are walked as they are.
+// (3.1*10^5 entries, pools of 10^7 pairs: 28 us plain, 36 us packed), and up to 4 GiB and an eighth of the memory that is
+// left (the scratch of training comes later); larger adjacencies, and one that finds no memory for it, are walked as
+// they are.
 int prepare_walks(gv_ctx *ctx) {
     const bool weighted = ctx->dev_nbr_table != nullptr;
     const uint64_t bytes = ctx->half_edges * (weighted ? 2 : 1) * sizeof(uint4);
@@ -307,7 +308,12 @@ int prepare_walks(gv_ctx *ctx) {
     }
     const uint64_t plain = ctx->half_edges * (sizeof(uint32_t) + (weighted ? sizeof(uint2) : 0)) + (uint64_t)ctx->n * sizeof(uint64_t);
     constexpr uint64_t kCached = 3ull << 20;
-    if (bytes <= 1ull << 32 && (bytes <= kCached || plain > kCached)) {
+    size_t left = 0, total = 0;
+    if (hipMemGetInfo(&left, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        left = 0;
+    }
+    if (bytes <= 1ull << 32 && bytes <= left / 8 && (bytes <= kCached || plain > kCached)) {
         if (hipMalloc((void **)&ctx->dev_steps, bytes) != hipSuccess) {
             (void)hipGetLastError();  // not an error: the walk does without
             ctx->dev_steps = nullptr;

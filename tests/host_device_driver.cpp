@@ -28,6 +28,7 @@ namespace {
 long host_allocations_left = -1;    // this many more, then one fails; negative: no limit
 long device_allocations_left = -1;  // the same of hipMalloc
 size_t device_largest = SIZE_MAX;   // bytes that a hipMalloc may ask for
+size_t device_free = SIZE_MAX;      // bytes that hipMemGetInfo says are left
 }  // namespace
 
 void *operator new(size_t size) {
@@ -58,6 +59,11 @@ hipError_t hipMalloc(void **p, size_t size) {
     if (device_allocations_left > 0) --device_allocations_left;
     *p = size <= device_largest ? malloc(size) : nullptr;
     return *p ? hipSuccess : last_error = hipErrorOutOfMemory;
+}
+hipError_t hipMemGetInfo(size_t *left, size_t *total) {
+    *left = device_free;
+    *total = SIZE_MAX;
+    return hipSuccess;
 }
 hipError_t hipFree(void *p) {
     free(p);
@@ -130,7 +136,7 @@ uint32_t levels_trained = 0;
 int training_reports = -1;  // word of the error flag that asynchronous training sets, if any
 bool tiled_launched = false;
 bool ranked_on_device = false;
-bool walked_weighted = false;  // by the device producer
+bool walked_weighted = false, walked_packed = false;  // by the device producer
 uint64_t touched = 0;  // of the arrays that a kernel would read
 
 uint32_t draw(uint64_t g, uint32_t k, uint32_t n) { return (uint32_t)((g * 0x9E3779B97F4A7C15ull + k * 0xD1B54A32D192ED03ull) >> 40) % n; }
@@ -247,6 +253,7 @@ hipError_t launch_departure_guide(const uint64_t *, uint32_t, uint64_t, uint32_t
 }
 hipError_t launch_augment(const AugmentArgs &a, hipStream_t) {
     walked_weighted = a.node_table != nullptr;
+    walked_packed = a.steps || a.weighted_steps;
     read_all(a.offsets, (uint64_t)a.n + 1);
     CHECK(!(a.steps && a.weighted_steps));
     if (a.node_table) {
@@ -567,6 +574,30 @@ void counted_launches() {
     }
 }
 
+// The packed adjacency takes no more than an eighth of the device memory that is left.
+void packed_walks_leave_room() {
+    const Ring ring;
+    std::vector<uint32_t> pairs(2 * 1000);
+    uint64_t walks = 0;
+    for (bool weighted : {false, true}) {
+        const size_t packed = ring.adj.size() * (weighted ? 32 : 16);
+        for (size_t left : {8 * packed, 8 * packed - 8}) {
+            gv_ctx *ctx = context(GV_MODE_HOGWILD, 1);
+            device_free = left;
+            if (weighted) {
+                CHECK(gv_set_weighted_graph(ctx, ring.n, ring.offsets.data(), ring.adj.data(), ring.weights.data()) == GV_OK);
+            } else {
+                CHECK(gv_set_degrees(ctx, ring.n, ring.degrees.data()) == GV_OK);
+                CHECK(gv_set_adjacency(ctx, ring.offsets.data(), ring.adj.data()) == GV_OK);
+            }
+            device_free = SIZE_MAX;
+            CHECK(gv_augment_device(ctx, 1, 5, 2, 0, 1000, GV_SHUFFLE_NONE, pairs.data(), &walks) == GV_OK);
+            CHECK(walked_weighted == weighted && walked_packed == (left == 8 * packed));
+            gv_destroy(ctx);
+        }
+    }
+}
+
 // Link prediction ranks few pairs on the host, more on the device, and more on the host where the device has no memory
 // left for it: the same result all ways.
 void ranking_where_it_can_be_done() {
@@ -616,6 +647,7 @@ int main(int argc, char **argv) {
         {"levels after failed allocations", levels_after_failed_allocations},
         {"pools in parts", pools_in_parts},
         {"walks after failed allocations", walks_after_failed_allocations},
+        {"packed walks leave room", packed_walks_leave_room},
         {"reports of evaluation", reports_of_evaluation},
         {"plans of pools", plans_of_pools},
         {"counted launches", counted_launches},

@@ -36,6 +36,7 @@ def driver(tmp_path_factory):
     "levels after failed allocations",
     "pools in parts",
     "walks after failed allocations",
+    "packed walks leave room",
     "reports of evaluation",
     "plans of pools",
     "counted launches",
