@@ -87,6 +87,7 @@ struct gv_ctx {
     uint16_t *dev_rank = nullptr;         // device, per node: hot rank (see gv::TrainArgs)
     uint32_t *dev_ranked = nullptr;       // device, bitmap of the nodes that have a hot rank
     uint32_t warm_ranks = 0;              // number of warm rows
+    uint32_t force_tile = 0;              // see gv_test_force_tile
     double hottest_share = 0.0;           // share of the samples that name the hottest context row
     // orthogonal blocks (cfg.partitions > 0): partition of every node, and one alias table per partition
     std::vector<uint32_t> part;           // host, per node
@@ -443,7 +444,8 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
     const gv::AsyncPlan plan = gv::async_plan(gv::AsyncPool{count, ctx->n, ctx->cfg.dim, ctx->cfg.num_neg, coherence, tiled,
                                                             ctx->cfg.schedule == GV_SCHEDULE_AUTO, block != nullptr,
                                                             ctx->warm_ranks,
-                                                            ctx->hottest_share * (block ? ctx->cfg.partitions : 1u)});
+                                                            ctx->hottest_share * (block ? ctx->cfg.partitions : 1u),
+                                                            ctx->force_tile});
     if (tiled && fixed_records) {
         const uint64_t words = count * (ctx->cfg.num_neg + 3);
         if (words > GV_STATIC_SCRATCH_WORDS)
@@ -1581,6 +1583,21 @@ int gv_set_position(gv_ctx *ctx, uint64_t next_g) {
     if (!ctx) return GV_EINVAL;
     ctx->next_g = next_g;
     ctx->stats.samples_trained = next_g;
+    return GV_OK;
+}
+
+// Not part of the boundary: lets a test run the kernels of long pools on short ones.  Launches that the schedule walks in
+// tiles take tiles of `samples` under the context's own policy; 0: as async_plan decides.  GV_EINVAL for a size that the
+// policy and the row length have no kernel for.
+int gv_test_force_tile(gv_ctx *ctx, uint32_t samples) {
+    if (!ctx) return GV_EINVAL;
+    const bool smaller = ctx->cfg.coherence == GV_COHERENCE_ATOMIC_AGENT ||
+                         (ctx->cfg.coherence == GV_COHERENCE_MIXED &&
+                          gv::short_rows(gv::floats_per_lane(ctx->cfg.dim), (int)ctx->cfg.num_neg));
+    const bool size = samples >= gv::kSmallestTile && samples <= gv::kLargestTile && !(samples & (samples - 1u));
+    if (samples != 0 && !(size && (smaller || samples == gv::kLargestTile)))
+        return fail(ctx, GV_EINVAL, "no kernel with tiles of %u samples", samples);
+    ctx->force_tile = samples;
     return GV_OK;
 }
 

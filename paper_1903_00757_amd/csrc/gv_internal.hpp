@@ -75,6 +75,7 @@ struct AsyncPool {
     bool part_of_pool;        // one block of a partitioned graph
     uint32_t warm_ranks;
     double hottest_share;     // share of these samples that name the hottest context row
+    uint32_t force_tile = 0;  // tests: the tile, under the policy asked for, whatever the rules say
 };
 struct AsyncPlan {
     bool tiled;               // k_train_tiled, otherwise k_train_hogwild

@@ -70,6 +70,7 @@ AsyncPlan async_plan(const AsyncPool &p) {
         return AsyncPlan{false, coherence, chunk, std::min((pieces(chunk) + kWaves - 1) / kWaves, blocks), 0u};
     };
     if (!p.tiled) return pool_order(p.coherence, kWave, limit);
+    if (p.force_tile) return tiled(p.coherence, p.force_tile);
     const AsyncPlan full = tiled(p.coherence, kLargestTile);
     // One block of a partitioned graph keeps tiles of 8192: it names its rows `partitions` times as often as a pool
     // does, and more samples in flight show in the loss (10^4 nodes, 8 x 8 blocks: +2.3 %).

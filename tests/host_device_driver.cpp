@@ -15,6 +15,8 @@
 #include "gv_internal.hpp"
 #include "gvhot.h"
 
+extern "C" int gv_test_force_tile(gv_ctx *ctx, uint32_t samples);
+
 #define CHECK(cond)                                                                  \
     do {                                                                             \
         if (!(cond)) {                                                               \
@@ -135,6 +137,7 @@ std::vector<Trained> trained;
 uint32_t levels_trained = 0;
 int training_reports = -1;  // word of the error flag that asynchronous training sets, if any
 bool tiled_launched = false;
+uint32_t launched_unit = 0;
 bool ranked_on_device = false;
 bool walked_weighted = false, walked_packed = false;  // by the device producer
 uint64_t touched = 0;  // of the arrays that a kernel would read
@@ -150,11 +153,13 @@ void read_all(const T *array, uint64_t count) {
 
 namespace gv {
 hipError_t launch_train_hogwild(const TrainArgs &a, uint32_t, uint32_t, uint32_t, hipStream_t) {
+    launched_unit = a.unit;
     if (training_reports >= 0) a.error_flag[training_reports] = 1u;
     return hipSuccess;
 }
 hipError_t launch_train_tiled(const TrainArgs &a, uint32_t, uint32_t, uint32_t, hipStream_t) {
     tiled_launched = true;
+    launched_unit = a.unit;
     if (training_reports >= 0) a.error_flag[training_reports] = 1u;
     return hipSuccess;
 }
@@ -570,6 +575,19 @@ void counted_launches() {
         gv_stats stats;
         CHECK(gv_get_stats(ctx, &stats) == GV_OK && stats.train_launches == 1);
         CHECK(tiled_launched == e.tiled && stats.tiled_launches == (e.tiled ? 1u : 0u));
+        gv_destroy(ctx);
+    }
+    // the tests' own choice of the tile: sizes that there are kernels for, where the schedule walks in tiles at all
+    for (uint32_t schedule : {GV_SCHEDULE_TILED, GV_SCHEDULE_POOL_ORDER}) {
+        gv_ctx *ctx = context(GV_MODE_HOGWILD, 1, schedule);
+        CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+        for (uint32_t bad : {1u, 8u, 4095u, 16384u}) CHECK(gv_test_force_tile(ctx, bad) == GV_EINVAL);
+        for (uint32_t tile : {16u, 4096u, 8192u}) {
+            CHECK(gv_test_force_tile(ctx, tile) == GV_OK && gv_train_device_pool(ctx, pool.data(), 100) == GV_OK);
+            CHECK(launched_unit == (schedule == GV_SCHEDULE_TILED ? tile : 64u));
+        }
+        CHECK(gv_test_force_tile(ctx, 0) == GV_OK && gv_train_device_pool(ctx, pool.data(), 100000) == GV_OK);
+        CHECK(launched_unit == 64u);
         gv_destroy(ctx);
     }
 }

@@ -1,5 +1,6 @@
 """Parity of the HIP path against the CPU oracle, through the C boundary (needs a GPU)."""
 import contextlib
+import ctypes
 import os
 
 import numpy as np
@@ -365,17 +366,30 @@ ALL_POLICIES = [(POOL_ORDER, PLAIN), (POOL_ORDER, AGENT), (POOL_ORDER, ATOMIC), 
                 (TILED, MIXED)]
 # policies that never drop an update of a contended row: these are held to the quality gate
 LOSSLESS_POLICIES = [(POOL_ORDER, ATOMIC), (TILED, ATOMIC), (TILED, MIXED)]
+# the kernels of long pools, which short ones do not reach by themselves: tiles of that many samples, whatever the pool
+LONG_POOL_POLICIES = [(TILED, MIXED, 8192), (TILED, MIXED, 4096), (TILED, ATOMIC, 8192)]
+
+
+def force_tile(gv, ctx, policy, d, K):
+    if len(policy) < 3:
+        return
+    if policy[1:] == (MIXED, 4096) and (1 if d <= 64 else 2 if d <= 128 else 4) * (K + 1) > 4:
+        pytest.skip("long rows have no such kernel")
+    lib = gv.load()
+    lib.gv_test_force_tile.argtypes = [ctypes.c_void_p, ctypes.c_uint32]
+    assert lib.gv_test_force_tile(ctx, policy[2]) == gv.GV_OK
 
 
 def hogwild_run(gv, n, deg, d, K, w, pools, vertex, context, T, seed, policy):
     cap = max(p.shape[0] for p in pools)
-    schedule, coherence = policy
+    schedule, coherence = policy[:2]
     with context_for(gv, dim=d, num_neg=K, neg_weight=w, mode=gv.GV_MODE_HOGWILD, total_samples=T, seed=seed,
                      pool_capacity=cap, lr0=LR0, coherence=coherence, schedule=schedule) as ctx:
         gv.gv_set_degrees(ctx, deg)
         gv.gv_build_alias(ctx, 0.75)
         gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
         gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+        force_tile(gv, ctx, policy, d, K)
         for p in pools:
             gv.gv_push_pool(ctx, p)
             gv.gv_train_pool(ctx)
@@ -468,7 +482,7 @@ def test_tiled_pools_of_changing_size(gv, policy):
     (200_000, 64, 1, 1), (200_000, 64, 1, 15), (200_000, 64, 1, 16), (200_000, 96, 2, 17), (200_000, 128, 1, 65),
     (200_000, 128, 1, 32_767), (200_000, 128, 1, 32_768), (200_000, 32, 5, 131_073),  # tiles of 16, 32, 64, 128 samples
     (3_000, 64, 1, 50_001),       # every row is warm, and a few workgroups stride over the tiles
-    (100_000, 64, 1, 6_500_001),  # the same with tiles of 2048 under a store policy
+    (100_000, 64, 1, 6_500_001),  # the same with tiles of 4096 under the mixed policy
 ])
 def test_tile_sizes_and_their_edges(gv, policy, n, d, K, count):
     """Samples planted at the edges of the pool and of every tile size, on nodes that nothing else names (they have no
@@ -480,7 +494,7 @@ def test_tile_sizes_and_their_edges(gv, policy, n, d, K, count):
     deg = rng.integers(1, 50, size=n).astype(np.uint32)
     deg[n - lone:] = 0
     pool = rng.integers(n - lone, size=(count, 2)).astype(np.uint32)
-    edges = {0, count - 1} | {t * m + e for t in (16, 32, 64, 128, 256, 2048, 8192) for m in (1, 3) for e in (-1, 0)}
+    edges = {0, count - 1} | {t * m + e for t in (16, 32, 64, 128, 256, 2048, 4096, 8192) for m in (1, 3) for e in (-1, 0)}
     at = np.array(sorted(e for e in edges if 0 <= e < count))
     u, v = n - lone + np.arange(at.size), n - 1 - np.arange(at.size)
     pool[at, 0], pool[at, 1] = u, v
@@ -497,14 +511,16 @@ def test_tile_sizes_and_their_edges(gv, policy, n, d, K, count):
     assert np.isfinite(got_v).all() and np.isfinite(got_c).all()
 
 
-@pytest.mark.parametrize("policy", [(TILED, AGENT), (TILED, ATOMIC), (TILED, MIXED)])
-def test_tiled_run_on_one_hub_row_is_sequential(gv, policy):
-    """60 samples that all name one high-degree node u: the tiled schedule keeps vertex[u] in registers
-    through the whole run and trades it with memory between batches.  Every context row involved is a
+@pytest.mark.parametrize("policy", [(TILED, AGENT), (TILED, ATOMIC), (TILED, MIXED)] + LONG_POOL_POLICIES)
+@pytest.mark.parametrize("d", [128, 64, 160])
+def test_tiled_run_on_one_hub_row_is_sequential(gv, policy, d):
+    """60 samples (32 at d = 64) that all name one high-degree node u: the tiled schedule keeps vertex[u] in registers
+    through the whole run and trades it with memory between batches (in tiles of 8192 and 4096; in the tiles that a pool
+    of 60 takes by itself a run is four samples).  Every context row involved is a
     multiple of its own unit vector, so the score of a sample does not depend on the other samples:
     vertex[u] must then equal the oracle's whatever the order within the run, and every context row
     must have moved by its coefficient times a value vertex[u] passed through."""
-    n, d, K, count, w, seed, hub = 200_000, 128, 1, 60, 5.0, 77, 4242
+    n, K, count, w, seed, hub = 200_000, 1, min(60, d // 2), 5.0, 77, 4242
     rng = np.random.default_rng(5)
     deg = rng.integers(1, 50, size=n).astype(np.uint32)
     deg[hub] = 10_000
@@ -536,7 +552,8 @@ def test_tiled_run_on_one_hub_row_is_sequential(gv, policy):
     assert np.array_equal(got_c[untouched], context[untouched])
 
 
-@pytest.mark.parametrize("policy", [(POOL_ORDER, ATOMIC), (TILED, AGENT), (TILED, ATOMIC), (TILED, MIXED)])
+@pytest.mark.parametrize("policy", [(POOL_ORDER, ATOMIC), (TILED, AGENT), (TILED, ATOMIC), (TILED, MIXED),
+                                    (TILED, MIXED, 8192)])
 def test_single_samples_with_repeated_rows(gv, policy):
     """Three nodes, K = 3: one-sample pools at positions whose negatives repeat v, repeat each other, or equal
     the row the tiled schedule keeps in registers.  One sample alone is one sequential step whatever the
@@ -553,12 +570,13 @@ def test_single_samples_with_repeated_rows(gv, policy):
                 pattern = (u, tuple(rows.index(r) for r in rows))  # which rows coincide, and who is u
                 cases.setdefault(pattern, (g, u, v))
     assert len(cases) >= 12
-    schedule, coherence = policy
+    schedule, coherence = policy[:2]
     vertex, context = random_embeddings(n, d, seed=11)
     with context_for(gv, dim=d, num_neg=K, neg_weight=w, mode=gv.GV_MODE_HOGWILD, total_samples=T, seed=seed,
                      pool_capacity=8, lr0=LR0, coherence=coherence, schedule=schedule) as ctx:
         gv.gv_set_degrees(ctx, deg)
         gv.gv_build_alias(ctx, 0.75)
+        force_tile(gv, ctx, policy, d, K)
         for pattern, (g, u, v) in sorted(cases.items()):
             pool = np.array([[u, v]], dtype=np.uint32)
             gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
@@ -577,9 +595,9 @@ def test_single_samples_with_repeated_rows(gv, policy):
                 assert np.abs(got - ref).max() <= 1e-4 * step + 1e-7, (pattern, g, u, v)
 
 
-@pytest.mark.parametrize("policy", [(TILED, AGENT), (TILED, MIXED), (TILED, ATOMIC), (POOL_ORDER, AGENT)])
+@pytest.mark.parametrize("policy", [(TILED, AGENT), (TILED, MIXED), (TILED, ATOMIC), (POOL_ORDER, AGENT)] + LONG_POOL_POLICIES)
 @pytest.mark.parametrize("shape", ["shared context", "shared vertex", "interleaved runs"])
-@pytest.mark.parametrize("d,K", [(128, 1), (128, 3), (512, 5)])  # the wave gathers 4, 2, 1 samples at once
+@pytest.mark.parametrize("d,K", [(128, 1), (128, 3), (512, 5), (64, 1)])  # the wave gathers 2, 2, 1, 2 samples at once
 @pytest.mark.parametrize("count", [2, 3, 4])
 def test_samples_of_one_wave_sharing_a_cold_row(gv, policy, shape, d, K, count):
     """Four samples that end up next to each other in one wave and share a cold row (one that the store
@@ -636,8 +654,8 @@ def test_samples_of_one_wave_sharing_a_cold_row(gv, policy, shape, d, K, count):
         assert np.abs(got[r] - ref[r]).max() <= 1e-4 * step + 1e-7, (shape, policy, int(r))
 
 
-@pytest.mark.parametrize("policy", [(TILED, AGENT), (TILED, MIXED), (TILED, ATOMIC), (POOL_ORDER, AGENT)])
-@pytest.mark.parametrize("d,K", [(128, 1), (128, 3), (512, 5), (96, 2)])  # (96, 2): rows that do not fill their lanes
+@pytest.mark.parametrize("policy", [(TILED, AGENT), (TILED, MIXED), (TILED, ATOMIC), (POOL_ORDER, AGENT)] + LONG_POOL_POLICIES)
+@pytest.mark.parametrize("d,K", [(128, 1), (128, 3), (512, 5), (96, 2), (64, 1)])  # (96, 2): rows that do not fill their lanes
 @pytest.mark.parametrize("samples,trial,filler", [(2, 0, 0), (3, 0, 0), (9, 0, 0), (64, 0, 0), (64, 1, 0), (64, 0, 300)])
 @pytest.mark.parametrize("kind", ["cold vertex", "warm vertex", "cold context", "warm context"])
 def test_random_sharing_of_a_few_rows_is_exact(gv, policy, d, K, trial, samples, filler, kind):
@@ -1212,11 +1230,12 @@ def c2_oracle_pool(c2_workload):
     return dict(vertex=vertex, context=context, ref_v=ref_v, ref_c=ref_c, eval_pool=eval_pool)
 
 
-@pytest.mark.parametrize("policy", [(TILED, MIXED), (TILED, ATOMIC)])
-def test_full_size_pool_tracks_the_sequential_oracle(gv, c2_workload, c2_oracle_pool, policy):
+@pytest.mark.parametrize("policy,pools", [((TILED, MIXED), 1), ((TILED, ATOMIC), 1), ((TILED, MIXED), 6)])
+def test_full_size_pool_tracks_the_sequential_oracle(gv, c2_workload, c2_oracle_pool, policy, pools):
     """Same launch configuration as the benchmark (2^24 samples, 10^6 nodes, thousands of samples in
     flight): after the pool the evaluation loss is within 2 % of the sequential oracle's, and the
-    hottest rows, which take part in tens of thousands of samples, moved as far as the oracle's."""
+    hottest rows, which take part in tens of thousands of samples, moved as far as the oracle's.  Six pools of a sixth
+    each take tiles of 4096 instead of 8192."""
     import torch
 
     c2, o = c2_workload, c2_oracle_pool
@@ -1231,9 +1250,12 @@ def test_full_size_pool_tracks_the_sequential_oracle(gv, c2_workload, c2_oracle_
         gv.gv_set_embeddings(ctx, gv.GV_VERTEX, o["vertex"])
         gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, o["context"])
         gv.gv_set_position(ctx, 1_000_000_000)
-        gv.gv_train_device_pool(ctx, dev_pool.data_ptr(), c2["pool"].shape[0])
+        cuts = np.linspace(0, c2["pool"].shape[0], pools + 1).astype(int)
+        for a, b in zip(cuts, cuts[1:]):
+            gv.gv_train_device_pool(ctx, dev_pool.data_ptr() + 8 * int(a), int(b - a))
         got_v = gv.gv_read_embeddings(ctx, gv.GV_VERTEX, n, d)
         got_c = gv.gv_read_embeddings(ctx, gv.GV_CONTEXT, n, d)
+        assert gv.gv_get_stats(ctx)["tiled_launches"] == pools
     kw = dict(K=K, w=w, seed=99, thresh=c2["thresh"], alias=c2["alias"])
     loss_start = oracle.loss(o["vertex"], o["context"], o["eval_pool"], **kw)
     loss_ref = oracle.loss(o["ref_v"], o["ref_c"], o["eval_pool"], **kw)
@@ -1244,7 +1266,7 @@ def test_full_size_pool_tracks_the_sequential_oracle(gv, c2_workload, c2_oracle_
         moved_gpu = np.linalg.norm((got[hot] - init[hot]).astype(np.float64), axis=1)
         moved_ref = np.linalg.norm((ref[hot] - init[hot]).astype(np.float64), axis=1)
         ratios.append(moved_gpu / moved_ref)
-    print(f"full size {policy}: loss {loss_start:.4f} -> gpu {loss_gpu:.4f} / oracle {loss_ref:.4f}; "
+    print(f"full size {policy}, {pools} pools: loss {loss_start:.4f} -> gpu {loss_gpu:.4f} / oracle {loss_ref:.4f}; "
           f"hot-row movement ratio vertex {np.median(ratios[0]):.2f} context {np.median(ratios[1]):.2f}")
     assert loss_ref < 0.95 * loss_start  # the pool does train
     assert abs(loss_gpu - loss_ref) <= 0.02 * loss_ref
@@ -1307,7 +1329,7 @@ def test_configuration_5_size_isolated_samples(gv):
     edges; 67.6 GB of embeddings) with a pool whose endpoints come from the degree marginal (the graph's adjacency
     is not generated): the alias table of that size equals the oracle's bit for bit, so do the negatives, and every
     sample of a 2^22-sample pool whose three rows nobody else names is exactly one oracle step from the initial
-    embeddings, in the launch configuration bench.py times for this workload (device pool, default policy)."""
+    embeddings, by the kernel that bench.py times for this workload with pools of 2^24 (tiles of 8192, default policy)."""
     import torch
 
     n, deg = W.expected_degrees("c5-marginal")
@@ -1328,6 +1350,7 @@ def test_configuration_5_size_isolated_samples(gv):
         del got_t, got_a
         assert np.array_equal(gv.gv_draw_negatives(ctx, first_g, 1 << 20, K), negs[:1 << 20])
         gv.gv_init_embeddings(ctx, 9)
+        force_tile(gv, ctx, (TILED, MIXED, 8192), d, K)
         gv.gv_set_position(ctx, first_g)
         gv.gv_train_device_pool(ctx, dev_pool.data_ptr(), count)
         gv.gv_sync(ctx)
@@ -1437,6 +1460,7 @@ def test_configuration_5_as_stated_walks_and_training(gv):
         buf.copy_(torch.from_numpy(pool.view(np.int32)))
         torch.cuda.synchronize()
         gv.gv_init_embeddings(ctx, 9)
+        force_tile(gv, ctx, (TILED, MIXED, 8192), d, K)
         gv.gv_set_position(ctx, first_g)
         gv.gv_train_device_pool(ctx, buf.data_ptr(), count)
         gv.gv_sync(ctx)
