@@ -67,17 +67,18 @@ enum { GV_COHERENCE_PLAIN = 0, GV_COHERENCE_AGENT = 1, GV_COHERENCE_ATOMIC_AGENT
  *                would not fill the chip, or the graph is small) and sort each tile
  *                by the hottest row of every sample (the highest-degree one of u, v and
  *                the negatives); a wave keeps that row in registers across the run of
- *                samples sharing it, trading its change with memory every four samples
- *                and at the end of the run.  The launch still moves through the pool
+ *                samples sharing it, trading its change with memory every two or four
+ *                samples and at the end of the run.  The launch still moves through the pool
  *                front to back, and each sample keeps the negatives and learning rate
  *                of its position in the pool.
  *   AUTO         TILED when the graph has rows that concurrent samples are likely to share
  *                (decided by gv_build_alias from the degrees), POOL_ORDER otherwise: on a
- *                graph without such rows the tile bookkeeping buys nothing.  A pool that
- *                is short, or of a graph so small that atomic adds are used for all rows,
- *                is walked in pool order where that is faster than tiles.  With
- *                GV_COHERENCE_MIXED the pool-order launch then uses AGENT stores (all rows
- *                are cold).                                                            */
+ *                graph without such rows the tile bookkeeping buys nothing, and with
+ *                GV_COHERENCE_MIXED the launch uses AGENT stores (all rows are cold).  A
+ *                pool of a graph with such rows that is short, or all of whose rows are
+ *                shared, is walked in pool order under GV_COHERENCE_MIXED where that is
+ *                faster than tiles: in chunks of 4 to 16 samples, with atomic adds on all
+ *                rows.                                                                  */
 enum { GV_SCHEDULE_POOL_ORDER = 0, GV_SCHEDULE_TILED = 1, GV_SCHEDULE_AUTO = 2 };
 
 /* gv_config.neg_weight value that asks for the paper's setting: 5 / K (Sec. 4.3: one
@@ -197,7 +198,8 @@ int gv_push_pool(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count);
  * asynchronous SGD): positive samples g .. g+count-1 where g is the
  * number of samples trained so far.  Returns after launching (asynchronous);
  * GV_ESTATE if nothing is queued.  The training calls keep device scratch sized
- * for the largest pool seen so far (a few words per sample): the first call, and
+ * for the largest pool seen so far (a few words per sample; in deterministic mode of
+ * at most 2^20 samples, the part of a pool that is sorted at a time): the first call, and
  * a call with a larger pool than any before, allocate (GV_ENOMEM / GV_EHIP if
  * that fails) and wait for the launches in flight.                              */
 int gv_train_pool(gv_ctx *ctx);
@@ -347,7 +349,9 @@ int gv_cosine(gv_ctx *ctx, const uint32_t *host_first, const uint32_t *host_seco
  *   code, no context.  GV_EINVAL for an empty set or a score that is not finite.
  * gv_link_prediction_auc: the same statistic of the cosines of num_edges pairs
  *   (host_edge_first[i], host_edge_second[i]) against num_others pairs
- *   (host_other_first[i], host_other_second[i]); waits for training first.             */
+ *   (host_other_first[i], host_other_second[i]); waits for training first.  Takes up to 16
+ *   bytes of the evaluation scratch a pair, or, where the device has not that much left, 12 a
+ *   pair of the larger set (the ranking is then done on the host).                      */
 int gv_auc(const float *host_pos, uint64_t num_pos, const float *host_neg, uint64_t num_neg, double *auc);
 int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const uint32_t *host_edge_second,
                            uint64_t num_edges, const uint32_t *host_other_first, const uint32_t *host_other_second,
