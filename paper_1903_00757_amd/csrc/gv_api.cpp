@@ -1,6 +1,6 @@
 // Host runtime behind the C boundary declared in include/gvhot.h: context,
 // alias-table builder, pinned double-buffered pool ring with asynchronous
-// host-to-device copies, launch sequencing, deterministic batch cutting.
+// host-to-device copies, launch sequencing, levels of deterministic mode.
 #include "gvhot.h"
 
 #include <math.h>

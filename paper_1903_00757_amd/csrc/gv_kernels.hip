@@ -887,7 +887,7 @@ __global__ __launch_bounds__(kBlock) void k_train_level(TrainArgs a) {
 
 // Consecutive narrow levels in one launch: one workgroup of 16 waves walks level after level, a barrier between them (its
 // waves share their L1 cache, so rows stored before the barrier are read after it).  A level costs the latency of
-// gathering, storing and the barrier, 1.3 us, where a launch of its own takes 3.5 us; the record of a wave's first
+// gathering, storing and the barrier, 1.3 us, where a launch of its own takes 3 us; the record of a wave's first
 // sample of the next level is on its way meanwhile.
 constexpr int kLevelBlock = 1024;
 template <int kV, int kK, bool kFull, bool kTrack>
