@@ -158,9 +158,11 @@ int guarded(gv_ctx *ctx, Body &&body) noexcept {
 #define GV_HIP(ctx, expr)                                                                          \
     do {                                                                                           \
         hipError_t e_ = (expr);                                                                    \
-        if (e_ != hipSuccess)                                                                      \
+        if (e_ != hipSuccess) {                                                                    \
+            (void)hipGetLastError(); /* or the next launch would return it as its own */           \
             return fail(ctx, e_ == hipErrorOutOfMemory ? GV_ENOMEM : GV_EHIP, "%s: %s", #expr,     \
                         hipGetErrorString(e_));                                                    \
+        }                                                                                          \
     } while (0)
 
 int bind_device(gv_ctx *ctx) {
@@ -1517,7 +1519,6 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
         const uint64_t sorting = few ? 0 : (gv::rank_scratch_words((uint32_t)num_others) + 3u) & ~3ull;
         rc = ensure_eval_scratch(ctx, sums + (sorting + 3 * count) * sizeof(uint32_t));
         if (rc == GV_ENOMEM && !few) {  // the cosines of one set after the other take less
-            (void)hipGetLastError();
             rc = sync_all(ctx);
             if (rc) return rc;
             std::vector<float> scores(count);
