@@ -45,7 +45,7 @@ constexpr uint64_t kStageWords = 16384, kDeterministicPart = 1u << 20;  // see t
 // What the host waits for at the end of a call, and short pools of deterministic mode, in pinned memory: copied there on the compute stream, so that one wait
 // for that stream is all (a blocking copy of a few bytes takes 20 us on top of it).
 struct HostResults {
-    uint32_t flag[3];
+    uint32_t flag[4];                                             // three words used: see gv_ctx.error_flag
     uint32_t stage[kStageWords];                                  // deterministic mode
     double loss_slots[gv::kLossSlots];
     union {
@@ -217,7 +217,7 @@ int sync_all(gv_ctx *ctx, bool *evaluation_ids = nullptr) {
     }
     const uint32_t flag[3] = {r.flag[0], r.flag[1], r.flag[2]};
     if (flag[0] || flag[1] || flag[2]) {
-        GV_HIP(ctx, hipMemset(ctx->error_flag, 0, sizeof flag));
+        GV_HIP(ctx, hipMemset(ctx->error_flag, 0, sizeof r.flag));
         if (flag[0])
             return fail(ctx, GV_EINVAL, "a trained pool named a node id >= n (%u); those samples were skipped", ctx->n);
         if (flag[1])
@@ -764,8 +764,8 @@ int gv_create(const gv_config *cfg, gv_ctx **out) {
         GV_TRY(hipStreamCreateWithFlags(&ctx->compute, hipStreamNonBlocking));
         GV_TRY(hipStreamCreateWithFlags(&ctx->copy, hipStreamNonBlocking));
         GV_TRY(hipHostMalloc((void **)&ctx->results, sizeof(HostResults), hipHostMallocDefault));
-        GV_TRY(hipMalloc((void **)&ctx->error_flag, 3 * sizeof(uint32_t)));
-        GV_TRY(hipMemset(ctx->error_flag, 0, 3 * sizeof(uint32_t)));
+        GV_TRY(hipMalloc((void **)&ctx->error_flag, 4 * sizeof(uint32_t)));
+        GV_TRY(hipMemset(ctx->error_flag, 0, 4 * sizeof(uint32_t)));
         if (cfg->track_loss) {
             GV_TRY(hipMalloc((void **)&ctx->dev_loss, gv::kLossSlots * sizeof(double)));
             GV_TRY(hipMemset(ctx->dev_loss, 0, gv::kLossSlots * sizeof(double)));

@@ -45,6 +45,7 @@ struct TrainArgs {
                               // so many nodes are ranked that the detour does not pay
     uint32_t warm_ranks;      // rows of hot rank below this are warm: their updates must not be lost
                               // (see gv_build_alias)
+    uint32_t exchange_every;  // tiled schedule: see AsyncPlan
     uint32_t *records;        // tiled schedule: scratch of count x (K + 3) words, written and read by the launch
                               // (u, v, the K negatives, warm flags of the negatives); deterministic mode: the
                               // samples of the launch in the order of their levels (u, v, the K negatives, place)
@@ -56,7 +57,7 @@ struct TrainArgs {
     uint64_t total;           // T of the learning-rate schedule
     uint64_t seed;            // Philox key of the negative stream
     uint32_t count;           // samples in this launch
-    uint32_t unit, blocks, exchange_every; // asynchronous launches: see AsyncPlan
+    uint32_t unit, blocks;    // asynchronous launches: see AsyncPlan
     uint32_t report_divergence; // pool order: nonzero: a score that is NaN sets error_flag[1]
     uint32_t n;               // |V|
     uint32_t dim;             // d: row length in floats
