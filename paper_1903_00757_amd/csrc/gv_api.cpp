@@ -42,8 +42,8 @@ struct PoolSlot {
 constexpr uint64_t kHostRanked = 4096;
 constexpr uint64_t kStageWords = 16384, kDeterministicPart = 1u << 20;  // see train_deterministic
 
-// What the host waits for at the end of a call, and short pools of deterministic mode, in pinned memory: copied there on the compute stream, so that one wait
-// for that stream is all (a blocking copy of a few bytes takes 20 us on top of it).
+// In pinned memory: what the host waits for at the end of a call, copied there on the compute stream, so that one wait for
+// that stream is all (a blocking copy of a few bytes takes 20 us on top of it), and short pools of deterministic mode.
 struct HostResults {
     uint32_t flag[4];                                             // three words used: see gv_ctx.error_flag
     uint32_t stage[kStageWords];                                  // deterministic mode
@@ -740,6 +740,7 @@ int gv_create(const gv_config *cfg, gv_ctx **out) {
     do {                                                                                                   \
         hipError_t e_ = (expr);                                                                            \
         if (e_ != hipSuccess) {                                                                            \
+            (void)hipGetLastError();                                                                       \
             fail(ctx, e_ == hipErrorOutOfMemory ? GV_ENOMEM : GV_EHIP, "%s: %s", #expr, hipGetErrorString(e_)); \
             return bail(e_ == hipErrorOutOfMemory ? GV_ENOMEM : GV_EHIP);                                  \
         }                                                                                                  \

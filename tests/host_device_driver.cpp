@@ -278,7 +278,7 @@ hipError_t launch_augment(const AugmentArgs &a, hipStream_t) {
 
 // ---------------------------------------------------------------------------------------------------- checks
 namespace {
-gv_ctx *context(uint32_t mode, uint32_t num_neg, uint32_t schedule = GV_SCHEDULE_AUTO) {
+gv_config configuration(uint32_t mode, uint32_t num_neg, uint32_t schedule) {
     gv_config cfg{};
     cfg.dim = 32;
     cfg.num_neg = num_neg;
@@ -289,6 +289,10 @@ gv_ctx *context(uint32_t mode, uint32_t num_neg, uint32_t schedule = GV_SCHEDULE
     cfg.pool_capacity = 8;
     cfg.coherence = GV_COHERENCE_MIXED;
     cfg.schedule = schedule;
+    return cfg;
+}
+gv_ctx *context(uint32_t mode, uint32_t num_neg, uint32_t schedule = GV_SCHEDULE_AUTO) {
+    const gv_config cfg = configuration(mode, num_neg, schedule);
     gv_ctx *ctx = nullptr;
     CHECK(gv_create(&cfg, &ctx) == GV_OK);
     return ctx;
@@ -616,6 +620,25 @@ void packed_walks_leave_room() {
     }
 }
 
+// A context that was refused for want of memory, wherever it ran out, does not spoil the next one.
+void contexts_after_failed_allocations() {
+    const std::vector<uint32_t> degrees(10, 3);
+    for (long at = 0;; ++at) {
+        gv_config cfg = configuration(GV_MODE_HOGWILD, 1, GV_SCHEDULE_AUTO);
+        cfg.track_loss = 1;
+        gv_ctx *ctx = nullptr;
+        device_allocations_left = at;
+        const int rc = gv_create(&cfg, &ctx);
+        const bool done = device_allocations_left >= 0;
+        device_allocations_left = -1;
+        CHECK(rc == (done ? GV_OK : GV_ENOMEM) && (ctx != nullptr) == done);
+        if (!ctx) ctx = context(GV_MODE_HOGWILD, 1);
+        CHECK(gv_set_degrees(ctx, 10, degrees.data()) == GV_OK && gv_init_embeddings(ctx, 1) == GV_OK);
+        gv_destroy(ctx);
+        if (done) break;
+    }
+}
+
 // Link prediction ranks few pairs on the host, more on the device, and more on the host where the device has no memory
 // left for it: the same result all ways.
 void ranking_where_it_can_be_done() {
@@ -663,6 +686,7 @@ void ranking_where_it_can_be_done() {
 
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
+        {"contexts after failed allocations", contexts_after_failed_allocations},
         {"levels after failed allocations", levels_after_failed_allocations},
         {"pools in parts", pools_in_parts},
         {"walks after failed allocations", walks_after_failed_allocations},

@@ -33,6 +33,7 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", [
+    "contexts after failed allocations",
     "levels after failed allocations",
     "pools in parts",
     "walks after failed allocations",
