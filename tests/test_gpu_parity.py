@@ -793,9 +793,9 @@ def short_pool_run(request):
     vertex, context = oracle.init_embeddings(1, n, d)
     ref_v, ref_c = run_oracle(deg, K, w, [pool], vertex, context, total, seed)
     na, nb = W.uniform_negative_pairs(n, te_s.size, seed=32)
-    judge = lambda v, c: (evaluation_loss(deg, v, c, eval_pool, K, w), oracle.link_prediction_auc(v, te_s, te_d, na, nb))
+    score = lambda v, c: (evaluation_loss(deg, v, c, eval_pool, K, w), oracle.link_prediction_auc(v, te_s, te_d, na, nb))
     return dict(name=request.param, n=n, d=d, K=K, w=w, seed=seed, total=total, deg=deg, pool=pool, vertex=vertex,
-                context=context, ref=judge(ref_v, ref_c), judge=judge)
+                context=context, ref=score(ref_v, ref_c), score=score)
 
 
 @pytest.mark.parametrize("size", [8_192, 65_536, 500_000])
@@ -815,7 +815,7 @@ def test_short_pools_at_full_learning_rate_track_the_oracle(gv, short_pool_run, 
             gv.gv_push_pool(ctx, p)
             gv.gv_train_pool(ctx)
         gv.gv_sync(ctx)
-        loss, auc = r["judge"](*(gv.gv_read_embeddings(ctx, m, r["n"], r["d"]) for m in (gv.GV_VERTEX, gv.GV_CONTEXT)))
+        loss, auc = r["score"](*(gv.gv_read_embeddings(ctx, m, r["n"], r["d"]) for m in (gv.GV_VERTEX, gv.GV_CONTEXT)))
     ref_loss, ref_auc = r["ref"]
     print(f"short pools of {size}, {r['name']}: loss {100 * (loss / ref_loss - 1):+.3f} %, auc {auc:.4f} vs {ref_auc:.4f}", flush=True)
     assert abs(loss - ref_loss) <= 0.006 * ref_loss
