@@ -198,8 +198,9 @@ int gv_push_pool(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count);
  * asynchronous SGD): positive samples g .. g+count-1 where g is the
  * number of samples trained so far.  Returns after launching (asynchronous);
  * GV_ESTATE if nothing is queued.  The training calls keep device scratch sized
- * for the largest pool seen so far (a few words per sample; in deterministic mode of
- * at most 2^20 samples, the part of a pool that is sorted at a time): the first call, and
+ * for the largest pool seen so far (a few words per sample; in deterministic mode some 6 (K + 2) words
+ * for each of at most 2^20 samples, the part of a pool that is sorted at a time, and 4 words a node, or, where that
+ * does not fit, K + 3 words a sample): the first call, and
  * a call with a larger pool than any before, allocate (GV_ENOMEM / GV_EHIP if
  * that fails) and wait for the launches in flight.                              */
 int gv_train_pool(gv_ctx *ctx);

@@ -41,12 +41,21 @@ struct PoolSlot {
 // 101 and 48).
 constexpr uint64_t kHostRanked = 4096;
 constexpr uint64_t kStageWords = 16384, kDeterministicPart = 1u << 20;  // see train_deterministic
+// Deterministic pools of more samples than this wait for each other on the device (train_flow) instead of being sorted into
+// levels on the host: 5000 samples on 200000 nodes 66 instead of 185 us, on 5000 nodes without hubs 60 instead of 180, and
+// fewer are levelled before the preparation's dozen launches are done.  Not where the hottest row is named by more than one
+// sample in 24: levels are narrow there, and a level of a few samples costs 0.7 us in one workgroup, a link of a chain 1.3
+// (d = 128, K = 1, a pass alone: hottest share 2.1 % 9.1 -> 4.0 ms, 3.6 % 2.29 -> 1.78, 4.6 % 0.93 -> 0.95; K = 5, 7.5 % 8.0
+// -> 10.6; a star 7.8 -> 12.4).
+constexpr uint64_t kFlowFrom = 4096;
+constexpr double kFlowShare = 1.0 / 24.0;
 
 // In pinned memory: what the host waits for at the end of a call, copied there on the compute stream, so that one wait for
 // that stream is all (a blocking copy of a few bytes takes 20 us on top of it), and short pools of deterministic mode.
 struct HostResults {
     uint32_t flag[4];                                             // three words used: see gv_ctx.error_flag
     uint32_t stage[kStageWords];                                  // deterministic mode
+    gv::FlowState flow;                                           // deterministic mode, see train_flow
     double loss_slots[gv::kLossSlots];
     union {
         double partial[gv::kEvalBlocks];                          // gv_eval_loss
@@ -120,6 +129,12 @@ struct gv_ctx {
     gv_stats stats{};
     std::vector<TimedSpan> spans;         // recorded, not yet folded into stats
     std::vector<hipEvent_t> spare_events;
+    uint64_t *flow_turns = nullptr;       // device, deterministic mode: see train_flow; 2 n words, then the state
+    gv::FlowState *flow_state = nullptr;
+    hipEvent_t flow_checked = nullptr;
+    bool flow_pending = false;            // its state counts batches that are not in stats yet
+    bool flow_fresh = false;              // its state is not cleared yet
+    uint64_t flow_counted = 0;            // batches of the state that are
     std::vector<uint32_t> level_vertex, level_context;  // deterministic mode: see train_deterministic
     uint32_t level_base = 0;
     std::string error;
@@ -199,12 +214,25 @@ void fold_spans(gv_ctx *ctx) {
     ctx->spans.clear();
 }
 
+// The state of deterministic pools as copied to the host: batches go into the statistics, a wave that gave up is an error.
+int fold_flow(gv_ctx *ctx) {
+    const gv::FlowState &flow = ctx->results->flow;
+    const uint64_t counted = flow.batches + flow.deepest;
+    ctx->stats.batches += counted - ctx->flow_counted;
+    ctx->flow_counted = counted;
+    ctx->flow_pending = false;
+    if (flow.stalled) return fail(ctx, GV_EHIP, "a deterministic pool was not trained to its end: the device scratch was overwritten");
+    return GV_OK;
+}
+
 // *evaluation_ids (may be null): set where the report is that the evaluation just queued names ids that are no nodes.
 int sync_all(gv_ctx *ctx, bool *evaluation_ids = nullptr) {
     HostResults &r = *ctx->results;
     if (ctx->dev_loss)
         GV_HIP(ctx, hipMemcpyAsync(r.loss_slots, ctx->dev_loss, sizeof r.loss_slots, hipMemcpyDeviceToHost, ctx->compute));
     GV_HIP(ctx, hipMemcpyAsync(r.flag, ctx->error_flag, sizeof r.flag, hipMemcpyDeviceToHost, ctx->compute));
+    if (ctx->flow_pending)
+        GV_HIP(ctx, hipMemcpyAsync(&r.flow, ctx->flow_state, sizeof r.flow, hipMemcpyDeviceToHost, ctx->compute));
     GV_HIP(ctx, hipStreamSynchronize(ctx->copy));
     GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
     fold_spans(ctx);
@@ -214,6 +242,10 @@ int sync_all(gv_ctx *ctx, bool *evaluation_ids = nullptr) {
         double total = 0.0;
         for (double x : r.loss_slots) total += x;
         ctx->stats.train_loss_sum = total;
+    }
+    if (ctx->flow_pending) {
+        int rc = fold_flow(ctx);
+        if (rc) return rc;
     }
     const uint32_t flag[3] = {r.flag[0], r.flag[1], r.flag[2]};
     if (flag[0] || flag[1] || flag[2]) {
@@ -247,6 +279,11 @@ void free_adjacency(gv_ctx *ctx) {
 }
 
 void free_matrices(gv_ctx *ctx) {
+    if (ctx->flow_turns) (void)hipFree(ctx->flow_turns);
+    ctx->flow_turns = nullptr;
+    ctx->flow_state = nullptr;
+    ctx->flow_pending = false;
+    ctx->flow_counted = 0;
     if (ctx->vertex) (void)hipFree(ctx->vertex);
     if (ctx->context) (void)hipFree(ctx->context);
     if (ctx->alias) (void)hipFree(ctx->alias);
@@ -490,6 +527,64 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
     return GV_OK;
 }
 
+// What train_flow needs on the device beside the pool: 6 words for every row that a sample of a part names, and 4 words a
+// node.  GV_ENOMEM where that does not fit (or the nodes' would take more than an eighth of the memory that is left).
+int ensure_flow(gv_ctx *ctx, uint64_t count) {
+    if (!ctx->flow_turns) {
+        const size_t bytes = (size_t)ctx->n * 2 * sizeof(uint64_t);
+        size_t left = 0, total = 0;
+        GV_HIP(ctx, hipMemGetInfo(&left, &total));
+        if (bytes > left / 8) return GV_ENOMEM;
+        if (!ctx->flow_checked) GV_HIP(ctx, hipEventCreateWithFlags(&ctx->flow_checked, hipEventDisableTiming));
+        uint64_t *turns = nullptr;
+        GV_HIP(ctx, hipMalloc((void **)&turns, bytes + sizeof(gv::FlowState)));
+        ctx->flow_turns = turns;
+        ctx->flow_state = (gv::FlowState *)((char *)turns + bytes);
+        ctx->flow_fresh = true;
+    }
+    return ensure_records(ctx, gv::flow_scratch_words((uint32_t)std::min(count, kDeterministicPart), ctx->cfg.num_neg));
+}
+
+// Deterministic training of a pool that is not short: every sample waits on the device for the earlier samples that name
+// one of its rows (k_train_flow).  The namings of the rows are sorted there, and the host waits only for the check of the
+// ids.
+int train_flow(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count) {
+    const uint32_t K = ctx->cfg.num_neg;
+    const uint64_t part = std::min(count, kDeterministicPart);
+    int rc = GV_OK;
+    GV_HIP(ctx, gv::launch_flow_check(dev_pairs, count, ctx->n, ctx->flow_state, ctx->flow_fresh, ctx->compute));
+    ctx->flow_fresh = false;
+    gv::FlowState &flow = ctx->results->flow;
+    GV_HIP(ctx, hipMemcpyAsync(&flow, ctx->flow_state, sizeof flow, hipMemcpyDeviceToHost, ctx->compute));
+    GV_HIP(ctx, hipEventRecord(ctx->flow_checked, ctx->compute));
+    for (uint64_t first = 0; first < count; first += part) {
+        const uint64_t here = std::min(part, count - first);
+        gv::TrainArgs a = train_args(ctx, dev_pairs + 2 * first, ctx->next_g + first, (uint32_t)here);
+        a.flow = ctx->flow_state;
+        GV_HIP(ctx, gv::launch_flow_prepare(a, K, ctx->records, ctx->flow_turns, ctx->compute));
+        if (first == 0) {  // the whole pool is looked at before any of it is trained
+            GV_HIP(ctx, hipEventSynchronize(ctx->flow_checked));
+            if (flow.first_bad != UINT32_MAX)
+                return fail(ctx, GV_EINVAL, "sample %llu names node id >= n (%u)", (unsigned long long)flow.first_bad, ctx->n);
+        }
+        TimedSpan span{};
+        const bool timed = ctx->cfg.profile != 0;
+        if (timed) {
+            rc = begin_span(ctx, 0, ctx->compute, &span);
+            if (rc) return rc;
+        }
+        GV_HIP(ctx, (ctx->dev_loss ? gv::launch_train_flow_tracked : gv::launch_train_flow)(a, ctx->cfg.dim, K, ctx->compute));
+        ctx->flow_pending = true;
+        ctx->stats.train_launches += 1;
+        if (ctx->dev_loss) ctx->stats.train_loss_samples += here;
+        if (timed) {
+            rc = end_span(ctx, ctx->compute, span);
+            if (rc) return rc;
+        }
+    }
+    return GV_OK;
+}
+
 // Deterministic training: draw the pool's negatives on the device, bring them and the pairs to the host, and sort
 // the samples into levels: a sample's level is one more than the highest level of the earlier samples that name
 // one of its rows (vertex[u], context[v] or a negative's).  Samples of one level commute exactly (Def. 1, Sec. 3.2) and
@@ -623,8 +718,15 @@ int train_deterministic(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *
 
 int train_any(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *host_pairs, uint64_t count) {
     if (count == 0) return GV_OK;
-    int rc = ctx->cfg.mode == GV_MODE_DETERMINISTIC ? train_deterministic(ctx, dev_pairs, host_pairs, count)
-                                                    : train_hogwild(ctx, dev_pairs, count);
+    int rc = GV_OK;
+    if (ctx->cfg.mode != GV_MODE_DETERMINISTIC) {
+        rc = train_hogwild(ctx, dev_pairs, count);
+    } else {
+        const bool flows = count > kFlowFrom && ctx->n <= 0x80000000u && ctx->hottest_share <= kFlowShare;
+        const int room = flows ? ensure_flow(ctx, count) : GV_ENOMEM;
+        if (room != GV_OK && room != GV_ENOMEM) return room;
+        rc = room == GV_OK ? train_flow(ctx, dev_pairs, count) : train_deterministic(ctx, dev_pairs, host_pairs, count);
+    }
     if (rc) return rc;
     ctx->next_g += count;
     ctx->stats.samples_trained = ctx->next_g;
@@ -811,6 +913,7 @@ void gv_destroy(gv_ctx *ctx) {
     if (ctx->error_flag) (void)hipFree(ctx->error_flag);
     if (ctx->results) (void)hipHostFree(ctx->results);
     if (ctx->dev_loss) (void)hipFree(ctx->dev_loss);
+    if (ctx->flow_checked) (void)hipEventDestroy(ctx->flow_checked);
     if (ctx->copy) (void)hipStreamDestroy(ctx->copy);
     if (ctx->compute) (void)hipStreamDestroy(ctx->compute);
     delete ctx;
@@ -1577,8 +1680,18 @@ int gv_sync(gv_ctx *ctx) {
 
 int gv_get_stats(gv_ctx *ctx, gv_stats *out) {
     if (!ctx || !out) return ctx ? fail(ctx, GV_EINVAL, "null output") : GV_EINVAL;
-    *out = ctx->stats;
-    return GV_OK;
+    return guarded(ctx, [&]() -> int {
+        if (ctx->flow_pending) {  // the batches of deterministic pools are counted on the device
+            int rc = bind_device(ctx);
+            if (rc) return rc;
+            GV_HIP(ctx, hipMemcpyAsync(&ctx->results->flow, ctx->flow_state, sizeof(gv::FlowState), hipMemcpyDeviceToHost, ctx->compute));
+            GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
+            rc = fold_flow(ctx);
+            if (rc) return rc;
+        }
+        *out = ctx->stats;
+        return GV_OK;
+    });
 }
 
 int gv_set_position(gv_ctx *ctx, uint64_t next_g) {

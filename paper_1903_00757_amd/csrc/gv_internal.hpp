@@ -24,6 +24,18 @@ constexpr uint32_t kSmallestTile = 16, kLargestTile = 8192;  // samples per work
 __host__ __device__ constexpr bool short_rows(int V, int K) { return V * (K + 1) <= 4; }
 __host__ __device__ constexpr int tiled_batch(int V, int K) { return V * (K + 1) <= 12 ? 2 : 1; }
 
+// Deterministic mode, pools trained by k_train_flow: on the device.
+struct FlowState {
+    unsigned long long batches;  // levels of the parts before this one
+    uint32_t deepest;            // levels of this part
+    uint32_t next_chunk;         // the samples that the next wave takes
+    uint32_t first_bad;          // the first sample of the pool that names an id that is no node; UINT32_MAX: none
+    uint32_t stalled;            // set where a wave gave up (see k_train_flow)
+    uint32_t started;            // workgroups that have begun
+    unsigned long long nowhere;  // takes the turns that are not handed on
+    unsigned long long slots[64];  // rows named often: namings << 32 | place of the first
+};
+
 // Everything a training launch needs; passed by value as the kernel argument.
 struct TrainArgs {
     float *vertex;            // |V| x d, row-major
@@ -49,6 +61,9 @@ struct TrainArgs {
     uint32_t *records;        // tiled schedule: scratch of count x (K + 3) words, written and read by the launch
                               // (u, v, the K negatives, warm flags of the negatives); deterministic mode: the
                               // samples of the launch in the order of their levels (u, v, the K negatives, place)
+    FlowState *flow;              // k_train_flow: see there, and launch_flow_prepare
+    const uint32_t *keys, *places, *sorted, *namings;
+    uint64_t *turns;              // per row, vertex rows first: low word the place whose turn it is, high word levels so far
     uint32_t *error_flag;     // two words: [0] set to 1 when a sample names a node id >= n (sample skipped), [1] set
                               // to 1 when the tiled kernel meets a row that holds NaN (training has diverged)
     double *loss_slots;       // null, or kLossSlots sums: every wave adds the losses its samples saw before their
@@ -100,6 +115,14 @@ constexpr uint32_t kNarrowLevel = 48;  // samples: three rounds of the one workg
 // records[i] = sample order[i] of the pool, as launch_train_levels takes it.
 hipError_t launch_level_records(const uint32_t *pairs, const uint32_t *negatives, const uint32_t *order, uint32_t count,
                                 uint32_t num_neg, uint32_t *records, hipStream_t stream);
+// Deterministic mode, a pool whose samples wait for each other on the device (see k_train_flow): the ids of the whole pool
+// are checked (fresh: the state is cleared first), then each part of it is prepared (which sets a.keys, a.places and a.turns; scratch of
+// flow_scratch_words(), turns of 2 n) and trained.  Part: a.pairs, a.count, a.first_g.
+uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg);
+hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, FlowState *state, bool fresh, hipStream_t stream);
+hipError_t launch_flow_prepare(TrainArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t stream);
+hipError_t launch_train_flow(TrainArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
+hipError_t launch_train_flow_tracked(TrainArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
 // The same three launches with kernels that also sum the running loss into a.loss_slots (which must be set for
 // these and null for the ones above).
 hipError_t launch_train_hogwild_tracked(const TrainArgs &a, uint32_t dim, uint32_t num_neg, uint32_t coherence,

@@ -273,13 +273,54 @@ __device__ __forceinline__ void hand_over_loss(double *slots, float &lane_loss, 
 
 // One positive sample with its K negatives (Alg. 1, the Train calls; Sec. 2.1
 // scores; Sec. 4.3 negative weight): rows[0] is the positive context row v,
-// rows[1..K] the negatives.  All 1+K scores come from the rows as loaded, then
+// rows[1..K] the negatives.  All 1+K scores come from the rows as loaded (x = vertex[u], c[k] =
+// context[rows[k]]), then
 //   vertex[u]      += sum_k coef_k * context[rows_k]
 //   context[rows_k] += coef_k * vertex[u]
 // with coef_0 = lr (1 - sigmoid(s_0)), coef_k = -lr w sigmoid(s_k).  A context
 // row named more than once in the sample is written once with the summed
 // coefficient.  u and rows[] are wave-uniform.  kTrack: the scores go to lane i of `scores`.
-// Returns the score of the positive.
+
+// The coefficients and the change of x; returns the score of the positive.
+template <int kV, int kK, bool kTrack>
+__device__ __forceinline__ float sgns_coefficients(const float (&x)[kV], const float (&c)[kK + 1][kV], float lr, float w,
+                                                   ChunkScores<kK> &scores, uint32_t i, float (&coef)[kK + 1], float (&dx)[kV]) {
+    float positive = 0.0f;
+#pragma unroll
+    for (int k = 0; k <= kK; ++k) {
+        float partial = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kV; ++j) partial = fmaf(x[j], c[k][j], partial);
+        const float score = wave_sum(partial);
+        if (k == 0) positive = score;
+        coef[k] = k == 0 ? lr * (1.0f - sigmoid(score)) : -(lr * w) * sigmoid(score);
+        if constexpr (kTrack) scores.put(k, i, score);
+    }
+#pragma unroll
+    for (int j = 0; j < kV; ++j) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int k = 0; k <= kK; ++k) acc = fmaf(coef[k], c[k][j], acc);
+        dx[j] = acc;
+    }
+    return positive;
+}
+// The first naming of a context row in a sample (the others are folded into it), and the coefficient of all of them.
+template <int kK>
+__device__ __forceinline__ bool first_naming(const uint32_t (&rows)[kK + 1], int k) {
+    bool repeated = false;
+#pragma unroll
+    for (int k2 = 0; k2 < k; ++k2) repeated |= rows[k2] == rows[k];
+    return !repeated;
+}
+template <int kK>
+__device__ __forceinline__ float total_coefficient(const uint32_t (&rows)[kK + 1], const float (&coef)[kK + 1], int k) {
+    float total = coef[k];
+#pragma unroll
+    for (int k2 = k + 1; k2 <= kK; ++k2) total += rows[k2] == rows[k] ? coef[k2] : 0.0f;
+    return total;
+}
+
 template <int kV, int kK, int kCoherence, bool kFull, bool kTrack>
 __device__ __forceinline__ float sgns_step(float *__restrict__ vertex, float *__restrict__ context, uint32_t u,
                                           const uint32_t (&rows)[kK + 1], float lr, float w, int lane, uint32_t D,
@@ -291,37 +332,12 @@ __device__ __forceinline__ float sgns_step(float *__restrict__ vertex, float *__
     Io::load(xp, lane, D, x);
 #pragma unroll
     for (int k = 0; k <= kK; ++k) Io::load(context + (size_t)rows[k] * D, lane, D, c[k]);
-
-    float coef[kK + 1], positive = 0.0f;
+    float coef[kK + 1], dx[kV];
+    const float positive = sgns_coefficients<kV, kK, kTrack>(x, c, lr, w, scores, i, coef, dx);
 #pragma unroll
     for (int k = 0; k <= kK; ++k) {
-        float partial = 0.0f;
-#pragma unroll
-        for (int j = 0; j < kV; ++j) partial = fmaf(x[j], c[k][j], partial);
-        const float score = wave_sum(partial);
-        if (k == 0) positive = score;
-        coef[k] = k == 0 ? lr * (1.0f - sigmoid(score)) : -(lr * w) * sigmoid(score);
-        if constexpr (kTrack) scores.put(k, i, score);
-    }
-
-    float dx[kV];
-#pragma unroll
-    for (int j = 0; j < kV; ++j) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int k = 0; k <= kK; ++k) acc = fmaf(coef[k], c[k][j], acc);
-        dx[j] = acc;
-    }
-
-#pragma unroll
-    for (int k = 0; k <= kK; ++k) {
-        bool repeated = false;
-#pragma unroll
-        for (int k2 = 0; k2 < k; ++k2) repeated |= rows[k2] == rows[k];
-        if (repeated) continue;  // wave-uniform: already folded into its first occurrence
-        float total = coef[k];
-#pragma unroll
-        for (int k2 = k + 1; k2 <= kK; ++k2) total += rows[k2] == rows[k] ? coef[k2] : 0.0f;
+        if (!first_naming<kK>(rows, k)) continue;  // wave-uniform
+        const float total = total_coefficient<kK>(rows, coef, k);
         if constexpr (is_atomic(kCoherence)) {
             float dc[kV];
 #pragma unroll
@@ -917,6 +933,487 @@ __global__ __launch_bounds__(kLevelBlock) void k_train_levels(TrainArgs a) {
     if constexpr (kTrack) hand_over_loss(a.loss_slots, lane_loss, lane);
 }
 
+// Rows in the order of lanes of the cached accesses (16-byte segments where the row allows), at device scope, in the
+// 8-byte words that such accesses come in: a sample is computed as in the level kernels.  `row` is the same in all lanes
+// (a scalar address), `at` the lane's byte offset in it.
+template <int kV, bool kFull>
+struct HandedRow {
+    static constexpr int W = kV >= 4 ? 4 : kV, S = kV / W;
+    static __device__ __forceinline__ uint32_t lane_offset(int lane) { return (uint32_t)lane * (W * 4); }
+    static __device__ __forceinline__ void load(const char *row, uint32_t at, uint32_t bytes, float (&x)[kV]) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const uint32_t here = at + (uint32_t)s * (kWave * W * 4);
+            const bool inside = kFull || here < bytes;
+            if constexpr (W == 1) {
+                x[s] = inside ? __uint_as_float(__hip_atomic_load((const uint32_t *)(row + here), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0.0f;
+            } else {
+#pragma unroll
+                for (int e = 0; e < W; e += 2) {
+                    const uint64_t bits =
+                        inside ? __hip_atomic_load((const uint64_t *)(row + here + 4 * e), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+                    x[s * W + e] = __uint_as_float((uint32_t)bits);
+                    x[s * W + e + 1] = __uint_as_float((uint32_t)(bits >> 32));
+                }
+            }
+        }
+    }
+    static __device__ __forceinline__ void store(char *row, uint32_t at, uint32_t bytes, const float (&x)[kV]) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const uint32_t here = at + (uint32_t)s * (kWave * W * 4);
+            if (!kFull && here >= bytes) continue;
+            if constexpr (W == 1) {
+                __hip_atomic_store((uint32_t *)(row + here), __float_as_uint(x[s]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+#pragma unroll
+                for (int e = 0; e < W; e += 2)
+                    __hip_atomic_store((uint64_t *)(row + here + 4 * e),
+                                       (uint64_t)__float_as_uint(x[s * W + e]) | ((uint64_t)__float_as_uint(x[s * W + e + 1]) << 32),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+};
+
+// A pool in one launch, every sample as soon as the earlier samples that name one of its rows are done.  a.places holds,
+// for every row that a sample names, the place of that naming among all of them, sorted by row and then by sample; a row's
+// turn is the place of the naming that comes next.  A wave takes the next a.unit samples of the pool, lane l looks after
+// sample l: it polls the turns of its rows, and the samples whose turns have all come are trained (those of different
+// lanes share no row), their rows stored, the stores waited for, and the turns of their rows passed on.
+//
+// What bounds it is the chain of samples that share the hottest rows, each link the latency of one wave.  A row goes from
+// one wave to another in 1.0 us (store, wait, turn, poll, load; the same within a die and across dies), with the
+// arithmetic and the polling 1.9 us a sample.  So each of the kFlowHubs rows named most has a wave of its own, which trains
+// the samples that name it one after the other with the row in registers: 1.3 us a sample, bound by the instructions of that
+// wave and the loads of the other rows (flow_hub).  2*10^5 samples on 10^4 nodes, 1190 levels, d = 128, K = 1: 4.1 ms as
+// launches of levels, 2.0 without chains, 1.67 now (three contexts in turn: 3.4, 0.87, 0.69 ms a pool); 1.5*10^5 on 10^5 nodes
+// with hubs, 3200 levels: 9.1, 5.1, 3.95.  1024 waves of 8 samples: 16 or more samples a wave wait for each other in the wave,
+// and twice as many waves only poll more (3.4 ms with 1024 waves of 64, 6.2 with 2048, before samples far from their turn were
+// left alone).
+//
+// Every wait ends: the waves of the hubs are those of one workgroup, the first that runs, together with one that takes
+// samples as all others do; samples are taken in pool order, so the first sample of the pool that is not done is at
+// the head of a hub's chain, or has been taken by a wave that runs, or is taken by the next one that has finished
+// its own, and its turns have come.  Should they fail to (memory overwritten by the caller), a wave gives up after
+// kFlowPolls polls without a sample and says so.
+constexpr uint32_t kFlowPolls = 1u << 22;
+constexpr uint32_t kFlowStep = 2000;  // cycles, about half of what a row takes from wave to wave
+constexpr int kFlowBlock = 512, kFlowHubs = kFlowBlock / kWave - 1;
+constexpr int flow_batch(int V, int K) { return V * (K + 2) <= 14 ? 2 : 1; }
+// The rows of two samples of a chain fit the 256 registers of a wave (with those of longer ones kept in memory, 20000 samples at
+// d = 512, K = 5 take 19 ms, without chains 5.5); without chains there are no hubs.
+constexpr bool flow_has_hubs(int V, int K) { return V * (K + 2) < 40; }
+
+// One sample in registers: the rows after their updates stand where they were.  A chain is as fast as one wave goes through
+// its instructions, so the sigmoids of the K + 1 scores are taken together, score k in lane k.
+template <int kV, int kK, bool kTrack>
+__device__ __forceinline__ void sgns_in_place(float (&x)[kV], float (&c)[kK + 1][kV], const uint32_t (&rows)[kK + 1], float lr, float w,
+                                              int lane, ChunkScores<kK> &scores, uint32_t i) {
+    float score = 0.0f;
+#pragma unroll
+    for (int k = 0; k <= kK; ++k) {
+        float partial = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kV; ++j) partial = fmaf(x[j], c[k][j], partial);
+        const float score_k = wave_sum(partial);
+        score = lane == k ? score_k : score;
+        if constexpr (kTrack) scores.put(k, i, score_k);
+    }
+    const float s = sigmoid(score), each = lane == 0 ? lr * (1.0f - s) : -(lr * w) * s;
+    float coef[kK + 1];
+#pragma unroll
+    for (int k = 0; k <= kK; ++k) coef[k] = __uint_as_float(lane_value(__float_as_uint(each), k));
+    float dx[kV];
+#pragma unroll
+    for (int j = 0; j < kV; ++j) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int k = 0; k <= kK; ++k) acc = fmaf(coef[k], c[k][j], acc);
+        dx[j] = acc;
+    }
+#pragma unroll
+    for (int k = 0; k <= kK; ++k) {
+        if (!first_naming<kK>(rows, k)) continue;
+        const float total = total_coefficient<kK>(rows, coef, k);
+#pragma unroll
+        for (int j = 0; j < kV; ++j) c[k][j] = fmaf(total, x[j], c[k][j]);
+    }
+#pragma unroll
+    for (int j = 0; j < kV; ++j) x[j] += dx[j];
+}
+
+// Every load has come and every store is in memory (vmcnt(0), the other counters untouched).
+__device__ __forceinline__ void memory_is_done() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    asm volatile("" ::: "memory");
+}
+
+// What lane l knows of the sample that it looks after.
+template <int kK>
+struct FlowSample {
+    static constexpr int kRows = kK + 2;
+    uint32_t key[kRows];        // its rows (context row v is n + v)
+    uint64_t *turn[kRows];      // their turns
+    uint32_t waits_for[kRows];  // the place of its naming (the first, where it names a row twice)
+    uint32_t hands_on[kRows];   // the place behind it (so the last one's stays)
+    uint32_t level = 0;         // the highest level of the samples before it at its rows
+
+    __device__ __forceinline__ void take(const TrainArgs &a, uint32_t sample, bool mine) {
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {
+            key[j] = mine ? a.keys[(size_t)sample * kRows + j] : 0u;
+            waits_for[j] = mine ? a.places[(size_t)sample * kRows + j] : 0u;
+            hands_on[j] = waits_for[j] + 1u;
+            turn[j] = a.turns + key[j];
+        }
+#pragma unroll
+        for (int j = 1; j < kRows; ++j)
+#pragma unroll
+            for (int j2 = j - 1; j2 >= 0; --j2) waits_for[j] = key[j2] == key[j] ? waits_for[j2] : waits_for[j];
+    }
+    // Bit j of `held`: row j is in this wave's registers, and its turn neither waited for nor handed on.
+    __device__ __forceinline__ void read(bool looks, uint64_t (&is)[kRows]) const {
+        if (looks) {
+#pragma unroll
+            for (int j = 0; j < kRows; ++j) is[j] = __hip_atomic_load(turn[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // how many samples come first at the row where most do (0: its turns have come)
+    __device__ __forceinline__ uint32_t seen(const uint64_t (&is)[kRows], uint32_t held) {
+        uint32_t away = 0, highest = 0;
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {
+            const bool free = (held >> j) & 1u;
+            away = max(away, free ? 0u : waits_for[j] - (uint32_t)is[j]);
+            highest = max(highest, free ? 0u : (uint32_t)(is[j] >> 32));
+        }
+        level = highest;
+        return away;
+    }
+    __device__ __forceinline__ void hand_on(uint64_t *nowhere, uint32_t held) const {
+#pragma unroll
+        for (int j = 0; j < kRows; ++j)
+            __hip_atomic_store((held >> j) & 1u ? nowhere : turn[j], (uint64_t)(level + 1u) << 32 | hands_on[j], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+
+// The rows that have a wave of their own: lane h < kFlowHubs holds the hub h, most namings first.
+struct FlowHubs {
+    uint32_t key, begin, namings;  // namings 0: none
+    __device__ __forceinline__ void find(const TrainArgs &a, int lane) {
+        unsigned long long slot = a.flow->slots[lane], mine = 0ull;
+        for (int h = 0; h < kFlowHubs; ++h) {
+            unsigned long long most = slot;
+            for (int d = kWave / 2; d > 0; d /= 2) {
+                const unsigned long long other = __shfl_xor(most, d);
+                most = other > most ? other : most;
+            }
+            if (lane == h) mine = most;
+            if (slot == most) slot = 0ull;  // slots are different or empty: they hold where a row's namings begin
+        }
+        namings = (uint32_t)(mine >> 32);
+        begin = (uint32_t)mine;
+        key = namings > 0u ? a.sorted[begin] : 0u;
+    }
+    // The first hub among the rows of a sample (kFlowHubs: none).  Every lane must take part: the values of other lanes are
+    // read, and a register that had to be kept in memory comes back for the lanes that take part only.
+    template <int kRows>
+    __device__ __forceinline__ uint32_t owner(const uint32_t (&rows)[kRows]) const {
+        uint32_t first = kFlowHubs;
+        for (int h = kFlowHubs - 1; h >= 0; --h) {
+            if (lane_value(namings, h) == 0u) continue;
+            const uint32_t hub = lane_value(key, h);
+            bool named = false;
+#pragma unroll
+            for (int j = 0; j < kRows; ++j) named |= rows[j] == hub;
+            first = named ? (uint32_t)h : first;
+        }
+        return first;
+    }
+};
+
+// Scalar addresses of the rows by key.
+struct FlowRows {
+    char *vertex, *context;  // of keys 0
+    uint32_t bytes;
+    __device__ __forceinline__ explicit FlowRows(const TrainArgs &a)
+        : vertex((char *)a.vertex), context((char *)a.context - (uint64_t)a.n * a.dim * sizeof(float)), bytes(a.dim * (uint32_t)sizeof(float)) {}
+    __device__ __forceinline__ char *of(int j, uint32_t key) const { return (j == 0 ? vertex : context) + (uint64_t)key * bytes; }
+};
+
+// The chain of hub h: its samples, except those that name a hub before it (the row is handed to the wave of that hub and
+// awaited back).  The row stays in registers y; the other rows of the next sample are on their way while one is computed,
+// and its stores are waited for after the next one's arithmetic.  false: gave up.
+template <int kV, int kK, bool kFull, bool kTrack>
+__device__ __forceinline__ bool flow_hub(const TrainArgs &a, const FlowHubs &hubs, uint32_t h, int lane, uint32_t &deepest,
+                                         float &lane_loss) {
+    constexpr int kRows = kK + 2;
+    constexpr uint32_t kNone = 0xFFFFFFFFu, kAhead = 16;  // samples ahead whose turns are looked at
+    using Io = HandedRow<kV, kFull>;
+    const FlowRows matrix(a);
+    const uint32_t at = Io::lane_offset(lane);
+    uint64_t *const nowhere = (uint64_t *)&a.flow->nowhere;
+    const uint32_t hub = lane_value(hubs.key, h), begin = lane_value(hubs.begin, h), end = begin + lane_value(hubs.namings, h);
+    char *const row = matrix.of(hub < a.n ? 0 : 1, hub);
+    float y[kV], ahead[kRows][kV];
+#pragma unroll
+    for (int e = 0; e < kV; ++e) y[e] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kRows; ++j)
+#pragma unroll
+        for (int e = 0; e < kV; ++e) ahead[j][e] = 0.0f;
+    bool held = false;
+    uint32_t level = 0, sample_before = kNone;  // of the row in registers; the sample of the naming before
+    for (uint32_t base = begin; base < end; base += kWave) {
+        const bool inside = (uint32_t)lane < end - base;
+        const uint32_t sample = inside ? a.namings[base + lane] / (uint32_t)kRows : kNone;
+        FlowSample<kK> s;
+        s.take(a, sample, inside);
+        const uint32_t lane_before = (uint32_t)__builtin_amdgcn_ds_bpermute((lane - 1) * 4, (int)sample);
+        const bool again = sample == (lane > 0 ? lane_before : sample_before);  // the second naming of the row by a sample
+        sample_before = lane_value(sample, kWave - 1);
+        uint32_t takes = 0u;  // bit j: row j is the hub
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) takes |= (s.key[j] == hub ? 1u : 0u) << j;
+        const uint32_t owner = hubs.owner<kRows>(s.key);
+        const uint64_t own = __ballot(inside && owner == h);
+        uint64_t todo = __ballot(inside && !again), come = 0;  // samples to do; those of which all other turns have come
+        const float lr = learning_rate(a.lr0, a.lr_min_ratio, a.first_g + (inside ? sample : 0u), a.total);
+        ChunkScores<kK> scores{};
+        uint32_t unhanded = kNone, loaded = kNone;  // the sample whose turns are to be passed on, the one whose rows are on their way
+        auto hand_on = [&]() {
+            if ((uint32_t)lane == unhanded) s.hand_on(nowhere, takes);
+        };
+        auto fetch = [&](uint32_t i) {
+            const uint32_t takes_i = lane_value(takes, i);
+#pragma unroll
+            for (int j = 0; j < kRows; ++j)
+                if (!((takes_i >> j) & 1u)) Io::load(matrix.of(j, lane_value(s.key[j], i)), at, matrix.bytes, ahead[j]);
+        };
+        while (todo) {
+            const uint32_t i = (uint32_t)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            uint64_t is[kRows];
+            if (!((own & (held ? come : 0ull)) >> i & 1u)) {  // not simply the next one of the row in registers
+                memory_is_done();
+                hand_on();
+                unhanded = kNone;
+                if (!((own >> i) & 1u)) {  // another hub's: the row has to be in memory when its turn comes
+                    if (held) {
+                        Io::store(row, at, matrix.bytes, y);
+                        memory_is_done();
+                        if (lane == 0)
+                            __hip_atomic_store(a.turns + hub, (uint64_t)level << 32 | (base + i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        held = false;
+                    }
+                    continue;
+                }
+                bool here = held;
+                for (uint32_t polls = 0;; ++polls) {
+                    const uint64_t hub_turn = __hip_atomic_load(a.turns + hub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const bool looks = (uint32_t)lane >= i && (uint32_t)lane <= i + kAhead && inside && !((come >> lane) & 1u);
+                    s.read(looks, is);
+                    bool came = false;
+                    if (looks) came = s.seen(is, takes) == 0u;
+                    come |= __ballot(came);
+                    if (!here && __builtin_amdgcn_readfirstlane((uint32_t)hub_turn) == base + i) {
+                        here = true;
+                        level = __builtin_amdgcn_readfirstlane((uint32_t)(hub_turn >> 32));
+                    }
+                    if (here && ((come >> i) & 1u)) break;
+                    if (polls >= kFlowPolls) {
+                        if (lane == 0) a.flow->stalled = 1u;
+                        return false;
+                    }
+                }
+                asm volatile("" ::: "memory");
+                if (!held) Io::load(row, at, matrix.bytes, y);
+                held = true;
+                if (loaded != i) fetch(i);
+                memory_is_done();
+            }
+            if (loaded != i && unhanded != kNone) {  // its turns came with the last look, too late to fetch ahead
+                fetch(i);
+                memory_is_done();
+                hand_on();
+                unhanded = kNone;
+            }
+            float x[kV], c[kK + 1][kV];
+            const uint32_t takes_i = lane_value(takes, i);
+            uint32_t rows[kK + 1];
+#pragma unroll
+            for (int e = 0; e < kV; ++e) x[e] = takes_i & 1u ? y[e] : ahead[0][e];
+#pragma unroll
+            for (int k = 0; k <= kK; ++k) {
+                rows[k] = lane_value(s.key[1 + k], i);
+#pragma unroll
+                for (int e = 0; e < kV; ++e) c[k][e] = (takes_i >> (1 + k)) & 1u ? y[e] : ahead[1 + k][e];
+            }
+            // the next sample: its rows if their turns have come (then it shares none but the hub with this one); the turns
+            // of those behind it, unless it and the one after it are known to have come
+            const uint64_t after = todo & (todo - 1), next_two = (todo ^ after) | (after ^ (after & (after - 1)));
+            const bool look = (next_two & own & ~come) != 0;
+            const bool looks = look && (uint32_t)lane > i && (uint32_t)lane <= i + kAhead && inside && !((come >> lane) & 1u);
+            s.read(looks, is);
+            loaded = kNone;
+            if (todo & ~after & own & come) {
+                loaded = (uint32_t)__builtin_ctzll(todo);
+                fetch(loaded);
+            }
+            level = max(level, lane_value(s.level, i));
+            sgns_in_place<kV, kK, kTrack>(x, c, rows, __uint_as_float(lane_value(__float_as_uint(lr), i)), a.neg_weight, lane, scores, i);
+            // the rows of the sample before are in memory, and so the turns can go on
+            memory_is_done();
+            hand_on();
+            if (!(takes_i & 1u)) {
+                Io::store(matrix.of(0, lane_value(s.key[0], i)), at, matrix.bytes, x);
+            } else {
+#pragma unroll
+                for (int e = 0; e < kV; ++e) y[e] = x[e];
+            }
+#pragma unroll
+            for (int k = 0; k <= kK; ++k) {
+                if (!first_naming<kK>(rows, k)) continue;
+                if (!((takes_i >> (1 + k)) & 1u)) {
+                    Io::store(matrix.of(1, rows[k]), at, matrix.bytes, c[k]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < kV; ++e) y[e] = c[k][e];
+                }
+            }
+            if (look) {
+                bool came = false;
+                if (looks) came = s.seen(is, takes) == 0u;
+                come |= __ballot(came);
+            }
+            if ((uint32_t)lane == i) s.level = level;
+            unhanded = i;
+            level += 1u;
+        }
+        memory_is_done();
+        hand_on();
+        deepest = max(deepest, level);
+        if constexpr (kTrack) {
+            if ((own >> lane) & 1u) lane_loss += again ? 0.0f : scores.loss(a.neg_weight);
+            hand_over_loss(a.loss_slots, lane_loss, lane);
+        }
+    }
+    if (held) Io::store(row, at, matrix.bytes, y);
+    return true;
+}
+
+template <int kV, int kK, bool kFull, bool kTrack>
+__global__ __launch_bounds__(kFlowBlock) void k_train_flow(TrainArgs a) {
+    constexpr int kRows = kK + 2, kBatch = flow_batch(kV, kK);
+    using Io = HandedRow<kV, kFull>;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    FlowState *const state = a.flow;
+    float lane_loss = 0.0f;
+    uint32_t deepest = 0, chunks_done = 0;
+    bool goes_on = true;
+    FlowHubs hubs{};
+    if constexpr (flow_has_hubs(kV, kK)) {
+        __shared__ uint32_t s_started;
+        hubs.find(a, lane);
+        if (threadIdx.x == 0) s_started = __hip_atomic_fetch_add(&state->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (s_started == 0u && wave < (uint32_t)kFlowHubs && lane_value(hubs.namings, wave) > 0u)
+            goes_on = flow_hub<kV, kK, kFull, kTrack>(a, hubs, wave, lane, deepest, lane_loss);
+    }
+    const FlowRows matrix(a);
+    const uint32_t at = Io::lane_offset(lane);
+    const uint32_t chunks = (a.count + a.unit - 1) / a.unit;
+    while (goes_on) {
+        uint32_t chunk = 0;
+        if (lane == 0) chunk = __hip_atomic_fetch_add(&state->next_chunk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        chunk = __builtin_amdgcn_readfirstlane(chunk);
+        if (chunk >= chunks) break;
+        const uint32_t base = chunk * a.unit;
+        const bool inside = (uint32_t)lane < min(a.unit, a.count - base);
+        FlowSample<kK> s;
+        s.take(a, base + lane, inside);
+        uint32_t owner = kFlowHubs;
+        if constexpr (flow_has_hubs(kV, kK)) owner = hubs.owner<kRows>(s.key);
+        const bool mine = inside && owner == (uint32_t)kFlowHubs;
+        const float lr = learning_rate(a.lr0, a.lr_min_ratio, a.first_g + base + lane, a.total);
+        ChunkScores<kK> scores{};
+        uint32_t polls = 0;
+        uint64_t pending = __ballot(mine), ready = 0;            // samples to do; those of which all turns have come
+        uint32_t due = (uint32_t)__builtin_readcyclecounter();  // lane l: when its turns are looked at again
+        while (pending) {
+            if ((uint32_t)__popcll(ready) < (uint32_t)kBatch) {
+                const uint32_t now = (uint32_t)__builtin_readcyclecounter();
+                const bool waits = (pending & ~ready) >> lane & 1u, looks = waits && (int32_t)(now - due) >= 0;
+                uint64_t is[kRows];
+                s.read(looks, is);
+                bool came = false;
+                if (looks) {
+                    const uint32_t away = s.seen(is, 0u);
+                    came = away == 0u;
+                    // a sample that others come before is not looked at again before they can be done
+                    if (away > 1u) due = now + min(away - 1u, 64u) * kFlowStep;
+                }
+                ready |= __ballot(came);
+                if (!ready) {
+                    if (++polls >= kFlowPolls) {
+                        if (lane == 0) state->stalled = 1u;
+                        break;
+                    }
+                    if (!__ballot(waits && (int32_t)(due - now) < (int32_t)kFlowStep)) __builtin_amdgcn_s_sleep(8);
+                    continue;
+                }
+            }
+            polls = 0;
+            asm volatile("" ::: "memory");
+            uint64_t taken = 0;
+            float x[kBatch][kV], c[kBatch][kK + 1][kV];
+            uint32_t u[kBatch], rows[kBatch][kK + 1], of[kBatch];
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                if (ready == 0) continue;
+                of[b] = (uint32_t)__builtin_ctzll(ready);
+                ready &= ready - 1;
+                taken |= 1ull << of[b];
+                u[b] = lane_value(s.key[0], of[b]);
+#pragma unroll
+                for (int k = 0; k <= kK; ++k) rows[b][k] = lane_value(s.key[1 + k], of[b]);
+                Io::load(matrix.of(0, u[b]), at, matrix.bytes, x[b]);
+#pragma unroll
+                for (int k = 0; k <= kK; ++k) Io::load(matrix.of(1, rows[b][k]), at, matrix.bytes, c[b][k]);
+            }
+            const uint32_t batch = (uint32_t)__popcll(taken);
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b)
+                if ((uint32_t)b < batch) {
+                    const float lr_b = __uint_as_float(lane_value(__float_as_uint(lr), of[b]));
+                    sgns_in_place<kV, kK, kTrack>(x[b], c[b], rows[b], lr_b, a.neg_weight, lane, scores, of[b]);
+#pragma unroll
+                    for (int k = 0; k <= kK; ++k)
+                        if (first_naming<kK>(rows[b], k)) Io::store(matrix.of(1, rows[b][k]), at, matrix.bytes, c[b][k]);
+                    Io::store(matrix.of(0, u[b]), at, matrix.bytes, x[b]);
+                }
+            memory_is_done();
+            if ((taken >> lane) & 1u) {
+                s.hand_on(nullptr, 0u);
+                deepest = max(deepest, s.level + 1u);
+            }
+            pending &= ~taken;
+        }
+        goes_on = !pending;
+        if constexpr (kTrack) {
+            if (mine) lane_loss += scores.loss(a.neg_weight);
+            if ((++chunks_done & 15u) == 0u) hand_over_loss(a.loss_slots, lane_loss, lane);
+        }
+    }
+    for (int d = kWave / 2; d > 0; d /= 2) deepest = max(deepest, (uint32_t)__shfl_xor((int)deepest, d));
+    if (lane == 0 && deepest > 0u) (void)__hip_atomic_fetch_max(&state->deepest, deepest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (kTrack) hand_over_loss(a.loss_slots, lane_loss, lane);
+}
+
 #if !GV_TRACK_LOSS
 // ---------------------------------------------------------------------------
 // Evaluation (no training runs meanwhile, so plain cached loads are fine).
@@ -1102,9 +1599,12 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_places(uint32_t *__restric
 }
 
 // ... and the keys go there in their order: 1024 at a time, a wave finds the lanes with its lane's digit by eight ballots.
-__global__ __launch_bounds__(kSortBlock) void k_radix_scatter(const uint32_t *__restrict__ keys, uint32_t count, uint32_t segment,
-                                                              uint32_t shift, const uint32_t *__restrict__ places,
-                                                              uint32_t *__restrict__ out) {
+// kCarried: each key takes a word with it, the one beside it in `words`, or, where that is null, its own place.
+template <bool kCarried>
+__global__ __launch_bounds__(kSortBlock) void k_radix_scatter(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ words,
+                                                              uint32_t count, uint32_t segment, uint32_t shift,
+                                                              const uint32_t *__restrict__ places, uint32_t *__restrict__ out,
+                                                              uint32_t *__restrict__ words_out) {
     __shared__ uint32_t s_next[kDigits];               // place of the workgroup's next key of a digit
     __shared__ uint32_t s_place[kSortWaves][kDigits];  // keys of a digit in a wave, then the place of the first of them
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -1135,7 +1635,11 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(const uint32_t *__
             s_next[threadIdx.x] = next;
         }
         __syncthreads();
-        if (mine) out[s_place[wave][digit] + rank] = key;
+        if (mine) {
+            const uint32_t to = s_place[wave][digit] + rank;
+            out[to] = key;
+            if constexpr (kCarried) words_out[to] = words ? words[base + threadIdx.x] : (uint32_t)(base + threadIdx.x);
+        }
         __syncthreads();
     }
 }
@@ -1199,6 +1703,64 @@ __global__ __launch_bounds__(kBlock) void k_level_records(const uint2 *__restric
         record[1] = p.y;
         for (uint32_t k = 0; k < num_neg; ++k) record[2 + k] = negatives[(size_t)place * num_neg + k];
         record[2 + num_neg] = place;
+    }
+}
+
+// Preparation of k_train_flow.  The state of a part: what the part before counted is folded into `batches`; of a pool: no
+// id is bad so far.
+__global__ __launch_bounds__(kWave) void k_flow_begin(FlowState *state, bool new_pool, bool fresh) {
+    state->slots[threadIdx.x] = 0ull;
+    if (threadIdx.x != 0) return;
+    if (fresh) {
+        state->batches = 0ull;
+        state->deepest = state->stalled = 0u;
+    }
+    state->started = 0u;
+    state->batches += state->deepest;
+    state->deepest = 0u;
+    state->next_chunk = 0u;
+    if (new_pool) state->first_bad = UINT32_MAX;
+}
+// first_bad = the first sample that names an id that is no node, if any does
+__global__ __launch_bounds__(kBlock) void k_flow_check(const uint2 *__restrict__ pairs, uint64_t count, uint32_t n, FlowState *state) {
+    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (uint64_t)gridDim.x * kBlock) {
+        const uint2 p = pairs[i];
+        if (p.x >= n || p.y >= n) atomicMin(&state->first_bad, (uint32_t)i);
+    }
+}
+// The rows that the samples name, K + 2 words a sample: u, n + v, n + every negative (row 0 in the place of a bad id: the
+// sort and the turns go over such a pool, the training does not).
+__global__ __launch_bounds__(kBlock) void k_flow_keys(const uint2 *__restrict__ pairs, const uint4 *__restrict__ alias, uint32_t n,
+                                                      uint64_t seed, uint64_t first_g, uint32_t count, uint32_t num_neg,
+                                                      uint32_t *__restrict__ keys) {
+    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (uint64_t)gridDim.x * kBlock) {
+        const uint2 p = pairs[i];
+        uint32_t *key = keys + i * (num_neg + 2);
+        key[0] = p.x < n ? p.x : 0u;
+        key[1] = n + (p.y < n ? p.y : 0u);
+        for (uint32_t k = 0; k < num_neg; ++k) key[2 + k] = n + draw_negative(alias, n, seed, first_g + i, k);
+    }
+}
+// From the sorted namings: the place of every naming; where a row's namings begin, the row's first turn, and, if there
+// are many, an entry {namings, begin} in one of 64 slots, which keeps the largest (FlowHubs takes the first of them).
+__global__ __launch_bounds__(kBlock) void k_flow_places(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ namings,
+                                                        uint32_t count, uint32_t *__restrict__ places, uint64_t *__restrict__ turns,
+                                                        FlowState *state) {
+    constexpr uint32_t kMany = 32;
+    for (uint64_t j = (uint64_t)blockIdx.x * kBlock + threadIdx.x; j < count; j += (uint64_t)gridDim.x * kBlock) {
+        places[namings[j]] = (uint32_t)j;
+        const uint32_t key = keys[j];
+        if (j > 0 && keys[j - 1] == key) continue;
+        turns[key] = j;
+        if (j + kMany > count || keys[j + kMany - 1] != key) continue;
+        uint64_t last = j + kMany - 1, step = kMany;  // a naming of the row; the last one is less than `step` on
+        while (last + step < count && keys[last + step] == key) {
+            last += step;
+            step *= 2;
+        }
+        for (; step > 1; step /= 2)
+            if (last + step / 2 < count && keys[last + step / 2] == key) last += step / 2;
+        atomicMax(&state->slots[(key * 0x9E3779B1u) >> 26], (unsigned long long)(last - j + 1) << 32 | j);
     }
 }
 
@@ -1520,6 +2082,19 @@ hipError_t launch_levels_vk(const TrainArgs &a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+template <int kV, int kK>
+hipError_t launch_flow_vk(const TrainArgs &a, hipStream_t stream) {
+    if (a.count == 0) return hipSuccess;
+    if ((a.loss_slots != nullptr) != (GV_TRACK_LOSS != 0) || a.unit == 0 || a.unit > (uint32_t)kWave || a.blocks == 0)
+        return hipErrorInvalidValue;
+    constexpr bool kTrack = GV_TRACK_LOSS != 0;
+    if (a.dim == (uint32_t)(kWave * kV))
+        hipLaunchKernelGGL((k_train_flow<kV, kK, true, kTrack>), dim3(a.blocks), dim3(kFlowBlock), 0, stream, a);
+    else
+        hipLaunchKernelGGL((k_train_flow<kV, kK, false, kTrack>), dim3(a.blocks), dim3(kFlowBlock), 0, stream, a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 #define GV_DISPATCH_K(V, CALL)                 \
@@ -1555,6 +2130,15 @@ hipError_t GV_TRAIN_NAME(launch_train_tiled)(const TrainArgs &a, uint32_t dim, u
 
 hipError_t GV_TRAIN_NAME(launch_train_levels)(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t stream) {
 #define GV_CALL(V, K) launch_levels_vk<V, K>(a, stream)
+    GV_DISPATCH(GV_CALL)
+#undef GV_CALL
+}
+
+hipError_t GV_TRAIN_NAME(launch_train_flow)(TrainArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream) {
+    a.unit = 8;
+    const uint32_t per_block = a.unit * (kFlowBlock / kWave);
+    a.blocks = std::min((a.count + per_block - 1) / per_block, 128u);
+#define GV_CALL(V, K) launch_flow_vk<V, K>(a, stream)
     GV_DISPATCH(GV_CALL)
 #undef GV_CALL
 }
@@ -1618,10 +2202,56 @@ hipError_t launch_rank_statistic(uint32_t *scores, uint32_t num_pos, uint32_t nu
     for (uint32_t shift = 0; shift < 32u; shift += 8u) {  // four passes: the keys end where they began
         hipLaunchKernelGGL(k_radix_count, dim3(blocks), dim3(kSortBlock), 0, stream, from, num_neg, segment, shift, counts);
         hipLaunchKernelGGL(k_radix_places, dim3(1), dim3(kSortBlock), 0, stream, counts, kDigits * blocks);
-        hipLaunchKernelGGL(k_radix_scatter, dim3(blocks), dim3(kSortBlock), 0, stream, from, num_neg, segment, shift, counts, to);
+        hipLaunchKernelGGL(k_radix_scatter<false>, dim3(blocks), dim3(kSortBlock), 0, stream, from, (const uint32_t *)nullptr, num_neg,
+                           segment, shift, counts, to, (uint32_t *)nullptr);
         std::swap(from, to);
     }
     hipLaunchKernelGGL(k_rank_sum, dim3(kRankBlocks), dim3(kBlock), 0, stream, scores, (uint64_t)num_pos, from, num_neg, twice);
+    return hipGetLastError();
+}
+
+// Keys, the sorted keys with their namings (twice, for the passes of the sort), the places and the counts of the sort.
+uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg) {
+    const uint64_t namings = (uint64_t)count * (num_neg + 2);
+    return 6 * ((namings + 3u) & ~3ull) + (uint64_t)kDigits * ((namings + rank_segment((uint32_t)namings) - 1) / rank_segment((uint32_t)namings));
+}
+
+hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, FlowState *state, bool fresh, hipStream_t stream) {
+    hipLaunchKernelGGL(k_flow_begin, dim3(1), dim3(kWave), 0, stream, state, true, fresh);
+    const uint64_t wanted = (count + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL(k_flow_check, dim3((uint32_t)std::min<uint64_t>(wanted, 4096u)), dim3(kBlock), 0, stream, (const uint2 *)pairs,
+                       count, n, state);
+    return hipGetLastError();
+}
+
+hipError_t launch_flow_prepare(TrainArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t stream) {
+    if (a.count == 0 || a.n > 0x80000000u) return hipErrorInvalidValue;
+    const uint32_t namings = a.count * (num_neg + 2);
+    const uint64_t stride = ((uint64_t)namings + 3u) & ~3ull;
+    uint32_t *const keys = scratch, *const places = scratch + stride;
+    uint32_t *to = scratch + 2 * stride, *other = scratch + 4 * stride, *const counts = scratch + 6 * stride;
+    hipLaunchKernelGGL(k_flow_begin, dim3(1), dim3(kWave), 0, stream, a.flow, false, false);
+    const uint32_t by_sample = std::min((a.count + kBlock - 1u) / kBlock, 65536u);
+    hipLaunchKernelGGL(k_flow_keys, dim3(by_sample), dim3(kBlock), 0, stream, (const uint2 *)a.pairs, a.alias, a.n, a.seed, a.first_g,
+                       a.count, num_neg, keys);
+    const uint32_t segment = rank_segment(namings), blocks = (namings + segment - 1u) / segment;
+    const uint32_t *from = keys, *words = nullptr;
+    for (uint32_t shift = 0; (2ull * a.n - 1u) >> shift; shift += 8u) {
+        hipLaunchKernelGGL(k_radix_count, dim3(blocks), dim3(kSortBlock), 0, stream, from, namings, segment, shift, counts);
+        hipLaunchKernelGGL(k_radix_places, dim3(1), dim3(kSortBlock), 0, stream, counts, kDigits * blocks);
+        hipLaunchKernelGGL(k_radix_scatter<true>, dim3(blocks), dim3(kSortBlock), 0, stream, from, words, namings, segment, shift, counts,
+                           to, to + stride);
+        from = to;
+        words = to + stride;
+        std::swap(to, other);
+    }
+    hipLaunchKernelGGL(k_flow_places, dim3(std::min((namings + kBlock - 1u) / kBlock, 65536u)), dim3(kBlock), 0, stream, from, words,
+                       namings, places, turns, a.flow);
+    a.sorted = from;
+    a.namings = words;
+    a.keys = keys;
+    a.places = places;
+    a.turns = turns;
     return hipGetLastError();
 }
 

@@ -135,6 +135,7 @@ struct Trained {  // of deterministic mode, in the order of training
 };
 std::vector<Trained> trained;
 uint32_t levels_trained = 0;
+uint64_t flowed = 0;  // samples trained by launch_train_flow
 int training_reports = -1;  // word of the error flag that asynchronous training sets, if any
 bool tiled_launched = false;
 uint32_t launched_unit = 0;
@@ -185,6 +186,44 @@ hipError_t launch_train_levels(const TrainArgs &a, uint32_t, uint32_t num_neg, h
 }
 hipError_t launch_train_levels_tracked(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t s) {
     return launch_train_levels(a, dim, num_neg, s);
+}
+uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg) { return 6ull * count * (num_neg + 2); }
+hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, FlowState *state, bool fresh, hipStream_t) {
+    if (fresh) state->batches = state->deepest = state->stalled = 0;
+    state->first_bad = UINT32_MAX;
+    for (uint64_t i = count; i-- > 0;)
+        if (pairs[2 * i] >= n || pairs[2 * i + 1] >= n) state->first_bad = (uint32_t)i;
+    return hipGetLastError();
+}
+hipError_t launch_flow_prepare(TrainArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t) {
+    a.flow->batches += a.flow->deepest;
+    a.flow->deepest = 0;
+    memset(scratch, 0, flow_scratch_words(a.count, num_neg) * sizeof *scratch);
+    memset(turns, 0, 2 * (size_t)a.n * sizeof *turns);
+    for (uint64_t i = 0; i < a.count; ++i) {
+        uint32_t *key = scratch + i * (num_neg + 2);
+        key[0] = a.pairs[2 * i];
+        key[1] = a.n + a.pairs[2 * i + 1];
+        for (uint32_t k = 0; k < num_neg; ++k) key[2 + k] = a.n + draw(a.first_g + i, k, a.n);
+    }
+    a.keys = scratch;
+    return hipGetLastError();
+}
+hipError_t launch_train_flow(TrainArgs a, uint32_t, uint32_t num_neg, hipStream_t) {
+    const long left = host_allocations_left;
+    host_allocations_left = -1;
+    CHECK(a.flow->first_bad == UINT32_MAX);
+    for (uint64_t i = 0; i < a.count; ++i) {  // one after the other
+        const uint32_t *key = a.keys + i * (num_neg + 2);
+        trained.push_back(Trained{levels_trained++, std::vector<uint32_t>(key, key + num_neg + 2), a.first_g + i});
+    }
+    a.flow->deepest = a.count;
+    flowed += a.count;
+    host_allocations_left = left;
+    return hipGetLastError();
+}
+hipError_t launch_train_flow_tracked(TrainArgs a, uint32_t dim, uint32_t num_neg, hipStream_t s) {
+    return launch_train_flow(a, dim, num_neg, s);
 }
 hipError_t launch_level_records(const uint32_t *pairs, const uint32_t *negatives, const uint32_t *order, uint32_t count,
                                 uint32_t num_neg, uint32_t *records, hipStream_t) {
@@ -379,6 +418,61 @@ void pools_in_parts() {
     }
     device_largest = SIZE_MAX;
     gv_destroy(ctx);
+}
+
+// Pools that are not short wait for each other on the device where that finds memory, and are levelled on the host where
+// it does not, or where the hottest row is named by many; a bad id is found before any sample is trained; the batches of
+// either way are counted.
+void flowing_pools() {
+    const uint32_t n = 2000, K = 2, count = 5000;
+    const std::vector<uint32_t> degrees(n, 3), pool = random_pool(n, count, 1);
+    std::vector<uint32_t> bad = pool;
+    bad[2 * 4321 + 1] = n;
+    uint64_t levelled = 0;
+    for (long at = 0;; ++at) {
+        gv_ctx *ctx = context(GV_MODE_DETERMINISTIC, K);
+        CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+        device_allocations_left = at;
+        flowed = 0;
+        CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK);
+        const bool done = device_allocations_left >= 0;
+        device_allocations_left = -1;
+        CHECK(flowed == (done ? count : 0));  // a node's or a sample's words do not fit: levels
+        levelled += flowed == 0;
+        check_levels(pool, 0, n, K);
+        CHECK(gv_train_device_pool(ctx, bad.data(), count) == GV_EINVAL && trained.empty());
+        CHECK(strstr(gv_last_error(ctx), "sample 4321 names node id >= n"));
+        flowed = 0;
+        CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK && flowed == count);
+        check_levels(pool, count, n, K);
+        gv_stats stats;
+        CHECK(gv_get_stats(ctx, &stats) == GV_OK && stats.batches >= count && stats.samples_trained == 2 * count);
+        CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK && gv_sync(ctx) == GV_OK);
+        const uint64_t before = stats.batches;
+        CHECK(gv_get_stats(ctx, &stats) == GV_OK && stats.batches == before + count);
+        trained.clear();
+        // a graph anew
+        CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+        CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK && gv_sync(ctx) == GV_OK);
+        CHECK(gv_get_stats(ctx, &stats) == GV_OK && stats.batches == before + 2 * count);
+        trained.clear();
+        gv_destroy(ctx);
+        if (done) break;
+    }
+    CHECK(levelled == 2);
+    // shorter, on a hub, and where the nodes' words would take more than an eighth of the memory that is left
+    std::vector<uint32_t> star(n, 1);
+    star[7] = n;
+    for (int which = 0; which < 3; ++which) {
+        gv_ctx *ctx = context(GV_MODE_DETERMINISTIC, K);
+        CHECK(gv_set_degrees(ctx, n, which == 1 ? star.data() : degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+        device_free = which == 2 ? 8 * 16 * n - 1 : SIZE_MAX;
+        flowed = 0;
+        CHECK(gv_train_device_pool(ctx, pool.data(), which == 0 ? 4096 : count) == GV_OK && flowed == 0);
+        device_free = SIZE_MAX;
+        trained.clear();
+        gv_destroy(ctx);
+    }
 }
 
 // A graph of a ring with chords: every node has its two neighbours and the nodes two steps away.
@@ -688,6 +782,7 @@ int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"contexts after failed allocations", contexts_after_failed_allocations},
         {"levels after failed allocations", levels_after_failed_allocations},
+        {"flowing pools", flowing_pools},
         {"pools in parts", pools_in_parts},
         {"walks after failed allocations", walks_after_failed_allocations},
         {"packed walks leave room", packed_walks_leave_room},

@@ -212,6 +212,64 @@ def test_deterministic_levels_of_every_width(gv, widths, d, K, track):
     assert stats["samples_trained"] == 2 * u.size and stats["batches"] >= 2 * len(widths) - 1
 
 
+def conflict_levels(pool, neg, n):
+    """Levels of a pool: one more than the highest level of the earlier samples that name one of a sample's rows."""
+    level = np.zeros(2 * n, dtype=np.int64)
+    for u, v, ks in zip(pool[:, 0].tolist(), pool[:, 1].tolist(), neg.tolist()):
+        rows = [u, n + v] + [n + k for k in ks]
+        level[rows] = level[rows].max() + 1
+    return int(level.max())
+
+
+@pytest.mark.parametrize("track", [0, 1])
+@pytest.mark.parametrize("d,K,count", [(128, 1, 9000), (64, 5, 4097), (32, 2, 5003), (96, 3, 6001), (256, 4, 4100), (352, 1, 4999),
+                                       (512, 2, 4200), (512, 5, 4300)])
+@pytest.mark.parametrize("hubs", [0, 1, 3, 12])
+def test_deterministic_pools_that_wait_on_the_device(gv, hubs, d, K, count, track):
+    """Pools that wait for each other sample by sample: without rows that many share; with a vertex row and a context row
+    that most samples name; with several of either, some of them twice in a sample (the graph has so few nodes that
+    negatives meet them), more than have a wave of their own.  Equal to the oracle, and in as many batches as the pool has
+    conflict-free levels."""
+    import torch
+
+    n, w, seed = 3000, 5.0 / K, 47
+    rng = np.random.default_rng(100 * hubs + d + K)
+    deg = rng.integers(20, 30, size=n).astype(np.uint32)
+    pool = rng.integers(n, size=(count, 2)).astype(np.uint32)
+    for i in range(hubs):  # every hub is u of some samples and v of others
+        for side in (0, 1):
+            pool[rng.random(count) < 0.6 / (i + 1), side] = 17 * i + side
+    vertex, context = random_embeddings(n, d, seed=15)
+    T = 3 * count
+    thresh, alias = oracle.alias_build(oracle.degree_weights(deg))
+    neg = oracle.draw_negatives(seed, 0, 2 * count, K, thresh, alias)
+    with context_for(gv, dim=d, num_neg=K, neg_weight=w, mode=gv.GV_MODE_DETERMINISTIC, total_samples=T, seed=seed,
+                     pool_capacity=count, lr0=LR0, track_loss=track, profile=track) as ctx:
+        gv.gv_set_degrees(ctx, deg)
+        gv.gv_build_alias(ctx, 0.75)
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+        held = torch.from_numpy(pool.view(np.int32)).cuda()
+        bad = held.clone()
+        bad[count - 2, 1] = n
+        torch.cuda.synchronize()
+        gv.gv_train_device_pool(ctx, held.data_ptr(), count)
+        with pytest.raises(gv.GvError, match=f"sample {count - 2} names node id"):
+            gv.gv_train_device_pool(ctx, bad.data_ptr(), count)
+        assert gv.gv_get_stats(ctx)["batches"] == conflict_levels(pool, neg[:count], n)
+        gv.gv_push_pool(ctx, pool)
+        gv.gv_train_pool(ctx)
+        got_v = gv.gv_read_embeddings(ctx, gv.GV_VERTEX, n, d)
+        got_c = gv.gv_read_embeddings(ctx, gv.GV_CONTEXT, n, d)
+        stats = gv.gv_get_stats(ctx)
+    ref_v, ref_c = run_oracle(deg, K, w, [pool, pool], vertex, context, T, seed)
+    for got, ref in ((got_v, ref_v), (got_c, ref_c)):
+        fro, mx = rel_errors(got, ref)
+        assert fro <= 1e-5 and mx <= 1e-4, (fro, mx)
+    assert stats["samples_trained"] == 2 * count and stats["train_launches"] == 2
+    assert stats["batches"] == sum(conflict_levels(pool, neg[i * count:(i + 1) * count], n) for i in (0, 1))
+
+
 @pytest.mark.parametrize("resident", [False, True])
 def test_deterministic_pool_of_several_parts(gv, resident):
     """A pool of more than the 2^20 samples that are sorted into levels at a time, pushed and resident; then

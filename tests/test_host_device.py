@@ -35,6 +35,7 @@ def driver(tmp_path_factory):
 @pytest.mark.parametrize("check", [
     "contexts after failed allocations",
     "levels after failed allocations",
+    "flowing pools",
     "pools in parts",
     "walks after failed allocations",
     "packed walks leave room",
