@@ -153,7 +153,7 @@ hipError_t launch_cosine(const float *vertex, uint32_t n, uint32_t dim, const ui
 // num_pos) against the num_neg scores behind them, num_pos + num_neg <= 2^31 (all are overwritten); not_finite[0 ..
 // kRankBlocks) holds a nonzero where a score is no number.  scratch: rank_scratch_words(num_neg) words at a multiple of
 // 16 bytes.
-constexpr uint32_t kRankBlocks = 512;
+constexpr uint32_t kRankBlocks = 256;
 uint64_t rank_scratch_words(uint32_t num_neg);
 hipError_t launch_rank_statistic(uint32_t *scores, uint32_t num_pos, uint32_t num_neg, uint32_t *scratch,
                                  unsigned long long *twice, unsigned long long *not_finite, hipStream_t stream);

@@ -1492,37 +1492,53 @@ __global__ __launch_bounds__(kBlock) void k_eval_loss(TrainArgs a, double *__res
 }
 
 // out[i] = cosine of vertex rows first[i], second[i] (0 when a row is zero), the score of
-// an edge in link prediction (Sec. 4.5).
-template <int kV>
+// an edge in link prediction (Sec. 4.5).  A wave takes `unit` pairs at a time, lane l the ids of pair l, gathers the rows
+// of a few pairs together and lays their sums into lanes, which take the roots and the quotients once per chunk.
+// (5*10^5 pairs, d = 128, a million nodes: 93 us with one pair at a time, 5.5 TB/s of rows, and 66 now, 7.7 TB/s, what a read of
+// random rows reaches.)
+constexpr int cosine_batch(int V) { return V <= 2 ? 4 : (V == 4 ? 2 : 1); }
+template <int kV, bool kFull>
 __global__ __launch_bounds__(kBlock) void k_cosine(const float *__restrict__ vertex, uint32_t n, uint32_t dim,
                                                    const uint32_t *__restrict__ first,
-                                                   const uint32_t *__restrict__ second, uint32_t count,
+                                                   const uint32_t *__restrict__ second, uint32_t count, uint32_t unit,
                                                    float *__restrict__ out, uint32_t *error_flag) {
-    using Io = RowIo<kV, kPlain>;
+    using Io = RowIo<kV, kPlain, kFull>;
+    constexpr int kBatch = cosine_batch(kV);
     const int lane = threadIdx.x & (kWave - 1);
-    const uint32_t waves = gridDim.x * (kBlock / kWave);
-    for (uint32_t i = __builtin_amdgcn_readfirstlane((blockIdx.x * kBlock + threadIdx.x) / kWave); i < count;
-         i += waves) {
-        const uint32_t ra = first[i], rb = second[i];
-        if (ra >= n || rb >= n) {
-            *error_flag = 1u;
-            if (lane == 0) out[i] = 0.0f;
-            continue;
-        }
-        float x[kV], y[kV];
-        Io::load(vertex + (size_t)ra * dim, lane, dim, x);
-        Io::load(vertex + (size_t)rb * dim, lane, dim, y);
+    const uint32_t waves = gridDim.x * (kBlock / kWave), chunks = (uint32_t)(((uint64_t)count + unit - 1) / unit);
+    for (uint32_t chunk = __builtin_amdgcn_readfirstlane((blockIdx.x * kBlock + threadIdx.x) / kWave); chunk < chunks; chunk += waves) {
+        const uint32_t base = chunk * unit, in_chunk = min(unit, count - base);
+        const bool mine = (uint32_t)lane < in_chunk;
+        uint32_t ra = mine ? first[base + lane] : 0u, rb = mine ? second[base + lane] : 0u;
+        const bool named = mine && ra < n && rb < n;
+        if (mine && !named) *error_flag = 1u;
+        if (!named) ra = rb = 0u;  // row 0 is read in its place, and its score dropped
         float xy = 0.0f, xx = 0.0f, yy = 0.0f;
+        for (uint32_t i0 = 0; i0 < in_chunk; i0 += kBatch) {
+            float x[kBatch][kV], y[kBatch][kV];
 #pragma unroll
-        for (int j = 0; j < kV; ++j) {
-            xy = fmaf(x[j], y[j], xy);
-            xx = fmaf(x[j], x[j], xx);
-            yy = fmaf(y[j], y[j], yy);
+            for (int b = 0; b < kBatch; ++b) {
+                const uint32_t i = min(i0 + b, in_chunk - 1u);  // past the end: the last pair again
+                Io::load(vertex + (size_t)lane_value(ra, i) * dim, lane, dim, x[b]);
+                Io::load(vertex + (size_t)lane_value(rb, i) * dim, lane, dim, y[b]);
+            }
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                float pxy = 0.0f, pxx = 0.0f, pyy = 0.0f;
+#pragma unroll
+                for (int j = 0; j < kV; ++j) {
+                    pxy = fmaf(x[b][j], y[b][j], pxy);
+                    pxx = fmaf(x[b][j], x[b][j], pxx);
+                    pyy = fmaf(y[b][j], y[b][j], pyy);
+                }
+                const bool here = (uint32_t)lane == i0 + b;
+                const float sxy = wave_sum(pxy), sxx = wave_sum(pxx), syy = wave_sum(pyy);
+                xy = here ? sxy : xy;
+                xx = here ? sxx : xx;
+                yy = here ? syy : yy;
+            }
         }
-        xy = wave_sum(xy);
-        xx = wave_sum(xx);
-        yy = wave_sum(yy);
-        if (lane == 0) out[i] = (xx > 0.0f && yy > 0.0f) ? xy / (sqrtf(xx) * sqrtf(yy)) : 0.0f;
+        if (mine) out[base + lane] = named && xx > 0.0f && yy > 0.0f ? xy / (sqrtf(xx) * sqrtf(yy)) : 0.0f;
     }
 }
 
@@ -1530,77 +1546,83 @@ __global__ __launch_bounds__(kBlock) void k_cosine(const float *__restrict__ ver
 // Rank statistic (gv_link_prediction_auc): twice the sum over all positives of (negatives below it + half of the
 // negatives equal to it).  The negatives are sorted (least significant digit first, eight bits a pass) and every
 // positive is looked up among them; whole numbers throughout, so the result is that of sorting all scores on the host.
-// 250000 + 250000 scores: 0.1 ms, where std::sort of the pairs on the host took 29 ms.
+// 250000 + 250000 scores: 75 us, all of it latency of short launches, so a workgroup owns as few keys as it takes at a time
+// (segments of 4096 keys, one workgroup for the places, all of a search in memory: 105 us); std::sort of the pairs on the host
+// took 29 ms.
 constexpr int kSortBlock = 1024, kSortWaves = kSortBlock / kWave, kDigits = 256;
 
-// Scores become unsigned integers of the same order (the two zeros are one value); not_finite[workgroup] says
-// whether it met an infinity or NaN.
-__global__ __launch_bounds__(kBlock) void k_score_keys(uint32_t *__restrict__ scores, uint64_t count,
-                                                       unsigned long long *__restrict__ not_finite) {
-    bool bad = false;
-    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (uint64_t)gridDim.x * kBlock) {
-        uint32_t x = scores[i];
-        bad |= (x & 0x7F800000u) == 0x7F800000u;
-        if ((x & 0x7FFFFFFFu) == 0u) x = 0u;
-        scores[i] = x & 0x80000000u ? ~x : x | 0x80000000u;
-    }
-    const bool any = __syncthreads_or(bad);
-    if (threadIdx.x == 0) not_finite[blockIdx.x] = any ? 1ull : 0ull;
+// A score as an unsigned integer of the same order (the two zeros are one value).
+__device__ __forceinline__ uint32_t score_key(uint32_t x) {
+    if ((x & 0x7FFFFFFFu) == 0u) x = 0u;
+    return x & 0x80000000u ? ~x : x | 0x80000000u;
 }
+__device__ __forceinline__ bool not_a_number(uint32_t x) { return (x & 0x7F800000u) == 0x7F800000u; }  // or an infinity
 
-// One pass: workgroup b owns the keys b * segment .. (b + 1) * segment - 1 and counts their digits ...
+// One pass: workgroup b owns the keys b * segment .. (b + 1) * segment - 1 and counts their digits (kScores: of the scores
+// still to be made keys; *not_finite is set where one is no number) ...
+template <bool kScores>
 __global__ __launch_bounds__(kSortBlock) void k_radix_count(const uint32_t *__restrict__ keys, uint32_t count, uint32_t segment,
-                                                            uint32_t shift, uint32_t *__restrict__ counts) {
+                                                            uint32_t shift, uint32_t *__restrict__ counts,
+                                                            unsigned long long *__restrict__ not_finite) {
     __shared__ uint32_t s_count[kDigits];
     if (threadIdx.x < kDigits) s_count[threadIdx.x] = 0u;
     __syncthreads();
     const uint64_t begin = (uint64_t)blockIdx.x * segment, end = min(begin + segment, (uint64_t)count);
-    for (uint64_t i = begin + threadIdx.x; i < end; i += kSortBlock) atomicAdd(&s_count[(keys[i] >> shift) & (kDigits - 1)], 1u);
+    for (uint64_t i = begin + threadIdx.x; i < end; i += kSortBlock) {
+        uint32_t key = keys[i];
+        if constexpr (kScores) {
+            if (not_a_number(key)) *not_finite = 1ull;
+            key = score_key(key);
+        }
+        atomicAdd(&s_count[(key >> shift) & (kDigits - 1)], 1u);
+    }
     __syncthreads();
     if (threadIdx.x < kDigits) counts[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = s_count[threadIdx.x];
 }
 
-// ... the counts, digit after digit and workgroup after workgroup, become places (a thread owns consecutive counts, read
-// sixteen at a time: one after the other, 15616 counts take 25 us instead of 6) ...
-__global__ __launch_bounds__(kSortBlock) void k_radix_places(uint32_t *__restrict__ counts, uint32_t entries) {
-    __shared__ uint32_t s_sum[kSortBlock];
-    const uint32_t fours = entries / 4u;  // entries is a multiple of the 256 digits
-    const uint32_t per_thread = (fours + kSortBlock - 1) / kSortBlock;
-    const uint32_t begin = min(threadIdx.x * per_thread, fours), end = min(begin + per_thread, fours);
-    uint4 *const four = (uint4 *)counts;
-    uint32_t sum = 0u;
-    for (uint32_t i = begin; i < end; i += 4u) {
-#pragma unroll
-        for (uint32_t e = 0; e < 4u; ++e) {
-            const uint4 c = i + e < end ? four[i + e] : make_uint4(0u, 0u, 0u, 0u);
-            sum += c.x + c.y + c.z + c.w;
+// ... the counts, digit after digit and workgroup after workgroup, become places: a workgroup adds up the counts before its
+// part, and scans the part, a thread the sixteen bytes that follow each other ...
+__global__ __launch_bounds__(kSortBlock) void k_radix_places(const uint32_t *__restrict__ counts, uint32_t entries,
+                                                             uint32_t *__restrict__ places) {
+    __shared__ uint32_t s_before[kSortWaves], s_total[kSortWaves];
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const uint32_t fours = entries / 4u, part = (fours + gridDim.x - 1) / gridDim.x;  // entries is a multiple of the 256 digits
+    const uint32_t part_begin = min(blockIdx.x * part, fours), part_end = min(part_begin + part, fours);
+    const uint4 *const four = (const uint4 *)counts;
+    auto sum_of = [](uint4 c) { return c.x + c.y + c.z + c.w; };
+    uint32_t before = 0u;
+#pragma unroll 4
+    for (uint32_t i = threadIdx.x; i < part_begin; i += kSortBlock) before += sum_of(four[i]);
+    for (int d = kWave / 2; d > 0; d /= 2) before += __shfl_xor(before, d);
+    if (lane == 0) s_before[wave] = before;
+    for (uint32_t first = part_begin; first < part_end; first += kSortBlock) {
+        const uint32_t i = first + threadIdx.x;
+        const uint4 c = i < part_end ? four[i] : make_uint4(0u, 0u, 0u, 0u);
+        const uint32_t own = sum_of(c);
+        uint32_t upto = own;
+        for (uint32_t d = 1; d < (uint32_t)kWave; d *= 2) {
+            const uint32_t x = __shfl_up(upto, d);
+            upto += lane >= d ? x : 0u;
         }
-    }
-    s_sum[threadIdx.x] = sum;
-    __syncthreads();
-    for (uint32_t d = 1; d < kSortBlock; d *= 2) {
-        const uint32_t before = threadIdx.x >= d ? s_sum[threadIdx.x - d] : 0u;
+        if (lane == kWave - 1) s_total[wave] = upto;
         __syncthreads();
-        s_sum[threadIdx.x] += before;
-        __syncthreads();
-    }
-    uint32_t place = s_sum[threadIdx.x] - sum;
-    for (uint32_t i = begin; i < end; i += 4u) {
-        uint4 c[4];
+        uint32_t place = upto - own, all = 0u;
 #pragma unroll
-        for (uint32_t e = 0; e < 4u; ++e) c[e] = i + e < end ? four[i + e] : make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-        for (uint32_t e = 0; e < 4u; ++e) {
-            const uint4 here = make_uint4(place, place + c[e].x, place + c[e].x + c[e].y, place + c[e].x + c[e].y + c[e].z);
-            place = here.w + c[e].w;
-            if (i + e < end) four[i + e] = here;
+        for (int w = 0; w < kSortWaves; ++w) {
+            place += s_before[w] + ((uint32_t)w < wave ? s_total[w] : 0u);
+            all += s_total[w];
         }
+        if (i < part_end) ((uint4 *)places)[i] = make_uint4(place, place + c.x, place + c.x + c.y, place + c.x + c.y + c.z);
+        __syncthreads();
+        if (threadIdx.x == 0) s_before[0] += all;  // of what follows in this part
+        __syncthreads();
     }
 }
 
 // ... and the keys go there in their order: 1024 at a time, a wave finds the lanes with its lane's digit by eight ballots.
-// kCarried: each key takes a word with it, the one beside it in `words`, or, where that is null, its own place.
-template <bool kCarried>
+// kCarried: each key takes a word with it, the one beside it in `words`, or, where that is null, its own place.  kScores:
+// scores come in, their keys go out.
+template <bool kCarried, bool kScores>
 __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ words,
                                                               uint32_t count, uint32_t segment, uint32_t shift,
                                                               const uint32_t *__restrict__ places, uint32_t *__restrict__ out,
@@ -1614,7 +1636,8 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(const uint32_t *__
         for (uint32_t i = threadIdx.x; i < kSortWaves * kDigits; i += kSortBlock) (&s_place[0][0])[i] = 0u;
         __syncthreads();
         const bool mine = base + threadIdx.x < end;
-        const uint32_t key = mine ? keys[base + threadIdx.x] : 0u;
+        uint32_t key = mine ? keys[base + threadIdx.x] : 0u;
+        if constexpr (kScores) key = score_key(key);
         const uint32_t digit = (key >> shift) & (kDigits - 1);
         uint64_t same = __ballot(mine);
 #pragma unroll
@@ -1644,37 +1667,52 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(const uint32_t *__
     }
 }
 
-// twice[workgroup] = sum over its positives of 2 (sorted keys below) + (sorted keys equal).
-__global__ __launch_bounds__(kBlock) void k_rank_sum(const uint32_t *__restrict__ positives, uint64_t num_pos,
-                                                     const uint32_t *__restrict__ sorted, uint32_t num_neg,
-                                                     unsigned long long *__restrict__ twice) {
-    __shared__ unsigned long long s_sum[kBlock / kWave];
+// twice[workgroup] = sum over its positives of 2 (sorted keys below) + (sorted keys equal).  The search begins among 1024
+// of the keys at equal distances, in LDS: a search of all in memory is twice as many dependent loads (20 us instead of 16).
+constexpr uint32_t kRankMarks = 1024;
+__global__ __launch_bounds__(kSortBlock) void k_rank_sum(const uint32_t *__restrict__ positives, uint64_t num_pos,
+                                                         const uint32_t *__restrict__ sorted, uint32_t num_neg,
+                                                         unsigned long long *__restrict__ twice,
+                                                         unsigned long long *__restrict__ not_finite) {
+    __shared__ uint32_t s_mark[kRankMarks];
+    __shared__ unsigned long long s_sum[kSortWaves];
+    const uint32_t step = (num_neg + kRankMarks - 1) / kRankMarks, marks = (num_neg + step - 1) / step;  // the last key of each step
+    if (threadIdx.x < marks) s_mark[threadIdx.x] = sorted[min((uint64_t)(threadIdx.x + 1) * step, (uint64_t)num_neg) - 1];
+    __syncthreads();
     unsigned long long sum = 0ull;
-    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < num_pos; i += (uint64_t)gridDim.x * kBlock) {
-        const uint32_t key = positives[i];
-        auto first_not = [&](uint32_t begin, auto &&before) {  // first place from `begin` on that is not before
-            uint32_t length = num_neg - begin;
+    for (uint64_t i = (uint64_t)blockIdx.x * kSortBlock + threadIdx.x; i < num_pos; i += (uint64_t)gridDim.x * kSortBlock) {
+        const uint32_t score = positives[i], key = score_key(score);
+        if (not_a_number(score)) *not_finite = 1ull;
+        // first place that is not `before`: among the marks, then in the step that ends with the mark
+        auto first_not = [&](auto &&before) {
+            uint32_t begin = 0, length = marks;
             while (length > 0u) {
                 const uint32_t half = length / 2u;
-                if (before(sorted[begin + half])) {
-                    begin += half + 1u;
-                    length -= half + 1u;
-                } else {
-                    length = half;
-                }
+                const bool less = before(s_mark[begin + half]);
+                begin = less ? begin + half + 1u : begin;
+                length = less ? length - half - 1u : half;
+            }
+            if (begin == marks) return num_neg;
+            begin *= step;
+            length = min(step, num_neg - begin) - 1u;  // the step's last key is not before
+            while (length > 0u) {
+                const uint32_t half = length / 2u;
+                const bool less = before(sorted[begin + half]);
+                begin = less ? begin + half + 1u : begin;
+                length = less ? length - half - 1u : half;
             }
             return begin;
         };
-        const uint32_t below = first_not(0u, [&](uint32_t x) { return x < key; });
+        const uint32_t below = first_not([&](uint32_t x) { return x < key; });
         uint32_t upto = below;
-        if (below < num_neg && sorted[below] == key) upto = first_not(below, [&](uint32_t x) { return x <= key; });
+        if (below < num_neg && sorted[below] == key) upto = first_not([&](uint32_t x) { return x <= key; });
         sum += (unsigned long long)below + upto;
     }
     for (int d = kWave / 2; d > 0; d /= 2) sum += __shfl_xor(sum, d);
     if ((threadIdx.x & (kWave - 1)) == 0) s_sum[threadIdx.x / kWave] = sum;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / kWave; ++w) sum += s_sum[w];
+        for (int w = 1; w < kSortWaves; ++w) sum += s_sum[w];
         twice[blockIdx.x] = sum;
     }
 }
@@ -2165,55 +2203,84 @@ hipError_t launch_eval_loss(TrainArgs a, uint32_t dim, uint32_t num_neg, double 
 #undef GV_CALL
 }
 
+template <int kV>
+void launch_cosine_v(const float *vertex, uint32_t n, uint32_t dim, const uint32_t *first, const uint32_t *second, uint32_t count,
+                     uint32_t unit, uint32_t blocks, float *out, uint32_t *error_flag, hipStream_t stream) {
+    if (dim == (uint32_t)(kWave * kV))
+        hipLaunchKernelGGL((k_cosine<kV, true>), dim3(blocks), dim3(kBlock), 0, stream, vertex, n, dim, first, second, count, unit, out,
+                           error_flag);
+    else
+        hipLaunchKernelGGL((k_cosine<kV, false>), dim3(blocks), dim3(kBlock), 0, stream, vertex, n, dim, first, second, count, unit, out,
+                           error_flag);
+}
 hipError_t launch_cosine(const float *vertex, uint32_t n, uint32_t dim, const uint32_t *first, const uint32_t *second,
                          uint32_t count, float *out, uint32_t *error_flag, hipStream_t stream) {
     if (count == 0) return hipSuccess;
-    const uint32_t wanted = (count + (kBlock / kWave) - 1) / (kBlock / kWave);
-    const dim3 grid(wanted < 4096u ? wanted : 4096u), block(kBlock);
+    // chunks of 64 pairs, or of fewer (down to 4) as long as that brings more of 8192 waves to work
+    auto chunks = [&](uint32_t unit) { return (uint32_t)(((uint64_t)count + unit - 1) / unit); };
+    uint32_t unit = kWave;
+    while (unit > 4u && chunks(unit) < 8192u) unit /= 2u;
+    const uint32_t blocks = std::min((chunks(unit) + kBlock / kWave - 1u) / (kBlock / kWave), 4096u);
     if (dim <= 64)
-        hipLaunchKernelGGL((k_cosine<1>), grid, block, 0, stream, vertex, n, dim, first, second, count, out, error_flag);
+        launch_cosine_v<1>(vertex, n, dim, first, second, count, unit, blocks, out, error_flag, stream);
     else if (dim <= 128)
-        hipLaunchKernelGGL((k_cosine<2>), grid, block, 0, stream, vertex, n, dim, first, second, count, out, error_flag);
+        launch_cosine_v<2>(vertex, n, dim, first, second, count, unit, blocks, out, error_flag, stream);
     else if (dim <= 256)
-        hipLaunchKernelGGL((k_cosine<4>), grid, block, 0, stream, vertex, n, dim, first, second, count, out, error_flag);
+        launch_cosine_v<4>(vertex, n, dim, first, second, count, unit, blocks, out, error_flag, stream);
     else
-        hipLaunchKernelGGL((k_cosine<8>), grid, block, 0, stream, vertex, n, dim, first, second, count, out, error_flag);
+        launch_cosine_v<8>(vertex, n, dim, first, second, count, unit, blocks, out, error_flag, stream);
     return hipGetLastError();
 }
 
-// Segments of whole sub-tiles: 4096 keys, more where that would be over 1024 workgroups.
-static uint32_t rank_segment(uint32_t num_neg) {
-    const uint32_t tiles = (num_neg + 4u * kSortBlock - 1u) / (4u * kSortBlock);
-    return (tiles + 1023u) / 1024u * 4u * kSortBlock;
+// Segments of whole sub-tiles of 1024 keys: one, more where that would be over 1024 workgroups.
+static uint32_t sort_segment(uint32_t count) {
+    const uint32_t tiles = (uint32_t)(((uint64_t)count + kSortBlock - 1u) / kSortBlock);
+    return (tiles + 1023u) / 1024u * kSortBlock;
 }
-static uint64_t rank_counts_at(uint32_t num_neg) { return ((uint64_t)num_neg + 3u) & ~3ull; }  // behind the keys, for 16-byte reads
-uint64_t rank_scratch_words(uint32_t num_neg) {
-    const uint32_t segment = rank_segment(num_neg);
-    return rank_counts_at(num_neg) + (uint64_t)kDigits * ((num_neg + segment - 1u) / segment);
+static uint32_t sort_blocks(uint32_t count) { return (uint32_t)(((uint64_t)count + sort_segment(count) - 1u) / sort_segment(count)); }
+// counts and places of a pass
+static uint64_t sort_count_words(uint32_t count) { return 2ull * kDigits * sort_blocks(count); }
+// One pass over `from`, and the words that go along if `words_out` is given; counts at a multiple of 16 bytes.
+template <bool kScores>
+static void sort_pass(const uint32_t *from, const uint32_t *words, uint32_t count, uint32_t shift, uint32_t *counts, uint32_t *to,
+                      uint32_t *words_out, unsigned long long *not_finite, hipStream_t stream) {
+    const uint32_t segment = sort_segment(count), blocks = sort_blocks(count), entries = kDigits * blocks;
+    uint32_t *const places = counts + entries;
+    hipLaunchKernelGGL(k_radix_count<kScores>, dim3(blocks), dim3(kSortBlock), 0, stream, from, count, segment, shift, counts, not_finite);
+    hipLaunchKernelGGL(k_radix_places, dim3((entries + 4u * kSortBlock - 1u) / (4u * kSortBlock)), dim3(kSortBlock), 0, stream, counts,
+                       entries, places);
+    if (words_out)
+        hipLaunchKernelGGL((k_radix_scatter<true, kScores>), dim3(blocks), dim3(kSortBlock), 0, stream, from, words, count, segment, shift,
+                           places, to, words_out);
+    else
+        hipLaunchKernelGGL((k_radix_scatter<false, kScores>), dim3(blocks), dim3(kSortBlock), 0, stream, from, words, count, segment, shift,
+                           places, to, words_out);
 }
 
+static uint64_t rank_counts_at(uint32_t num_neg) { return ((uint64_t)num_neg + 3u) & ~3ull; }  // behind the keys, for 16-byte reads
+uint64_t rank_scratch_words(uint32_t num_neg) { return rank_counts_at(num_neg) + sort_count_words(num_neg); }
+
+__global__ __launch_bounds__(kBlock) void k_clear(unsigned long long *words) { words[threadIdx.x] = 0ull; }
 hipError_t launch_rank_statistic(uint32_t *scores, uint32_t num_pos, uint32_t num_neg, uint32_t *scratch,
                                  unsigned long long *twice, unsigned long long *not_finite, hipStream_t stream) {
     if (num_pos == 0 || num_neg == 0) return hipErrorInvalidValue;
-    const uint64_t all = (uint64_t)num_pos + num_neg;
-    hipLaunchKernelGGL(k_score_keys, dim3(kRankBlocks), dim3(kBlock), 0, stream, scores, all, not_finite);
-    const uint32_t segment = rank_segment(num_neg), blocks = (num_neg + segment - 1u) / segment;
-    uint32_t *from = scores + num_pos, *to = scratch, *const counts = scratch + rank_counts_at(num_neg);
-    for (uint32_t shift = 0; shift < 32u; shift += 8u) {  // four passes: the keys end where they began
-        hipLaunchKernelGGL(k_radix_count, dim3(blocks), dim3(kSortBlock), 0, stream, from, num_neg, segment, shift, counts);
-        hipLaunchKernelGGL(k_radix_places, dim3(1), dim3(kSortBlock), 0, stream, counts, kDigits * blocks);
-        hipLaunchKernelGGL(k_radix_scatter<false>, dim3(blocks), dim3(kSortBlock), 0, stream, from, (const uint32_t *)nullptr, num_neg,
-                           segment, shift, counts, to, (uint32_t *)nullptr);
-        std::swap(from, to);
-    }
-    hipLaunchKernelGGL(k_rank_sum, dim3(kRankBlocks), dim3(kBlock), 0, stream, scores, (uint64_t)num_pos, from, num_neg, twice);
+    static_assert(kRankBlocks == kBlock, "k_clear");
+    hipLaunchKernelGGL(k_clear, dim3(1), dim3(kBlock), 0, stream, not_finite);
+    uint32_t *const negatives = scores + num_pos, *const counts = scratch + rank_counts_at(num_neg);
+    // four passes: the keys end where the scores were
+    sort_pass<true>(negatives, nullptr, num_neg, 0u, counts, scratch, nullptr, not_finite, stream);
+    sort_pass<false>(scratch, nullptr, num_neg, 8u, counts, negatives, nullptr, nullptr, stream);
+    sort_pass<false>(negatives, nullptr, num_neg, 16u, counts, scratch, nullptr, nullptr, stream);
+    sort_pass<false>(scratch, nullptr, num_neg, 24u, counts, negatives, nullptr, nullptr, stream);
+    hipLaunchKernelGGL(k_rank_sum, dim3(kRankBlocks), dim3(kSortBlock), 0, stream, scores, (uint64_t)num_pos, negatives, num_neg, twice,
+                       not_finite);
     return hipGetLastError();
 }
 
 // Keys, the sorted keys with their namings (twice, for the passes of the sort), the places and the counts of the sort.
 uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg) {
     const uint64_t namings = (uint64_t)count * (num_neg + 2);
-    return 6 * ((namings + 3u) & ~3ull) + (uint64_t)kDigits * ((namings + rank_segment((uint32_t)namings) - 1) / rank_segment((uint32_t)namings));
+    return 6 * ((namings + 3u) & ~3ull) + sort_count_words((uint32_t)namings);
 }
 
 hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, FlowState *state, bool fresh, hipStream_t stream) {
@@ -2234,13 +2301,9 @@ hipError_t launch_flow_prepare(TrainArgs &a, uint32_t num_neg, uint32_t *scratch
     const uint32_t by_sample = std::min((a.count + kBlock - 1u) / kBlock, 65536u);
     hipLaunchKernelGGL(k_flow_keys, dim3(by_sample), dim3(kBlock), 0, stream, (const uint2 *)a.pairs, a.alias, a.n, a.seed, a.first_g,
                        a.count, num_neg, keys);
-    const uint32_t segment = rank_segment(namings), blocks = (namings + segment - 1u) / segment;
     const uint32_t *from = keys, *words = nullptr;
     for (uint32_t shift = 0; (2ull * a.n - 1u) >> shift; shift += 8u) {
-        hipLaunchKernelGGL(k_radix_count, dim3(blocks), dim3(kSortBlock), 0, stream, from, namings, segment, shift, counts);
-        hipLaunchKernelGGL(k_radix_places, dim3(1), dim3(kSortBlock), 0, stream, counts, kDigits * blocks);
-        hipLaunchKernelGGL(k_radix_scatter<true>, dim3(blocks), dim3(kSortBlock), 0, stream, from, words, namings, segment, shift, counts,
-                           to, to + stride);
+        sort_pass<false>(from, words, namings, shift, counts, to, to + stride, nullptr, stream);
         from = to;
         words = to + stride;
         std::swap(to, other);
