@@ -50,6 +50,15 @@ constexpr uint64_t kStageWords = 16384, kDeterministicPart = 1u << 20;  // see t
 constexpr uint64_t kFlowFrom = 4096;
 constexpr double kFlowShare = 1.0 / 24.0;
 
+// The pairs of gv_eval_loss and gv_link_prediction_auc are read by the kernels from pinned memory, piece by piece, while the
+// next piece is copied there: the host copies 77 GB/s and the kernels read 50, where a copy to the device from the caller's
+// pageable arrays takes 78 us for 2 MB and 131 for 4 (25 to 58 for 64 KB to 128 KB), before the first kernel starts.  Evaluation
+// loss of 2^18 samples 152 -> 130 us, of 10^4 62 -> 29, link prediction of 500000 pairs 288 -> 284, of 10^4 124 -> 78, of
+// two 36 -> 25.  A piece has enough pairs to fill the chip; the fifth waits for the first.  (Copies of the pieces on the copy
+// stream, waited for by the host, 180 us for 2^18 samples; workgroups of the kernel that copy for the others, 142 to 159.)
+constexpr uint64_t kPiecePairs = 1u << 17;
+constexpr int kPieces = 4;
+
 // In pinned memory: what the host waits for at the end of a call, copied there on the compute stream, so that one wait for
 // that stream is all (a blocking copy of a few bytes takes 20 us on top of it), and short pools of deterministic mode.
 struct HostResults {
@@ -57,8 +66,9 @@ struct HostResults {
     uint32_t stage[kStageWords];                                  // deterministic mode
     gv::FlowState flow;                                           // deterministic mode, see train_flow
     double loss_slots[gv::kLossSlots];
-    union {
-        double partial[gv::kEvalBlocks];                          // gv_eval_loss
+    uint32_t piece[kPieces][2 * kPiecePairs];                     // gv_eval_loss, gv_link_prediction_auc: see kPiecePairs
+    union {                                                       // written by the kernels
+        double partial[kPieces][gv::kEvalBlocks];                 // gv_eval_loss
         unsigned long long sums[2 * gv::kRankBlocks];             // gv_link_prediction_auc
         float scores[kHostRanked];                                // gv_link_prediction_auc of few pairs
     };
@@ -120,6 +130,7 @@ struct gv_ctx {
     uint32_t *static_records = nullptr;   // this GPU's copy of the `scratch` array (GV_STATIC_SCRATCH_WORDS words)
     void *eval_scratch = nullptr;         // device scratch of gv_eval_loss / gv_cosine / gv_auc, grown on demand
     uint64_t eval_capacity = 0;           // in bytes
+    hipEvent_t piece_read[kPieces] = {};  // the kernel that reads a piece of an evaluation's pairs has ended
     hipStream_t compute = nullptr;
     hipStream_t copy = nullptr;
     std::vector<PoolSlot> slot;           // ring of cfg.pool_slots pinned slots, each with a device twin
@@ -761,6 +772,23 @@ int pick_free_slot(gv_ctx *ctx, int *index) {
     return fail(ctx, GV_ESTATE, "all %d pool slots are filling or queued: train a pool first", slots);
 }
 
+// body(first, pairs, slot) for every piece of `count` pairs, in order: it may write ctx->results->piece[slot] and launches
+// what reads it on the compute stream.
+template <class Body>
+int in_pieces(gv_ctx *ctx, uint64_t count, Body &&body) {
+    const bool again = count > kPieces * kPiecePairs;  // some slot is used twice
+    uint64_t number = 0;
+    for (uint64_t first = 0; first < count; first += kPiecePairs, ++number) {
+        const int slot = (int)(number % kPieces);
+        if (again && !ctx->piece_read[slot]) GV_HIP(ctx, hipEventCreateWithFlags(&ctx->piece_read[slot], hipEventDisableTiming));
+        if (number >= kPieces) GV_HIP(ctx, hipEventSynchronize(ctx->piece_read[slot]));
+        int rc = body(first, std::min(kPiecePairs, count - first), slot);
+        if (rc) return rc;
+        if (again) GV_HIP(ctx, hipEventRecord(ctx->piece_read[slot], ctx->compute));
+    }
+    return GV_OK;
+}
+
 // Device scratch shared by the evaluation calls: grown when a call needs more, kept otherwise.
 int ensure_eval_scratch(gv_ctx *ctx, uint64_t bytes) {
     if (bytes <= ctx->eval_capacity) return GV_OK;
@@ -914,6 +942,8 @@ void gv_destroy(gv_ctx *ctx) {
     if (ctx->results) (void)hipHostFree(ctx->results);
     if (ctx->dev_loss) (void)hipFree(ctx->dev_loss);
     if (ctx->flow_checked) (void)hipEventDestroy(ctx->flow_checked);
+    for (hipEvent_t e : ctx->piece_read)
+        if (e) (void)hipEventDestroy(e);
     if (ctx->copy) (void)hipStreamDestroy(ctx->copy);
     if (ctx->compute) (void)hipStreamDestroy(ctx->compute);
     delete ctx;
@@ -1524,31 +1554,32 @@ int gv_draw_negatives(gv_ctx *ctx, uint64_t first_g, uint64_t count, uint32_t *h
 
 int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64_t eval_seed, double *mean_loss) {
     return guarded(ctx, [&]() -> int {
-        int rc = need_trainable(ctx);
-        if (rc) return rc;
+        if (int rc = need_trainable(ctx)) return rc;
         if (!mean_loss || (count > 0 && !host_pairs)) return fail(ctx, GV_EINVAL, "null argument");
         if (count == 0 || count > (1ull << 32) - 1) return fail(ctx, GV_EINVAL, "count must be in 1 .. 2^32-1");
         // everything below is ordered behind the training on the compute stream; what that has to report is read at
         // the end, together with the result
-        // scratch layout: the partial sums, then the pairs
-        constexpr uint64_t kSums = gv::kEvalBlocks * sizeof(double);
-        rc = ensure_eval_scratch(ctx, kSums + count * 2 * sizeof(uint32_t));
+        HostResults &r = *ctx->results;
+        double total = 0.0;
+        uint32_t blocks[kPieces] = {};
+        auto take_in = [&](int slot) {
+            for (uint32_t b = 0; b < blocks[slot]; ++b) total += r.partial[slot][b];
+            blocks[slot] = 0;
+        };
+        int rc = in_pieces(ctx, count, [&](uint64_t first, uint64_t here, int slot) -> int {
+            take_in(slot);
+            memcpy(r.piece[slot], host_pairs + 2 * first, here * 2 * sizeof(uint32_t));
+            gv::TrainArgs a = train_args(ctx, r.piece[slot], first, (uint32_t)here);
+            a.seed = eval_seed;
+            a.error_flag = ctx->error_flag + 2;
+            GV_HIP(ctx, gv::launch_eval_loss(a, ctx->cfg.dim, ctx->cfg.num_neg, r.partial[slot], &blocks[slot], ctx->compute));
+            return GV_OK;
+        });
         if (rc) return rc;
-        double *dev_partial = (double *)ctx->eval_scratch;
-        uint32_t *dev_pairs = (uint32_t *)((char *)ctx->eval_scratch + kSums);
-        GV_HIP(ctx, hipMemcpyAsync(dev_pairs, host_pairs, count * 2 * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
-        gv::TrainArgs a = train_args(ctx, dev_pairs, 0, (uint32_t)count);
-        a.seed = eval_seed;
-        a.error_flag = ctx->error_flag + 2;
-        uint32_t blocks = 0;
-        GV_HIP(ctx, gv::launch_eval_loss(a, ctx->cfg.dim, ctx->cfg.num_neg, dev_partial, &blocks, ctx->compute));
-        const double *partial = ctx->results->partial;
-        GV_HIP(ctx, hipMemcpyAsync(ctx->results->partial, dev_partial, blocks * sizeof(double), hipMemcpyDeviceToHost, ctx->compute));
         bool bad_ids = false;  // then the result covers the other pairs
         rc = sync_all(ctx, &bad_ids);
         if (rc && !bad_ids) return rc;
-        double total = 0.0;
-        for (uint32_t b = 0; b < blocks; ++b) total += partial[b];
+        for (int slot = 0; slot < kPieces; ++slot) take_in(slot);
         *mean_loss = total / (double)count;
         return rc;
     });
@@ -1616,8 +1647,8 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
             *auc = rank_auc(scores, num_edges, scores + num_edges, num_others);
             return GV_OK;
         };
-        // scratch: what ranking on the device needs (the partial sums and flags, then the sort), the ends of the pairs, the
-        // scores
+        // scratch: what ranking on the device needs (the partial sums and flags, then the sort), the scores, and room
+        // for the ends of the pairs, without which the call falls back to cosine_scores as well
         const bool few = count <= kHostRanked;
         const uint64_t sums = few ? 0 : 2 * gv::kRankBlocks * sizeof(unsigned long long);
         const uint64_t sorting = few ? 0 : (gv::rank_scratch_words((uint32_t)num_others) + 3u) & ~3ull;
@@ -1634,27 +1665,28 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
             return rc ? rc : rank_on_host(scores.data());
         }
         if (rc) return rc;
-        unsigned long long *dev_sums = (unsigned long long *)ctx->eval_scratch;
-        uint32_t *dev_sorting = (uint32_t *)((char *)ctx->eval_scratch + sums);
-        uint32_t *dev_first = dev_sorting + sorting, *dev_second = dev_first + count;
-        float *dev_scores = (float *)(dev_second + count);
-        auto upload = [&](uint32_t *to, const uint32_t *from, uint64_t ids) {
-            return hipMemcpyAsync(to, from, ids * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute);
-        };
-        GV_HIP(ctx, upload(dev_first, host_edge_first, num_edges));
-        GV_HIP(ctx, upload(dev_first + num_edges, host_other_first, num_others));
-        GV_HIP(ctx, upload(dev_second, host_edge_second, num_edges));
-        GV_HIP(ctx, upload(dev_second + num_edges, host_other_second, num_others));
-        GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, dev_first, dev_second, (uint32_t)count, dev_scores,
-                                      ctx->error_flag + 2, ctx->compute));
         HostResults &r = *ctx->results;
-        if (few) {
-            GV_HIP(ctx, hipMemcpyAsync(r.scores, dev_scores, count * sizeof(float), hipMemcpyDeviceToHost, ctx->compute));
-        } else {
-            GV_HIP(ctx, gv::launch_rank_statistic((uint32_t *)dev_scores, (uint32_t)num_edges, (uint32_t)num_others, dev_sorting,
-                                                  dev_sums, dev_sums + gv::kRankBlocks, ctx->compute));
-            GV_HIP(ctx, hipMemcpyAsync(r.sums, dev_sums, sizeof r.sums, hipMemcpyDeviceToHost, ctx->compute));
-        }
+        uint32_t *dev_sorting = (uint32_t *)ctx->eval_scratch;
+        float *const scores = few ? r.scores : (float *)(dev_sorting + sorting);
+        rc = in_pieces(ctx, count, [&](uint64_t first, uint64_t here, int slot) -> int {
+            uint32_t *const firsts = r.piece[slot], *const seconds = firsts + here;
+            const uint64_t edges = first < num_edges ? std::min(here, num_edges - first) : 0, other = first + edges - num_edges;
+            if (edges > 0) {
+                memcpy(firsts, host_edge_first + first, edges * sizeof(uint32_t));
+                memcpy(seconds, host_edge_second + first, edges * sizeof(uint32_t));
+            }
+            if (edges < here) {
+                memcpy(firsts + edges, host_other_first + other, (here - edges) * sizeof(uint32_t));
+                memcpy(seconds + edges, host_other_second + other, (here - edges) * sizeof(uint32_t));
+            }
+            GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, firsts, seconds, (uint32_t)here, scores + first,
+                                          ctx->error_flag + 2, ctx->compute));
+            return GV_OK;
+        });
+        if (rc) return rc;
+        if (!few)
+            GV_HIP(ctx, gv::launch_rank_statistic((uint32_t *)scores, (uint32_t)num_edges, (uint32_t)num_others, dev_sorting, r.sums,
+                                                  r.sums + gv::kRankBlocks, ctx->compute));
         rc = sync_all(ctx);  // also reports ids >= n, and what training before had to report
         if (rc) return rc;
         if (few) return rank_on_host(r.scores);

@@ -142,7 +142,8 @@ hipError_t launch_draw_negatives_partitioned(const uint4 *tables, const uint64_t
 // vertex ~ U(-0.5/d, 0.5/d) from Philox stream 1 (context is cleared by the caller).
 hipError_t launch_init_vertex(float *vertex, uint64_t rows, uint32_t dim, uint64_t seed, hipStream_t stream);
 
-// Sum of the per-sample losses of a.pairs[0 .. a.count) (a.seed = evaluation seed), in *blocks partial sums (at most
+// Sum of the per-sample losses of a.pairs[0 .. a.count), samples a.first_g on (a.seed = evaluation seed), in *blocks partial
+// sums (at most
 // kEvalBlocks).
 constexpr uint32_t kEvalBlocks = 2048;
 hipError_t launch_eval_loss(TrainArgs a, uint32_t dim, uint32_t num_neg, double *partial, uint32_t *blocks, hipStream_t stream);

@@ -1454,7 +1454,7 @@ __global__ __launch_bounds__(kBlock) void k_eval_loss(TrainArgs a, double *__res
         uint32_t neg[kK];
 #pragma unroll
         for (int k = 0; k < kK; ++k)
-            neg[k] = mine ? draw_negative(a.alias, a.alias_n, a.seed, (uint64_t)base + lane, k, 2u) : 0u;
+            neg[k] = mine ? draw_negative(a.alias, a.alias_n, a.seed, a.first_g + base + lane, k, 2u) : 0u;
         ChunkScores<kK> scores{};
         for (uint32_t i0 = 0; i0 < in_chunk; i0 += kBatch) {
             float x[kBatch][kV], c[kBatch][kK + 1][kV];
@@ -2193,10 +2193,11 @@ hipError_t launch_eval_vk(const TrainArgs &a, double *partial, hipStream_t strea
 }
 
 hipError_t launch_eval_loss(TrainArgs a, uint32_t dim, uint32_t num_neg, double *partial, uint32_t *blocks, hipStream_t stream) {
-    // chunks of 64 samples, or of fewer (down to 4) as long as that brings more of 8192 waves to work
+    // chunks of 64 samples, or of fewer (down to 4) as long as that brings more of 2048 waves to work: the pairs may lie in
+    // host memory, where reads of 64 bytes are slow
     auto chunks = [&](uint32_t unit) { return (uint32_t)(((uint64_t)a.count + unit - 1) / unit); };
     a.unit = kWave;
-    while (a.unit > 4u && chunks(a.unit) < 8192u) a.unit /= 2u;
+    while (a.unit > 4u && chunks(a.unit) < 2048u) a.unit /= 2u;
     a.blocks = *blocks = std::min((chunks(a.unit) + kBlock / kWave - 1u) / (kBlock / kWave), kEvalBlocks);
 #define GV_CALL(V, K) launch_eval_vk<V, K>(a, partial, stream)
     GV_DISPATCH(GV_CALL)
@@ -2216,10 +2217,10 @@ void launch_cosine_v(const float *vertex, uint32_t n, uint32_t dim, const uint32
 hipError_t launch_cosine(const float *vertex, uint32_t n, uint32_t dim, const uint32_t *first, const uint32_t *second,
                          uint32_t count, float *out, uint32_t *error_flag, hipStream_t stream) {
     if (count == 0) return hipSuccess;
-    // chunks of 64 pairs, or of fewer (down to 4) as long as that brings more of 8192 waves to work
+    // as in launch_eval_loss
     auto chunks = [&](uint32_t unit) { return (uint32_t)(((uint64_t)count + unit - 1) / unit); };
     uint32_t unit = kWave;
-    while (unit > 4u && chunks(unit) < 8192u) unit /= 2u;
+    while (unit > 4u && chunks(unit) < 2048u) unit /= 2u;
     const uint32_t blocks = std::min((chunks(unit) + kBlock / kWave - 1u) / (kBlock / kWave), 4096u);
     if (dim <= 64)
         launch_cosine_v<1>(vertex, n, dim, first, second, count, unit, blocks, out, error_flag, stream);
