@@ -772,22 +772,28 @@ int pick_free_slot(gv_ctx *ctx, int *index) {
     return fail(ctx, GV_ESTATE, "all %d pool slots are filling or queued: train a pool first", slots);
 }
 
-// body(first, pairs, slot) for every piece of `count` pairs, in order: it may write ctx->results->piece[slot] and launches
-// what reads it on the compute stream.
-template <class Body>
-int in_pieces(gv_ctx *ctx, uint64_t count, Body &&body) {
-    const bool again = count > kPieces * kPiecePairs;  // some slot is used twice
+// The pieces of an evaluation's pairs.  No kernel that reads one waits for one before it, except that a piece's memory is used
+// again.
+struct Pieces {
+    gv_ctx *ctx;
+    const bool again;  // some piece's memory is used twice
     uint64_t number = 0;
-    for (uint64_t first = 0; first < count; first += kPiecePairs, ++number) {
-        const int slot = (int)(number % kPieces);
-        if (again && !ctx->piece_read[slot]) GV_HIP(ctx, hipEventCreateWithFlags(&ctx->piece_read[slot], hipEventDisableTiming));
-        if (number >= kPieces) GV_HIP(ctx, hipEventSynchronize(ctx->piece_read[slot]));
-        int rc = body(first, std::min(kPiecePairs, count - first), slot);
-        if (rc) return rc;
-        if (again) GV_HIP(ctx, hipEventRecord(ctx->piece_read[slot], ctx->compute));
+    Pieces(gv_ctx *c, uint64_t count) : ctx(c), again(count > (kPieces - 1) * kPiecePairs) {}
+    // body(first, pairs, slot) for every piece of `count` pairs, in order: it may write ctx->results->piece[slot] and launches
+    // what reads it on `stream`
+    template <class Body>
+    int take(uint64_t count, hipStream_t stream, Body &&body) {
+        for (uint64_t first = 0; first < count; first += kPiecePairs, ++number) {
+            const int slot = (int)(number % kPieces);
+            if (again && !ctx->piece_read[slot]) GV_HIP(ctx, hipEventCreateWithFlags(&ctx->piece_read[slot], hipEventDisableTiming));
+            if (number >= kPieces) GV_HIP(ctx, hipEventSynchronize(ctx->piece_read[slot]));
+            int rc = body(first, std::min(kPiecePairs, count - first), slot);
+            if (rc) return rc;
+            if (again) GV_HIP(ctx, hipEventRecord(ctx->piece_read[slot], stream));
+        }
+        return GV_OK;
     }
-    return GV_OK;
-}
+};
 
 // Device scratch shared by the evaluation calls: grown when a call needs more, kept otherwise.
 int ensure_eval_scratch(gv_ctx *ctx, uint64_t bytes) {
@@ -1566,7 +1572,8 @@ int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64
             for (uint32_t b = 0; b < blocks[slot]; ++b) total += r.partial[slot][b];
             blocks[slot] = 0;
         };
-        int rc = in_pieces(ctx, count, [&](uint64_t first, uint64_t here, int slot) -> int {
+        Pieces pieces(ctx, count);
+        int rc = pieces.take(count, ctx->compute, [&](uint64_t first, uint64_t here, int slot) -> int {
             take_in(slot);
             memcpy(r.piece[slot], host_pairs + 2 * first, here * 2 * sizeof(uint32_t));
             gv::TrainArgs a = train_args(ctx, r.piece[slot], first, (uint32_t)here);
@@ -1668,25 +1675,34 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
         HostResults &r = *ctx->results;
         uint32_t *dev_sorting = (uint32_t *)ctx->eval_scratch;
         float *const scores = few ? r.scores : (float *)(dev_sorting + sorting);
-        rc = in_pieces(ctx, count, [&](uint64_t first, uint64_t here, int slot) -> int {
-            uint32_t *const firsts = r.piece[slot], *const seconds = firsts + here;
-            const uint64_t edges = first < num_edges ? std::min(here, num_edges - first) : 0, other = first + edges - num_edges;
-            if (edges > 0) {
-                memcpy(firsts, host_edge_first + first, edges * sizeof(uint32_t));
-                memcpy(seconds, host_edge_second + first, edges * sizeof(uint32_t));
-            }
-            if (edges < here) {
-                memcpy(firsts + edges, host_other_first + other, (here - edges) * sizeof(uint32_t));
-                memcpy(seconds + edges, host_other_second + other, (here - edges) * sizeof(uint32_t));
-            }
-            GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, firsts, seconds, (uint32_t)here, scores + first,
-                                          ctx->error_flag + 2, ctx->compute));
-            return GV_OK;
-        });
+        // Many edges are scored on another stream while the others are sorted, which is latency of short launches (500000 pairs
+        // 278 -> 258 us, 2*10^6 903 -> 820; two streams cost more than they hide up to 200000: 165 and 165, 40000 101 and 129).
+        // It has nothing to wait for but the training before, and the host waits for that.
+        hipStream_t const beside = count > 1u << 18 ? ctx->copy : ctx->compute;
+        if (beside != ctx->compute) GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
+        Pieces pieces(ctx, count + kPiecePairs);
+        auto score = [&](const uint32_t *host_first, const uint32_t *host_second, uint64_t pairs, float *to, hipStream_t on) {
+            return pieces.take(pairs, on, [&](uint64_t first, uint64_t here, int slot) -> int {
+                uint32_t *const firsts = r.piece[slot], *const seconds = firsts + here;
+                memcpy(firsts, host_first + first, here * sizeof(uint32_t));
+                memcpy(seconds, host_second + first, here * sizeof(uint32_t));
+                GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, firsts, seconds, (uint32_t)here, to + first,
+                                              ctx->error_flag + 2, on));
+                return GV_OK;
+            });
+        };
+        rc = score(host_other_first, host_other_second, num_others, scores + num_edges, ctx->compute);
         if (rc) return rc;
         if (!few)
-            GV_HIP(ctx, gv::launch_rank_statistic((uint32_t *)scores, (uint32_t)num_edges, (uint32_t)num_others, dev_sorting, r.sums,
-                                                  r.sums + gv::kRankBlocks, ctx->compute));
+            GV_HIP(ctx, gv::launch_rank_sort((uint32_t *)scores + num_edges, (uint32_t)num_others, dev_sorting, r.sums + gv::kRankBlocks,
+                                             ctx->compute));
+        rc = score(host_edge_first, host_edge_second, num_edges, scores, beside);
+        if (rc) return rc;
+        if (!few) {
+            if (beside != ctx->compute) GV_HIP(ctx, hipStreamSynchronize(beside));
+            GV_HIP(ctx, gv::launch_rank_sum((uint32_t *)scores, (uint32_t)num_edges, (uint32_t)num_others, r.sums, r.sums + gv::kRankBlocks,
+                                            ctx->compute));
+        }
         rc = sync_all(ctx);  // also reports ids >= n, and what training before had to report
         if (rc) return rc;
         if (few) return rank_on_host(r.scores);

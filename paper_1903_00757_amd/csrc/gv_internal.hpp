@@ -151,13 +151,14 @@ hipError_t launch_cosine(const float *vertex, uint32_t n, uint32_t dim, const ui
                          uint32_t count, float *out, uint32_t *error_flag, hipStream_t stream);
 
 // The sum of twice[0 .. kRankBlocks) is 2 (pairs of a positive above a negative) + (pairs of equal score) of scores[0 ..
-// num_pos) against the num_neg scores behind them, num_pos + num_neg <= 2^31 (all are overwritten); not_finite[0 ..
-// kRankBlocks) holds a nonzero where a score is no number.  scratch: rank_scratch_words(num_neg) words at a multiple of
-// 16 bytes.
+// num_pos) against the num_neg scores behind them, num_pos + num_neg <= 2^31; not_finite[0 .. kRankBlocks) holds a nonzero where
+// a score is no number (cleared by the sort).  The negatives are sorted first, and overwritten.  scratch:
+// rank_scratch_words(num_neg) words at a multiple of 16 bytes.
 constexpr uint32_t kRankBlocks = 256;
 uint64_t rank_scratch_words(uint32_t num_neg);
-hipError_t launch_rank_statistic(uint32_t *scores, uint32_t num_pos, uint32_t num_neg, uint32_t *scratch,
-                                 unsigned long long *twice, unsigned long long *not_finite, hipStream_t stream);
+hipError_t launch_rank_sort(uint32_t *negatives, uint32_t num_neg, uint32_t *scratch, unsigned long long *not_finite, hipStream_t stream);
+hipError_t launch_rank_sum(const uint32_t *scores, uint32_t num_pos, uint32_t num_neg, unsigned long long *twice,
+                           unsigned long long *not_finite, hipStream_t stream);
 
 // One pool of walk samples written on the device (see k_augment).
 struct AugmentArgs {

@@ -2262,19 +2262,23 @@ static uint64_t rank_counts_at(uint32_t num_neg) { return ((uint64_t)num_neg + 3
 uint64_t rank_scratch_words(uint32_t num_neg) { return rank_counts_at(num_neg) + sort_count_words(num_neg); }
 
 __global__ __launch_bounds__(kBlock) void k_clear(unsigned long long *words) { words[threadIdx.x] = 0ull; }
-hipError_t launch_rank_statistic(uint32_t *scores, uint32_t num_pos, uint32_t num_neg, uint32_t *scratch,
-                                 unsigned long long *twice, unsigned long long *not_finite, hipStream_t stream) {
-    if (num_pos == 0 || num_neg == 0) return hipErrorInvalidValue;
+hipError_t launch_rank_sort(uint32_t *negatives, uint32_t num_neg, uint32_t *scratch, unsigned long long *not_finite, hipStream_t stream) {
+    if (num_neg == 0) return hipErrorInvalidValue;
     static_assert(kRankBlocks == kBlock, "k_clear");
     hipLaunchKernelGGL(k_clear, dim3(1), dim3(kBlock), 0, stream, not_finite);
-    uint32_t *const negatives = scores + num_pos, *const counts = scratch + rank_counts_at(num_neg);
+    uint32_t *const counts = scratch + rank_counts_at(num_neg);
     // four passes: the keys end where the scores were
     sort_pass<true>(negatives, nullptr, num_neg, 0u, counts, scratch, nullptr, not_finite, stream);
     sort_pass<false>(scratch, nullptr, num_neg, 8u, counts, negatives, nullptr, nullptr, stream);
     sort_pass<false>(negatives, nullptr, num_neg, 16u, counts, scratch, nullptr, nullptr, stream);
     sort_pass<false>(scratch, nullptr, num_neg, 24u, counts, negatives, nullptr, nullptr, stream);
-    hipLaunchKernelGGL(k_rank_sum, dim3(kRankBlocks), dim3(kSortBlock), 0, stream, scores, (uint64_t)num_pos, negatives, num_neg, twice,
-                       not_finite);
+    return hipGetLastError();
+}
+hipError_t launch_rank_sum(const uint32_t *scores, uint32_t num_pos, uint32_t num_neg, unsigned long long *twice,
+                           unsigned long long *not_finite, hipStream_t stream) {
+    if (num_pos == 0 || num_neg == 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_rank_sum, dim3(kRankBlocks), dim3(kSortBlock), 0, stream, scores, (uint64_t)num_pos, scores + num_pos, num_neg,
+                       twice, not_finite);
     return hipGetLastError();
 }
 

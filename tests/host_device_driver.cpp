@@ -265,11 +265,14 @@ hipError_t launch_cosine(const float *, uint32_t n, uint32_t, const uint32_t *fi
     return hipGetLastError();
 }
 uint64_t rank_scratch_words(uint32_t num_neg) { return num_neg; }
-hipError_t launch_rank_statistic(uint32_t *scores, uint32_t num_pos, uint32_t num_neg, uint32_t *, unsigned long long *twice,
-                                 unsigned long long *not_finite, hipStream_t) {
+hipError_t launch_rank_sort(uint32_t *, uint32_t, uint32_t *, unsigned long long *not_finite, hipStream_t) {
     ranked_on_device = true;
-    memset(twice, 0, kRankBlocks * sizeof *twice);
     memset(not_finite, 0, kRankBlocks * sizeof *not_finite);
+    return hipGetLastError();
+}
+hipError_t launch_rank_sum(const uint32_t *scores, uint32_t num_pos, uint32_t num_neg, unsigned long long *twice, unsigned long long *,
+                           hipStream_t) {
+    memset(twice, 0, kRankBlocks * sizeof *twice);
     const float *positive = (const float *)scores, *negative = positive + num_pos;
     for (uint32_t i = 0; i < num_pos; ++i)
         for (uint32_t j = 0; j < num_neg; ++j) twice[0] += positive[i] > negative[j] ? 2u : positive[i] == negative[j] ? 1u : 0u;
