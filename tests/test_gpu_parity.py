@@ -1189,6 +1189,30 @@ def test_link_prediction_auc_is_the_rank_statistic_of_the_cosines(gv, edges, oth
     assert got == gv.gv_auc(pos, neg)
 
 
+@pytest.mark.parametrize("edges,others", [((1 << 17) + 1, 1 << 17), (1 << 17, 5 * (1 << 17) + 3), (5 * (1 << 17) - 1, 20_000), (90_000, 40_000)])
+@pytest.mark.parametrize("d", [32, 128, 256, 480])
+def test_link_prediction_of_many_pieces(gv, edges, others, d):
+    """Pairs that reach the device in several pieces of 2^17, more of them than are in pinned memory at a time, the edges
+    scored beside the sort of the others (from 2^18 pairs on) or before it: the rank statistic of the same scores, twice; a bad
+    id in the last piece of either set is reported and the next call is whole again."""
+    n = 700
+    rng = np.random.default_rng(edges + others + d)
+    vertex = rng.standard_normal((n, d)).astype(np.float32)
+    with context_for(gv, dim=d, num_neg=1, total_samples=1000, pool_capacity=8) as ctx:
+        gv.gv_set_degrees(ctx, np.ones(n, dtype=np.uint32))
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        ends = [rng.integers(n, size=k).astype(np.uint32) for k in (edges, edges, others, others)]
+        expected = gv.gv_auc(gv.gv_cosine(ctx, *ends[:2]), gv.gv_cosine(ctx, *ends[2:]))
+        assert gv.gv_link_prediction_auc(ctx, *ends) == expected
+        for which in range(4):
+            bad = [e.copy() for e in ends]
+            bad[which][-1] = n
+            with pytest.raises(gv.GvError) as e:
+                gv.gv_link_prediction_auc(ctx, *bad)
+            assert e.value.code == gv.GV_EINVAL
+            assert gv.gv_link_prediction_auc(ctx, *ends) == expected
+
+
 @pytest.mark.parametrize("count", [1, 3, 4, 5, 63, 65, 8192 * 4 - 1, 8192 * 4 + 1, 8192 * 64 + 65])
 @pytest.mark.parametrize("d,K", [(128, 1), (96, 3), (512, 5)])  # rows of 4, 2 and 1 samples gathered together
 def test_evaluation_loss_of_every_chunk_size(gv, tiny_graph, tiny_alias, count, d, K):
