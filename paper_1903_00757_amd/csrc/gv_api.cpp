@@ -232,7 +232,11 @@ int fold_flow(gv_ctx *ctx) {
     ctx->stats.batches += counted - ctx->flow_counted;
     ctx->flow_counted = counted;
     ctx->flow_pending = false;
-    if (flow.stalled) return fail(ctx, GV_EHIP, "a deterministic pool was not trained to its end: the device scratch was overwritten");
+    if (flow.stalled) {
+        ctx->flow_fresh = true;  // reported once; the next pool starts from a cleared state
+        ctx->flow_counted = 0;
+        return fail(ctx, GV_EHIP, "a deterministic pool was not trained to its end: the device scratch was overwritten");
+    }
     return GV_OK;
 }
 
