@@ -574,7 +574,8 @@ int train_flow(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count) {
     GV_HIP(ctx, hipEventRecord(ctx->flow_checked, ctx->compute));
     for (uint64_t first = 0; first < count; first += part) {
         const uint64_t here = std::min(part, count - first);
-        gv::TrainArgs a = train_args(ctx, dev_pairs + 2 * first, ctx->next_g + first, (uint32_t)here);
+        gv::FlowArgs a{};
+        (gv::TrainArgs &)a = train_args(ctx, dev_pairs + 2 * first, ctx->next_g + first, (uint32_t)here);
         a.flow = ctx->flow_state;
         GV_HIP(ctx, gv::launch_flow_prepare(a, K, ctx->records, ctx->flow_turns, ctx->compute));
         if (first == 0) {  // the whole pool is looked at before any of it is trained

@@ -61,9 +61,6 @@ struct TrainArgs {
     uint32_t *records;        // tiled schedule: scratch of count x (K + 3) words, written and read by the launch
                               // (u, v, the K negatives, warm flags of the negatives); deterministic mode: the
                               // samples of the launch in the order of their levels (u, v, the K negatives, place)
-    FlowState *flow;              // k_train_flow: see there, and launch_flow_prepare
-    const uint32_t *keys, *places, *sorted, *namings;
-    uint64_t *turns;              // per row, vertex rows first: low word the place whose turn it is, high word levels so far
     uint32_t *error_flag;     // two words: [0] set to 1 when a sample names a node id >= n (sample skipped), [1] set
                               // to 1 when the tiled kernel meets a row that holds NaN (training has diverged)
     double *loss_slots;       // null, or kLossSlots sums: every wave adds the losses its samples saw before their
@@ -77,6 +74,14 @@ struct TrainArgs {
     uint32_t n;               // |V|
     uint32_t dim;             // d: row length in floats
     float lr0, lr_min_ratio, neg_weight;
+};
+
+// k_train_flow takes these beside (see there, and launch_flow_prepare).  They are no part of TrainArgs, which every launch of
+// asynchronous training carries by value.
+struct FlowArgs : TrainArgs {
+    FlowState *flow;
+    const uint32_t *keys, *places, *sorted, *namings;
+    uint64_t *turns;              // per row, vertex rows first: low word the place whose turn it is, high word levels so far
 };
 
 constexpr uint32_t kLossSlots = 64;
@@ -120,9 +125,9 @@ hipError_t launch_level_records(const uint32_t *pairs, const uint32_t *negatives
 // flow_scratch_words(), turns of 2 n) and trained.  Part: a.pairs, a.count, a.first_g.
 uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg);
 hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, FlowState *state, bool fresh, hipStream_t stream);
-hipError_t launch_flow_prepare(TrainArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t stream);
-hipError_t launch_train_flow(TrainArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
-hipError_t launch_train_flow_tracked(TrainArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
+hipError_t launch_flow_prepare(FlowArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t stream);
+hipError_t launch_train_flow(FlowArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
+hipError_t launch_train_flow_tracked(FlowArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
 // The same three launches with kernels that also sum the running loss into a.loss_slots (which must be set for
 // these and null for the ones above).
 hipError_t launch_train_hogwild_tracked(const TrainArgs &a, uint32_t dim, uint32_t num_neg, uint32_t coherence,

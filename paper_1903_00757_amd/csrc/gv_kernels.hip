@@ -1060,7 +1060,7 @@ struct FlowSample {
     uint32_t hands_on[kRows];   // the place behind it (so the last one's stays)
     uint32_t level = 0;         // the highest level of the samples before it at its rows
 
-    __device__ __forceinline__ void take(const TrainArgs &a, uint32_t sample, bool mine) {
+    __device__ __forceinline__ void take(const FlowArgs &a, uint32_t sample, bool mine) {
 #pragma unroll
         for (int j = 0; j < kRows; ++j) {
             key[j] = mine ? a.keys[(size_t)sample * kRows + j] : 0u;
@@ -1103,7 +1103,7 @@ struct FlowSample {
 // The rows that have a wave of their own: lane h < kFlowHubs holds the hub h, most namings first.
 struct FlowHubs {
     uint32_t key, begin, namings;  // namings 0: none
-    __device__ __forceinline__ void find(const TrainArgs &a, int lane) {
+    __device__ __forceinline__ void find(const FlowArgs &a, int lane) {
         unsigned long long slot = a.flow->slots[lane], mine = 0ull;
         for (int h = 0; h < kFlowHubs; ++h) {
             unsigned long long most = slot;
@@ -1139,7 +1139,7 @@ struct FlowHubs {
 struct FlowRows {
     char *vertex, *context;  // of keys 0
     uint32_t bytes;
-    __device__ __forceinline__ explicit FlowRows(const TrainArgs &a)
+    __device__ __forceinline__ explicit FlowRows(const FlowArgs &a)
         : vertex((char *)a.vertex), context((char *)a.context - (uint64_t)a.n * a.dim * sizeof(float)), bytes(a.dim * (uint32_t)sizeof(float)) {}
     __device__ __forceinline__ char *of(int j, uint32_t key) const { return (j == 0 ? vertex : context) + (uint64_t)key * bytes; }
 };
@@ -1148,7 +1148,7 @@ struct FlowRows {
 // awaited back).  The row stays in registers y; the other rows of the next sample are on their way while one is computed,
 // and its stores are waited for after the next one's arithmetic.  false: gave up.
 template <int kV, int kK, bool kFull, bool kTrack>
-__device__ __forceinline__ bool flow_hub(const TrainArgs &a, const FlowHubs &hubs, uint32_t h, int lane, uint32_t &deepest,
+__device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs, uint32_t h, int lane, uint32_t &deepest,
                                          float &lane_loss) {
     constexpr int kRows = kK + 2;
     constexpr uint32_t kNone = 0xFFFFFFFFu, kAhead = 16;  // samples ahead whose turns are looked at
@@ -1306,7 +1306,7 @@ __device__ __forceinline__ bool flow_hub(const TrainArgs &a, const FlowHubs &hub
 }
 
 template <int kV, int kK, bool kFull, bool kTrack>
-__global__ __launch_bounds__(kFlowBlock) void k_train_flow(TrainArgs a) {
+__global__ __launch_bounds__(kFlowBlock) void k_train_flow(FlowArgs a) {
     constexpr int kRows = kK + 2, kBatch = flow_batch(kV, kK);
     using Io = HandedRow<kV, kFull>;
     const int lane = threadIdx.x & (kWave - 1);
@@ -2121,7 +2121,7 @@ hipError_t launch_levels_vk(const TrainArgs &a, hipStream_t stream) {
 }
 
 template <int kV, int kK>
-hipError_t launch_flow_vk(const TrainArgs &a, hipStream_t stream) {
+hipError_t launch_flow_vk(const FlowArgs &a, hipStream_t stream) {
     if (a.count == 0) return hipSuccess;
     if ((a.loss_slots != nullptr) != (GV_TRACK_LOSS != 0) || a.unit == 0 || a.unit > (uint32_t)kWave || a.blocks == 0)
         return hipErrorInvalidValue;
@@ -2172,7 +2172,7 @@ hipError_t GV_TRAIN_NAME(launch_train_levels)(const TrainArgs &a, uint32_t dim, 
 #undef GV_CALL
 }
 
-hipError_t GV_TRAIN_NAME(launch_train_flow)(TrainArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream) {
+hipError_t GV_TRAIN_NAME(launch_train_flow)(FlowArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream) {
     a.unit = 8;
     const uint32_t per_block = a.unit * (kFlowBlock / kWave);
     a.blocks = std::min((a.count + per_block - 1) / per_block, 128u);
@@ -2296,7 +2296,7 @@ hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, 
     return hipGetLastError();
 }
 
-hipError_t launch_flow_prepare(TrainArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t stream) {
+hipError_t launch_flow_prepare(FlowArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t stream) {
     if (a.count == 0 || a.n > 0x80000000u) return hipErrorInvalidValue;
     const uint32_t namings = a.count * (num_neg + 2);
     const uint64_t stride = ((uint64_t)namings + 3u) & ~3ull;

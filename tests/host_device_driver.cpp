@@ -187,6 +187,7 @@ hipError_t launch_train_levels(const TrainArgs &a, uint32_t, uint32_t num_neg, h
 hipError_t launch_train_levels_tracked(const TrainArgs &a, uint32_t dim, uint32_t num_neg, hipStream_t s) {
     return launch_train_levels(a, dim, num_neg, s);
 }
+static_assert(sizeof(TrainArgs) == 176, "carried by every launch of asynchronous training: arguments of one kernel go into a struct of their own");
 uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg) { return 6ull * count * (num_neg + 2); }
 hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, FlowState *state, bool fresh, hipStream_t) {
     if (fresh) state->batches = state->deepest = state->stalled = 0;
@@ -195,7 +196,7 @@ hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, 
         if (pairs[2 * i] >= n || pairs[2 * i + 1] >= n) state->first_bad = (uint32_t)i;
     return hipGetLastError();
 }
-hipError_t launch_flow_prepare(TrainArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t) {
+hipError_t launch_flow_prepare(FlowArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t) {
     a.flow->batches += a.flow->deepest;
     a.flow->deepest = 0;
     memset(scratch, 0, flow_scratch_words(a.count, num_neg) * sizeof *scratch);
@@ -209,7 +210,7 @@ hipError_t launch_flow_prepare(TrainArgs &a, uint32_t num_neg, uint32_t *scratch
     a.keys = scratch;
     return hipGetLastError();
 }
-hipError_t launch_train_flow(TrainArgs a, uint32_t, uint32_t num_neg, hipStream_t) {
+hipError_t launch_train_flow(FlowArgs a, uint32_t, uint32_t num_neg, hipStream_t) {
     const long left = host_allocations_left;
     host_allocations_left = -1;
     CHECK(a.flow->first_bad == UINT32_MAX);
@@ -222,7 +223,7 @@ hipError_t launch_train_flow(TrainArgs a, uint32_t, uint32_t num_neg, hipStream_
     host_allocations_left = left;
     return hipGetLastError();
 }
-hipError_t launch_train_flow_tracked(TrainArgs a, uint32_t dim, uint32_t num_neg, hipStream_t s) {
+hipError_t launch_train_flow_tracked(FlowArgs a, uint32_t dim, uint32_t num_neg, hipStream_t s) {
     return launch_train_flow(a, dim, num_neg, s);
 }
 hipError_t launch_level_records(const uint32_t *pairs, const uint32_t *negatives, const uint32_t *order, uint32_t count,
