@@ -235,7 +235,7 @@ int fold_flow(gv_ctx *ctx) {
     if (flow.stalled) {
         ctx->flow_fresh = true;  // reported once; the next pool starts from a cleared state
         ctx->flow_counted = 0;
-        return fail(ctx, GV_EHIP, "a deterministic pool was not trained to its end: the device scratch was overwritten");
+        return fail(ctx, GV_EHIP, "a deterministic pool was not trained to its end: a sample waited for one that never came (device memory overwritten?)");
     }
     return GV_OK;
 }

@@ -32,8 +32,27 @@ struct FlowState {
     uint32_t first_bad;          // the first sample of the pool that names an id that is no node; UINT32_MAX: none
     uint32_t stalled;            // set where a wave gave up (see k_train_flow)
     uint32_t started;            // workgroups that have begun
+    uint32_t chained;            // times 64 namings of a hub are done
     unsigned long long nowhere;  // takes the turns that are not handed on
     unsigned long long slots[64];  // rows named often: namings << 32 | place of the first
+};
+
+// How long a wave of k_train_flow waits for a turn: until nothing of the pool has got on for 2^22 looks at the turns, half a
+// second or more.  What has got on is read every 2^16 looks: samples taken (next_chunk) and namings of the hubs done (chained),
+// of which one moves before 10^4 links of a chain are done one after the other, 50 ms at most.  The whole wait may be
+// longer by any factor: waves run ahead of the hubs' samples, whose chain can be most of a part, 2^20 links of 1.3 us and more.
+struct FlowPatience {
+    static constexpr uint32_t kLooks = 1u << 16, kIdle = 64;
+    uint32_t looks = 0, idle = 0, before = 0;
+    // after a look in vain; progress(): what has got on so far
+    template <class Progress>
+    __host__ __device__ bool ends(Progress &&progress) {
+        if (++looks % kLooks != 0u) return false;
+        const uint32_t now = progress();
+        idle = now == before ? idle + 1u : 0u;
+        before = now;
+        return idle >= kIdle;
+    }
 };
 
 // Everything a training launch needs; passed by value as the kernel argument.

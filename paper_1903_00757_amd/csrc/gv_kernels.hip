@@ -995,11 +995,14 @@ struct HandedRow {
 // Every wait ends: the waves of the hubs are those of one workgroup, the first that runs, together with one that takes
 // samples as all others do; samples are taken in pool order, so the first sample of the pool that is not done is at
 // the head of a hub's chain, or has been taken by a wave that runs, or is taken by the next one that has finished
-// its own, and its turns have come.  Should they fail to (memory overwritten by the caller), a wave gives up after
-// kFlowPolls polls without a sample and says so.
-constexpr uint32_t kFlowPolls = 1u << 22;
+// its own, and its turns have come.  Should they fail to (memory overwritten by the caller), a wave gives up and says so
+// (FlowPatience).
 constexpr uint32_t kFlowStep = 2000;  // cycles, about half of what a row takes from wave to wave
 constexpr int kFlowBlock = 512, kFlowHubs = kFlowBlock / kWave - 1;
+__device__ __forceinline__ uint32_t flow_progress(const FlowState *state) {
+    return __hip_atomic_load(&state->next_chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+           __hip_atomic_load(&state->chained, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 constexpr int flow_batch(int V, int K) { return V * (K + 2) <= 14 ? 2 : 1; }
 // The rows of two samples of a chain fit the 256 registers of a wave (with those of longer ones kept in memory, 20000 samples at
 // d = 512, K = 5 take 19 ms, without chains 5.5); without chains there are no hubs.
@@ -1212,7 +1215,7 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
                     continue;
                 }
                 bool here = held;
-                for (uint32_t polls = 0;; ++polls) {
+                for (FlowPatience patience;;) {
                     const uint64_t hub_turn = __hip_atomic_load(a.turns + hub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     const bool looks = (uint32_t)lane >= i && (uint32_t)lane <= i + kAhead && inside && !((come >> lane) & 1u);
                     s.read(looks, is);
@@ -1224,7 +1227,7 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
                         level = __builtin_amdgcn_readfirstlane((uint32_t)(hub_turn >> 32));
                     }
                     if (here && ((come >> i) & 1u)) break;
-                    if (polls >= kFlowPolls) {
+                    if (patience.ends([&] { return __builtin_amdgcn_readfirstlane(flow_progress(a.flow)); })) {
                         if (lane == 0) a.flow->stalled = 1u;
                         return false;
                     }
@@ -1295,6 +1298,7 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
         }
         memory_is_done();
         hand_on();
+        if (lane == 0) (void)__hip_atomic_fetch_add(&a.flow->chained, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         deepest = max(deepest, level);
         if constexpr (kTrack) {
             if ((own >> lane) & 1u) lane_loss += again ? 0.0f : scores.loss(a.neg_weight);
@@ -1341,7 +1345,7 @@ __global__ __launch_bounds__(kFlowBlock) void k_train_flow(FlowArgs a) {
         const bool mine = inside && owner == (uint32_t)kFlowHubs;
         const float lr = learning_rate(a.lr0, a.lr_min_ratio, a.first_g + base + lane, a.total);
         ChunkScores<kK> scores{};
-        uint32_t polls = 0;
+        FlowPatience patience;
         uint64_t pending = __ballot(mine), ready = 0;            // samples to do; those of which all turns have come
         uint32_t due = (uint32_t)__builtin_readcyclecounter();  // lane l: when its turns are looked at again
         while (pending) {
@@ -1354,12 +1358,13 @@ __global__ __launch_bounds__(kFlowBlock) void k_train_flow(FlowArgs a) {
                 if (looks) {
                     const uint32_t away = s.seen(is, 0u);
                     came = away == 0u;
-                    // a sample that others come before is not looked at again before they can be done
-                    if (away > 1u) due = now + min(away - 1u, 64u) * kFlowStep;
+                    // a sample that others come before is not looked at again before they can be done; `due` is never far
+                    // behind `now` while the lane waits (their difference has 31 bits)
+                    if (away > 0u) due = now + min(away - 1u, 64u) * kFlowStep;
                 }
                 ready |= __ballot(came);
                 if (!ready) {
-                    if (++polls >= kFlowPolls) {
+                    if (__ballot(looks) && patience.ends([&] { return __builtin_amdgcn_readfirstlane(flow_progress(state)); })) {
                         if (lane == 0) state->stalled = 1u;
                         break;
                     }
@@ -1367,7 +1372,7 @@ __global__ __launch_bounds__(kFlowBlock) void k_train_flow(FlowArgs a) {
                     continue;
                 }
             }
-            polls = 0;
+            patience = FlowPatience{};
             asm volatile("" ::: "memory");
             uint64_t taken = 0;
             float x[kBatch][kV], c[kBatch][kK + 1][kV];
@@ -1753,7 +1758,7 @@ __global__ __launch_bounds__(kWave) void k_flow_begin(FlowState *state, bool new
         state->batches = 0ull;
         state->deepest = state->stalled = 0u;
     }
-    state->started = 0u;
+    state->started = state->chained = 0u;
     state->batches += state->deepest;
     state->deepest = 0u;
     state->next_chunk = 0u;

@@ -479,6 +479,28 @@ void flowing_pools() {
     }
 }
 
+// A wave that waits for a turn gives up where nothing of the pool gets on, and there within a bounded number of looks; not for as
+// long as the chain that it waits for gets on, however long that is: here 2^20 links of 10 us, which are counted 64 at a time,
+// while the wave looks every 130 ns, and the samples taken stand still.
+void patience_of_waiting() {
+    constexpr double kLook = 0.13, kLink = 10.0;  // us
+    constexpr uint64_t kLinks = 1u << 20;
+    gv::FlowPatience patience;
+    uint64_t look = 0;
+    for (; (double)look * kLook < (double)kLinks * kLink; ++look) {
+        const uint64_t links = (uint64_t)((double)look * kLook / kLink);
+        CHECK(!patience.ends([&] { return 4711u + (uint32_t)(links / 64u); }));
+    }
+    uint32_t in_vain = 0;
+    while (!patience.ends([&] { return 4711u + (uint32_t)(kLinks / 64u); })) CHECK(++in_vain < 1u << 23);
+    CHECK(in_vain >= 1u << 21);
+    // nothing from the first look on
+    gv::FlowPatience fresh;
+    in_vain = 0;
+    while (!fresh.ends([] { return 0u; })) CHECK(++in_vain < 1u << 23);
+    CHECK(in_vain >= (1u << 22) - 1);
+}
+
 // A graph of a ring with chords: every node has its two neighbours and the nodes two steps away.
 struct Ring {
     static constexpr uint32_t n = 50;
@@ -787,6 +809,7 @@ int main(int argc, char **argv) {
         {"contexts after failed allocations", contexts_after_failed_allocations},
         {"levels after failed allocations", levels_after_failed_allocations},
         {"flowing pools", flowing_pools},
+        {"patience of waiting", patience_of_waiting},
         {"pools in parts", pools_in_parts},
         {"walks after failed allocations", walks_after_failed_allocations},
         {"packed walks leave room", packed_walks_leave_room},
