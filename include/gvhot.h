@@ -43,7 +43,8 @@ enum { GV_OK = 0, GV_EINVAL = -1, GV_ENOMEM = -2, GV_ESTATE = -3, GV_EHIP = -4 }
  *   sharing rows (Def. 1, Sec. 3.2) and is not meant for graphs on which a single node takes part in a large
  *   share of all samples (a star): those train in DETERMINISTIC mode.
  * DETERMINISTIC: samples sorted into batches without shared rows, those that share a row in pool order; equals
- *   sequential SGD up to fp32 rounding inside a sample.                                                  */
+ *   sequential SGD up to fp32 rounding inside a sample.  The resulting rows depend on the samples and their
+ *   positions alone, bit for bit: not on how they are cut into pools, nor on the memory that is left for scratch. */
 enum { GV_MODE_HOGWILD = 0, GV_MODE_DETERMINISTIC = 1 };
 enum { GV_VERTEX = 0, GV_CONTEXT = 1 };
 /* How embedding rows travel between compute units and memory while an

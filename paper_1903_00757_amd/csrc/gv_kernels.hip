@@ -315,6 +315,9 @@ __device__ __forceinline__ bool first_naming(const uint32_t (&rows)[kK + 1], int
 }
 template <int kK>
 __device__ __forceinline__ float total_coefficient(const uint32_t (&rows)[kK + 1], const float (&coef)[kK + 1], int k) {
+    // the sum of rounded coefficients in every kernel: joined to the product of a coefficient that happens to stand beside it,
+    // the bits of deterministic training would depend on the kernel
+#pragma clang fp contract(off)
     float total = coef[k];
 #pragma unroll
     for (int k2 = k + 1; k2 <= kK; ++k2) total += rows[k2] == rows[k] ? coef[k2] : 0.0f;

@@ -270,6 +270,42 @@ def test_deterministic_pools_that_wait_on_the_device(gv, hubs, d, K, count, trac
     assert stats["batches"] == sum(conflict_levels(pool, neg[i * count:(i + 1) * count], n) for i in (0, 1))
 
 
+@pytest.mark.parametrize("d,K", [(128, 1), (64, 5), (32, 2), (96, 3), (256, 4), (352, 1), (512, 2), (512, 5)])
+@pytest.mark.parametrize("hubs", [0, 3])
+def test_deterministic_bits_do_not_depend_on_the_way(gv, hubs, d, K):
+    """A pool whose samples wait for each other on the device, and the same samples in two pools so short that they are sorted
+    into levels: the same bits, also of rows that a sample names several times (every ninth positive is one of the
+    sample's own negatives)."""
+    import torch
+
+    n, count, seed = 4000, 8192, 53
+    rng = np.random.default_rng(d + K)
+    deg = rng.integers(20, 30, size=n).astype(np.uint32)
+    pool = rng.integers(n, size=(count, 2)).astype(np.uint32)
+    for i in range(hubs):
+        pool[rng.random(count) < 0.015, i % 2] = 17 * i
+    vertex, context = random_embeddings(n, d, seed=16)
+    got = []
+    for parts in (1, 2):
+        with context_for(gv, dim=d, num_neg=K, neg_weight=5.0 / K, mode=gv.GV_MODE_DETERMINISTIC, total_samples=3 * count,
+                         seed=seed, pool_capacity=8, lr0=LR0) as ctx:
+            gv.gv_set_degrees(ctx, deg)
+            gv.gv_build_alias(ctx, 0.75)
+            gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+            gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+            if not got:
+                pool[::9, 1] = gv.gv_draw_negatives(ctx, 0, count, K)[::9, K - 1]
+            held = torch.from_numpy(pool.view(np.int32)).cuda()
+            torch.cuda.synchronize()
+            for k in range(parts):
+                gv.gv_train_device_pool(ctx, held.data_ptr() + k * (count // parts) * 8, count // parts)
+            stats = gv.gv_get_stats(ctx)
+            assert stats["samples_trained"] == count and (stats["train_launches"] == 1) == (parts == 1)
+            got.append([gv.gv_read_embeddings(ctx, which, n, d) for which in (gv.GV_VERTEX, gv.GV_CONTEXT)])
+    for one, two in zip(*got):
+        assert np.array_equal(one.view(np.uint32), two.view(np.uint32))
+
+
 @pytest.mark.parametrize("resident", [False, True])
 def test_deterministic_pool_of_several_parts(gv, resident):
     """A pool of more than the 2^20 samples that are sorted into levels at a time, pushed and resident; then
