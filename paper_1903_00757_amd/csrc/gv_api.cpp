@@ -43,12 +43,18 @@ constexpr uint64_t kHostRanked = 4096;
 constexpr uint64_t kStageWords = 16384, kDeterministicPart = 1u << 20;  // see train_deterministic
 // Deterministic pools of more samples than this wait for each other on the device (train_flow) instead of being sorted into
 // levels on the host: 5000 samples on 200000 nodes 66 instead of 185 us, on 5000 nodes without hubs 60 instead of 180, and
-// fewer are levelled before the preparation's dozen launches are done.  Not where the hottest row is named by more than one
-// sample in 24: levels are narrow there, and a level of a few samples costs 0.7 us in one workgroup, a link of a chain 1.3
-// (d = 128, K = 1, a pass alone: hottest share 2.1 % 9.1 -> 4.0 ms, 3.6 % 2.29 -> 1.78, 4.6 % 0.93 -> 0.95; K = 5, 7.5 % 8.0
-// -> 10.6; a star 7.8 -> 12.4).
+// fewer are levelled before the preparation's dozen launches are done.  Not where levels are narrow: a level of a few samples
+// costs 0.7 us in one workgroup, a link of a chain 1.3, and 1.9 from wave to wave.  That is so where the graph's hottest row is
+// named by more than one sample in 24 (d = 128, K = 1, a pass alone: hottest share 2.1 % 9.1 -> 4.0 ms, 3.6 % 2.29 -> 1.78,
+// 4.6 % 0.93 -> 0.95; K = 5, 7.5 % 8.0 -> 10.6; a star 7.8 -> 12.4), and in pools that put samples of a row close together
+// whatever the graph, such as walks in their own order: those are known by the levels of the samples that launch_flow_check
+// looks at (narrow_levels), fewer than 16 samples a level on average.  60000 samples, levels -> waiting on the device, ms, by
+// samples a level of those looked at: K = 1, d = 128: 3.6 12.6 -> 31.4, 8.9 6.7 -> 12.1, 15.5 5.1 -> 5.9, 17.4 4.9 -> 4.7, 30 4.3
+// -> 3.0, 89 2.0 -> 0.84; K = 5, d = 128: 2.9 27 -> 60, 12 11.4 -> 10.3, 27 9.7 -> 4.8; d = 512: 3.3 36 -> 49, 12 24 -> 14; K = 3:
+// 5.4 13.3 -> 20, 23.8 6.9 -> 4.4.  The same samples in the producer's shuffled order have 40 to 200 a level.
 constexpr uint64_t kFlowFrom = 4096;
 constexpr double kFlowShare = 1.0 / 24.0;
+constexpr uint32_t kFlowWidth = 16, kMostRows = 5 + 2;  // of a sample: num_neg <= 5
 
 // The pairs of gv_eval_loss and gv_link_prediction_auc are read by the kernels from pinned memory, piece by piece, while the
 // next piece is copied there: the host copies 77 GB/s and the kernels read 50, where a copy to the device from the caller's
@@ -146,6 +152,8 @@ struct gv_ctx {
     bool flow_pending = false;            // its state counts batches that are not in stats yet
     bool flow_fresh = false;              // its state is not cleared yet
     uint64_t flow_counted = 0;            // batches of the state that are
+    std::vector<uint64_t> flow_rows;      // see narrow_levels
+    uint32_t force_way = 0;               // see gv_test_force_way
     std::vector<uint32_t> level_vertex, level_context;  // deterministic mode: see train_deterministic
     uint32_t level_base = 0;
     std::string error;
@@ -560,14 +568,59 @@ int ensure_flow(gv_ctx *ctx, uint64_t count) {
     return ensure_records(ctx, gv::flow_scratch_words((uint32_t)std::min(count, kDeterministicPart), ctx->cfg.num_neg));
 }
 
+// The levels (see train_deterministic) of the first `per_run` samples of each of `runs` runs, one run after the other;
+// named[runs][kFlowRun][num_neg + 2].  The rows met so far stand in a table of `slots` entries, row + 1 << 32 | level, a
+// power of two and more than twice their number.
+uint32_t levels_of(const uint32_t *named, uint32_t runs, uint32_t per_run, uint32_t num_neg, uint64_t *table, uint32_t slots) {
+    const uint32_t rows = num_neg + 2;
+    const int shift = 32 - __builtin_ctz(slots);
+    memset(table, 0, slots * sizeof *table);
+    uint32_t deepest = 0;
+    for (uint32_t r = 0; r < runs; ++r) {
+        for (uint32_t i = 0; i < per_run; ++i) {
+            const uint32_t *const row = named + ((size_t)r * gv::kFlowRun + i) * rows;
+            uint64_t *entry[kMostRows];
+            uint32_t level = 0;
+            for (uint32_t j = 0; j < rows; ++j) {
+                const uint64_t key = (uint64_t)row[j] + 1u << 32;  // the rows are less than 2^32 - 1
+                uint32_t slot = (row[j] * 0x9E3779B1u) >> shift;
+                while (table[slot] != 0 && (table[slot] ^ key) >> 32 != 0) slot = (slot + 1u) & (slots - 1u);
+                if (table[slot] == 0) table[slot] = key;
+                entry[j] = table + slot;
+                level = std::max(level, (uint32_t)table[slot]);
+            }
+            ++level;
+            for (uint32_t j = 0; j < rows; ++j) *entry[j] = (*entry[j] >> 32 << 32) | level;
+            deepest = std::max(deepest, level);
+        }
+    }
+    return deepest;
+}
+
+// Whether the samples that launch_flow_check looked at have levels of fewer than kFlowWidth samples on average.  Most pools
+// are seen to have half as many again by a quarter of those samples (10 us of the host at K = 1, while the device prepares the
+// pool; all of them take 100, and 200 at K = 5).
+bool narrow_levels(gv_ctx *ctx, const uint32_t *named, uint32_t num_neg) {
+    constexpr uint32_t kSlots = 1u << 16, kFew = gv::kFlowRun / 4;
+    static_assert(2 * gv::kFlowRuns * gv::kFlowRun * kMostRows < kSlots, "room");
+    ctx->flow_rows.resize(kSlots);
+    const uint64_t few = levels_of(named, gv::kFlowRuns, kFew, num_neg, ctx->flow_rows.data(), kSlots / 4);
+    if (few * kFlowWidth * 3u <= gv::kFlowRuns * kFew * 2u) return false;
+    const uint64_t all = levels_of(named, gv::kFlowRuns, gv::kFlowRun, num_neg, ctx->flow_rows.data(), kSlots);
+    return all * kFlowWidth > gv::kFlowRuns * gv::kFlowRun;
+}
+
 // Deterministic training of a pool that is not short: every sample waits on the device for the earlier samples that name
 // one of its rows (k_train_flow).  The namings of the rows are sorted there, and the host waits only for the check of the
-// ids.
-int train_flow(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count) {
+// ids.  *narrow: set, and nothing trained, where the levels are narrow (see kFlowFrom).
+int train_flow(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, bool *narrow) {
     const uint32_t K = ctx->cfg.num_neg;
     const uint64_t part = std::min(count, kDeterministicPart);
     int rc = GV_OK;
-    GV_HIP(ctx, gv::launch_flow_check(dev_pairs, count, ctx->n, ctx->flow_state, ctx->flow_fresh, ctx->compute));
+    uint32_t *const named = ctx->results->piece[0];  // no evaluation runs meanwhile
+    static_assert(sizeof ctx->results->piece >= gv::kFlowRuns * gv::kFlowRun * kMostRows * sizeof(uint32_t), "room");
+    GV_HIP(ctx, gv::launch_flow_check(train_args(ctx, dev_pairs, ctx->next_g, 0), count, K, ctx->flow_state, ctx->flow_fresh, named,
+                                      ctx->compute));
     ctx->flow_fresh = false;
     gv::FlowState &flow = ctx->results->flow;
     GV_HIP(ctx, hipMemcpyAsync(&flow, ctx->flow_state, sizeof flow, hipMemcpyDeviceToHost, ctx->compute));
@@ -582,6 +635,8 @@ int train_flow(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count) {
             GV_HIP(ctx, hipEventSynchronize(ctx->flow_checked));
             if (flow.first_bad != UINT32_MAX)
                 return fail(ctx, GV_EINVAL, "sample %llu names node id >= n (%u)", (unsigned long long)flow.first_bad, ctx->n);
+            *narrow = !ctx->force_way && narrow_levels(ctx, named, K);
+            if (*narrow) return GV_OK;
         }
         TimedSpan span{};
         const bool timed = ctx->cfg.profile != 0;
@@ -738,10 +793,12 @@ int train_any(gv_ctx *ctx, const uint32_t *dev_pairs, const uint32_t *host_pairs
     if (ctx->cfg.mode != GV_MODE_DETERMINISTIC) {
         rc = train_hogwild(ctx, dev_pairs, count);
     } else {
-        const bool flows = count > kFlowFrom && ctx->n <= 0x80000000u && ctx->hottest_share <= kFlowShare;
-        const int room = flows ? ensure_flow(ctx, count) : GV_ENOMEM;
+        const bool flows = ctx->force_way ? ctx->force_way == 1 : count > kFlowFrom && ctx->hottest_share <= kFlowShare;
+        const int room = flows && ctx->n <= 0x80000000u ? ensure_flow(ctx, count) : GV_ENOMEM;
         if (room != GV_OK && room != GV_ENOMEM) return room;
-        rc = room == GV_OK ? train_flow(ctx, dev_pairs, count) : train_deterministic(ctx, dev_pairs, host_pairs, count);
+        bool narrow = false;
+        if (room == GV_OK) rc = train_flow(ctx, dev_pairs, count, &narrow);
+        if (room != GV_OK || narrow) rc = train_deterministic(ctx, dev_pairs, host_pairs, count);
     }
     if (rc) return rc;
     ctx->next_g += count;
@@ -1766,6 +1823,15 @@ int gv_test_force_tile(gv_ctx *ctx, uint32_t samples) {
     if (samples != 0 && !(size && (smaller || samples == gv::kLargestTile)))
         return fail(ctx, GV_EINVAL, "no kernel with tiles of %u samples", samples);
     ctx->force_tile = samples;
+    return GV_OK;
+}
+
+// Not part of the boundary: lets a test take either way of deterministic pools.  1: they wait on the device, whatever their
+// length and rows (where that finds memory); 2: they are sorted into levels; 0: as kFlowFrom tells.
+int gv_test_force_way(gv_ctx *ctx, uint32_t way) {
+    if (!ctx) return GV_EINVAL;
+    if (way > 2) return fail(ctx, GV_EINVAL, "no way %u", way);
+    ctx->force_way = way;
     return GV_OK;
 }
 

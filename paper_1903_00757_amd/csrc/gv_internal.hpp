@@ -143,7 +143,18 @@ hipError_t launch_level_records(const uint32_t *pairs, const uint32_t *negatives
 // are checked (fresh: the state is cleared first), then each part of it is prepared (which sets a.keys, a.places and a.turns; scratch of
 // flow_scratch_words(), turns of 2 n) and trained.  Part: a.pairs, a.count, a.first_g.
 uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg);
-hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, FlowState *state, bool fresh, hipStream_t stream);
+// The check also writes the rows that some samples name (as launch_flow_prepare does: u, n + v, n + every negative) to
+// `named`, which may be host memory: eight runs of 512 samples at equal distances, the one at place t being sample
+// flow_look(t, count); count >= kFlowRuns * kFlowRun, or the whole pool and places up to its length.
+constexpr uint32_t kFlowRun = 512, kFlowRuns = 8;
+__host__ __device__ inline uint32_t flow_looked_at(uint64_t count) {
+    return count < kFlowRun * kFlowRuns ? (uint32_t)count : kFlowRun * kFlowRuns;
+}
+__host__ __device__ inline uint64_t flow_look(uint32_t t, uint64_t count) {
+    return count < kFlowRun * kFlowRuns ? t : t / kFlowRun * (count / kFlowRuns) + t % kFlowRun;
+}
+hipError_t launch_flow_check(const TrainArgs &pool, uint64_t count, uint32_t num_neg, FlowState *state, bool fresh, uint32_t *named,
+                             hipStream_t stream);
 hipError_t launch_flow_prepare(FlowArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t stream);
 hipError_t launch_train_flow(FlowArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream);
 hipError_t launch_train_flow_tracked(FlowArgs a, uint32_t dim, uint32_t num_neg, hipStream_t stream);

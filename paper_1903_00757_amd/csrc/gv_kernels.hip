@@ -1767,25 +1767,33 @@ __global__ __launch_bounds__(kWave) void k_flow_begin(FlowState *state, bool new
     state->next_chunk = 0u;
     if (new_pool) state->first_bad = UINT32_MAX;
 }
-// first_bad = the first sample that names an id that is no node, if any does
-__global__ __launch_bounds__(kBlock) void k_flow_check(const uint2 *__restrict__ pairs, uint64_t count, uint32_t n, FlowState *state) {
-    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (uint64_t)gridDim.x * kBlock) {
+// The rows that a sample names, K + 2 words: u, n + v, n + every negative (row 0 in the place of a bad id: the sort and the
+// turns go over such a pool, the training does not).
+__device__ __forceinline__ void flow_keys(uint2 p, const uint4 *__restrict__ alias, uint32_t n, uint64_t seed, uint64_t g, uint32_t num_neg,
+                                          uint32_t *__restrict__ key) {
+    key[0] = p.x < n ? p.x : 0u;
+    key[1] = n + (p.y < n ? p.y : 0u);
+    for (uint32_t k = 0; k < num_neg; ++k) key[2 + k] = n + draw_negative(alias, n, seed, g, k);
+}
+// first_bad = the first sample that names an id that is no node, if any does; `named`: see launch_flow_check
+__global__ __launch_bounds__(kBlock) void k_flow_check(const uint2 *__restrict__ pairs, uint64_t count, const uint4 *__restrict__ alias,
+                                                       uint32_t n, uint64_t seed, uint64_t first_g, uint32_t num_neg, FlowState *state,
+                                                       uint32_t *__restrict__ named) {
+    const uint32_t thread = blockIdx.x * kBlock + threadIdx.x;
+    for (uint32_t t = thread; t < flow_looked_at(count); t += gridDim.x * kBlock) {
+        const uint64_t i = flow_look(t, count);
+        flow_keys(pairs[i], alias, n, seed, first_g + i, num_neg, named + (size_t)t * (num_neg + 2));
+    }
+    for (uint64_t i = thread; i < count; i += (uint64_t)gridDim.x * kBlock) {
         const uint2 p = pairs[i];
         if (p.x >= n || p.y >= n) atomicMin(&state->first_bad, (uint32_t)i);
     }
 }
-// The rows that the samples name, K + 2 words a sample: u, n + v, n + every negative (row 0 in the place of a bad id: the
-// sort and the turns go over such a pool, the training does not).
 __global__ __launch_bounds__(kBlock) void k_flow_keys(const uint2 *__restrict__ pairs, const uint4 *__restrict__ alias, uint32_t n,
                                                       uint64_t seed, uint64_t first_g, uint32_t count, uint32_t num_neg,
                                                       uint32_t *__restrict__ keys) {
-    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (uint64_t)gridDim.x * kBlock) {
-        const uint2 p = pairs[i];
-        uint32_t *key = keys + i * (num_neg + 2);
-        key[0] = p.x < n ? p.x : 0u;
-        key[1] = n + (p.y < n ? p.y : 0u);
-        for (uint32_t k = 0; k < num_neg; ++k) key[2 + k] = n + draw_negative(alias, n, seed, first_g + i, k);
-    }
+    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (uint64_t)gridDim.x * kBlock)
+        flow_keys(pairs[i], alias, n, seed, first_g + i, num_neg, keys + i * (num_neg + 2));
 }
 // From the sorted namings: the place of every naming; where a row's namings begin, the row's first turn, and, if there
 // are many, an entry {namings, begin} in one of 64 slots, which keeps the largest (FlowHubs takes the first of them).
@@ -2296,11 +2304,12 @@ uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg) {
     return 6 * ((namings + 3u) & ~3ull) + sort_count_words((uint32_t)namings);
 }
 
-hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, FlowState *state, bool fresh, hipStream_t stream) {
+hipError_t launch_flow_check(const TrainArgs &pool, uint64_t count, uint32_t num_neg, FlowState *state, bool fresh, uint32_t *named,
+                             hipStream_t stream) {
     hipLaunchKernelGGL(k_flow_begin, dim3(1), dim3(kWave), 0, stream, state, true, fresh);
     const uint64_t wanted = (count + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_flow_check, dim3((uint32_t)std::min<uint64_t>(wanted, 4096u)), dim3(kBlock), 0, stream, (const uint2 *)pairs,
-                       count, n, state);
+    hipLaunchKernelGGL(k_flow_check, dim3((uint32_t)std::min<uint64_t>(wanted, 4096u)), dim3(kBlock), 0, stream, (const uint2 *)pool.pairs,
+                       count, pool.alias, pool.n, pool.seed, pool.first_g, num_neg, state, named);
     return hipGetLastError();
 }
 

@@ -16,6 +16,7 @@
 #include "gvhot.h"
 
 extern "C" int gv_test_force_tile(gv_ctx *ctx, uint32_t samples);
+extern "C" int gv_test_force_way(gv_ctx *ctx, uint32_t way);
 
 #define CHECK(cond)                                                                  \
     do {                                                                             \
@@ -189,7 +190,16 @@ hipError_t launch_train_levels_tracked(const TrainArgs &a, uint32_t dim, uint32_
 }
 static_assert(sizeof(TrainArgs) == 176, "carried by every launch of asynchronous training: arguments of one kernel go into a struct of their own");
 uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg) { return 6ull * count * (num_neg + 2); }
-hipError_t launch_flow_check(const uint32_t *pairs, uint64_t count, uint32_t n, FlowState *state, bool fresh, hipStream_t) {
+hipError_t launch_flow_check(const TrainArgs &pool, uint64_t count, uint32_t num_neg, FlowState *state, bool fresh, uint32_t *named,
+                             hipStream_t) {
+    const uint32_t *const pairs = pool.pairs, n = pool.n;
+    for (uint32_t t = 0; t < flow_looked_at(count); ++t) {
+        const uint64_t i = flow_look(t, count);
+        CHECK(i < count && (t == 0 || i > flow_look(t - 1, count)));
+        *named++ = pairs[2 * i] < n ? pairs[2 * i] : 0u;
+        *named++ = n + (pairs[2 * i + 1] < n ? pairs[2 * i + 1] : 0u);
+        for (uint32_t k = 0; k < num_neg; ++k) *named++ = n + draw(pool.first_g + i, k, n);
+    }
     if (fresh) state->batches = state->deepest = state->stalled = 0;
     state->first_bad = UINT32_MAX;
     for (uint64_t i = count; i-- > 0;)
@@ -477,6 +487,49 @@ void flowing_pools() {
         trained.clear();
         gv_destroy(ctx);
     }
+}
+
+// Pools whose levels are narrow are levelled, whatever the degrees of the graph: walks in their own order, and a row that one
+// sample in ten names; the same walks shuffled, a row that one sample in forty names, and a long pool of random pairs are not.
+void narrow_pools() {
+    const uint32_t n = 20000, K = 1, count = 30000, length = 40, window = 5;
+    const std::vector<uint32_t> degrees(n, 3);
+    std::vector<uint32_t> walks;
+    for (uint32_t w = 0; walks.size() < 2 * count; ++w) {
+        uint32_t walk[length];
+        for (uint32_t i = 0; i < length; ++i) walk[i] = draw(w * 64ull + i, 3, 40) < 36 ? draw(w * 64ull + i, 5, n) : draw(w * 64ull + i, 7, 50);
+        for (uint32_t i = 0; i < length; ++i)
+            for (uint32_t j = i + 1; j < std::min(i + window + 1, length); ++j) walks.insert(walks.end(), {walk[i], walk[j]});
+    }
+    walks.resize(2 * count);
+    std::vector<uint32_t> shuffled;
+    for (uint32_t b = 0; b < window; ++b)
+        for (uint32_t i = b; i < count; i += window) shuffled.insert(shuffled.end(), {walks[2 * i], walks[2 * i + 1]});
+    auto planted = [&](uint32_t one_in) {
+        std::vector<uint32_t> pool = random_pool(n, count, 9);
+        for (uint32_t i = 0; i < count; ++i)
+            if (draw(i, 11, one_in) == 0) pool[2 * i] = 7;
+        return pool;
+    };
+    const std::vector<uint32_t> tenth = planted(10), fortieth = planted(40), random = random_pool(n, 9 * count, 2);
+    struct Pool {
+        const std::vector<uint32_t> &pairs;
+        bool flows;
+    };
+    gv_ctx *ctx = context(GV_MODE_DETERMINISTIC, K);
+    CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+    uint64_t g = 0;
+    for (const Pool &p : {Pool{walks, false}, Pool{shuffled, true}, Pool{tenth, false}, Pool{fortieth, true}, Pool{random, true}}) {
+        for (uint32_t way : {0u, 1u, 2u}) {
+            flowed = 0;
+            CHECK(gv_test_force_way(ctx, way) == GV_OK);
+            CHECK(gv_train_device_pool(ctx, p.pairs.data(), p.pairs.size() / 2) == GV_OK);
+            CHECK(flowed == ((way ? way == 1 : p.flows) ? p.pairs.size() / 2 : 0));
+            check_levels(p.pairs, g, n, K);
+            g += p.pairs.size() / 2;
+        }
+    }
+    gv_destroy(ctx);
 }
 
 // A wave that waits for a turn gives up where nothing of the pool gets on, and there within a bounded number of looks; not for as
@@ -809,6 +862,7 @@ int main(int argc, char **argv) {
         {"contexts after failed allocations", contexts_after_failed_allocations},
         {"levels after failed allocations", levels_after_failed_allocations},
         {"flowing pools", flowing_pools},
+        {"narrow pools", narrow_pools},
         {"patience of waiting", patience_of_waiting},
         {"pools in parts", pools_in_parts},
         {"walks after failed allocations", walks_after_failed_allocations},

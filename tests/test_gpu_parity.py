@@ -221,6 +221,13 @@ def conflict_levels(pool, neg, n):
     return int(level.max())
 
 
+def force_way(gv, ctx, way):
+    """Deterministic pools of any kind: 1 wait on the device, 2 are sorted into levels."""
+    lib = gv.load()
+    lib.gv_test_force_way.argtypes = [ctypes.c_void_p, ctypes.c_uint32]
+    assert lib.gv_test_force_way(ctx, way) == gv.GV_OK
+
+
 @pytest.mark.parametrize("track", [0, 1])
 @pytest.mark.parametrize("d,K,count", [(128, 1, 9000), (64, 5, 4097), (32, 2, 5003), (96, 3, 6001), (256, 4, 4100), (352, 1, 4999),
                                        (512, 2, 4200), (512, 5, 4300)])
@@ -245,6 +252,7 @@ def test_deterministic_pools_that_wait_on_the_device(gv, hubs, d, K, count, trac
     neg = oracle.draw_negatives(seed, 0, 2 * count, K, thresh, alias)
     with context_for(gv, dim=d, num_neg=K, neg_weight=w, mode=gv.GV_MODE_DETERMINISTIC, total_samples=T, seed=seed,
                      pool_capacity=count, lr0=LR0, track_loss=track, profile=track) as ctx:
+        force_way(gv, ctx, 1)  # with hubs, most would be sorted into levels
         gv.gv_set_degrees(ctx, deg)
         gv.gv_build_alias(ctx, 0.75)
         gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
@@ -306,9 +314,50 @@ def test_deterministic_bits_do_not_depend_on_the_way(gv, hubs, d, K):
         assert np.array_equal(one.view(np.uint32), two.view(np.uint32))
 
 
+@pytest.mark.parametrize("K", [1, 3])
+def test_deterministic_pools_with_narrow_levels(gv, K):
+    """Walks in their own order, which are levelled, and in shuffled order, which wait on the device, on a graph without
+    hubs; then a pool of which every sample names one row, and pools of either kind again.  Equal to the oracle, in as many
+    batches as the pools have conflict-free levels."""
+    n, d, count, w, seed = 5000, 64, 20_000, 5.0 / K, 59
+    rng = np.random.default_rng(13)
+    adj = np.concatenate([np.roll(np.arange(n), s)[:, None] for s in (1, -1, 7, -7, 411, -411)], axis=1).astype(np.uint32)
+    offsets = np.arange(n + 1, dtype=np.uint64) * 6
+    deg = np.full(n, 6, dtype=np.uint32)
+    pools = [gv.gv_augment(offsets, adj.reshape(-1), seed=s, count=count, shuffle=order)[0]
+             for s, order in ((1, gv.GV_SHUFFLE_NONE), (2, gv.GV_SHUFFLE_PSEUDO))]
+    star = rng.integers(n, size=(6000, 2)).astype(np.uint32)
+    star[:, 1] = 77
+    pools += [star, *pools]
+    vertex, context = random_embeddings(n, d, seed=17)
+    T = 2 * sum(p.shape[0] for p in pools)
+    with context_for(gv, dim=d, num_neg=K, neg_weight=w, mode=gv.GV_MODE_DETERMINISTIC, total_samples=T, seed=seed,
+                     pool_capacity=count, lr0=LR0) as ctx:
+        gv.gv_set_degrees(ctx, deg)
+        gv.gv_build_alias(ctx, 0.75)
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+        for p in pools:
+            gv.gv_push_pool(ctx, p)
+            gv.gv_train_pool(ctx)
+        got_v = gv.gv_read_embeddings(ctx, gv.GV_VERTEX, n, d)
+        got_c = gv.gv_read_embeddings(ctx, gv.GV_CONTEXT, n, d)
+        batches = gv.gv_get_stats(ctx)["batches"]
+    ref_v, ref_c = run_oracle(deg, K, w, pools, vertex, context, T, seed)
+    for got, ref in ((got_v, ref_v), (got_c, ref_c)):
+        fro, mx = rel_errors(got, ref)
+        assert fro <= 1e-5 and mx <= 1e-4, (fro, mx)
+    thresh, alias = oracle.alias_build(oracle.degree_weights(deg))
+    neg = oracle.draw_negatives(seed, 0, T // 2, K, thresh, alias)
+    ends = np.cumsum([p.shape[0] for p in pools])
+    assert batches == sum(conflict_levels(p, neg[e - p.shape[0]:e], n) for p, e in zip(pools, ends))
+
+
+@pytest.mark.parametrize("way", [0, 2])  # the long pool waits on the device; is sorted into levels
 @pytest.mark.parametrize("resident", [False, True])
-def test_deterministic_pool_of_several_parts(gv, resident):
-    """A pool of more than the 2^20 samples that are sorted into levels at a time, pushed and resident; then
+def test_deterministic_pool_of_several_parts(gv, resident, way):
+    """A pool of more than the 2^20 samples that are prepared at a time, pushed and resident, with a row that one sample in
+    thirty names, so that a part holds a chain of 35000 links, and another row that the last of that chain share; then
     pools at either side of what goes through the pinned stage (16384 words: at K = 2, 5 a sample of a pushed pool and 7 of
     a resident one, and one over)."""
     import torch
@@ -318,10 +367,13 @@ def test_deterministic_pool_of_several_parts(gv, resident):
     deg = rng.integers(1, 50, size=n).astype(np.uint32)
     sizes = [(1 << 20) + 777, 1, 2340, 2341, 3276, 3277, 5]
     pools = [rng.integers(n, size=(size, 2)).astype(np.uint32) for size in sizes]
+    pools[0][::30, 0] = 4711
+    pools[0][(1 << 20) - 3000:1 << 20:3, 1] = 815
     vertex, context = random_embeddings(n, d, seed=14)
     T = 2 * sum(sizes)
     with context_for(gv, dim=d, num_neg=K, neg_weight=w, mode=gv.GV_MODE_DETERMINISTIC, total_samples=T, seed=seed,
                      pool_capacity=max(sizes), lr0=LR0, profile=1) as ctx:
+        force_way(gv, ctx, way)
         gv.gv_set_degrees(ctx, deg)
         gv.gv_build_alias(ctx, 0.75)
         gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
@@ -334,6 +386,9 @@ def test_deterministic_pool_of_several_parts(gv, resident):
             else:
                 gv.gv_push_pool(ctx, p)
                 gv.gv_train_pool(ctx)
+            if p is pools[0]:
+                launches = gv.gv_get_stats(ctx)["train_launches"]
+                assert launches == 2 if way == 0 else launches > 10
         got_v = gv.gv_read_embeddings(ctx, gv.GV_VERTEX, n, d)
         got_c = gv.gv_read_embeddings(ctx, gv.GV_CONTEXT, n, d)
         assert gv.gv_get_stats(ctx)["samples_trained"] == sum(sizes)

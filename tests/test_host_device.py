@@ -36,6 +36,7 @@ def driver(tmp_path_factory):
     "contexts after failed allocations",
     "levels after failed allocations",
     "flowing pools",
+    "narrow pools",
     "patience of waiting",
     "pools in parts",
     "walks after failed allocations",
