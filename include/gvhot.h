@@ -361,10 +361,12 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
 
 /* Wait for all queued device work of the context; folds event timings into the
  * statistics; reports samples that named an id >= n (GV_EINVAL, once), and training that has
- * diverged: an embedding row holding NaN met by an asynchronous launch under the tiled schedule (GV_ESTATE, once).
- * (Housekeeping, no passage.)                                                   */
+ * diverged: an embedding row holding NaN met by an asynchronous launch under the tiled schedule (GV_ESTATE, once);
+ * and a deterministic pool that was not trained to its end, because the device memory that orders its samples was
+ * overwritten (GV_ESTATE, once).  (Housekeeping, no passage.)                   */
 int gv_sync(gv_ctx *ctx);
-/* Counters of the context so far.  (Diagnostic hook, no passage.)               */
+/* Counters of the context so far.  Waits for the deterministic pools in flight, whose batches are counted on the
+ * device, and leaves what they have to report to gv_sync.  (Diagnostic hook, no passage.)   */
 int gv_get_stats(gv_ctx *ctx, gv_stats *out);
 /* Set the position g of the next positive sample: g selects the negatives (stream 0,
  * counter (g, k)) and the learning rate lr0 * max(1 - g / T, floor) of Sec. 4.3, so a run

@@ -151,6 +151,7 @@ struct gv_ctx {
     hipEvent_t flow_checked = nullptr;
     bool flow_pending = false;            // its state counts batches that are not in stats yet
     bool flow_fresh = false;              // its state is not cleared yet
+    bool flow_stalled = false;            // a wave of it gave up: to be reported
     uint64_t flow_counted = 0;            // batches of the state that are
     std::vector<uint64_t> flow_rows;      // see narrow_levels
     uint32_t force_way = 0;               // see gv_test_force_way
@@ -233,19 +234,18 @@ void fold_spans(gv_ctx *ctx) {
     ctx->spans.clear();
 }
 
-// The state of deterministic pools as copied to the host: batches go into the statistics, a wave that gave up is an error.
-int fold_flow(gv_ctx *ctx) {
+// The state of deterministic pools as copied to the host: batches go into the statistics, a wave that gave up is noted.
+void fold_flow(gv_ctx *ctx) {
     const gv::FlowState &flow = ctx->results->flow;
     const uint64_t counted = flow.batches + flow.deepest;
     ctx->stats.batches += counted - ctx->flow_counted;
     ctx->flow_counted = counted;
     ctx->flow_pending = false;
     if (flow.stalled) {
-        ctx->flow_fresh = true;  // reported once; the next pool starts from a cleared state
+        ctx->flow_stalled = true;
+        ctx->flow_fresh = true;  // the next pool starts from a cleared state
         ctx->flow_counted = 0;
-        return fail(ctx, GV_EHIP, "a deterministic pool was not trained to its end: a sample waited for one that never came (device memory overwritten?)");
     }
-    return GV_OK;
 }
 
 // *evaluation_ids (may be null): set where the report is that the evaluation just queued names ids that are no nodes.
@@ -266,13 +266,15 @@ int sync_all(gv_ctx *ctx, bool *evaluation_ids = nullptr) {
         for (double x : r.loss_slots) total += x;
         ctx->stats.train_loss_sum = total;
     }
-    if (ctx->flow_pending) {
-        int rc = fold_flow(ctx);
-        if (rc) return rc;
-    }
+    if (ctx->flow_pending) fold_flow(ctx);
+    const bool stalled = ctx->flow_stalled;
     const uint32_t flag[3] = {r.flag[0], r.flag[1], r.flag[2]};
-    if (flag[0] || flag[1] || flag[2]) {
+    if (stalled || flag[0] || flag[1] || flag[2]) {  // the gravest is reported, and none of them again
         GV_HIP(ctx, hipMemset(ctx->error_flag, 0, sizeof r.flag));
+        ctx->flow_stalled = false;
+        if (stalled)
+            return fail(ctx, GV_ESTATE, "a deterministic pool was not trained to its end: a sample waited for one that never came "
+                        "(device memory overwritten?)");
         if (flag[0])
             return fail(ctx, GV_EINVAL, "a trained pool named a node id >= n (%u); those samples were skipped", ctx->n);
         if (flag[1])
@@ -1790,18 +1792,17 @@ int gv_sync(gv_ctx *ctx) {
 
 int gv_get_stats(gv_ctx *ctx, gv_stats *out) {
     if (!ctx || !out) return ctx ? fail(ctx, GV_EINVAL, "null output") : GV_EINVAL;
-    return guarded(ctx, [&]() -> int {
-        if (ctx->flow_pending) {  // the batches of deterministic pools are counted on the device
-            int rc = bind_device(ctx);
-            if (rc) return rc;
-            GV_HIP(ctx, hipMemcpyAsync(&ctx->results->flow, ctx->flow_state, sizeof(gv::FlowState), hipMemcpyDeviceToHost, ctx->compute));
-            GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
-            rc = fold_flow(ctx);
-            if (rc) return rc;
-        }
-        *out = ctx->stats;
+    const int rc = guarded(ctx, [&]() -> int {
+        if (!ctx->flow_pending) return GV_OK;
+        int rc = bind_device(ctx);
+        if (rc) return rc;
+        GV_HIP(ctx, hipMemcpyAsync(&ctx->results->flow, ctx->flow_state, sizeof(gv::FlowState), hipMemcpyDeviceToHost, ctx->compute));
+        GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
+        fold_flow(ctx);  // what it has to report is left to the next synchronising call
         return GV_OK;
     });
+    *out = ctx->stats;
+    return rc;
 }
 
 int gv_set_position(gv_ctx *ctx, uint64_t next_g) {

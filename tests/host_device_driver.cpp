@@ -137,6 +137,7 @@ struct Trained {  // of deterministic mode, in the order of training
 std::vector<Trained> trained;
 uint32_t levels_trained = 0;
 uint64_t flowed = 0;  // samples trained by launch_train_flow
+bool stall_next = false;  // the next launch_train_flow gives up
 int training_reports = -1;  // word of the error flag that asynchronous training sets, if any
 bool tiled_launched = false;
 uint32_t launched_unit = 0;
@@ -229,6 +230,8 @@ hipError_t launch_train_flow(FlowArgs a, uint32_t, uint32_t num_neg, hipStream_t
         trained.push_back(Trained{levels_trained++, std::vector<uint32_t>(key, key + num_neg + 2), a.first_g + i});
     }
     a.flow->deepest = a.count;
+    if (stall_next) a.flow->stalled = 1;
+    stall_next = false;
     flowed += a.count;
     host_allocations_left = left;
     return hipGetLastError();
@@ -528,6 +531,38 @@ void narrow_pools() {
             check_levels(p.pairs, g, n, K);
             g += p.pairs.size() / 2;
         }
+    }
+    gv_destroy(ctx);
+}
+
+// A pool that was not trained to its end is reported once, by the next call that synchronises, not by gv_get_stats; it hides
+// no other report for longer than that, does not stop calls that begin anew, and the batches of pools behind it are counted.
+void pools_that_give_up() {
+    const uint32_t n = 2000, K = 2, count = 5000;
+    const std::vector<uint32_t> degrees(n, 3), pool = random_pool(n, count, 1);
+    std::vector<uint32_t> bad(pool.begin(), pool.begin() + 20);
+    bad[3] = n;
+    gv_ctx *ctx = context(GV_MODE_DETERMINISTIC, K);
+    CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+    double loss = 0.0;
+    gv_stats stats;
+    for (int which = 0; which < 4; ++which) {
+        stall_next = true;
+        memset(&stats, 0xFF, sizeof stats);
+        CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK);
+        const uint64_t trained_so_far = (uint64_t)(3 * which + 1) * count;
+        CHECK(gv_get_stats(ctx, &stats) == GV_OK && stats.samples_trained == trained_so_far && stats.batches == trained_so_far);
+        if (which == 0) CHECK(gv_sync(ctx) == GV_ESTATE && strstr(gv_last_error(ctx), "not trained to its end"));
+        if (which == 1) CHECK(gv_eval_loss(ctx, bad.data(), 10, 7, &loss) == GV_ESTATE && strstr(gv_last_error(ctx), "not trained to its end"));
+        if (which == 2) CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+        if (which == 3) CHECK(gv_init_embeddings(ctx, 5) == GV_OK);
+        CHECK(gv_eval_loss(ctx, pool.data(), 10, 7, &loss) == GV_OK && gv_sync(ctx) == GV_OK);
+        for (int again = 0; again < 2; ++again) {
+            CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK);
+            if (again == which % 2) CHECK(gv_sync(ctx) == GV_OK);
+        }
+        CHECK(gv_get_stats(ctx, &stats) == GV_OK && stats.batches == trained_so_far + 2 * count && gv_sync(ctx) == GV_OK);
+        trained.clear();
     }
     gv_destroy(ctx);
 }
@@ -864,6 +899,7 @@ int main(int argc, char **argv) {
         {"flowing pools", flowing_pools},
         {"narrow pools", narrow_pools},
         {"patience of waiting", patience_of_waiting},
+        {"pools that give up", pools_that_give_up},
         {"pools in parts", pools_in_parts},
         {"walks after failed allocations", walks_after_failed_allocations},
         {"packed walks leave room", packed_walks_leave_room},

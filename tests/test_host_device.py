@@ -38,6 +38,7 @@ def driver(tmp_path_factory):
     "flowing pools",
     "narrow pools",
     "patience of waiting",
+    "pools that give up",
     "pools in parts",
     "walks after failed allocations",
     "packed walks leave room",
