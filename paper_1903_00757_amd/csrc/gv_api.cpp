@@ -553,13 +553,33 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
 }
 
 // What train_flow needs on the device beside the pool: 6 words for every row that a sample of a part names, and 4 words a
-// node.  GV_ENOMEM where that does not fit (or the nodes' would take more than an eighth of the memory that is left).
+// node.  GV_ENOMEM where that does not fit (or the nodes' would take more than an eighth of the memory that is left): then
+// nothing is held for it, and the scratch of levels stays, for every pool asks anew.
 int ensure_flow(gv_ctx *ctx, uint64_t count) {
+    const uint64_t words = gv::flow_scratch_words((uint32_t)std::min(count, kDeterministicPart), ctx->cfg.num_neg);
+    if (ctx->flow_turns && words <= ctx->records_capacity) return GV_OK;
+    size_t left = 0, total = 0;
+    GV_HIP(ctx, hipMemGetInfo(&left, &total));
+    const size_t bytes = (size_t)ctx->n * 2 * sizeof(uint64_t);
+    if (!ctx->flow_turns && bytes > left / 8) return GV_ENOMEM;
+    if (words > ctx->records_capacity) {
+        if ((words - ctx->records_capacity) * sizeof(uint32_t) > left) return GV_ENOMEM;
+        if (words * sizeof(uint32_t) > left) {  // in the place of the old scratch only
+            int rc = ensure_records(ctx, words);
+            if (rc) return rc;
+        } else {
+            uint32_t *records = nullptr;
+            GV_HIP(ctx, hipMalloc((void **)&records, words * sizeof(uint32_t)));
+            std::swap(records, ctx->records);
+            ctx->records_capacity = words;
+            if (records) {
+                const hipError_t e = hipStreamSynchronize(ctx->compute);
+                (void)hipFree(records);
+                GV_HIP(ctx, e);
+            }
+        }
+    }
     if (!ctx->flow_turns) {
-        const size_t bytes = (size_t)ctx->n * 2 * sizeof(uint64_t);
-        size_t left = 0, total = 0;
-        GV_HIP(ctx, hipMemGetInfo(&left, &total));
-        if (bytes > left / 8) return GV_ENOMEM;
         if (!ctx->flow_checked) GV_HIP(ctx, hipEventCreateWithFlags(&ctx->flow_checked, hipEventDisableTiming));
         uint64_t *turns = nullptr;
         GV_HIP(ctx, hipMalloc((void **)&turns, bytes + sizeof(gv::FlowState)));
@@ -567,7 +587,7 @@ int ensure_flow(gv_ctx *ctx, uint64_t count) {
         ctx->flow_state = (gv::FlowState *)((char *)turns + bytes);
         ctx->flow_fresh = true;
     }
-    return ensure_records(ctx, gv::flow_scratch_words((uint32_t)std::min(count, kDeterministicPart), ctx->cfg.num_neg));
+    return GV_OK;
 }
 
 // The levels (see train_deterministic) of the first `per_run` samples of each of `runs` runs, one run after the other;

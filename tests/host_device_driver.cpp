@@ -30,6 +30,7 @@ extern "C" int gv_test_force_way(gv_ctx *ctx, uint32_t way);
 namespace {
 long host_allocations_left = -1;    // this many more, then one fails; negative: no limit
 long device_allocations_left = -1;  // the same of hipMalloc
+uint64_t device_allocations = 0, device_frees = 0;
 size_t device_largest = SIZE_MAX;   // bytes that a hipMalloc may ask for
 size_t device_free = SIZE_MAX;      // bytes that hipMemGetInfo says are left
 }  // namespace
@@ -61,6 +62,7 @@ hipError_t hipMalloc(void **p, size_t size) {
     }
     if (device_allocations_left > 0) --device_allocations_left;
     *p = size <= device_largest ? malloc(size) : nullptr;
+    device_allocations += *p != nullptr;
     return *p ? hipSuccess : last_error = hipErrorOutOfMemory;
 }
 hipError_t hipMemGetInfo(size_t *left, size_t *total) {
@@ -69,6 +71,7 @@ hipError_t hipMemGetInfo(size_t *left, size_t *total) {
     return hipSuccess;
 }
 hipError_t hipFree(void *p) {
+    device_frees += 1;
     free(p);
     return hipSuccess;
 }
@@ -589,6 +592,33 @@ void patience_of_waiting() {
     CHECK(in_vain >= (1u << 22) - 1);
 }
 
+// Where the words of a sample do not fit, in whole or beside what is there, a second pool of the same size changes nothing on the
+// device, and nothing is held for the way that was refused; where they fit in the place of the old ones, they take it.
+void refused_scratch() {
+    const uint32_t n = 2000, K = 2, count = 5000;
+    const std::vector<uint32_t> degrees(n, 3), pool = random_pool(n, count, 1);
+    const size_t levels = (size_t)count * (K + 3) * sizeof(uint32_t), waiting = 6 * (size_t)count * (K + 2) * sizeof(uint32_t);
+    for (int which = 0; which < 3; ++which) {
+        gv_ctx *ctx = context(GV_MODE_DETERMINISTIC, K);
+        CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+        flowed = 0;
+        if (which == 0) device_largest = waiting - 1;
+        else device_free = waiting - levels - 1;
+        CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK && flowed == 0);
+        const uint64_t allocations = device_allocations, frees = device_frees;
+        CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK && flowed == 0);
+        CHECK(device_allocations == allocations && device_frees == frees);
+        if (which == 2) {
+            device_free = waiting - levels;
+            CHECK(gv_train_device_pool(ctx, pool.data(), count) == GV_OK && flowed == count);
+            CHECK(device_allocations == allocations + 2 && device_frees == frees + 1);
+        }
+        device_largest = device_free = SIZE_MAX;
+        trained.clear();
+        gv_destroy(ctx);
+    }
+}
+
 // A graph of a ring with chords: every node has its two neighbours and the nodes two steps away.
 struct Ring {
     static constexpr uint32_t n = 50;
@@ -900,6 +930,7 @@ int main(int argc, char **argv) {
         {"narrow pools", narrow_pools},
         {"patience of waiting", patience_of_waiting},
         {"pools that give up", pools_that_give_up},
+        {"refused scratch", refused_scratch},
         {"pools in parts", pools_in_parts},
         {"walks after failed allocations", walks_after_failed_allocations},
         {"packed walks leave room", packed_walks_leave_room},

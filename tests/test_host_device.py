@@ -39,6 +39,7 @@ def driver(tmp_path_factory):
     "narrow pools",
     "patience of waiting",
     "pools that give up",
+    "refused scratch",
     "pools in parts",
     "walks after failed allocations",
     "packed walks leave room",
