@@ -136,7 +136,8 @@ typedef struct gv_stats {
 } gv_stats;
 
 /* Create a context on cfg->device (one GPU holds all rows: the single-GPU case of
- * Sec. 3.4).  Allocates the pool slots only; the graph decides the matrix sizes later.
+ * Sec. 3.4).  Allocates the pool slots and 4.2 MB of pinned memory; the graph decides the matrix sizes
+ * later.
  * *out is NULL on failure (GV_EINVAL for a bad field, GV_EHIP without a usable device,
  * GV_ENOMEM).                                                                        */
 int gv_create(const gv_config *cfg, gv_ctx **out);
@@ -340,8 +341,9 @@ int gv_draw_negatives(gv_ctx *ctx, uint64_t first_g, uint64_t count, uint32_t *h
  *   drawn from the alias table with Philox stream 2 of eval_seed, counter (i, k).
  * gv_cosine: host_out[i] = cosine of vertex rows host_first[i], host_second[i] (0 for a
  *   zero row): the score of a node pair in link prediction (Sec. 4.5).
- * Ids >= n give GV_EINVAL.  Both keep one device scratch buffer that grows with the largest
- * call.                                                                              */
+ * Ids >= n give GV_EINVAL.  gv_cosine and gv_link_prediction_auc keep one device scratch buffer
+ * that grows with the largest call; the pairs of gv_eval_loss and gv_link_prediction_auc go
+ * through 4 MB of pinned memory that every context holds.                            */
 int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64_t eval_seed, double *mean_loss);
 int gv_cosine(gv_ctx *ctx, const uint32_t *host_first, const uint32_t *host_second, uint64_t count, float *host_out);
 /* Link prediction (Sec. 4.5): the held-out edges are ranked against other node pairs by the
@@ -351,9 +353,10 @@ int gv_cosine(gv_ctx *ctx, const uint32_t *host_first, const uint32_t *host_seco
  *   code, no context.  GV_EINVAL for an empty set or a score that is not finite.
  * gv_link_prediction_auc: the same statistic of the cosines of num_edges pairs
  *   (host_edge_first[i], host_edge_second[i]) against num_others pairs
- *   (host_other_first[i], host_other_second[i]); waits for training first.  Takes up to 16
- *   bytes of the evaluation scratch a pair, or, where the device has not that much left, 12 a
- *   pair of the larger set (the ranking is then done on the host).                      */
+ *   (host_other_first[i], host_other_second[i]); waits for training first.  Takes 4 bytes of the
+ *   evaluation scratch a pair and up to 6 more for each of the others (of up to 4096 pairs none), or,
+ *   where the device has not that much left, 12 a pair of the larger set (the ranking is then done
+ *   on the host).                                                                       */
 int gv_auc(const float *host_pos, uint64_t num_pos, const float *host_neg, uint64_t num_neg, double *auc);
 int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const uint32_t *host_edge_second,
                            uint64_t num_edges, const uint32_t *host_other_first, const uint32_t *host_other_second,

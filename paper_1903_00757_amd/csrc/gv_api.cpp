@@ -1738,13 +1738,11 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
             *auc = rank_auc(scores, num_edges, scores + num_edges, num_others);
             return GV_OK;
         };
-        // scratch: what ranking on the device needs (the partial sums and flags, then the sort), the scores, and room
-        // for the ends of the pairs, without which the call falls back to cosine_scores as well
+        // scratch: the sort's, then the scores; those of few pairs go to pinned memory
         const bool few = count <= kHostRanked;
-        const uint64_t sums = few ? 0 : 2 * gv::kRankBlocks * sizeof(unsigned long long);
         const uint64_t sorting = few ? 0 : (gv::rank_scratch_words((uint32_t)num_others) + 3u) & ~3ull;
-        rc = ensure_eval_scratch(ctx, sums + (sorting + 3 * count) * sizeof(uint32_t));
-        if (rc == GV_ENOMEM && !few) {  // the cosines of one set after the other take less
+        rc = few ? GV_OK : ensure_eval_scratch(ctx, (sorting + count) * sizeof(uint32_t));
+        if (rc == GV_ENOMEM) {  // the cosines of one set after the other may take less
             rc = sync_all(ctx);
             if (rc) return rc;
             std::vector<float> scores(count);

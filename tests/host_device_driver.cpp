@@ -281,7 +281,7 @@ hipError_t launch_cosine(const float *, uint32_t n, uint32_t, const uint32_t *fi
     }
     return hipGetLastError();
 }
-uint64_t rank_scratch_words(uint32_t num_neg) { return num_neg; }
+uint64_t rank_scratch_words(uint32_t num_neg) { return num_neg + num_neg / 2; }
 hipError_t launch_rank_sort(uint32_t *, uint32_t, uint32_t *, unsigned long long *not_finite, hipStream_t) {
     ranked_on_device = true;
     memset(not_finite, 0, kRankBlocks * sizeof *not_finite);
@@ -889,7 +889,8 @@ void ranking_where_it_can_be_done() {
     };
     for (const Expected &e : {Expected{1, 1, SIZE_MAX, false}, Expected{2048, 2048, SIZE_MAX, false},
                               Expected{2049, 2048, SIZE_MAX, true}, Expected{3000, 4000, SIZE_MAX, true},
-                              Expected{3000, 4000, 60000, false}, Expected{4000, 3000, 50000, false}}) {
+                              Expected{3000, 4000, 51999, false}, Expected{3000, 4000, 52000, true},
+                              Expected{4000, 3000, 46000, true}, Expected{100, 4000, 40400, true}, Expected{4000, 4000, 48000, false}}) {
         gv_ctx *ctx = context(GV_MODE_HOGWILD, 1);
         CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK);
         const std::vector<uint32_t> edges = random_pool(n, e.edges, 5), others = random_pool(n, e.others, 6);
@@ -911,9 +912,13 @@ void ranking_where_it_can_be_done() {
         gv_ctx *full = context(GV_MODE_HOGWILD, 1);
         float scores[1];
         CHECK(gv_set_degrees(full, n, degrees.data()) == GV_OK);
-        device_largest = 12 * std::max(e.edges, e.others) - 1;  // not even for the cosines of the larger set
+        // not even for the cosines of the larger set; few pairs need none
+        device_largest = std::min<size_t>(12 * std::max(e.edges, e.others), 4 * (e.edges + e.others + ((gv::rank_scratch_words(e.others) + 3) & ~3ull))) - 1;
+        const bool few = e.edges + e.others <= 4096;
+        const uint64_t allocations = device_allocations;
         CHECK(gv_link_prediction_auc(full, ends[0].data(), ends[1].data(), e.edges, ends[2].data(), ends[3].data(), e.others,
-                                     &got) == GV_ENOMEM);
+                                     &got) == (few ? GV_OK : GV_ENOMEM));
+        CHECK(!few || device_allocations == allocations);
         device_largest = SIZE_MAX;
         CHECK(gv_cosine(full, ends[0].data(), ends[1].data(), 1, &scores[0]) == GV_OK);  // the failure is not reported again
         gv_destroy(full);
