@@ -552,6 +552,18 @@ int train_hogwild(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, uint32
     return GV_OK;
 }
 
+// The kernels of an evaluation, and the check of a deterministic pool, use pinned memory of the context that the next call
+// writes: whatever ends a call early, they have ended when it returns.
+struct PinnedInUse {
+    gv_ctx *ctx;
+    bool ended = false;  // waited for already
+    ~PinnedInUse() {
+        if (ended) return;
+        (void)hipStreamSynchronize(ctx->copy);
+        (void)hipStreamSynchronize(ctx->compute);
+    }
+};
+
 // What train_flow needs on the device beside the pool: 6 words for every row that a sample of a part names, and 4 words a
 // node.  GV_ENOMEM where that does not fit (or the nodes' would take more than an eighth of the memory that is left): then
 // nothing is held for it, and the scratch of levels stays, for every pool asks anew.
@@ -639,6 +651,7 @@ int train_flow(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, bool *nar
     const uint32_t K = ctx->cfg.num_neg;
     const uint64_t part = std::min(count, kDeterministicPart);
     int rc = GV_OK;
+    PinnedInUse in_use{ctx};
     uint32_t *const named = ctx->results->piece[0];  // no evaluation runs meanwhile
     static_assert(sizeof ctx->results->piece >= gv::kFlowRuns * gv::kFlowRun * kMostRows * sizeof(uint32_t), "room");
     GV_HIP(ctx, gv::launch_flow_check(train_args(ctx, dev_pairs, ctx->next_g, 0), count, K, ctx->flow_state, ctx->flow_fresh, named,
@@ -655,6 +668,7 @@ int train_flow(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, bool *nar
         GV_HIP(ctx, gv::launch_flow_prepare(a, K, ctx->records, ctx->flow_turns, ctx->compute));
         if (first == 0) {  // the whole pool is looked at before any of it is trained
             GV_HIP(ctx, hipEventSynchronize(ctx->flow_checked));
+            in_use.ended = true;
             if (flow.first_bad != UINT32_MAX)
                 return fail(ctx, GV_EINVAL, "sample %llu names node id >= n (%u)", (unsigned long long)flow.first_bad, ctx->n);
             *narrow = !ctx->force_way && narrow_levels(ctx, named, K);
@@ -1656,6 +1670,7 @@ int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64
             for (uint32_t b = 0; b < blocks[slot]; ++b) total += r.partial[slot][b];
             blocks[slot] = 0;
         };
+        PinnedInUse in_use{ctx};
         Pieces pieces(ctx, count);
         int rc = pieces.take(count, ctx->compute, [&](uint64_t first, uint64_t here, int slot) -> int {
             take_in(slot);
@@ -1669,6 +1684,7 @@ int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64
         if (rc) return rc;
         bool bad_ids = false;  // then the result covers the other pairs
         rc = sync_all(ctx, &bad_ids);
+        in_use.ended = rc != GV_EHIP;
         if (rc && !bad_ids) return rc;
         for (int slot = 0; slot < kPieces; ++slot) take_in(slot);
         *mean_loss = total / (double)count;
@@ -1762,6 +1778,7 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
         // It has nothing to wait for but the training before, and the host waits for that.
         hipStream_t const beside = count > 1u << 18 ? ctx->copy : ctx->compute;
         if (beside != ctx->compute) GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
+        PinnedInUse in_use{ctx};
         Pieces pieces(ctx, count + kPiecePairs);
         auto score = [&](const uint32_t *host_first, const uint32_t *host_second, uint64_t pairs, float *to, hipStream_t on) {
             return pieces.take(pairs, on, [&](uint64_t first, uint64_t here, int slot) -> int {
@@ -1786,6 +1803,7 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
                                             ctx->compute));
         }
         rc = sync_all(ctx);  // also reports ids >= n, and what training before had to report
+        in_use.ended = rc != GV_EHIP;
         if (rc) return rc;
         if (few) return rank_on_host(r.scores);
         unsigned long long twice = 0, not_finite = 0;

@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <map>
+#include <set>
 #include <new>
 #include <vector>
 
@@ -31,6 +32,8 @@ namespace {
 long host_allocations_left = -1;    // this many more, then one fails; negative: no limit
 long device_allocations_left = -1;  // the same of hipMalloc
 uint64_t device_allocations = 0, device_frees = 0;
+long launches_left = -1;            // of kernels that use pinned memory, the same
+std::set<hipStream_t> using_pinned; // streams with such kernels that nothing has waited for
 size_t device_largest = SIZE_MAX;   // bytes that a hipMalloc may ask for
 size_t device_free = SIZE_MAX;      // bytes that hipMemGetInfo says are left
 }  // namespace
@@ -92,13 +95,18 @@ hipError_t hipMemset(void *p, int value, size_t size) {
     return hipSuccess;
 }
 hipError_t hipMemsetAsync(void *p, int value, size_t size, hipStream_t) { return hipMemset(p, value, size); }
-static int handle;  // streams and events: everything is done in the order of the calls
+static int handle;  // events: everything is done in the order of the calls
+static char stream_names[1024];
+static int streams = 0;
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
-    *s = (hipStream_t)&handle;
+    *s = (hipStream_t)&stream_names[streams++ % 1024];
     return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    using_pinned.erase(s);
+    return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t *e) {
     *e = (hipEvent_t)&handle;
@@ -193,9 +201,19 @@ hipError_t launch_train_levels_tracked(const TrainArgs &a, uint32_t dim, uint32_
     return launch_train_levels(a, dim, num_neg, s);
 }
 static_assert(sizeof(TrainArgs) == 176, "carried by every launch of asynchronous training: arguments of one kernel go into a struct of their own");
+bool launches(hipStream_t stream) {
+    if (launches_left == 0) {
+        launches_left = -1;
+        return false;
+    }
+    if (launches_left > 0) --launches_left;
+    using_pinned.insert(stream);
+    return true;
+}
 uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg) { return 6ull * count * (num_neg + 2); }
 hipError_t launch_flow_check(const TrainArgs &pool, uint64_t count, uint32_t num_neg, FlowState *state, bool fresh, uint32_t *named,
-                             hipStream_t) {
+                             hipStream_t stream) {
+    if (!launches(stream)) return hipErrorUnknown;
     const uint32_t *const pairs = pool.pairs, n = pool.n;
     for (uint32_t t = 0; t < flow_looked_at(count); ++t) {
         const uint64_t i = flow_look(t, count);
@@ -210,7 +228,8 @@ hipError_t launch_flow_check(const TrainArgs &pool, uint64_t count, uint32_t num
         if (pairs[2 * i] >= n || pairs[2 * i + 1] >= n) state->first_bad = (uint32_t)i;
     return hipGetLastError();
 }
-hipError_t launch_flow_prepare(FlowArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t) {
+hipError_t launch_flow_prepare(FlowArgs &a, uint32_t num_neg, uint32_t *scratch, uint64_t *turns, hipStream_t stream) {
+    if (!launches(stream)) return hipErrorUnknown;
     a.flow->batches += a.flow->deepest;
     a.flow->deepest = 0;
     memset(scratch, 0, flow_scratch_words(a.count, num_neg) * sizeof *scratch);
@@ -264,7 +283,8 @@ hipError_t launch_draw_negatives_partitioned(const uint4 *, const uint64_t *, co
     return hipGetLastError();
 }
 hipError_t launch_init_vertex(float *, uint64_t, uint32_t, uint64_t, hipStream_t) { return hipGetLastError(); }
-hipError_t launch_eval_loss(TrainArgs a, uint32_t, uint32_t, double *partial, uint32_t *blocks, hipStream_t) {
+hipError_t launch_eval_loss(TrainArgs a, uint32_t, uint32_t, double *partial, uint32_t *blocks, hipStream_t stream) {
+    if (!launches(stream)) return hipErrorUnknown;
     *blocks = 1;
     partial[0] = 0.0;
     for (uint32_t i = 0; i < a.count; ++i) {
@@ -274,7 +294,8 @@ hipError_t launch_eval_loss(TrainArgs a, uint32_t, uint32_t, double *partial, ui
     return hipGetLastError();
 }
 hipError_t launch_cosine(const float *, uint32_t n, uint32_t, const uint32_t *first, const uint32_t *second, uint32_t count,
-                         float *out, uint32_t *error_flag, hipStream_t) {
+                         float *out, uint32_t *error_flag, hipStream_t stream) {
+    if (!launches(stream)) return hipErrorUnknown;
     for (uint32_t i = 0; i < count; ++i) {
         out[i] = (float)first[i] - (float)second[i];
         if (first[i] >= n || second[i] >= n) *error_flag = 1u;
@@ -282,13 +303,15 @@ hipError_t launch_cosine(const float *, uint32_t n, uint32_t, const uint32_t *fi
     return hipGetLastError();
 }
 uint64_t rank_scratch_words(uint32_t num_neg) { return num_neg + num_neg / 2; }
-hipError_t launch_rank_sort(uint32_t *, uint32_t, uint32_t *, unsigned long long *not_finite, hipStream_t) {
+hipError_t launch_rank_sort(uint32_t *, uint32_t, uint32_t *, unsigned long long *not_finite, hipStream_t stream) {
+    if (!launches(stream)) return hipErrorUnknown;
     ranked_on_device = true;
     memset(not_finite, 0, kRankBlocks * sizeof *not_finite);
     return hipGetLastError();
 }
 hipError_t launch_rank_sum(const uint32_t *scores, uint32_t num_pos, uint32_t num_neg, unsigned long long *twice, unsigned long long *,
-                           hipStream_t) {
+                           hipStream_t stream) {
+    if (!launches(stream)) return hipErrorUnknown;
     memset(twice, 0, kRankBlocks * sizeof *twice);
     const float *positive = (const float *)scores, *negative = positive + num_pos;
     for (uint32_t i = 0; i < num_pos; ++i)
@@ -619,6 +642,44 @@ void refused_scratch() {
     }
 }
 
+// A launch that fails, wherever it stands in an evaluation or a deterministic pool, leaves no kernel behind that uses the pinned
+// memory of the context, and the next call is whole.
+void early_ends() {
+    const uint32_t n = 2000, count = 300000;
+    const std::vector<uint32_t> degrees(n, 3), pool = random_pool(n, count, 1), other = random_pool(n, 20, 2);
+    for (uint32_t mode : {GV_MODE_HOGWILD, GV_MODE_DETERMINISTIC}) {
+        gv_ctx *ctx = context(mode, 1);
+        CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+        for (uint32_t pairs : {1000u, count})
+            for (int which = 0; which < (mode == GV_MODE_DETERMINISTIC ? 3 : 2); ++which) {
+                double got = -1.0, whole = -1.0;
+                auto call = [&](double *result) -> int {
+                    if (which == 0) return gv_eval_loss(ctx, pool.data(), pairs, 7, result);
+                    if (which == 1)
+                        return gv_link_prediction_auc(ctx, pool.data(), pool.data() + pairs, pairs, other.data(), other.data() + 20, 20,
+                                                      result);
+                    *result = whole;
+                    return gv_train_device_pool(ctx, pool.data(), 5000);
+                };
+                CHECK(call(&whole) == GV_OK && gv_sync(ctx) == GV_OK && using_pinned.empty());
+                int failures = 0;
+                for (long at = 0;; ++at) {
+                    launches_left = at;
+                    const int rc = call(&got);
+                    const bool done = launches_left >= 0;
+                    launches_left = -1;
+                    if (done) break;
+                    CHECK(rc == GV_EHIP && using_pinned.empty());
+                    CHECK(call(&got) == GV_OK && got == whole && gv_sync(ctx) == GV_OK);
+                    ++failures;
+                }
+                CHECK(failures >= (which == 0 && pairs == 1000 ? 1 : 2));
+                trained.clear();
+            }
+        gv_destroy(ctx);
+    }
+}
+
 // A graph of a ring with chords: every node has its two neighbours and the nodes two steps away.
 struct Ring {
     static constexpr uint32_t n = 50;
@@ -936,6 +997,7 @@ int main(int argc, char **argv) {
         {"patience of waiting", patience_of_waiting},
         {"pools that give up", pools_that_give_up},
         {"refused scratch", refused_scratch},
+        {"early ends", early_ends},
         {"pools in parts", pools_in_parts},
         {"walks after failed allocations", walks_after_failed_allocations},
         {"packed walks leave room", packed_walks_leave_room},

@@ -40,6 +40,7 @@ def driver(tmp_path_factory):
     "patience of waiting",
     "pools that give up",
     "refused scratch",
+    "early ends",
     "pools in parts",
     "walks after failed allocations",
     "packed walks leave room",
