@@ -153,7 +153,7 @@ struct gv_ctx {
     bool flow_fresh = false;              // its state is not cleared yet
     bool flow_stalled = false;            // a wave of it gave up: to be reported
     uint64_t flow_counted = 0;            // batches of the state that are
-    std::vector<uint64_t> flow_rows;      // see narrow_levels
+    std::unique_ptr<uint64_t[]> flow_rows;  // see narrow_levels
     uint32_t force_way = 0;               // see gv_test_force_way
     std::vector<uint32_t> level_vertex, level_context;  // deterministic mode: see train_deterministic
     uint32_t level_base = 0;
@@ -637,10 +637,11 @@ uint32_t levels_of(const uint32_t *named, uint32_t runs, uint32_t per_run, uint3
 bool narrow_levels(gv_ctx *ctx, const uint32_t *named, uint32_t num_neg) {
     constexpr uint32_t kSlots = 1u << 16, kFew = gv::kFlowRun / 4;
     static_assert(2 * gv::kFlowRuns * gv::kFlowRun * kMostRows < kSlots, "room");
-    ctx->flow_rows.resize(kSlots);
-    const uint64_t few = levels_of(named, gv::kFlowRuns, kFew, num_neg, ctx->flow_rows.data(), kSlots / 4);
+    if (!ctx->flow_rows) ctx->flow_rows.reset(new (std::nothrow) uint64_t[kSlots]);
+    if (!ctx->flow_rows) return false;  // the results are the same either way
+    const uint64_t few = levels_of(named, gv::kFlowRuns, kFew, num_neg, ctx->flow_rows.get(), kSlots / 4);
     if (few * kFlowWidth * 3u <= gv::kFlowRuns * kFew * 2u) return false;
-    const uint64_t all = levels_of(named, gv::kFlowRuns, gv::kFlowRun, num_neg, ctx->flow_rows.data(), kSlots);
+    const uint64_t all = levels_of(named, gv::kFlowRuns, gv::kFlowRun, num_neg, ctx->flow_rows.get(), kSlots);
     return all * kFlowWidth > gv::kFlowRuns * gv::kFlowRun;
 }
 

@@ -559,6 +559,16 @@ void narrow_pools() {
         }
     }
     gv_destroy(ctx);
+    // without host memory for the look they wait on the device
+    ctx = context(GV_MODE_DETERMINISTIC, K);
+    CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
+    flowed = 0;
+    host_allocations_left = 0;
+    CHECK(gv_train_device_pool(ctx, walks.data(), count) == GV_OK && flowed == count && host_allocations_left == -1);
+    trained.clear();
+    CHECK(gv_train_device_pool(ctx, walks.data(), count) == GV_OK && flowed == count);
+    check_levels(walks, count, n, K);
+    gv_destroy(ctx);
 }
 
 // A pool that was not trained to its end is reported once, by the next call that synchronises, not by gv_get_stats; it hides
