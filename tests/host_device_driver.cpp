@@ -207,7 +207,10 @@ bool launches(hipStream_t stream) {
         return false;
     }
     if (launches_left > 0) --launches_left;
+    const long left = host_allocations_left;
+    host_allocations_left = -1;
     using_pinned.insert(stream);
+    host_allocations_left = left;
     return true;
 }
 uint64_t flow_scratch_words(uint32_t count, uint32_t num_neg) { return 6ull * count * (num_neg + 2); }
