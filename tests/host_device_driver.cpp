@@ -50,6 +50,13 @@ void *operator new(size_t size) {
 }
 void *operator new[](size_t size) { return operator new(size); }
 void *operator new(size_t size, const std::nothrow_t &) noexcept { return malloc(size); }
+void *operator new[](size_t size, const std::nothrow_t &) noexcept {
+    try {
+        return operator new(size);
+    } catch (const std::bad_alloc &) {
+        return nullptr;
+    }
+}
 void operator delete(void *p) noexcept { free(p); }
 void operator delete(void *p, size_t) noexcept { free(p); }
 void operator delete[](void *p) noexcept { free(p); }
@@ -562,13 +569,13 @@ void narrow_pools() {
         }
     }
     gv_destroy(ctx);
-    // without host memory for the look they wait on the device
+    // without host memory for the look at the first pool, that one waits on the device
     ctx = context(GV_MODE_DETERMINISTIC, K);
     CHECK(gv_set_degrees(ctx, n, degrees.data()) == GV_OK && gv_build_alias(ctx, 0.75) == GV_OK);
     flowed = 0;
     host_allocations_left = 0;
     CHECK(gv_train_device_pool(ctx, walks.data(), count) == GV_OK && flowed == count && host_allocations_left == -1);
-    trained.clear();
+    check_levels(walks, 0, n, K);
     CHECK(gv_train_device_pool(ctx, walks.data(), count) == GV_OK && flowed == count);
     check_levels(walks, count, n, K);
     gv_destroy(ctx);
