@@ -60,7 +60,10 @@ constexpr uint32_t kFlowWidth = 16, kMostRows = 5 + 2;  // of a sample: num_neg 
 // next piece is copied there: the host copies 77 GB/s and the kernels read 50, where a copy to the device from the caller's
 // pageable arrays takes 78 us for 2 MB and 131 for 4 (25 to 58 for 64 KB to 128 KB), before the first kernel starts.  Evaluation
 // loss of 2^18 samples 152 -> 130 us, of 10^4 62 -> 29, link prediction of 500000 pairs 288 -> 284, of 10^4 124 -> 78, of
-// two 36 -> 25.  A piece has enough pairs to fill the chip; the fifth waits for the first.  (Copies of the pieces on the copy
+// two 36 -> 25.  A piece has enough pairs to fill the chip; the fifth waits for the first.  The loss of more than 3*2^17
+// samples takes pieces of 2^18, two of which fit: 2^20 samples, copied to the device / in pieces of 2^17 / of 2^18, us, d = 32, K = 1
+// 365 / 420 / 338, d = 128, K = 1 491 / 466 / 428, d = 512, K = 5 2357 / 2330 / 2273; 300000 of them 186 / 161 / 178 at d = 128,
+// for nothing runs beside the copy of the first piece.  (Copies of the pieces on the copy
 // stream, waited for by the host, 180 us for 2^18 samples; workgroups of the kernel that copy for the others, 142 to 159.)
 constexpr uint64_t kPiecePairs = 1u << 17;
 constexpr int kPieces = 4;
@@ -72,7 +75,7 @@ struct HostResults {
     uint32_t stage[kStageWords];                                  // deterministic mode
     gv::FlowState flow;                                           // deterministic mode, see train_flow
     double loss_slots[gv::kLossSlots];
-    uint32_t piece[kPieces][2 * kPiecePairs];                     // gv_eval_loss, gv_link_prediction_auc: see kPiecePairs
+    uint32_t pieces[kPieces * 2 * kPiecePairs];                   // gv_eval_loss, gv_link_prediction_auc: see kPiecePairs
     union {                                                       // written by the kernels
         double partial[kPieces][gv::kEvalBlocks];                 // gv_eval_loss
         unsigned long long sums[2 * gv::kRankBlocks];             // gv_link_prediction_auc
@@ -653,8 +656,8 @@ int train_flow(gv_ctx *ctx, const uint32_t *dev_pairs, uint64_t count, bool *nar
     const uint64_t part = std::min(count, kDeterministicPart);
     int rc = GV_OK;
     PinnedInUse in_use{ctx};
-    uint32_t *const named = ctx->results->piece[0];  // no evaluation runs meanwhile
-    static_assert(sizeof ctx->results->piece >= gv::kFlowRuns * gv::kFlowRun * kMostRows * sizeof(uint32_t), "room");
+    uint32_t *const named = ctx->results->pieces;  // no evaluation runs meanwhile
+    static_assert(sizeof ctx->results->pieces >= gv::kFlowRuns * gv::kFlowRun * kMostRows * sizeof(uint32_t), "room");
     GV_HIP(ctx, gv::launch_flow_check(train_args(ctx, dev_pairs, ctx->next_g, 0), count, K, ctx->flow_state, ctx->flow_fresh, named,
                                       ctx->compute));
     ctx->flow_fresh = false;
@@ -875,18 +878,21 @@ int pick_free_slot(gv_ctx *ctx, int *index) {
 // again.
 struct Pieces {
     gv_ctx *ctx;
-    const bool again;  // some piece's memory is used twice
+    const uint64_t size;   // pairs of a piece
+    const uint64_t slots;
+    const bool again;      // some piece's memory is used twice
     uint64_t number = 0;
-    Pieces(gv_ctx *c, uint64_t count) : ctx(c), again(count > (kPieces - 1) * kPiecePairs) {}
-    // body(first, pairs, slot) for every piece of `count` pairs, in order: it may write ctx->results->piece[slot] and launches
-    // what reads it on `stream`
+    Pieces(gv_ctx *c, uint64_t count, uint64_t size_)
+        : ctx(c), size(size_), slots(kPieces * kPiecePairs / size_), again(count > (slots - 1) * size_) {}
+    // body(first, pairs, slot, memory) for every piece of `count` pairs, in order: it may write `memory` and launches what
+    // reads it on `stream`
     template <class Body>
     int take(uint64_t count, hipStream_t stream, Body &&body) {
-        for (uint64_t first = 0; first < count; first += kPiecePairs, ++number) {
-            const int slot = (int)(number % kPieces);
+        for (uint64_t first = 0; first < count; first += size, ++number) {
+            const int slot = (int)(number % slots);
             if (again && !ctx->piece_read[slot]) GV_HIP(ctx, hipEventCreateWithFlags(&ctx->piece_read[slot], hipEventDisableTiming));
-            if (number >= kPieces) GV_HIP(ctx, hipEventSynchronize(ctx->piece_read[slot]));
-            int rc = body(first, std::min(kPiecePairs, count - first), slot);
+            if (number >= slots) GV_HIP(ctx, hipEventSynchronize(ctx->piece_read[slot]));
+            int rc = body(first, std::min(size, count - first), slot, ctx->results->pieces + slot * 2 * size);
             if (rc) return rc;
             if (again) GV_HIP(ctx, hipEventRecord(ctx->piece_read[slot], stream));
         }
@@ -1672,11 +1678,11 @@ int gv_eval_loss(gv_ctx *ctx, const uint32_t *host_pairs, uint64_t count, uint64
             blocks[slot] = 0;
         };
         PinnedInUse in_use{ctx};
-        Pieces pieces(ctx, count);
-        int rc = pieces.take(count, ctx->compute, [&](uint64_t first, uint64_t here, int slot) -> int {
+        Pieces pieces(ctx, count, count > 3 * kPiecePairs ? 2 * kPiecePairs : kPiecePairs);
+        int rc = pieces.take(count, ctx->compute, [&](uint64_t first, uint64_t here, int slot, uint32_t *pairs) -> int {
             take_in(slot);
-            memcpy(r.piece[slot], host_pairs + 2 * first, here * 2 * sizeof(uint32_t));
-            gv::TrainArgs a = train_args(ctx, r.piece[slot], first, (uint32_t)here);
+            memcpy(pairs, host_pairs + 2 * first, here * 2 * sizeof(uint32_t));
+            gv::TrainArgs a = train_args(ctx, pairs, first, (uint32_t)here);
             a.seed = eval_seed;
             a.error_flag = ctx->error_flag + 2;
             GV_HIP(ctx, gv::launch_eval_loss(a, ctx->cfg.dim, ctx->cfg.num_neg, r.partial[slot], &blocks[slot], ctx->compute));
@@ -1780,10 +1786,10 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
         hipStream_t const beside = count > 1u << 18 ? ctx->copy : ctx->compute;
         if (beside != ctx->compute) GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
         PinnedInUse in_use{ctx};
-        Pieces pieces(ctx, count + kPiecePairs);
+        Pieces pieces(ctx, count + kPiecePairs, kPiecePairs);
         auto score = [&](const uint32_t *host_first, const uint32_t *host_second, uint64_t pairs, float *to, hipStream_t on) {
-            return pieces.take(pairs, on, [&](uint64_t first, uint64_t here, int slot) -> int {
-                uint32_t *const firsts = r.piece[slot], *const seconds = firsts + here;
+            return pieces.take(pairs, on, [&](uint64_t first, uint64_t here, int, uint32_t *firsts) -> int {
+                uint32_t *const seconds = firsts + here;
                 memcpy(firsts, host_first + first, here * sizeof(uint32_t));
                 memcpy(seconds, host_second + first, here * sizeof(uint32_t));
                 GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, firsts, seconds, (uint32_t)here, to + first,

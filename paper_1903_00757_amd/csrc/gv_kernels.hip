@@ -2209,11 +2209,13 @@ hipError_t launch_eval_vk(const TrainArgs &a, double *partial, hipStream_t strea
 }
 
 hipError_t launch_eval_loss(TrainArgs a, uint32_t dim, uint32_t num_neg, double *partial, uint32_t *blocks, hipStream_t stream) {
-    // chunks of 64 samples, or of fewer (down to 4) as long as that brings more of 2048 waves to work: the pairs may lie in
-    // host memory, where reads of 64 bytes are slow
+    // Chunks of 64 samples, or of fewer (down to 4) as long as that brings more waves to work: 2048, for the pairs lie in host
+    // memory, where reads of 64 bytes are slow (50000 samples, d = 128, K = 5: 65 us, with 8192 waves 73), and 8192 of the
+    // larger pieces, which read 256 bytes a wave then (2^20 samples in pieces of 2^18: 428 us, with 2048 waves 471).
     auto chunks = [&](uint32_t unit) { return (uint32_t)(((uint64_t)a.count + unit - 1) / unit); };
+    const uint32_t waves = a.count > 1u << 17 ? 8192u : 2048u;
     a.unit = kWave;
-    while (a.unit > 4u && chunks(a.unit) < 2048u) a.unit /= 2u;
+    while (a.unit > 4u && chunks(a.unit) < waves) a.unit /= 2u;
     a.blocks = *blocks = std::min((chunks(a.unit) + kBlock / kWave - 1u) / (kBlock / kWave), kEvalBlocks);
 #define GV_CALL(V, K) launch_eval_vk<V, K>(a, partial, stream)
     GV_DISPATCH(GV_CALL)

@@ -1304,10 +1304,12 @@ def test_link_prediction_of_many_pieces(gv, edges, others, d):
             assert gv.gv_link_prediction_auc(ctx, *ends) == expected
 
 
-@pytest.mark.parametrize("count", [1, 3, 4, 5, 63, 65, 8192 * 4 - 1, 8192 * 4 + 1, 8192 * 64 + 65])
-@pytest.mark.parametrize("d,K", [(128, 1), (96, 3), (512, 5)])  # rows of 4, 2 and 1 samples gathered together
+@pytest.mark.parametrize("count", [1, 3, 4, 5, 63, 65, 8192 * 4 - 1, 8192 * 4 + 1, 1 << 18, 3 << 17, (3 << 17) + 1,
+                                   8192 * 64 + 65, 3 * (1 << 18) + 9000])
+@pytest.mark.parametrize("d,K", [(128, 1), (32, 2), (96, 3), (512, 5)])  # rows of 4, 2 and 1 samples gathered together
 def test_evaluation_loss_of_every_chunk_size(gv, tiny_graph, tiny_alias, count, d, K):
-    """Remainders of a chunk and of a batch, and chunks of 4 to 64 samples, against the oracle."""
+    """Remainders of a chunk and of a batch, chunks of 4 to 64 samples, and pieces of 2^17 and 2^18 samples, more of them than are
+    in pinned memory at a time, against the oracle."""
     g, w, seed = tiny_graph, 5.0 / K, 77
     rng = np.random.default_rng(count)
     pairs = rng.integers(g["n"], size=(count, 2)).astype(np.uint32)
