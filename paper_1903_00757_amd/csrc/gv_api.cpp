@@ -1708,8 +1708,8 @@ static int cosine_scores(gv_ctx *ctx, const uint32_t *host_first, const uint32_t
     float *dev_out = (float *)(dev_ids + 2 * count);
     GV_HIP(ctx, hipMemcpyAsync(dev_ids, host_first, count * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
     GV_HIP(ctx, hipMemcpyAsync(dev_ids + count, host_second, count * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->compute));
-    GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, dev_ids, dev_ids + count, (uint32_t)count, dev_out,
-                                  ctx->error_flag + 2, ctx->compute));
+    GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, dev_ids, dev_ids + count, (uint32_t)count,
+                                  gv::kWavesOnDevicePairs, dev_out, ctx->error_flag + 2, ctx->compute));
     GV_HIP(ctx, hipMemcpyAsync(host_out, dev_out, count * sizeof(float), hipMemcpyDeviceToHost, ctx->compute));
     GV_HIP(ctx, hipStreamSynchronize(ctx->compute));
     return GV_OK;
@@ -1792,8 +1792,8 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
                 uint32_t *const seconds = firsts + here;
                 memcpy(firsts, host_first + first, here * sizeof(uint32_t));
                 memcpy(seconds, host_second + first, here * sizeof(uint32_t));
-                GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, firsts, seconds, (uint32_t)here, to + first,
-                                              ctx->error_flag + 2, on));
+                GV_HIP(ctx, gv::launch_cosine(ctx->vertex, ctx->n, ctx->cfg.dim, firsts, seconds, (uint32_t)here,
+                                              gv::kWavesOnHostPairs, to + first, ctx->error_flag + 2, on));
                 return GV_OK;
             });
         };

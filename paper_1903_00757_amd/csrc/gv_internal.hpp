@@ -182,8 +182,10 @@ hipError_t launch_init_vertex(float *vertex, uint64_t rows, uint32_t dim, uint64
 // kEvalBlocks).
 constexpr uint32_t kEvalBlocks = 2048;
 hipError_t launch_eval_loss(TrainArgs a, uint32_t dim, uint32_t num_neg, double *partial, uint32_t *blocks, hipStream_t stream);
+// waves: that come to work where there are pairs enough.
+constexpr uint32_t kWavesOnHostPairs = 2048, kWavesOnDevicePairs = 8192;
 hipError_t launch_cosine(const float *vertex, uint32_t n, uint32_t dim, const uint32_t *first, const uint32_t *second,
-                         uint32_t count, float *out, uint32_t *error_flag, hipStream_t stream);
+                         uint32_t count, uint32_t waves, float *out, uint32_t *error_flag, hipStream_t stream);
 
 // The sum of twice[0 .. kRankBlocks) is 2 (pairs of a positive above a negative) + (pairs of equal score) of scores[0 ..
 // num_pos) against the num_neg scores behind them, num_pos + num_neg <= 2^31; not_finite[0 .. kRankBlocks) holds a nonzero where

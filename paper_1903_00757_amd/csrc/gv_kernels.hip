@@ -2213,7 +2213,7 @@ hipError_t launch_eval_loss(TrainArgs a, uint32_t dim, uint32_t num_neg, double 
     // memory, where reads of 64 bytes are slow (50000 samples, d = 128, K = 5: 65 us, with 8192 waves 73), and 8192 of the
     // larger pieces, which read 256 bytes a wave then (2^20 samples in pieces of 2^18: 428 us, with 2048 waves 471).
     auto chunks = [&](uint32_t unit) { return (uint32_t)(((uint64_t)a.count + unit - 1) / unit); };
-    const uint32_t waves = a.count > 1u << 17 ? 8192u : 2048u;
+    const uint32_t waves = a.count > 1u << 17 ? 8192u : kWavesOnHostPairs;
     a.unit = kWave;
     while (a.unit > 4u && chunks(a.unit) < waves) a.unit /= 2u;
     a.blocks = *blocks = std::min((chunks(a.unit) + kBlock / kWave - 1u) / (kBlock / kWave), kEvalBlocks);
@@ -2233,12 +2233,13 @@ void launch_cosine_v(const float *vertex, uint32_t n, uint32_t dim, const uint32
                            error_flag);
 }
 hipError_t launch_cosine(const float *vertex, uint32_t n, uint32_t dim, const uint32_t *first, const uint32_t *second,
-                         uint32_t count, float *out, uint32_t *error_flag, hipStream_t stream) {
+                         uint32_t count, uint32_t waves, float *out, uint32_t *error_flag, hipStream_t stream) {
     if (count == 0) return hipSuccess;
-    // as in launch_eval_loss
+    // as in launch_eval_loss; pairs on the device are read as well in short pieces (gv_cosine of 3*10^5 pairs, d = 512: 400 us
+    // with 8192 waves, 411 with 2048)
     auto chunks = [&](uint32_t unit) { return (uint32_t)(((uint64_t)count + unit - 1) / unit); };
     uint32_t unit = kWave;
-    while (unit > 4u && chunks(unit) < 2048u) unit /= 2u;
+    while (unit > 4u && chunks(unit) < waves) unit /= 2u;
     const uint32_t blocks = std::min((chunks(unit) + kBlock / kWave - 1u) / (kBlock / kWave), 4096u);
     if (dim <= 64)
         launch_cosine_v<1>(vertex, n, dim, first, second, count, unit, blocks, out, error_flag, stream);

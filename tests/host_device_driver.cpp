@@ -303,7 +303,7 @@ hipError_t launch_eval_loss(TrainArgs a, uint32_t, uint32_t, double *partial, ui
     }
     return hipGetLastError();
 }
-hipError_t launch_cosine(const float *, uint32_t n, uint32_t, const uint32_t *first, const uint32_t *second, uint32_t count,
+hipError_t launch_cosine(const float *, uint32_t n, uint32_t, const uint32_t *first, const uint32_t *second, uint32_t count, uint32_t,
                          float *out, uint32_t *error_flag, hipStream_t stream) {
     if (!launches(stream)) return hipErrorUnknown;
     for (uint32_t i = 0; i < count; ++i) {
