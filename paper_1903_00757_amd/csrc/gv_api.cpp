@@ -36,15 +36,16 @@ struct PoolSlot {
     SlotState state = kFree;
 };
 
-// Pairs that gv_link_prediction_auc ranks on the host: a sort of a few thousand there is over before the fourteen launches
-// of the device's sort are (a call of one pair against one: 103 us with the sort on the device, 37 on the host; 1000 against 1000:
-// 101 and 48).
+// Pairs that gv_link_prediction_auc ranks on the host: a sort of one or two thousand there is over before the launches of the
+// device's sort are (a call of one pair against one 26 us, of 1000 against 1000 40, with the sort on the device 80; of 2048 against
+// 2048 the host takes 155).
 constexpr uint64_t kHostRanked = 4096;
 constexpr uint64_t kStageWords = 16384, kDeterministicPart = 1u << 20;  // see train_deterministic
 // Deterministic pools of more samples than this wait for each other on the device (train_flow) instead of being sorted into
-// levels on the host: 5000 samples on 200000 nodes 66 instead of 185 us, on 5000 nodes without hubs 60 instead of 180, and
-// fewer are levelled before the preparation's dozen launches are done.  Not where levels are narrow: a level of a few samples
-// costs 0.7 us in one workgroup, a link of a chain 1.3, and 1.9 from wave to wave.  That is so where the graph's hottest row is
+// levels on the host: call and gv_sync, d = 128, K = 1, 10000 samples on 200000 nodes 116 instead of 144 us, 5000 on 5000 nodes 106
+// instead of 133, 5000 on 200000 nodes 99 instead of 104, and fewer are levelled before the preparation's dozen launches are
+// done.  Not where levels are narrow: a level of a few samples costs 0.8 to 1 us in one workgroup, a link of a chain 1.3, and 1.9
+// from wave to wave.  That is so where the graph's hottest row is
 // named by more than one sample in 24 (d = 128, K = 1, a pass alone: hottest share 2.1 % 9.1 -> 4.0 ms, 3.6 % 2.29 -> 1.78,
 // 4.6 % 0.93 -> 0.95; K = 5, 7.5 % 8.0 -> 10.6; a star 7.8 -> 12.4), and in pools that put samples of a row close together
 // whatever the graph, such as walks in their own order: those are known by the levels of the samples that launch_flow_check
@@ -59,8 +60,8 @@ constexpr uint32_t kFlowWidth = 16, kMostRows = 5 + 2;  // of a sample: num_neg 
 // The pairs of gv_eval_loss and gv_link_prediction_auc are read by the kernels from pinned memory, piece by piece, while the
 // next piece is copied there: the host copies 77 GB/s and the kernels read 50, where a copy to the device from the caller's
 // pageable arrays takes 78 us for 2 MB and 131 for 4 (25 to 58 for 64 KB to 128 KB), before the first kernel starts.  Evaluation
-// loss of 2^18 samples 152 -> 130 us, of 10^4 62 -> 29, link prediction of 500000 pairs 288 -> 284, of 10^4 124 -> 78, of
-// two 36 -> 25.  A piece has enough pairs to fill the chip; the fifth waits for the first.  The loss of more than 3*2^17
+// loss of 2^18 samples 158 -> 138 us, of 10^4 34 -> 26, link prediction of two pairs 35 -> 26; of 10^4, with the shorter launches
+// of its sort, 126 -> 79.  A piece has enough pairs to fill the chip; the fifth waits for the first.  The loss of more than 3*2^17
 // samples takes pieces of 2^18, two of which fit: 2^20 samples, copied to the device / in pieces of 2^17 / of 2^18, us, d = 32, K = 1
 // 365 / 420 / 338, d = 128, K = 1 491 / 466 / 428, d = 512, K = 5 2357 / 2330 / 2273; 300000 of them 186 / 161 / 178 at d = 128,
 // for nothing runs beside the copy of the first piece.  (Copies of the pieces on the copy

@@ -1304,6 +1304,39 @@ def test_link_prediction_of_many_pieces(gv, edges, others, d):
             assert gv.gv_link_prediction_auc(ctx, *ends) == expected
 
 
+def test_link_prediction_between_pushed_pools(gv):
+    """Link prediction of so many pairs that it uses the copy stream too, while pushed pools are on that stream or wait to be
+    trained: the rank statistic of the rows as they are, and the same rows at the end, bit for bit, as without it."""
+    n, d, K, size = 3000, 64, 2, 6000
+    rng = np.random.default_rng(21)
+    deg = np.full(n, 9, dtype=np.uint32)
+    pools = [rng.integers(n, size=(size, 2)).astype(np.uint32) for _ in range(6)]
+    ends = [rng.integers(n, size=k).astype(np.uint32) for k in (200_000, 200_000, 90_000, 90_000)]
+    vertex, context = random_embeddings(n, d, seed=23)
+    rows = []
+    for evaluates in (False, True):
+        with context_for(gv, dim=d, num_neg=K, mode=gv.GV_MODE_DETERMINISTIC, total_samples=20 * size, pool_capacity=size,
+                         pool_slots=3, lr0=LR0) as ctx:
+            gv.gv_set_degrees(ctx, deg)
+            gv.gv_build_alias(ctx, 0.75)
+            gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+            gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+            for k in range(0, len(pools), 2):
+                for p in pools[k:k + 2]:
+                    gv.gv_push_pool(ctx, p)
+                for _ in range(2):
+                    got = gv.gv_link_prediction_auc(ctx, *ends) if evaluates else None
+                    gv.gv_train_pool(ctx)
+                    if evaluates:
+                        assert got != gv.gv_link_prediction_auc(ctx, *ends)
+                if evaluates:
+                    expected = gv.gv_auc(gv.gv_cosine(ctx, *ends[:2]), gv.gv_cosine(ctx, *ends[2:]))
+                    assert gv.gv_link_prediction_auc(ctx, *ends) == expected
+            rows.append([gv.gv_read_embeddings(ctx, which, n, d).view(np.uint32) for which in (gv.GV_VERTEX, gv.GV_CONTEXT)])
+    for one, two in zip(*rows):
+        assert np.array_equal(one, two)
+
+
 @pytest.mark.parametrize("count", [1, 3, 4, 5, 63, 65, 8192 * 4 - 1, 8192 * 4 + 1, 1 << 18, 3 << 17, (3 << 17) + 1,
                                    8192 * 64 + 65, 3 * (1 << 18) + 9000])
 @pytest.mark.parametrize("d,K", [(128, 1), (32, 2), (96, 3), (512, 5)])  # rows of 4, 2 and 1 samples gathered together
