@@ -606,16 +606,16 @@ int ensure_flow(gv_ctx *ctx, uint64_t count) {
     return GV_OK;
 }
 
-// The levels (see train_deterministic) of the first `per_run` samples of each of `runs` runs, one run after the other;
-// named[runs][kFlowRun][num_neg + 2].  The rows met so far stand in a table of `slots` entries, row + 1 << 32 | level, a
-// power of two and more than twice their number.
-uint32_t levels_of(const uint32_t *named, uint32_t runs, uint32_t per_run, uint32_t num_neg, uint64_t *table, uint32_t slots) {
+// The levels (see train_deterministic) of the first `per_run` samples of every run, one run after the other, counted as far as
+// `enough`; named[kFlowRuns][kFlowRun][num_neg + 2].  The rows met so far stand in a table of `slots` entries, row + 1 << 32 |
+// level, a power of two and, with fewer rows, twice their number.
+uint32_t levels_of(const uint32_t *named, uint32_t per_run, uint32_t num_neg, uint32_t enough, uint64_t *table, uint32_t slots) {
     const uint32_t rows = num_neg + 2;
     const int shift = 32 - __builtin_ctz(slots);
     memset(table, 0, slots * sizeof *table);
     uint32_t deepest = 0;
-    for (uint32_t r = 0; r < runs; ++r) {
-        for (uint32_t i = 0; i < per_run; ++i) {
+    for (uint32_t r = 0; r < gv::kFlowRuns; ++r) {
+        for (uint32_t i = 0; i < per_run && deepest < enough; ++i) {
             const uint32_t *const row = named + ((size_t)r * gv::kFlowRun + i) * rows;
             uint64_t *entry[kMostRows];
             uint32_t level = 0;
@@ -635,18 +635,25 @@ uint32_t levels_of(const uint32_t *named, uint32_t runs, uint32_t per_run, uint3
     return deepest;
 }
 
-// Whether the samples that launch_flow_check looked at have levels of fewer than kFlowWidth samples on average.  Most pools
-// are seen to have half as many again by a quarter of those samples (10 us of the host at K = 1, while the device prepares the
-// pool; all of them take 100, and 200 at K = 5).
+// Whether the samples that launch_flow_check looked at have levels of fewer than kFlowWidth samples on average.  For most pools
+// an eighth of those samples tells, the heads of the runs (5 us of the host at K = 1, 25 at K = 5, while the device prepares the
+// pool; all of them take 100 and 200).  Of walks in their own order, where a sample often names the vertex of the one before,
+// the heads have to do half as well again: (i, j) comes after (i, j - 1) and (i - 1, j), and such chains are longer than a head.
 bool narrow_levels(gv_ctx *ctx, const uint32_t *named, uint32_t num_neg) {
-    constexpr uint32_t kSlots = 1u << 16, kFew = gv::kFlowRun / 4;
+    constexpr uint32_t kSlots = 1u << 16, kFew = gv::kFlowRun / 8;
     static_assert(2 * gv::kFlowRuns * gv::kFlowRun * kMostRows < kSlots, "room");
     if (!ctx->flow_rows) ctx->flow_rows.reset(new (std::nothrow) uint64_t[kSlots]);
     if (!ctx->flow_rows) return false;  // the results are the same either way
-    const uint64_t few = levels_of(named, gv::kFlowRuns, kFew, num_neg, ctx->flow_rows.get(), kSlots / 4);
-    if (few * kFlowWidth * 3u <= gv::kFlowRuns * kFew * 2u) return false;
-    const uint64_t all = levels_of(named, gv::kFlowRuns, gv::kFlowRun, num_neg, ctx->flow_rows.get(), kSlots);
-    return all * kFlowWidth > gv::kFlowRuns * gv::kFlowRun;
+    uint32_t same = 0;  // samples of the heads that name the vertex of the sample before
+    for (uint32_t r = 0; r < gv::kFlowRuns; ++r)
+        for (uint32_t i = 1; i < kFew; ++i) {
+            const uint32_t *const row = named + ((size_t)r * gv::kFlowRun + i) * (num_neg + 2);
+            same += row[0] == *(row - (num_neg + 2));
+        }
+    const uint32_t wide = gv::kFlowRuns * kFew / kFlowWidth, few_levels = (same * 4 > gv::kFlowRuns * kFew ? wide * 2 / 3 : wide) + 1;
+    if (levels_of(named, kFew, num_neg, few_levels, ctx->flow_rows.get(), kSlots / 8) < few_levels) return false;
+    constexpr uint32_t kLevels = gv::kFlowRuns * gv::kFlowRun / kFlowWidth + 1;
+    return levels_of(named, gv::kFlowRun, num_neg, kLevels, ctx->flow_rows.get(), kSlots) == kLevels;
 }
 
 // Deterministic training of a pool that is not short: every sample waits on the device for the earlier samples that name
