@@ -98,6 +98,25 @@ __device__ __forceinline__ float wave_sum(float x) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
+// Several of them, step by step together.
+template <int kN>
+__device__ __forceinline__ void wave_sums(float (&x)[kN]) {
+#pragma unroll
+    for (int n = 0; n < kN; ++n) x[n] += dpp_take<0xB1, 0xF>(x[n]);
+#pragma unroll
+    for (int n = 0; n < kN; ++n) x[n] += dpp_take<0x4E, 0xF>(x[n]);
+#pragma unroll
+    for (int n = 0; n < kN; ++n) x[n] += dpp_take<0x141, 0xF>(x[n]);
+#pragma unroll
+    for (int n = 0; n < kN; ++n) x[n] += dpp_take<0x140, 0xF>(x[n]);
+#pragma unroll
+    for (int n = 0; n < kN; ++n) x[n] += dpp_take<0x142, 0xA>(x[n]);
+#pragma unroll
+    for (int n = 0; n < kN; ++n) x[n] += dpp_take<0x143, 0xC>(x[n]);
+#pragma unroll
+    for (int n = 0; n < kN; ++n) x[n] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[n]), 63));
+}
+
 __device__ __forceinline__ uint32_t lane_value(uint32_t x, uint32_t lane) {
     return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)lane);
 }
@@ -989,10 +1008,12 @@ struct HandedRow {
 // What bounds it is the chain of samples that share the hottest rows, each link the latency of one wave.  A row goes from
 // one wave to another in 1.0 us (store, wait, turn, poll, load; the same within a die and across dies), with the
 // arithmetic and the polling 1.9 us a sample.  So each of the kFlowHubs rows named most has a wave of its own, which trains
-// the samples that name it one after the other with the row in registers: 1.3 us a sample, bound by the instructions of that
-// wave and the loads of the other rows (flow_hub).  2*10^5 samples on 10^4 nodes, 1190 levels, d = 128, K = 1: 4.1 ms as
-// launches of levels, 2.0 without chains, 1.67 now (three contexts in turn: 3.4, 0.87, 0.69 ms a pool); 1.5*10^5 on 10^5 nodes
-// with hubs, 3200 levels: 9.1, 5.1, 3.95.  1024 waves of 8 samples: 16 or more samples a wave wait for each other in the wave,
+// the samples that name it one after the other with the row in registers: 0.75 us a sample, most of it the loads of the next
+// sample's other rows, which the arithmetic hides in part (flow_hub; 1.07 us with loops for every kind of sample instead of
+// one for the plain ones).  What is left is the way from wave to wave.  2*10^5 samples on 10^4 nodes, 1190 levels, d = 128, K = 1:
+// 4.1 ms as launches of levels, 2.0 without chains, 1.58 now (three contexts in turn: 3.4, 0.87, 0.65 ms a pool);
+// 1.5*10^5 on 10^5 nodes, exponent 2.5: 1.14 ms with the slower chains, 0.88 now; 5*10^4 on 3*10^4, exponent 2.3, d = 96, K = 3:
+// 1.86 and 1.64.  1024 waves of 8 samples: 16 or more samples a wave wait for each other in the wave,
 // and twice as many waves only poll more (3.4 ms with 1024 waves of 64, 6.2 with 2048, before samples far from their turn were
 // left alone).
 //
@@ -1055,6 +1076,40 @@ __device__ __forceinline__ void memory_is_done() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0x0F70);
     asm volatile("" ::: "memory");
+}
+
+// The same (bit for bit) of a sample whose rows are all different, the sums of its scores side by side.
+template <int kV, int kK, bool kTrack>
+__device__ __forceinline__ void sgns_plain(float (&x)[kV], float (&c)[kK + 1][kV], float lr, float w, int lane,
+                                           ChunkScores<kK> &scores, uint32_t i) {
+    float part[kK + 1];
+#pragma unroll
+    for (int k = 0; k <= kK; ++k) {
+        part[k] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kV; ++j) part[k] = fmaf(x[j], c[k][j], part[k]);
+    }
+    wave_sums<kK + 1>(part);
+    float score = 0.0f;
+#pragma unroll
+    for (int k = 0; k <= kK; ++k) {
+        score = lane == k ? part[k] : score;
+        if constexpr (kTrack) scores.put(k, i, part[k]);
+    }
+    const float s = sigmoid(score), each = lane == 0 ? lr * (1.0f - s) : -(lr * w) * s;
+    float coef[kK + 1];
+#pragma unroll
+    for (int k = 0; k <= kK; ++k) coef[k] = __uint_as_float(lane_value(__float_as_uint(each), k));
+#pragma unroll
+    for (int j = 0; j < kV; ++j) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int k = 0; k <= kK; ++k) {
+            acc = fmaf(coef[k], c[k][j], acc);
+            c[k][j] = fmaf(k < kK ? coef[k] + 0.0f : coef[k], x[j], c[k][j]);  // (total_coefficient adds nothing to it)
+        }
+        x[j] += acc;
+    }
 }
 
 // What lane l knows of the sample that it looks after.
@@ -1153,11 +1208,14 @@ struct FlowRows {
 
 // The chain of hub h: its samples, except those that name a hub before it (the row is handed to the wave of that hub and
 // awaited back).  The row stays in registers y; the other rows of the next sample are on their way while one is computed,
-// and its stores are waited for after the next one's arithmetic.  false: gave up.
+// and its stores are waited for after the next one's arithmetic.  What a link takes are the instructions of one wave (one every
+// five cycles or so, a branch more), so the samples that name the hub once and their other rows once, nearly all of them, have
+// a loop without branches on the rows, with the addresses that it needs worked out by the lanes, 64 samples at once: 2420 -> 1700
+// cycles a link at d = 128, K = 1.  false: gave up.
 template <int kV, int kK, bool kFull, bool kTrack>
 __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs, uint32_t h, int lane, uint32_t &deepest,
                                          float &lane_loss) {
-    constexpr int kRows = kK + 2;
+    constexpr int kRows = kK + 2, kOthers = kK + 1;
     constexpr uint32_t kNone = 0xFFFFFFFFu, kAhead = 16;  // samples ahead whose turns are looked at
     using Io = HandedRow<kV, kFull>;
     const FlowRows matrix(a);
@@ -1165,13 +1223,9 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
     uint64_t *const nowhere = (uint64_t *)&a.flow->nowhere;
     const uint32_t hub = lane_value(hubs.key, h), begin = lane_value(hubs.begin, h), end = begin + lane_value(hubs.namings, h);
     char *const row = matrix.of(hub < a.n ? 0 : 1, hub);
-    float y[kV], ahead[kRows][kV];
+    float y[kV];
 #pragma unroll
     for (int e = 0; e < kV; ++e) y[e] = 0.0f;
-#pragma unroll
-    for (int j = 0; j < kRows; ++j)
-#pragma unroll
-        for (int e = 0; e < kV; ++e) ahead[j][e] = 0.0f;
     bool held = false;
     uint32_t level = 0, sample_before = kNone;  // of the row in registers; the sample of the naming before
     for (uint32_t base = begin; base < end; base += kWave) {
@@ -1189,43 +1243,67 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
         const uint64_t own = __ballot(inside && owner == h);
         uint64_t todo = __ballot(inside && !again), come = 0;  // samples to do; those of which all other turns have come
         const float lr = learning_rate(a.lr0, a.lr_min_ratio, a.first_g + (inside ? sample : 0u), a.total);
-        ChunkScores<kK> scores{};
-        uint32_t unhanded = kNone, loaded = kNone;  // the sample whose turns are to be passed on, the one whose rows are on their way
-        auto hand_on = [&]() {
-            if ((uint32_t)lane == unhanded) s.hand_on(nowhere, takes);
-        };
-        auto fetch = [&](uint32_t i) {
-            const uint32_t takes_i = lane_value(takes, i);
+        // Most samples name the hub once and kOthers other rows, all different: what the wave needs of those, one after the other.
+        bool differ = (takes & (takes - 1u)) == 0u;
 #pragma unroll
-            for (int j = 0; j < kRows; ++j)
-                if (!((takes_i >> j) & 1u)) Io::load(matrix.of(j, lane_value(s.key[j], i)), at, matrix.bytes, ahead[j]);
+        for (int j1 = 1; j1 < kRows; ++j1)
+#pragma unroll
+            for (int j2 = j1 + 1; j2 < kRows; ++j2) differ &= s.key[j1] != s.key[j2];
+        const uint64_t plain = own & __ballot(differ);
+        uint64_t other_at[kOthers], other_turn[kOthers];
+        uint32_t other_next[kOthers];
+#pragma unroll
+        for (int m = 0; m < kOthers; ++m) {
+            const bool behind = (takes & ((2u << m) - 1u)) != 0u;  // the hub comes first: the row is number m + 1
+            other_at[m] = (uint64_t)(behind ? matrix.of(m + 1, s.key[m + 1]) : matrix.of(m, s.key[m]));
+            other_turn[m] = (uint64_t)(behind ? s.turn[m + 1] : s.turn[m]);
+            other_next[m] = behind ? s.hands_on[m + 1] : s.hands_on[m];
+        }
+        ChunkScores<kK> scores{};
+        uint32_t unhanded = kNone;  // the sample whose turns are to be passed on once its rows are in memory
+        auto hand_on = [&]() {
+            if ((uint32_t)lane != unhanded) return;
+            if ((plain >> lane) & 1u) {
+#pragma unroll
+                for (int m = 0; m < kOthers; ++m)
+                    __hip_atomic_store((uint64_t *)other_turn[m], (uint64_t)(s.level + 1u) << 32 | other_next[m], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                s.hand_on(nowhere, takes);
+            }
+        };
+        uint64_t is[kRows];
+        auto looked = [&](bool looks) {
+            bool came = false;
+            if (looks) came = s.seen(is, takes) == 0u;
+            come |= __ballot(came);
+        };
+        auto waits = [&](uint32_t first) {
+            return (uint32_t)lane >= first && (uint32_t)lane <= first + kAhead && inside && !((come >> lane) & 1u);
         };
         while (todo) {
-            const uint32_t i = (uint32_t)__builtin_ctzll(todo);
-            todo &= todo - 1;
-            uint64_t is[kRows];
-            if (!((own & (held ? come : 0ull)) >> i & 1u)) {  // not simply the next one of the row in registers
-                memory_is_done();
-                hand_on();
-                unhanded = kNone;
-                if (!((own >> i) & 1u)) {  // another hub's: the row has to be in memory when its turn comes
-                    if (held) {
-                        Io::store(row, at, matrix.bytes, y);
-                        memory_is_done();
-                        if (lane == 0)
-                            __hip_atomic_store(a.turns + hub, (uint64_t)level << 32 | (base + i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        held = false;
-                    }
-                    continue;
+            uint32_t i = (uint32_t)__builtin_ctzll(todo);
+            memory_is_done();
+            hand_on();
+            unhanded = kNone;
+            if (!((own >> i) & 1u)) {  // another hub's: the row has to be in memory when its turn comes
+                if (held) {
+                    Io::store(row, at, matrix.bytes, y);
+                    memory_is_done();
+                    if (lane == 0)
+                        __hip_atomic_store(a.turns + hub, (uint64_t)level << 32 | (base + i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    held = false;
                 }
+                todo &= todo - 1;
+                continue;
+            }
+            if (!held || !((come >> i) & 1u)) {
                 bool here = held;
                 for (FlowPatience patience;;) {
                     const uint64_t hub_turn = __hip_atomic_load(a.turns + hub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const bool looks = (uint32_t)lane >= i && (uint32_t)lane <= i + kAhead && inside && !((come >> lane) & 1u);
+                    const bool looks = waits(i);
                     s.read(looks, is);
-                    bool came = false;
-                    if (looks) came = s.seen(is, takes) == 0u;
-                    come |= __ballot(came);
+                    looked(looks);
                     if (!here && __builtin_amdgcn_readfirstlane((uint32_t)hub_turn) == base + i) {
                         here = true;
                         level = __builtin_amdgcn_readfirstlane((uint32_t)(hub_turn >> 32));
@@ -1239,66 +1317,128 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
                 asm volatile("" ::: "memory");
                 if (!held) Io::load(row, at, matrix.bytes, y);
                 held = true;
-                if (loaded != i) fetch(i);
+            }
+            if (!((plain >> i) & 1u)) {
+                const uint32_t takes_i = lane_value(takes, i);
+                float x[kV], c[kK + 1][kV];
+                uint32_t rows[kK + 1];
+#pragma unroll
+                for (int e = 0; e < kV; ++e) x[e] = 0.0f;
+                if (!(takes_i & 1u)) Io::load(matrix.of(0, lane_value(s.key[0], i)), at, matrix.bytes, x);
+#pragma unroll
+                for (int k = 0; k <= kK; ++k) {
+                    rows[k] = lane_value(s.key[1 + k], i);
+#pragma unroll
+                    for (int e = 0; e < kV; ++e) c[k][e] = 0.0f;
+                    if (!((takes_i >> (1 + k)) & 1u)) Io::load(matrix.of(1, rows[k]), at, matrix.bytes, c[k]);
+                }
                 memory_is_done();
-            }
-            if (loaded != i && unhanded != kNone) {  // its turns came with the last look, too late to fetch ahead
-                fetch(i);
-                memory_is_done();
-                hand_on();
-                unhanded = kNone;
-            }
-            float x[kV], c[kK + 1][kV];
-            const uint32_t takes_i = lane_value(takes, i);
-            uint32_t rows[kK + 1];
 #pragma unroll
-            for (int e = 0; e < kV; ++e) x[e] = takes_i & 1u ? y[e] : ahead[0][e];
+                for (int e = 0; e < kV; ++e) x[e] = takes_i & 1u ? y[e] : x[e];
 #pragma unroll
-            for (int k = 0; k <= kK; ++k) {
-                rows[k] = lane_value(s.key[1 + k], i);
+                for (int k = 0; k <= kK; ++k)
 #pragma unroll
-                for (int e = 0; e < kV; ++e) c[k][e] = (takes_i >> (1 + k)) & 1u ? y[e] : ahead[1 + k][e];
-            }
-            // the next sample: its rows if their turns have come (then it shares none but the hub with this one); the turns
-            // of those behind it, unless it and the one after it are known to have come
-            const uint64_t after = todo & (todo - 1), next_two = (todo ^ after) | (after ^ (after & (after - 1)));
-            const bool look = (next_two & own & ~come) != 0;
-            const bool looks = look && (uint32_t)lane > i && (uint32_t)lane <= i + kAhead && inside && !((come >> lane) & 1u);
-            s.read(looks, is);
-            loaded = kNone;
-            if (todo & ~after & own & come) {
-                loaded = (uint32_t)__builtin_ctzll(todo);
-                fetch(loaded);
-            }
-            level = max(level, lane_value(s.level, i));
-            sgns_in_place<kV, kK, kTrack>(x, c, rows, __uint_as_float(lane_value(__float_as_uint(lr), i)), a.neg_weight, lane, scores, i);
-            // the rows of the sample before are in memory, and so the turns can go on
-            memory_is_done();
-            hand_on();
-            if (!(takes_i & 1u)) {
-                Io::store(matrix.of(0, lane_value(s.key[0], i)), at, matrix.bytes, x);
-            } else {
-#pragma unroll
-                for (int e = 0; e < kV; ++e) y[e] = x[e];
-            }
-#pragma unroll
-            for (int k = 0; k <= kK; ++k) {
-                if (!first_naming<kK>(rows, k)) continue;
-                if (!((takes_i >> (1 + k)) & 1u)) {
-                    Io::store(matrix.of(1, rows[k]), at, matrix.bytes, c[k]);
+                    for (int e = 0; e < kV; ++e) c[k][e] = (takes_i >> (1 + k)) & 1u ? y[e] : c[k][e];
+                sgns_in_place<kV, kK, kTrack>(x, c, rows, __uint_as_float(lane_value(__float_as_uint(lr), i)), a.neg_weight, lane, scores, i);
+                if (!(takes_i & 1u)) {
+                    Io::store(matrix.of(0, lane_value(s.key[0], i)), at, matrix.bytes, x);
                 } else {
 #pragma unroll
-                    for (int e = 0; e < kV; ++e) y[e] = c[k][e];
+                    for (int e = 0; e < kV; ++e) y[e] = x[e];
+                }
+#pragma unroll
+                for (int k = 0; k <= kK; ++k) {
+                    if (!first_naming<kK>(rows, k)) continue;
+                    if (!((takes_i >> (1 + k)) & 1u)) {
+                        Io::store(matrix.of(1, rows[k]), at, matrix.bytes, c[k]);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < kV; ++e) y[e] = c[k][e];
+                    }
+                }
+                level = max(level, lane_value(s.level, i));
+                if ((uint32_t)lane == i) s.level = level;
+                unhanded = i;
+                level += 1u;
+                todo &= todo - 1;
+                continue;
+            }
+            // The chain: from here on as long as the next sample is one of these and its turns have come (then it shares none of
+            // its other rows with this one).
+            float o[kOthers][kV];
+            char *o_at[kOthers];
+            auto fetch = [&](uint32_t sample, float (&rows)[kOthers][kV], char *(&rows_at)[kOthers]) {
+#pragma unroll
+                for (int m = 0; m < kOthers; ++m) {
+                    rows_at[m] = (char *)((uint64_t)lane_value((uint32_t)(other_at[m] >> 32), sample) << 32 | lane_value((uint32_t)other_at[m], sample));
+                    Io::load(rows_at[m], at, matrix.bytes, rows[m]);
+                }
+            };
+            fetch(i, o, o_at);
+            memory_is_done();
+            for (;;) {
+                const uint64_t rest = todo & (todo - 1), next = rest & (0 - rest), behind = rest ^ next;
+                const bool goes_on = (next & plain & come) != 0;
+                // the turns of those behind it, unless the next two are known to have come
+                const bool look = ((next | (behind & (0 - behind))) & own & ~come) != 0;
+                const bool looks = look && waits(i + 1u);
+                if (look) s.read(looks, is);
+                float ahead[kOthers][kV];
+                char *ahead_at[kOthers];
+                const uint32_t n = goes_on ? (uint32_t)__builtin_ctzll(next) : i;
+                if (goes_on) fetch(n, ahead, ahead_at);
+                level = max(level, lane_value(s.level, i));
+                const float lr_i = __uint_as_float(lane_value(__float_as_uint(lr), i));
+                // where the hub stands among the context rows; 0 and none of them where it is a vertex row
+                const uint32_t stands = lane_value(takes, i) >> 1;
+                float x[kV], c[kK + 1][kV];
+#pragma unroll
+                for (int e = 0; e < kV; ++e) {
+                    x[e] = stands == 0u ? y[e] : o[0][e];
+#pragma unroll
+                    for (int k = 0; k <= kK; ++k) {
+                        // rows before the hub are one further back among the others, for u comes first there
+                        c[k][e] = k < kK ? (stands >> (k + 1) ? o[k + 1 <= kK ? k + 1 : kK][e] : o[k][e]) : o[k][e];
+                        c[k][e] = (stands >> k) & 1u ? y[e] : c[k][e];
+                    }
+                }
+                sgns_plain<kV, kK, kTrack>(x, c, lr_i, a.neg_weight, lane, scores, i);
+                // (without this the compiler moves the wait up into the sums, and the rows of the next sample come before, not
+                // beside them: 1678 -> 1612 us the pool on 10^4 nodes that is named above k_train_flow)
+#pragma unroll
+                for (int e = 0; e < kV; ++e) {
+                    asm volatile("" : "+v"(x[e]));
+#pragma unroll
+                    for (int k = 0; k <= kK; ++k) asm volatile("" : "+v"(c[k][e]));
+                }
+                // the rows of the sample before are in memory, and so the turns can go on
+                memory_is_done();
+                hand_on();
+#pragma unroll
+                for (int e = 0; e < kV; ++e) {
+                    y[e] = x[e];
+                    o[0][e] = stands == 0u ? c[0][e] : x[e];
+#pragma unroll
+                    for (int k = 0; k <= kK; ++k) y[e] = (stands >> k) & 1u ? c[k][e] : y[e];
+#pragma unroll
+                    for (int m = 1; m <= kK; ++m) o[m][e] = stands >> m ? c[m - 1][e] : c[m][e];
+                }
+#pragma unroll
+                for (int m = 0; m < kOthers; ++m) Io::store(o_at[m], at, matrix.bytes, o[m]);
+                if (look) looked(looks);
+                if ((uint32_t)lane == i) s.level = level;
+                level += 1u;
+                unhanded = i;
+                todo = rest;
+                if (!goes_on) break;
+                i = n;
+#pragma unroll
+                for (int m = 0; m < kOthers; ++m) {
+                    o_at[m] = ahead_at[m];
+#pragma unroll
+                    for (int e = 0; e < kV; ++e) o[m][e] = ahead[m][e];
                 }
             }
-            if (look) {
-                bool came = false;
-                if (looks) came = s.seen(is, takes) == 0u;
-                come |= __ballot(came);
-            }
-            if ((uint32_t)lane == i) s.level = level;
-            unhanded = i;
-            level += 1u;
         }
         memory_is_done();
         hand_on();
