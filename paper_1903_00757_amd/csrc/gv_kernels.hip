@@ -2005,7 +2005,6 @@ __global__ __launch_bounds__(kBlock) void k_init_vertex(float *__restrict__ vert
 // j; sample number t of the pool (walks concatenated) goes to position t, or, pseudo-shuffled,
 // to block t mod window at offset t / window.  Random numbers: Philox stream 4, counter
 // (walk number, step): the pool depends on nothing but the seed and the walk numbers.
-constexpr int kWalkBlock = 128;    // threads (= walks) per workgroup
 constexpr int kMaxWalkLength = 64;
 
 __device__ __forceinline__ uint64_t pick_below(uint4 r, uint64_t range) {
@@ -2077,19 +2076,28 @@ __device__ __forceinline__ uint64_t place_of(uint64_t t, uint32_t s, uint64_t co
     return b * whole + (b < extra ? b : extra) + q;
 }
 
-__global__ __launch_bounds__(kWalkBlock) void k_augment(AugmentArgs a) {
+// A workgroup of kThreads threads makes kWalks walks, a thread each, and all of its threads write their pairs.  Where walks are
+// few, what they cost is latency: of the steps, and of the writing, a thread some 600 pairs (64 steps, window 10: 134 us alone
+// with the walks' own 128 threads to 128 walks, 93 with 256 to 64).  So below 2^16 walks there are 64 to a workgroup, on more
+// compute units, and four threads to each; us among other launches (alone), 128 walks and threads -> 64 and 256: 1053 walks of 40
+// steps, window 5, 13.0 (51) -> 8.3 (36); 21053 24.3 (68) -> 22.1 (55); 63158 59.9 (90) -> 59.4 (86); weighted, window 2, 37975 35.9
+// (54) -> 31.9 (49).  With more of them the reads of the steps and the pairs written fill the memory, and bursts of writes only
+// get in the way of the reads: 88301 walks 89.8 (124) and 101 (120), weighted 75950 60.2 and 61.3, of 20 steps, 838861, 353 and 356.
+constexpr uint64_t kFewWalks = 1u << 16;
+template <int kWalks, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_augment(AugmentArgs a) {
     // a walk's nodes, one row per thread (65 words: the rows start in different banks)
-    __shared__ uint32_t s_path[kWalkBlock][kMaxWalkLength + 1];
+    __shared__ uint32_t s_path[kWalks][kMaxWalkLength + 1];
     // the pairs of a walk in order: i << 8 | j of pair number t (i < j <= i + s, in order of i then j)
     __shared__ uint16_t s_pair[(kMaxWalkLength + 1) * kMaxWalkLength / 2];
-    const uint64_t w0 = (uint64_t)blockIdx.x * kWalkBlock, w = w0 + threadIdx.x;
+    const uint64_t w0 = (uint64_t)blockIdx.x * kWalks, w = w0 + threadIdx.x;
     const uint32_t L = a.length, s = a.window;
-    for (uint32_t i = threadIdx.x; i < L; i += kWalkBlock) {
+    for (uint32_t i = threadIdx.x; i < L; i += kThreads) {
         uint32_t start = 0;  // pairs of the nodes before i
         for (uint32_t before = 0; before < i; ++before) start += min(s, L - before);
         for (uint32_t j = i + 1; j <= L && j - i <= s; ++j) s_pair[start + (j - i - 1)] = (uint16_t)(i << 8 | j);
     }
-    if (w < a.walks) {
+    if (threadIdx.x < kWalks && w < a.walks) {
         const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
         const uint64_t walk = a.first_walk + w;
         uint32_t x;
@@ -2146,7 +2154,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_augment(AugmentArgs a) {
     // The workgroup's walks cover the samples t_lo .. t_hi - 1 of the pool; the workgroup writes them together, a
     // thread per sample, in the order of their places in the pool, so that neighbouring threads write
     // neighbouring pairs (one thread writing its own walk's 190 pairs scatters 8-byte stores over the pool).
-    const uint32_t here = (uint32_t)min((uint64_t)kWalkBlock, a.walks - w0);
+    const uint32_t here = (uint32_t)min((uint64_t)kWalks, a.walks - w0);
     const uint64_t t_lo = w0 * a.per_walk;
     const uint64_t t_hi = min(t_lo + (uint64_t)here * a.per_walk, a.count);
     if (t_lo >= t_hi) return;
@@ -2158,9 +2166,9 @@ __global__ __launch_bounds__(kWalkBlock) void k_augment(AugmentArgs a) {
         a.pairs[place] = make_uint2(s_path[walk][pair >> 8], s_path[walk][pair & 0xFFu]);
     };
     if (!a.pseudo_shuffle) {
-        for (uint32_t t_rel = threadIdx.x; t_rel < span; t_rel += kWalkBlock) emit(t_rel, t_lo + t_rel);
+        for (uint32_t t_rel = threadIdx.x; t_rel < span; t_rel += kThreads) emit(t_rel, t_lo + t_rel);
     } else if (s > span) {
-        for (uint32_t t_rel = threadIdx.x; t_rel < span; t_rel += kWalkBlock)
+        for (uint32_t t_rel = threadIdx.x; t_rel < span; t_rel += kThreads)
             emit(t_rel, place_of(t_lo + t_rel, s, a.count, true));
     } else {
         // block after block: within block b the workgroup's samples are b + q s for consecutive q
@@ -2169,7 +2177,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_augment(AugmentArgs a) {
         for (uint32_t b = 0; b < s; ++b) {
             const uint64_t first = b * whole + (b < extra ? b : extra) + q_lo;
 #pragma unroll 4
-            for (uint32_t q = threadIdx.x; q < steps; q += kWalkBlock) {
+            for (uint32_t q = threadIdx.x; q < steps; q += kThreads) {
                 const uint32_t t_rel = q * s + b - skip;  // wraps below t_lo, and is past the end there as well
                 if (t_rel < span) emit(t_rel, first + q);
             }
@@ -2556,9 +2564,12 @@ hipError_t launch_departure_guide(const uint64_t *offsets, uint32_t n, uint64_t 
 hipError_t launch_augment(const AugmentArgs &a, hipStream_t stream) {
     if (a.walks == 0) return hipSuccess;
     if (a.length == 0 || a.length > (uint32_t)kMaxWalkLength || a.window == 0) return hipErrorInvalidValue;
-    const uint64_t blocks = (a.walks + kWalkBlock - 1) / kWalkBlock;
+    const uint64_t of_block = a.walks < kFewWalks ? 64u : 128u, blocks = (a.walks + of_block - 1) / of_block;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_augment, dim3((uint32_t)blocks), dim3(kWalkBlock), 0, stream, a);
+    if (of_block == 64u)
+        hipLaunchKernelGGL((k_augment<64, 256>), dim3((uint32_t)blocks), dim3(256), 0, stream, a);
+    else
+        hipLaunchKernelGGL((k_augment<128, 128>), dim3((uint32_t)blocks), dim3(128), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -1804,6 +1804,34 @@ def test_device_producer_at_its_edges(gv, graph, weighted, L, s, count, shuffle)
     assert np.array_equal(out.cpu().numpy().view(np.uint32), ref)
 
 
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("L,s,shuffle", [(2, 1, 1), (3, 5, 1), (9, 2, 0), (17, 4, 1)])
+@pytest.mark.parametrize("walks,short", [(63, 0), (64, 0), (65, 1), (65_535, 1), (65_536, 0), (65_536, 1), (65_537, 0), (65_665, 1)])
+def test_device_producer_by_number_of_walks(gv, tiny_graph, walks, short, L, s, shuffle, weighted):
+    """The pools of the host producer, bit for bit, where the walks of a workgroup change and at the edges of a workgroup,
+    the last walk whole or cut short by a pair."""
+    import torch
+
+    g = tiny_graph
+    count = walks * sum(L + 1 - d for d in range(1, min(s, L) + 1)) - short
+    out = torch.full((count + 3, 2), -1, dtype=torch.int32, device="cuda")
+    with context_for(gv, dim=32, num_neg=1, total_samples=1000, pool_capacity=8) as ctx:
+        kw = dict(seed=12, walk_length=L, window=s, first_walk=99, count=count, shuffle=shuffle)
+        if weighted:
+            weights = np.ones(g["adj"].size, dtype=np.float32)
+            gv.gv_set_weighted_graph(ctx, g["offsets"], g["adj"], weights)
+            ref, used = gv.gv_augment_weighted(g["offsets"], g["adj"], gv.gv_build_walk_tables(g["offsets"], weights)[1:], **kw)
+        else:
+            gv.gv_set_degrees(ctx, g["deg"])
+            gv.gv_set_adjacency(ctx, g["offsets"], g["adj"])
+            ref, used = gv.gv_augment(g["offsets"], g["adj"], **kw)
+        assert gv.gv_augment_device(ctx, out.data_ptr(), **kw) == used == walks
+        gv.gv_sync(ctx)
+        got = out.cpu().numpy().view(np.uint32)
+    assert np.array_equal(got[:count], ref)
+    assert (got[count:] == 0xFFFFFFFF).all()
+
+
 def test_device_producer_feeds_training_like_the_host_producer(gv, tiny_graph):
     """A pool produced on the device and trained from there gives the same embeddings as the same pool
     produced by the host producer and pushed (deterministic mode: bit-identical)."""
