@@ -1807,9 +1807,11 @@ int gv_link_prediction_auc(gv_ctx *ctx, const uint32_t *host_edge_first, const u
         };
         rc = score(host_other_first, host_other_second, num_others, scores + num_edges, ctx->compute);
         if (rc) return rc;
-        if (!few)
+        if (!few) {
+            std::fill_n(r.sums + gv::kRankBlocks, gv::kRankBlocks, 0ull);  // in use by no kernel: every call waits for its own
             GV_HIP(ctx, gv::launch_rank_sort((uint32_t *)scores + num_edges, (uint32_t)num_others, dev_sorting, r.sums + gv::kRankBlocks,
                                              ctx->compute));
+        }
         rc = score(host_edge_first, host_edge_second, num_edges, scores, beside);
         if (rc) return rc;
         if (!few) {

@@ -189,7 +189,7 @@ hipError_t launch_cosine(const float *vertex, uint32_t n, uint32_t dim, const ui
 
 // The sum of twice[0 .. kRankBlocks) is 2 (pairs of a positive above a negative) + (pairs of equal score) of scores[0 ..
 // num_pos) against the num_neg scores behind them, num_pos + num_neg <= 2^31; not_finite[0 .. kRankBlocks) holds a nonzero where
-// a score is no number (cleared by the sort).  The negatives are sorted first, and overwritten.  scratch:
+// a score is no number (cleared by the caller).  The negatives are sorted first, and overwritten.  scratch:
 // rank_scratch_words(num_neg) words at a multiple of 16 bytes.
 constexpr uint32_t kRankBlocks = 256;
 uint64_t rank_scratch_words(uint32_t num_neg);

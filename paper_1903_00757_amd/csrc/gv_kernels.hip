@@ -1695,7 +1695,8 @@ __global__ __launch_bounds__(kBlock) void k_cosine(const float *__restrict__ ver
 // Rank statistic (gv_link_prediction_auc): twice the sum over all positives of (negatives below it + half of the
 // negatives equal to it).  The negatives are sorted (least significant digit first, eight bits a pass) and every
 // positive is looked up among them; whole numbers throughout, so the result is that of sorting all scores on the host.
-// 250000 + 250000 scores: 75 us, all of it latency of short launches, so a workgroup owns as few keys as it takes at a time
+// 250000 + 250000 scores: 75 us with three launches a pass, all of it latency of short launches, so a workgroup owns as few keys as
+// it takes at a time and up to 256 of them do without a launch for the places (own_places; the whole call 263 -> 252)
 // (segments of 4096 keys, one workgroup for the places, all of a search in memory: 105 us); std::sort of the pairs on the host
 // took 29 ms.
 constexpr int kSortBlock = 1024, kSortWaves = kSortBlock / kWave, kDigits = 256;
@@ -1707,11 +1708,12 @@ __device__ __forceinline__ uint32_t score_key(uint32_t x) {
 }
 __device__ __forceinline__ bool not_a_number(uint32_t x) { return (x & 0x7F800000u) == 0x7F800000u; }  // or an infinity
 
-// One pass: workgroup b owns the keys b * segment .. (b + 1) * segment - 1 and counts their digits (kScores: of the scores
+// One pass: workgroup b owns the keys b * segment .. (b + 1) * segment - 1 and counts their digits (by_block: digit after digit
+// of one workgroup, for own_places; kScores: of the scores
 // still to be made keys; *not_finite is set where one is no number) ...
 template <bool kScores>
 __global__ __launch_bounds__(kSortBlock) void k_radix_count(const uint32_t *__restrict__ keys, uint32_t count, uint32_t segment,
-                                                            uint32_t shift, uint32_t *__restrict__ counts,
+                                                            uint32_t shift, bool by_block, uint32_t *__restrict__ counts,
                                                             unsigned long long *__restrict__ not_finite) {
     __shared__ uint32_t s_count[kDigits];
     if (threadIdx.x < kDigits) s_count[threadIdx.x] = 0u;
@@ -1726,7 +1728,8 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_count(const uint32_t *__re
         atomicAdd(&s_count[(key >> shift) & (kDigits - 1)], 1u);
     }
     __syncthreads();
-    if (threadIdx.x < kDigits) counts[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = s_count[threadIdx.x];
+    if (threadIdx.x < kDigits)
+        counts[by_block ? (size_t)blockIdx.x * kDigits + threadIdx.x : (size_t)threadIdx.x * gridDim.x + blockIdx.x] = s_count[threadIdx.x];
 }
 
 // ... the counts, digit after digit and workgroup after workgroup, become places: a workgroup adds up the counts before its
@@ -1768,10 +1771,51 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_places(const uint32_t *__r
     }
 }
 
+// ... or, of few workgroups, each adds up the places of its own keys: a wave takes whole rows of counts, a lane four digits of
+// each, into s_next[digit] = the counts of lower digits, and of this one in the workgroups before.  (A launch of
+// k_radix_places takes 5 to 8 us with the way to it, a pass: link prediction of 10000 against 10000 pairs 95 -> 83 us, of 80000 155 ->
+// 147, of 150000 207 -> 194; deterministic pools of 10000 samples 148 -> 138, of 50000 200 -> 189.)
+__device__ __forceinline__ void own_places(const uint32_t *__restrict__ counts, uint32_t (&s_part)[kSortWaves][kDigits],
+                                           uint32_t (&s_next)[kDigits]) {
+    __shared__ uint32_t s_before[kSortWaves][kDigits], s_total[kDigits / kWave];
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    uint4 all = make_uint4(0u, 0u, 0u, 0u), before = all;
+#pragma unroll 8
+    for (uint32_t b = wave; b < gridDim.x; b += kSortWaves) {
+        const uint4 c = ((const uint4 *)counts)[(size_t)b * (kDigits / 4) + lane];
+        const uint32_t earlier = b < blockIdx.x ? ~0u : 0u;
+        all = make_uint4(all.x + c.x, all.y + c.y, all.z + c.z, all.w + c.w);
+        before = make_uint4(before.x + (c.x & earlier), before.y + (c.y & earlier), before.z + (c.z & earlier), before.w + (c.w & earlier));
+    }
+    ((uint4 *)s_part[wave])[lane] = all;
+    ((uint4 *)s_before[wave])[lane] = before;
+    __syncthreads();
+    uint32_t own = 0u, next = 0u, upto = 0u;
+    if (threadIdx.x < kDigits) {  // whole waves
+        for (int w = 0; w < kSortWaves; ++w) {
+            own += s_part[w][threadIdx.x];
+            next += s_before[w][threadIdx.x];
+        }
+        upto = own;
+        for (uint32_t d = 1; d < (uint32_t)kWave; d *= 2) {
+            const uint32_t x = __shfl_up(upto, d);
+            upto += lane >= d ? x : 0u;
+        }
+        if (lane == kWave - 1) s_total[wave] = upto;
+    }
+    __syncthreads();
+    if (threadIdx.x < kDigits) {
+        for (uint32_t w = 0; w < wave; ++w) next += s_total[w];
+        s_next[threadIdx.x] = next + upto - own;
+    }
+    __syncthreads();  // s_part is used again
+}
+
 // ... and the keys go there in their order: 1024 at a time, a wave finds the lanes with its lane's digit by eight ballots.
 // kCarried: each key takes a word with it, the one beside it in `words`, or, where that is null, its own place.  kScores:
 // scores come in, their keys go out.
-template <bool kCarried, bool kScores>
+// kOwnPlaces: `places` are the counts, workgroup after workgroup, and each workgroup adds up its own places (own_places).
+template <bool kCarried, bool kScores, bool kOwnPlaces>
 __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ words,
                                                               uint32_t count, uint32_t segment, uint32_t shift,
                                                               const uint32_t *__restrict__ places, uint32_t *__restrict__ out,
@@ -1779,7 +1823,10 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(const uint32_t *__
     __shared__ uint32_t s_next[kDigits];               // place of the workgroup's next key of a digit
     __shared__ uint32_t s_place[kSortWaves][kDigits];  // keys of a digit in a wave, then the place of the first of them
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if (threadIdx.x < kDigits) s_next[threadIdx.x] = places[(size_t)threadIdx.x * gridDim.x + blockIdx.x];
+    if constexpr (kOwnPlaces)
+        own_places(places, s_place, s_next);
+    else if (threadIdx.x < kDigits)
+        s_next[threadIdx.x] = places[(size_t)threadIdx.x * gridDim.x + blockIdx.x];
     const uint64_t begin = (uint64_t)blockIdx.x * segment, end = min(begin + segment, (uint64_t)count);
     for (uint64_t base = begin; base < end; base += kSortBlock) {
         for (uint32_t i = threadIdx.x; i < kSortWaves * kDigits; i += kSortBlock) (&s_place[0][0])[i] = 0u;
@@ -2409,31 +2456,32 @@ static uint32_t sort_segment(uint32_t count) {
 static uint32_t sort_blocks(uint32_t count) { return (uint32_t)(((uint64_t)count + sort_segment(count) - 1u) / sort_segment(count)); }
 // counts and places of a pass
 static uint64_t sort_count_words(uint32_t count) { return 2ull * kDigits * sort_blocks(count); }
+// Every workgroup reads the counts of all of them: a megabyte each and more from 1024 on (10^6 against 10^6 pairs 850 us, 908 with
+// own places; 500000, 489 workgroups, 453 and 462; 256 workgroups and fewer are faster that way).
+constexpr uint32_t kOwnPlacesBlocks = 256;
 // One pass over `from`, and the words that go along if `words_out` is given; counts at a multiple of 16 bytes.
 template <bool kScores>
 static void sort_pass(const uint32_t *from, const uint32_t *words, uint32_t count, uint32_t shift, uint32_t *counts, uint32_t *to,
                       uint32_t *words_out, unsigned long long *not_finite, hipStream_t stream) {
     const uint32_t segment = sort_segment(count), blocks = sort_blocks(count), entries = kDigits * blocks;
     uint32_t *const places = counts + entries;
-    hipLaunchKernelGGL(k_radix_count<kScores>, dim3(blocks), dim3(kSortBlock), 0, stream, from, count, segment, shift, counts, not_finite);
-    hipLaunchKernelGGL(k_radix_places, dim3((entries + 4u * kSortBlock - 1u) / (4u * kSortBlock)), dim3(kSortBlock), 0, stream, counts,
-                       entries, places);
-    if (words_out)
-        hipLaunchKernelGGL((k_radix_scatter<true, kScores>), dim3(blocks), dim3(kSortBlock), 0, stream, from, words, count, segment, shift,
-                           places, to, words_out);
-    else
-        hipLaunchKernelGGL((k_radix_scatter<false, kScores>), dim3(blocks), dim3(kSortBlock), 0, stream, from, words, count, segment, shift,
-                           places, to, words_out);
+    const bool own = blocks <= kOwnPlacesBlocks;
+    hipLaunchKernelGGL(k_radix_count<kScores>, dim3(blocks), dim3(kSortBlock), 0, stream, from, count, segment, shift, own, counts,
+                       not_finite);
+    if (!own)
+        hipLaunchKernelGGL(k_radix_places, dim3((entries + 4u * kSortBlock - 1u) / (4u * kSortBlock)), dim3(kSortBlock), 0, stream,
+                           counts, entries, places);
+    const auto scatter = words_out ? (own ? k_radix_scatter<true, kScores, true> : k_radix_scatter<true, kScores, false>)
+                                   : (own ? k_radix_scatter<false, kScores, true> : k_radix_scatter<false, kScores, false>);
+    hipLaunchKernelGGL(scatter, dim3(blocks), dim3(kSortBlock), 0, stream, from, words, count, segment, shift, own ? counts : places, to,
+                       words_out);
 }
 
 static uint64_t rank_counts_at(uint32_t num_neg) { return ((uint64_t)num_neg + 3u) & ~3ull; }  // behind the keys, for 16-byte reads
 uint64_t rank_scratch_words(uint32_t num_neg) { return rank_counts_at(num_neg) + sort_count_words(num_neg); }
 
-__global__ __launch_bounds__(kBlock) void k_clear(unsigned long long *words) { words[threadIdx.x] = 0ull; }
 hipError_t launch_rank_sort(uint32_t *negatives, uint32_t num_neg, uint32_t *scratch, unsigned long long *not_finite, hipStream_t stream) {
     if (num_neg == 0) return hipErrorInvalidValue;
-    static_assert(kRankBlocks == kBlock, "k_clear");
-    hipLaunchKernelGGL(k_clear, dim3(1), dim3(kBlock), 0, stream, not_finite);
     uint32_t *const counts = scratch + rank_counts_at(num_neg);
     // four passes: the keys end where the scores were
     sort_pass<true>(negatives, nullptr, num_neg, 0u, counts, scratch, nullptr, not_finite, stream);

@@ -314,6 +314,32 @@ def test_deterministic_bits_do_not_depend_on_the_way(gv, hubs, d, K):
         assert np.array_equal(one.view(np.uint32), two.view(np.uint32))
 
 
+@pytest.mark.parametrize("count", [4097, 87_381, 87_382, 120_000])
+def test_deterministic_pools_by_number_of_namings(gv, count):
+    """Pools whose namings, three a sample, take up to and over 256 workgroups of the sort: as the oracle trains them."""
+    import torch
+
+    n, d, K, w, seed = 30_000, 32, 1, 5.0, 61
+    rng = np.random.default_rng(count)
+    deg = rng.integers(20, 30, size=n).astype(np.uint32)
+    pool = rng.integers(n, size=(count, 2)).astype(np.uint32)
+    vertex, context = random_embeddings(n, d, seed=18)
+    with context_for(gv, dim=d, num_neg=K, neg_weight=w, mode=gv.GV_MODE_DETERMINISTIC, total_samples=3 * count, seed=seed,
+                     pool_capacity=8, lr0=LR0) as ctx:
+        gv.gv_set_degrees(ctx, deg)
+        gv.gv_build_alias(ctx, 0.75)
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+        held = torch.from_numpy(pool.view(np.int32)).cuda()
+        torch.cuda.synchronize()
+        gv.gv_train_device_pool(ctx, held.data_ptr(), count)
+        gv.gv_sync(ctx)
+        got = [gv.gv_read_embeddings(ctx, which, n, d) for which in (gv.GV_VERTEX, gv.GV_CONTEXT)]
+    for one, ref in zip(got, run_oracle(deg, K, w, [pool], vertex, context, 3 * count, seed)):
+        fro, mx = rel_errors(one, ref)
+        assert fro <= 1e-5 and mx <= 1e-4, (fro, mx)
+
+
 @pytest.mark.parametrize("K", [1, 3])
 def test_deterministic_pools_with_narrow_levels(gv, K):
     """Walks in their own order, which are levelled, and in shuffled order, which wait on the device, on a graph without
@@ -1278,6 +1304,25 @@ def test_link_prediction_auc_is_the_rank_statistic_of_the_cosines(gv, edges, oth
         got = gv.gv_link_prediction_auc(ctx, a, b, c, e)
         pos, neg = gv.gv_cosine(ctx, a, b), gv.gv_cosine(ctx, c, e)
     assert got == gv.gv_auc(pos, neg)
+
+
+@pytest.mark.parametrize("others", [4095, 4096, 4097, 16 * 1024 + 1, 256 * 1024 - 1, 256 * 1024, 256 * 1024 + 1, 257 * 1024 + 5])
+@pytest.mark.parametrize("shape", ["spread", "two values"])
+def test_sort_of_scores_by_number_of_workgroups(gv, others, shape):
+    """The rank statistic of the same scores, bit for bit, where the workgroups of the sort add up their own places (256 of
+    1024 keys and fewer) and where a launch does it for them; with keys of every digit, and of two digits only."""
+    n, d = 500, 64
+    rng = np.random.default_rng(others)
+    vertex = rng.standard_normal((n, d)).astype(np.float32)
+    if shape == "two values":
+        vertex[:, :] = np.where(rng.random(n) < 0.5, 1.0, -1.0)[:, None]
+    with context_for(gv, dim=d, num_neg=1, total_samples=1000, pool_capacity=8) as ctx:
+        gv.gv_set_degrees(ctx, np.ones(n, dtype=np.uint32))
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        a, b, c, e = (rng.integers(n, size=k).astype(np.uint32) for k in (5000, 5000, others, others))
+        expected = gv.gv_auc(gv.gv_cosine(ctx, a, b), gv.gv_cosine(ctx, c, e))
+        assert gv.gv_link_prediction_auc(ctx, a, b, c, e) == expected
+        assert gv.gv_link_prediction_auc(ctx, a, b, c, e) == expected
 
 
 @pytest.mark.parametrize("edges,others", [((1 << 17) + 1, 1 << 17), (1 << 17, 5 * (1 << 17) + 3), (5 * (1 << 17) - 1, 20_000), (90_000, 40_000)])
