@@ -2124,13 +2124,14 @@ __device__ __forceinline__ uint64_t place_of(uint64_t t, uint32_t s, uint64_t co
 }
 
 // A workgroup of kThreads threads makes kWalks walks, a thread each, and all of its threads write their pairs.  Where walks are
-// few, what they cost is latency: of the steps, and of the writing, a thread some 600 pairs (64 steps, window 10: 134 us alone
-// with the walks' own 128 threads to 128 walks, 93 with 256 to 64).  So below 2^16 walks there are 64 to a workgroup, on more
-// compute units, and four threads to each; us among other launches (alone), 128 walks and threads -> 64 and 256: 1053 walks of 40
-// steps, window 5, 13.0 (51) -> 8.3 (36); 21053 24.3 (68) -> 22.1 (55); 63158 59.9 (90) -> 59.4 (86); weighted, window 2, 37975 35.9
-// (54) -> 31.9 (49).  With more of them the reads of the steps and the pairs written fill the memory, and bursts of writes only
-// get in the way of the reads: 88301 walks 89.8 (124) and 101 (120), weighted 75950 60.2 and 61.3, of 20 steps, 838861, 353 and 356.
-constexpr uint64_t kFewWalks = 1u << 16;
+// few, what they cost is latency: of the steps, and of the writing, a thread some 600 pairs with as many threads as walks.  So
+// below 2^16 walks and 2^23 pairs there are 64 walks to a workgroup, on more compute units, and four threads to each; us among other
+// launches (alone), 128 walks and threads -> 64 and 256: 10^6 nodes, 40 steps, window 5, 1053 walks 13.0 (51) -> 8.3 (36), 21053 24.3
+// (68) -> 22.1 (55), 42106 40.6 (78) -> 40.4 (65); 10^4 nodes, 64 steps, window 10, 7050 walks 32.4 (104) -> 17.7 (60); weighted, window
+// 2, 37975 walks 35.9 (54) -> 31.9 (49).  With more of them the reads of the steps and the pairs written fill the memory, and
+// bursts of writes get in the way of the reads: 88301 walks, 2^24 pairs, 89.8 (124) and 101 (120); weighted 75950 walks 60.2 and 61.3.
+// (Between 2^23 and 2^24 pairs of few walks both were seen: 57 -> 51, and slower by a sixth.)
+constexpr uint64_t kFewWalks = 1u << 16, kFewPairs = 1u << 23;
 template <int kWalks, int kThreads>
 __global__ __launch_bounds__(kThreads) void k_augment(AugmentArgs a) {
     // a walk's nodes, one row per thread (65 words: the rows start in different banks)
@@ -2612,7 +2613,7 @@ hipError_t launch_departure_guide(const uint64_t *offsets, uint32_t n, uint64_t 
 hipError_t launch_augment(const AugmentArgs &a, hipStream_t stream) {
     if (a.walks == 0) return hipSuccess;
     if (a.length == 0 || a.length > (uint32_t)kMaxWalkLength || a.window == 0) return hipErrorInvalidValue;
-    const uint64_t of_block = a.walks < kFewWalks ? 64u : 128u, blocks = (a.walks + of_block - 1) / of_block;
+    const uint64_t of_block = a.walks < kFewWalks && a.count <= kFewPairs ? 64u : 128u, blocks = (a.walks + of_block - 1) / of_block;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (of_block == 64u)
         hipLaunchKernelGGL((k_augment<64, 256>), dim3((uint32_t)blocks), dim3(256), 0, stream, a);
