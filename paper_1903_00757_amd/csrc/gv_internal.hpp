@@ -33,7 +33,6 @@ struct FlowState {
     uint32_t stalled;            // set where a wave gave up (see k_train_flow)
     uint32_t started;            // workgroups that have begun
     uint32_t chained;            // times 64 namings of a hub are done
-    unsigned long long nowhere;  // takes the turns that are not handed on
     unsigned long long slots[64];  // rows named often: namings << 32 | place of the first
 };
 

@@ -1029,8 +1029,11 @@ __device__ __forceinline__ uint32_t flow_progress(const FlowState *state) {
            __hip_atomic_load(&state->chained, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 constexpr int flow_batch(int V, int K) { return V * (K + 2) <= 14 ? 2 : 1; }
-// The rows of two samples of a chain fit the 256 registers of a wave (with those of longer ones kept in memory, 20000 samples at
-// d = 512, K = 5 take 19 ms, without chains 5.5); without chains there are no hubs.
+// The rows of two samples of a chain fit the 256 registers of a wave, with 226 used at most, 242 where the loss is tracked (with
+// those of longer ones kept in memory, 20000 samples at d = 512, K = 5 take 19 ms, without chains 5.5); without chains there are no
+// hubs.  Beyond 128 registers a compute unit has room for one workgroup only, and pools of three contexts wait for each other: 2*10^4
+// samples on 2000 nodes, d = 64, K = 3, three contexts in turn 470 us a pool with 153 registers, 400 with 112; 5*10^4 on 10^4 nodes, the
+// hottest row in 4 % of them, d = 256, K = 1 922 with 133, 751 with 109 (on 2*10^5 nodes without hubs 174 and 187).
 constexpr bool flow_has_hubs(int V, int K) { return V * (K + 2) < 40; }
 
 // One sample in registers: the rows after their updates stand where they were.  A chain is as fast as one wave goes through
@@ -1117,7 +1120,6 @@ template <int kK>
 struct FlowSample {
     static constexpr int kRows = kK + 2;
     uint32_t key[kRows];        // its rows (context row v is n + v)
-    uint64_t *turn[kRows];      // their turns
     uint32_t waits_for[kRows];  // the place of its naming (the first, where it names a row twice)
     uint32_t hands_on[kRows];   // the place behind it (so the last one's stays)
     uint32_t level = 0;         // the highest level of the samples before it at its rows
@@ -1128,39 +1130,49 @@ struct FlowSample {
             key[j] = mine ? a.keys[(size_t)sample * kRows + j] : 0u;
             waits_for[j] = mine ? a.places[(size_t)sample * kRows + j] : 0u;
             hands_on[j] = waits_for[j] + 1u;
-            turn[j] = a.turns + key[j];
         }
 #pragma unroll
         for (int j = 1; j < kRows; ++j)
 #pragma unroll
             for (int j2 = j - 1; j2 >= 0; --j2) waits_for[j] = key[j2] == key[j] ? waits_for[j2] : waits_for[j];
     }
-    __device__ __forceinline__ void read(bool looks, uint64_t (&is)[kRows]) const {
+    // The turns of the first kN rows.
+    template <int kN>
+    __device__ __forceinline__ void read(uint64_t *turns, bool looks, uint64_t (&is)[kN]) const {
         if (looks) {
 #pragma unroll
-            for (int j = 0; j < kRows; ++j) is[j] = __hip_atomic_load(turn[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int j = 0; j < kN; ++j) is[j] = __hip_atomic_load(turns + key[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    // How many samples come first at the row where most do (0: its turns have come).  Bit j of `held`, here and below: row j is
-    // in this wave's registers, and its turn neither waited for nor handed on.
-    __device__ __forceinline__ uint32_t seen(const uint64_t (&is)[kRows], uint32_t held) {
+    // How many samples come first at the row where most do (0: its turns have come).
+    template <int kN>
+    __device__ __forceinline__ uint32_t seen(const uint64_t (&is)[kN]) {
         uint32_t away = 0, highest = 0;
 #pragma unroll
-        for (int j = 0; j < kRows; ++j) {
-            const bool free = (held >> j) & 1u;
-            away = max(away, free ? 0u : waits_for[j] - (uint32_t)is[j]);
-            highest = max(highest, free ? 0u : (uint32_t)(is[j] >> 32));
+        for (int j = 0; j < kN; ++j) {
+            away = max(away, waits_for[j] - (uint32_t)is[j]);
+            highest = max(highest, (uint32_t)(is[j] >> 32));
         }
         level = highest;
         return away;
     }
-    __device__ __forceinline__ void hand_on(uint64_t *nowhere, uint32_t held) const {
+    __device__ __forceinline__ void hand_on(uint64_t *turns) const {
 #pragma unroll
         for (int j = 0; j < kRows; ++j)
-            __hip_atomic_store((held >> j) & 1u ? nowhere : turn[j], (uint64_t)(level + 1u) << 32 | hands_on[j], __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(turns + key[j], (uint64_t)(level + 1u) << 32 | hands_on[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 };
+
+// The same value, from which nothing is worked out ahead of a loop to be kept in registers over it.
+template <class T>
+__device__ __forceinline__ T *afresh(T *x) {
+    asm volatile("" : "+s"(x));
+    return x;
+}
+__device__ __forceinline__ uint32_t afresh(uint32_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
 
 // The rows that have a wave of their own: lane h < kFlowHubs holds the hub h, most namings first.
 struct FlowHubs {
@@ -1220,7 +1232,6 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
     using Io = HandedRow<kV, kFull>;
     const FlowRows matrix(a);
     const uint32_t at = Io::lane_offset(lane);
-    uint64_t *const nowhere = (uint64_t *)&a.flow->nowhere;
     const uint32_t hub = lane_value(hubs.key, h), begin = lane_value(hubs.begin, h), end = begin + lane_value(hubs.namings, h);
     char *const row = matrix.of(hub < a.n ? 0 : 1, hub);
     float y[kV];
@@ -1250,32 +1261,49 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
 #pragma unroll
             for (int j2 = j1 + 1; j2 < kRows; ++j2) differ &= s.key[j1] != s.key[j2];
         const uint64_t plain = own & __ballot(differ);
-        uint64_t other_at[kOthers], other_turn[kOthers];
-        uint32_t other_next[kOthers];
+        // From here on a sample's rows are those beside its first naming of the hub, in their order, and the first of them stands
+        // where it names the hub again, whose turn is neither waited for nor handed on.  (In place, the addresses of turns worked
+        // out where they are used: with copies in the chain's order kept beside them, 16 to 100 registers more, see flow_has_hubs.)
+        const uint32_t first_other = takes & 1u ? s.key[1] : s.key[0], first_waits_for = takes & 1u ? s.waits_for[1] : s.waits_for[0];
+        uint64_t other_at[kOthers];
 #pragma unroll
         for (int m = 0; m < kOthers; ++m) {
-            const bool behind = (takes & ((2u << m) - 1u)) != 0u;  // the hub comes first: the row is number m + 1
-            other_at[m] = (uint64_t)(behind ? matrix.of(m + 1, s.key[m + 1]) : matrix.of(m, s.key[m]));
-            other_turn[m] = (uint64_t)(behind ? s.turn[m + 1] : s.turn[m]);
-            other_next[m] = behind ? s.hands_on[m + 1] : s.hands_on[m];
+            const bool behind = (takes & ((2u << m) - 1u)) != 0u;  // the hub comes first: the row was number m + 1
+            const bool again_hub = behind && ((takes >> (m + 1)) & 1u);
+            s.key[m] = again_hub ? first_other : behind ? s.key[m + 1] : s.key[m];
+            s.waits_for[m] = again_hub ? first_waits_for : behind ? s.waits_for[m + 1] : s.waits_for[m];
+            other_at[m] = (uint64_t)matrix.of(m == 0 && !behind ? 0 : 1, s.key[m]);
         }
         ChunkScores<kK> scores{};
         uint32_t unhanded = kNone;  // the sample whose turns are to be passed on once its rows are in memory
         auto hand_on = [&]() {
             if ((uint32_t)lane != unhanded) return;
+            uint64_t *const turns = afresh(a.turns);
             if ((plain >> lane) & 1u) {
 #pragma unroll
                 for (int m = 0; m < kOthers; ++m)
-                    __hip_atomic_store((uint64_t *)other_turn[m], (uint64_t)(s.level + 1u) << 32 | other_next[m], __ATOMIC_RELAXED,
+                    __hip_atomic_store(turns + s.key[m], (uint64_t)(s.level + 1u) << 32 | (s.waits_for[m] + 1u), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
             } else {
-                s.hand_on(nowhere, takes);
+                const uint32_t takes_it = afresh(takes);
+                uint32_t key[kOthers];
+                bool hubs_own[kOthers];
+#pragma unroll
+                for (int m = 0; m < kOthers; ++m) {
+                    key[m] = afresh(s.key[m]);
+                    hubs_own[m] = (takes_it & ((2u << m) - 1u)) != 0u && ((takes_it >> (m + 1)) & 1u);
+                    uint32_t next = s.waits_for[m] + 1u;  // the namings of a row by one sample have places one behind the other
+#pragma unroll
+                    for (int m2 = 0; m2 < m; ++m2) next += key[m2] == key[m] && !hubs_own[m2] ? 1u : 0u;
+                    if (!hubs_own[m])
+                        __hip_atomic_store(turns + key[m], (uint64_t)(s.level + 1u) << 32 | next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
         };
-        uint64_t is[kRows];
+        uint64_t is[kOthers];
         auto looked = [&](bool looks) {
             bool came = false;
-            if (looks) came = s.seen(is, takes) == 0u;
+            if (looks) came = s.seen(is) == 0u;
             come |= __ballot(came);
         };
         auto waits = [&](uint32_t first) {
@@ -1302,7 +1330,7 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
                 for (FlowPatience patience;;) {
                     const uint64_t hub_turn = __hip_atomic_load(a.turns + hub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     const bool looks = waits(i);
-                    s.read(looks, is);
+                    s.read(afresh(a.turns), looks, is);
                     looked(looks);
                     if (!here && __builtin_amdgcn_readfirstlane((uint32_t)hub_turn) == base + i) {
                         here = true;
@@ -1319,15 +1347,16 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
                 held = true;
             }
             if (!((plain >> i) & 1u)) {
-                const uint32_t takes_i = lane_value(takes, i);
+                const uint32_t takes_i = lane_value(takes, i), u = lane_value(s.key[0], i);
                 float x[kV], c[kK + 1][kV];
                 uint32_t rows[kK + 1];
 #pragma unroll
                 for (int e = 0; e < kV; ++e) x[e] = 0.0f;
-                if (!(takes_i & 1u)) Io::load(matrix.of(0, lane_value(s.key[0], i)), at, matrix.bytes, x);
+                if (!(takes_i & 1u)) Io::load(matrix.of(0, u), at, matrix.bytes, x);
 #pragma unroll
                 for (int k = 0; k <= kK; ++k) {
-                    rows[k] = lane_value(s.key[1 + k], i);
+                    const uint32_t here = lane_value(s.key[min(1 + k, kK)], i), before = lane_value(s.key[k], i);
+                    rows[k] = (takes_i >> (1 + k)) & 1u ? hub : (takes_i & ((2u << k) - 1u)) != 0u ? before : here;
 #pragma unroll
                     for (int e = 0; e < kV; ++e) c[k][e] = 0.0f;
                     if (!((takes_i >> (1 + k)) & 1u)) Io::load(matrix.of(1, rows[k]), at, matrix.bytes, c[k]);
@@ -1341,7 +1370,7 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
                     for (int e = 0; e < kV; ++e) c[k][e] = (takes_i >> (1 + k)) & 1u ? y[e] : c[k][e];
                 sgns_in_place<kV, kK, kTrack>(x, c, rows, __uint_as_float(lane_value(__float_as_uint(lr), i)), a.neg_weight, lane, scores, i);
                 if (!(takes_i & 1u)) {
-                    Io::store(matrix.of(0, lane_value(s.key[0], i)), at, matrix.bytes, x);
+                    Io::store(matrix.of(0, u), at, matrix.bytes, x);
                 } else {
 #pragma unroll
                     for (int e = 0; e < kV; ++e) y[e] = x[e];
@@ -1382,7 +1411,7 @@ __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs
                 // the turns of those behind it, unless the next two are known to have come
                 const bool look = ((next | (behind & (0 - behind))) & own & ~come) != 0;
                 const bool looks = look && waits(i + 1u);
-                if (look) s.read(looks, is);
+                if (look) s.read(afresh(a.turns), looks, is);
                 float ahead[kOthers][kV];
                 char *ahead_at[kOthers];
                 const uint32_t n = goes_on ? (uint32_t)__builtin_ctzll(next) : i;
@@ -1497,10 +1526,10 @@ __global__ __launch_bounds__(kFlowBlock) void k_train_flow(FlowArgs a) {
                 const uint32_t now = (uint32_t)__builtin_readcyclecounter();
                 const bool waits = (pending & ~ready) >> lane & 1u, looks = waits && (int32_t)(now - due) >= 0;
                 uint64_t is[kRows];
-                s.read(looks, is);
+                s.read(a.turns, looks, is);
                 bool came = false;
                 if (looks) {
-                    const uint32_t away = s.seen(is, 0u);
+                    const uint32_t away = s.seen(is);
                     came = away == 0u;
                     // a sample that others come before is not looked at again before they can be done; `due` is never far
                     // behind `now` while the lane waits (their difference has 31 bits)
@@ -1547,7 +1576,7 @@ __global__ __launch_bounds__(kFlowBlock) void k_train_flow(FlowArgs a) {
                 }
             memory_is_done();
             if ((taken >> lane) & 1u) {
-                s.hand_on(nullptr, 0u);
+                s.hand_on(a.turns);
                 deepest = max(deepest, s.level + 1u);
             }
             pending &= ~taken;

@@ -230,7 +230,7 @@ def force_way(gv, ctx, way):
 
 @pytest.mark.parametrize("track", [0, 1])
 @pytest.mark.parametrize("d,K,count", [(128, 1, 9000), (64, 5, 4097), (32, 2, 5003), (96, 3, 6001), (256, 4, 4100), (352, 1, 4999),
-                                       (512, 2, 4200), (512, 5, 4300)])
+                                       (512, 2, 4200), (512, 5, 4300), (32, 5, 4111), (160, 5, 4099), (256, 5, 4200)])
 @pytest.mark.parametrize("hubs", [0, 1, 3, 12])
 def test_deterministic_pools_that_wait_on_the_device(gv, hubs, d, K, count, track):
     """Pools that wait for each other sample by sample: without rows that many share; with a vertex row and a context row
@@ -278,7 +278,7 @@ def test_deterministic_pools_that_wait_on_the_device(gv, hubs, d, K, count, trac
     assert stats["batches"] == sum(conflict_levels(pool, neg[i * count:(i + 1) * count], n) for i in (0, 1))
 
 
-@pytest.mark.parametrize("d,K", [(128, 1), (64, 5), (32, 2), (96, 3), (256, 4), (352, 1), (512, 2), (512, 5)])
+@pytest.mark.parametrize("d,K", [(128, 1), (64, 5), (32, 2), (96, 3), (256, 4), (352, 1), (512, 2), (512, 5), (32, 5), (160, 5), (256, 5)])
 @pytest.mark.parametrize("hubs", [0, 3])
 def test_deterministic_bits_do_not_depend_on_the_way(gv, hubs, d, K):
     """A pool whose samples wait for each other on the device, and the same samples in two pools so short that they are sorted
@@ -310,6 +310,46 @@ def test_deterministic_bits_do_not_depend_on_the_way(gv, hubs, d, K):
             stats = gv.gv_get_stats(ctx)
             assert stats["samples_trained"] == count and (stats["train_launches"] == 1) == (parts == 1)
             got.append([gv.gv_read_embeddings(ctx, which, n, d) for which in (gv.GV_VERTEX, gv.GV_CONTEXT)])
+    for one, two in zip(*got):
+        assert np.array_equal(one.view(np.uint32), two.view(np.uint32))
+
+
+@pytest.mark.parametrize("d,K", [(128, 1), (32, 2), (96, 3), (160, 3), (64, 5), (256, 5)])
+def test_deterministic_bits_of_hubs_named_several_times_by_a_sample(gv, d, K):
+    """Twelve nodes that most negatives meet, and positives that are the sample's own negatives: hubs named twice and more by one
+    sample, before and behind its other rows.  Waiting on the device and sorted into levels: the same bits."""
+    import torch
+
+    n, count, seed = 4000, 6000, 59
+    rng = np.random.default_rng(d + K)
+    deg = rng.integers(20, 30, size=n).astype(np.uint32)
+    deg[::350] = 20_000
+    pool = rng.integers(n, size=(count, 2)).astype(np.uint32)
+    pool[rng.random(count) < 0.05, 0] = 17
+    vertex, context = random_embeddings(n, d, seed=19)
+    got = []
+    for way in (1, 2):
+        with context_for(gv, dim=d, num_neg=K, neg_weight=5.0 / K, mode=gv.GV_MODE_DETERMINISTIC, total_samples=3 * count,
+                         seed=seed, pool_capacity=8, lr0=LR0) as ctx:
+            force_way(gv, ctx, way)
+            gv.gv_set_degrees(ctx, deg)
+            gv.gv_build_alias(ctx, 0.75)
+            gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+            gv.gv_set_embeddings(ctx, gv.GV_CONTEXT, context)
+            if not got:
+                negs = np.asarray(gv.gv_draw_negatives(ctx, 0, count, K)).reshape(count, K)
+                pool[::4, 1] = negs[::4, K - 1]
+                named = np.concatenate([pool[:, 1:], negs], axis=1)
+                hubs = np.argsort(-np.bincount(named.ravel(), minlength=n))[:7]
+                twice = (named[:, :, None] == hubs).sum(axis=1)
+                assert ((twice >= 2).sum(axis=0) >= 20).all()  # by every hub's wave
+            held = torch.from_numpy(pool.view(np.int32)).cuda()
+            torch.cuda.synchronize()
+            gv.gv_train_device_pool(ctx, held.data_ptr(), count)
+            stats = gv.gv_get_stats(ctx)
+            assert stats["samples_trained"] == count
+            got.append([gv.gv_read_embeddings(ctx, which, n, d) for which in (gv.GV_VERTEX, gv.GV_CONTEXT)] + [stats["batches"]])
+    assert got[0].pop() == got[1].pop()
     for one, two in zip(*got):
         assert np.array_equal(one.view(np.uint32), two.view(np.uint32))
 
