@@ -2158,9 +2158,14 @@ __device__ __forceinline__ uint64_t place_of(uint64_t t, uint32_t s, uint64_t co
 // launches (alone), 128 walks and threads -> 64 and 256: 10^6 nodes, 40 steps, window 5, 1053 walks 13.0 (51) -> 8.3 (36), 21053 24.3
 // (68) -> 22.1 (55), 42106 40.6 (78) -> 40.4 (65); 10^4 nodes, 64 steps, window 10, 7050 walks 32.4 (104) -> 17.7 (60); weighted, window
 // 2, 37975 walks 35.9 (54) -> 31.9 (49).  With more of them the reads of the steps and the pairs written fill the memory, and
-// bursts of writes get in the way of the reads: 88301 walks, 2^24 pairs, 89.8 (124) and 101 (120); weighted 75950 walks 60.2 and 61.3.
-// (Between 2^23 and 2^24 pairs of few walks both were seen: 57 -> 51, and slower by a sixth.)
-constexpr uint64_t kFewWalks = 1u << 16, kFewPairs = 1u << 23;
+// the four threads gain nothing: 88301 walks, 2^24 pairs, 89.8 (124) and 101 (120); weighted 75950 walks 60.2 and 61.3.  Between 2^23
+// and 2^24 pairs of few walks the pools differ, by what is not known: 63158 walks of 40 steps, window 5, 59.9 (90) -> 59.4 (86), 28197 of
+// 64 steps, window 10, 61.7 (134) -> 61.0 (93), another 48.9 -> 57.3; so those keep the larger workgroups.
+// Walks of few pairs leave three of the four threads idle, which shows once the chip is full: window 1, 65535 walks of 5 steps 12.4 ->
+// 12.9 on 10^6 nodes, 2 to 5 % more on all graphs, of 2 steps 6.5 -> 6.8; 40000 walks gain or keep their time (5 steps 8.5 -> 8.3).  So
+// those are few up to 3 * 2^14 only.  With 8 to 11 pairs a walk, 55000 and more lose 2 to 4 % on 10^6 nodes and gain 3 to 7 % on 10^4;
+// with 15 and more none loses.
+constexpr uint64_t kFewWalks = 1u << 16, kFewShortWalks = 3u << 14, kShortWalk = 8, kFewPairs = 1u << 23;
 template <int kWalks, int kThreads>
 __global__ __launch_bounds__(kThreads) void k_augment(AugmentArgs a) {
     // a walk's nodes, one row per thread (65 words: the rows start in different banks)
@@ -2642,7 +2647,8 @@ hipError_t launch_departure_guide(const uint64_t *offsets, uint32_t n, uint64_t 
 hipError_t launch_augment(const AugmentArgs &a, hipStream_t stream) {
     if (a.walks == 0) return hipSuccess;
     if (a.length == 0 || a.length > (uint32_t)kMaxWalkLength || a.window == 0) return hipErrorInvalidValue;
-    const uint64_t of_block = a.walks < kFewWalks && a.count <= kFewPairs ? 64u : 128u, blocks = (a.walks + of_block - 1) / of_block;
+    const uint64_t few = a.count >= kShortWalk * a.walks ? kFewWalks : kFewShortWalks;
+    const uint64_t of_block = a.walks < few && a.count <= kFewPairs ? 64u : 128u, blocks = (a.walks + of_block - 1) / of_block;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (of_block == 64u)
         hipLaunchKernelGGL((k_augment<64, 256>), dim3((uint32_t)blocks), dim3(256), 0, stream, a);

@@ -1891,7 +1891,7 @@ def test_device_producer_at_its_edges(gv, graph, weighted, L, s, count, shuffle)
 
 @pytest.mark.parametrize("weighted", [False, True])
 @pytest.mark.parametrize("L,s,shuffle", [(2, 1, 1), (3, 5, 1), (9, 2, 0), (17, 4, 1)])
-@pytest.mark.parametrize("walks,short", [(63, 0), (64, 0), (65, 1), (65_535, 1), (65_536, 0), (65_536, 1), (65_537, 0), (65_665, 1)])
+@pytest.mark.parametrize("walks,short", [(63, 0), (64, 0), (65, 1), (49_151, 0), (49_152, 0), (49_153, 1), (65_535, 1), (65_536, 0), (65_536, 1), (65_537, 0), (65_665, 1)])
 def test_device_producer_by_number_of_walks(gv, tiny_graph, walks, short, L, s, shuffle, weighted):
     """The pools of the host producer, bit for bit, where the walks of a workgroup change and at the edges of a workgroup,
     the last walk whole or cut short by a pair."""
