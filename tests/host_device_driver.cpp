@@ -3,6 +3,7 @@
 // defined here (they take precedence over the runtime's), and so are the launches: each of them reads and writes what
 // its kernel would, so that AddressSanitizer sees an array that is too short, and checks what its kernel relies on.
 // One argument: the name of the check.  Exit code 0 = it passed.
+#include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -34,6 +35,7 @@ long device_allocations_left = -1;  // the same of hipMalloc
 uint64_t device_allocations = 0, device_frees = 0;
 long launches_left = -1;            // of kernels that use pinned memory, the same
 std::set<hipStream_t> using_pinned; // streams with such kernels that nothing has waited for
+uint32_t row_without_end = UINT32_MAX;  // node whose cosines are not finite
 size_t device_largest = SIZE_MAX;   // bytes that a hipMalloc may ask for
 size_t device_free = SIZE_MAX;      // bytes that hipMemGetInfo says are left
 }  // namespace
@@ -307,23 +309,27 @@ hipError_t launch_cosine(const float *, uint32_t n, uint32_t, const uint32_t *fi
                          float *out, uint32_t *error_flag, hipStream_t stream) {
     if (!launches(stream)) return hipErrorUnknown;
     for (uint32_t i = 0; i < count; ++i) {
-        out[i] = (float)first[i] - (float)second[i];
+        out[i] = first[i] == row_without_end || second[i] == row_without_end ? INFINITY : (float)first[i] - (float)second[i];
         if (first[i] >= n || second[i] >= n) *error_flag = 1u;
     }
     return hipGetLastError();
 }
 uint64_t rank_scratch_words(uint32_t num_neg) { return num_neg + num_neg / 2; }
-hipError_t launch_rank_sort(uint32_t *, uint32_t, uint32_t *, unsigned long long *not_finite, hipStream_t stream) {
+hipError_t launch_rank_sort(uint32_t *negatives, uint32_t num_neg, uint32_t *, unsigned long long *not_finite, hipStream_t stream) {
     if (!launches(stream)) return hipErrorUnknown;
     ranked_on_device = true;
-    memset(not_finite, 0, kRankBlocks * sizeof *not_finite);
+    for (uint32_t b = 0; b < kRankBlocks; ++b) CHECK(not_finite[b] == 0);  // the caller clears them
+    for (uint32_t j = 0; j < num_neg; ++j)
+        if (((const float *)negatives)[j] == INFINITY) not_finite[j % kRankBlocks] = 1ull;
     return hipGetLastError();
 }
-hipError_t launch_rank_sum(const uint32_t *scores, uint32_t num_pos, uint32_t num_neg, unsigned long long *twice, unsigned long long *,
-                           hipStream_t stream) {
+hipError_t launch_rank_sum(const uint32_t *scores, uint32_t num_pos, uint32_t num_neg, unsigned long long *twice,
+                           unsigned long long *not_finite, hipStream_t stream) {
     if (!launches(stream)) return hipErrorUnknown;
     memset(twice, 0, kRankBlocks * sizeof *twice);
     const float *positive = (const float *)scores, *negative = positive + num_pos;
+    for (uint32_t i = 0; i < num_pos; ++i)
+        if (positive[i] == INFINITY) not_finite[i % kRankBlocks] = 1ull;
     for (uint32_t i = 0; i < num_pos; ++i)
         for (uint32_t j = 0; j < num_neg; ++j) twice[0] += positive[i] > negative[j] ? 2u : positive[i] == negative[j] ? 1u : 0u;
     return hipGetLastError();
@@ -990,6 +996,19 @@ void ranking_where_it_can_be_done() {
                                               e.others, &got);
         device_largest = SIZE_MAX;
         CHECK(rc == GV_OK && got == wins / ((double)e.edges * e.others) && ranked_on_device == e.on_device);
+        // a row that is not finite among the edges, among the others: refused, and the next call is not
+        for (int set : {1, 3}) {
+            const uint32_t node = ends[set].back();
+            row_without_end = ends[set].back() = n - 1;
+            for (std::vector<uint32_t> &all : ends) std::replace(all.begin(), &all == &ends[set] ? all.end() - 1 : all.end(), n - 1, n - 2);
+            auto auc = [&] {
+                return gv_link_prediction_auc(ctx, ends[0].data(), ends[1].data(), e.edges, ends[2].data(), ends[3].data(), e.others, &got);
+            };
+            CHECK(auc() == GV_EINVAL && auc() == GV_EINVAL);
+            ends[set].back() = std::min(node, n - 2);
+            CHECK(auc() == GV_OK);
+        }
+        row_without_end = UINT32_MAX;
         gv_ctx *full = context(GV_MODE_HOGWILD, 1);
         float scores[1];
         CHECK(gv_set_degrees(full, n, degrees.data()) == GV_OK);

@@ -1365,6 +1365,30 @@ def test_sort_of_scores_by_number_of_workgroups(gv, others, shape):
         assert gv.gv_link_prediction_auc(ctx, a, b, c, e) == expected
 
 
+@pytest.mark.parametrize("edges,others", [(1000, 1000), (5000, 5000), (3, 5000), (300_000, 5000), (10_000, 300_000)])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_link_prediction_of_rows_that_are_not_finite(gv, edges, others, value):
+    """One pair that names a row that is not finite, among the edges and among the others: refused, twice, and the next call
+    without it gives the rank statistic; ranked on the host, and on the device with and without a launch for the places."""
+    n, d = 600, 64
+    rng = np.random.default_rng(edges + others)
+    vertex = rng.standard_normal((n, d)).astype(np.float32)
+    vertex[n - 1, 7] = value
+    with context_for(gv, dim=d, num_neg=1, total_samples=1000, pool_capacity=8) as ctx:
+        gv.gv_set_degrees(ctx, np.ones(n, dtype=np.uint32))
+        gv.gv_set_embeddings(ctx, gv.GV_VERTEX, vertex)
+        ends = [rng.integers(n - 1, size=k).astype(np.uint32) for k in (edges, edges, others, others)]
+        expected = gv.gv_auc(gv.gv_cosine(ctx, *ends[:2]), gv.gv_cosine(ctx, *ends[2:]))
+        for which, at in ((0, 0), (1, -1), (2, -1), (3, len(ends[3]) // 2)):
+            bad = [e.copy() for e in ends]
+            bad[which][at] = n - 1
+            for _ in range(2):
+                with pytest.raises(gv.GvError, match="not finite") as e:
+                    gv.gv_link_prediction_auc(ctx, *bad)
+                assert e.value.code == gv.GV_EINVAL
+            assert gv.gv_link_prediction_auc(ctx, *ends) == expected
+
+
 @pytest.mark.parametrize("edges,others", [((1 << 17) + 1, 1 << 17), (1 << 17, 5 * (1 << 17) + 3), (5 * (1 << 17) - 1, 20_000), (90_000, 40_000)])
 @pytest.mark.parametrize("d", [32, 128, 256, 480])
 def test_link_prediction_of_many_pieces(gv, edges, others, d):
