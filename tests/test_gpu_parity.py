@@ -1366,7 +1366,7 @@ def test_sort_of_scores_by_number_of_workgroups(gv, others, shape):
 
 
 @pytest.mark.parametrize("edges,others", [(1000, 1000), (5000, 5000), (3, 5000), (300_000, 5000), (10_000, 300_000)])
-@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
 def test_link_prediction_of_rows_that_are_not_finite(gv, edges, others, value):
     """One pair that names a row that is not finite, among the edges and among the others: refused, twice, and the next call
     without it gives the rank statistic; ranked on the host, and on the device with and without a launch for the places."""
@@ -1914,8 +1914,9 @@ def test_device_producer_at_its_edges(gv, graph, weighted, L, s, count, shuffle)
 
 
 @pytest.mark.parametrize("weighted", [False, True])
-@pytest.mark.parametrize("L,s,shuffle", [(2, 1, 1), (3, 5, 1), (9, 2, 0), (17, 4, 1)])
-@pytest.mark.parametrize("walks,short", [(63, 0), (64, 0), (65, 1), (49_151, 0), (49_152, 0), (49_153, 1), (65_535, 1), (65_536, 0), (65_536, 1), (65_537, 0), (65_665, 1)])
+@pytest.mark.parametrize("L,s,shuffle", [(2, 1, 1), (3, 5, 1), (8, 1, 1), (9, 2, 0), (17, 4, 1)])
+@pytest.mark.parametrize("walks,short", [(63, 0), (64, 0), (65, 1), (49_151, 0), (49_152, 0), (49_153, 1), (65_535, 1), (65_536, 0),
+                                         (65_536, 1), (65_537, 0), (65_665, 1)])
 def test_device_producer_by_number_of_walks(gv, tiny_graph, walks, short, L, s, shuffle, weighted):
     """The pools of the host producer, bit for bit, where the walks of a workgroup change and at the edges of a workgroup,
     the last walk whole or cut short by a pair."""
@@ -1927,13 +1928,50 @@ def test_device_producer_by_number_of_walks(gv, tiny_graph, walks, short, L, s, 
     with context_for(gv, dim=32, num_neg=1, total_samples=1000, pool_capacity=8) as ctx:
         kw = dict(seed=12, walk_length=L, window=s, first_walk=99, count=count, shuffle=shuffle)
         if weighted:
-            weights = np.ones(g["adj"].size, dtype=np.float32)
+            weights = W.csr_edge_weights(g["src"], g["dst"], seed=4)
             gv.gv_set_weighted_graph(ctx, g["offsets"], g["adj"], weights)
             ref, used = gv.gv_augment_weighted(g["offsets"], g["adj"], gv.gv_build_walk_tables(g["offsets"], weights)[1:], **kw)
         else:
             gv.gv_set_degrees(ctx, g["deg"])
             gv.gv_set_adjacency(ctx, g["offsets"], g["adj"])
             ref, used = gv.gv_augment(g["offsets"], g["adj"], **kw)
+        assert gv.gv_augment_device(ctx, out.data_ptr(), **kw) == used == walks
+        gv.gv_sync(ctx)
+        got = out.cpu().numpy().view(np.uint32)
+    assert np.array_equal(got[:count], ref)
+    assert (got[count:] == 0xFFFFFFFF).all()
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("graph", ["sixteen nodes", "hub"])
+@pytest.mark.parametrize("L,s,walks,shuffle", [(64, 64, 4033, 1), (64, 64, 4034, 0), (64, 70, 4034, 1), (64, 3, 65_600, 1),
+                                               (40, 1, 65_601, 0), (5, 9, 65_536, 1)])
+def test_device_producer_of_long_walks_by_size(gv, graph, L, s, walks, shuffle, weighted):
+    """The pools of the host producer, bit for bit, on either side of 2^23 pairs (2080 of each walk of 64 steps) and from 2^16 walks
+    on: the longest walks, windows beyond the walk, a graph too small for a guide and one with a hub, uneven weights."""
+    import torch
+
+    rng = np.random.default_rng(6)
+    if graph == "sixteen nodes":
+        n, src, dst = 16, np.array([3, 3, 3, 5, 7, 7, 13]), np.array([5, 7, 13, 13, 5, 12, 12])
+    else:
+        n = 5000
+        src = np.concatenate([np.zeros(3000, dtype=np.int64), rng.integers(n, size=12_000)])
+        dst = np.concatenate([np.arange(1, 3001), (src[3000:] + 1 + rng.integers(n - 1, size=12_000)) % n])
+    src, dst = src.astype(np.uint32), dst.astype(np.uint32)
+    offsets, adj = W.csr_from_edges(n, src, dst)
+    count = walks * sum(L + 1 - d for d in range(1, min(s, L) + 1))
+    out = torch.full((count + 3, 2), -1, dtype=torch.int32, device="cuda")
+    with context_for(gv, dim=32, num_neg=1, total_samples=1000, pool_capacity=8) as ctx:
+        kw = dict(seed=13, walk_length=L, window=s, first_walk=7, count=count, shuffle=shuffle)
+        if weighted:
+            weights = W.csr_edge_weights(src, dst, seed=4)
+            gv.gv_set_weighted_graph(ctx, offsets, adj, weights)
+            ref, used = gv.gv_augment_weighted(offsets, adj, gv.gv_build_walk_tables(offsets, weights)[1:], **kw)
+        else:
+            gv.gv_set_degrees(ctx, W.degrees(n, src, dst))
+            gv.gv_set_adjacency(ctx, offsets, adj)
+            ref, used = gv.gv_augment(offsets, adj, **kw)
         assert gv.gv_augment_device(ctx, out.data_ptr(), **kw) == used == walks
         gv.gv_sync(ctx)
         got = out.cpu().numpy().view(np.uint32)
