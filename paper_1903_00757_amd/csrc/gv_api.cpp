@@ -44,15 +44,20 @@ constexpr uint64_t kStageWords = 16384, kDeterministicPart = 1u << 20;  // see t
 // Deterministic pools of more samples than this wait for each other on the device (train_flow) instead of being sorted into
 // levels on the host: call and gv_sync, d = 128, K = 1, 10000 samples on 200000 nodes 116 instead of 144 us, 5000 on 5000 nodes 106
 // instead of 133, 5000 on 200000 nodes 99 instead of 104, and fewer are levelled before the preparation's dozen launches are
-// done.  Not where levels are narrow: a level of a few samples costs 0.8 to 1 us in one workgroup, a link of a chain 1.3, and 1.9
-// from wave to wave.  That is so where the graph's hottest row is
-// named by more than one sample in 24 (d = 128, K = 1, a pass alone: hottest share 2.1 % 9.1 -> 4.0 ms, 3.6 % 2.29 -> 1.78,
-// 4.6 % 0.93 -> 0.95; K = 5, 7.5 % 8.0 -> 10.6; a star 7.8 -> 12.4), and in pools that put samples of a row close together
-// whatever the graph, such as walks in their own order: those are known by the levels of the samples that launch_flow_check
-// looks at (narrow_levels), fewer than 16 samples a level on average.  60000 samples, levels -> waiting on the device, ms, by
-// samples a level of those looked at: K = 1, d = 128: 3.6 12.6 -> 31.4, 8.9 6.7 -> 12.1, 15.5 5.1 -> 5.9, 17.4 4.9 -> 4.7, 30 4.3
-// -> 3.0, 89 2.0 -> 0.84; K = 5, d = 128: 2.9 27 -> 60, 12 11.4 -> 10.3, 27 9.7 -> 4.8; d = 512: 3.3 36 -> 49, 12 24 -> 14; K = 3:
-// 5.4 13.3 -> 20, 23.8 6.9 -> 4.4.  The same samples in the producer's shuffled order have 40 to 200 a level.
+// done.  Not where levels are narrow: a level of a few samples costs 0.8 to 1 us in one workgroup, a link of a chain 0.5 to 1.1, and
+// 1.5 to 2.3 from wave to wave.  That is so where the graph's hottest row is named by more than one sample in 24, and in pools that put
+// samples of a row close together whatever the graph, such as walks in their own order: those are known by the levels of the samples
+// that launch_flow_check looks at (narrow_levels), fewer than 16 samples a level on average.  Both lines were drawn with links of
+// 0.9 us (K = 1) to 1.8 (K = 5, d = 256); as things are, levels -> waiting on the device, ms, a pass alone:
+// by the hottest row's share, 50000 pairs drawn by degree on 10^4 nodes: K = 1, d = 128: 2 % 2.95 -> 0.91, 4.2 % 3.87 -> 2.00, 8 % 4.74 ->
+// 4.23, 12 % 5.93 -> 7.06; K = 5, d = 128: 4.2 % 8.5 -> 4.3, 8 % 10.3 -> 8.0, 12 % 12.3 -> 12.2, 20 % 16.2 -> 21.8; d = 256: 8 % 11.3 -> 9.7, 12 %
+// 13.6 -> 14.4 (so the first line lies on the safe side, by a factor of two);
+// by samples a level, 30000 pairs on graphs without hubs: K = 1, d = 128: 16.6 2.3 -> 4.3, 27 2.0 -> 2.6, 41 2.1 -> 1.7, 60 1.5 -> 1.2; K = 3:
+// 18 3.6 -> 4.4, 27 3.3 -> 3.3; K = 5: 13.5 6.0 -> 8.0, 18 5.4 -> 5.8, 27 5.0 -> 4.0; d = 256: 18 5.6 -> 6.5, 27 5.3 -> 4.5;
+// the same of 60000 samples of walks in their own order on graphs with hubs, with the longer links: K = 1: 3.6 12.6 -> 31.4, 8.9 6.7 ->
+// 12.1, 15.5 5.1 -> 5.9, 17.4 4.9 -> 4.7, 30 4.3 -> 3.0; K = 5: 2.9 27 -> 60, 12 11.4 -> 10.3, 27 9.7 -> 4.8 (so where hubs make the levels the
+// second line lies about right, and graphs of some hundred equal nodes lie on the wrong side of it up to 20 to 40 samples a level).
+// The same samples in the producer's shuffled order have 40 to 200 a level.
 constexpr uint64_t kFlowFrom = 4096;
 constexpr double kFlowShare = 1.0 / 24.0;
 constexpr uint32_t kFlowWidth = 16, kMostRows = 5 + 2;  // of a sample: num_neg <= 5

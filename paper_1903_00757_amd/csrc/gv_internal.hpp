@@ -39,7 +39,7 @@ struct FlowState {
 // How long a wave of k_train_flow waits for a turn: until nothing of the pool has got on for 2^22 looks at the turns, half a
 // second or more.  What has got on is read every 2^16 looks: samples taken (next_chunk) and namings of the hubs done (chained),
 // of which one moves before 10^4 links of a chain are done one after the other, 50 ms at most.  The whole wait may be
-// longer by any factor: waves run ahead of the hubs' samples, whose chain can be most of a part, 2^20 links of 0.7 us and more.
+// longer by any factor: waves run ahead of the hubs' samples, whose chain can be most of a part, 2^20 links of 0.5 us and more.
 struct FlowPatience {
     static constexpr uint32_t kLooks = 1u << 16, kIdle = 64;
     uint32_t looks = 0, idle = 0, before = 0;

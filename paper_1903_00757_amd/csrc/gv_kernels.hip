@@ -1007,15 +1007,16 @@ struct HandedRow {
 //
 // What bounds it is the chain of samples that share the hottest rows, each link the latency of one wave.  A row goes from
 // one wave to another in 1.0 us (store, wait, turn, poll, load; the same within a die and across dies), with the
-// arithmetic and the polling 1.9 us a sample.  So each of the kFlowHubs rows named most has a wave of its own, which trains
-// the samples that name it one after the other with the row in registers: 0.75 us a sample, most of it the loads of the next
-// sample's other rows, which the arithmetic hides in part (flow_hub; 1.07 us with loops for every kind of sample instead of
-// one for the plain ones).  What is left is the way from wave to wave.  2*10^5 samples on 10^4 nodes, 1190 levels, d = 128, K = 1:
-// 4.1 ms as launches of levels, 2.0 without chains, 1.58 now (three contexts in turn: 3.4, 0.87, 0.65 ms a pool);
-// 1.5*10^5 on 10^5 nodes, exponent 2.5: 1.14 ms with the slower chains, 0.88 now; 5*10^4 on 3*10^4, exponent 2.3, d = 96, K = 3:
-// 1.86 and 1.64.  1024 waves of 8 samples: 16 or more samples a wave wait for each other in the wave,
-// and twice as many waves only poll more (3.4 ms with 1024 waves of 64, 6.2 with 2048, before samples far from their turn were
-// left alone).
+// arithmetic 1.5 us a sample (K = 5: 2.3; a chain of 8000, one in eight samples of its pool), about 1.9 with a whole pool polling.  So
+// each of the kFlowHubs rows named most has a wave of its own, which trains the samples that name it one after the other with the row
+// in registers: a link of such a chain takes 0.52 us at d = 128, K = 1 where nothing else is waited for, 0.87 at K = 5 (flow_hub).
+// 2*10^5 samples on 10^4 nodes, d = 128, K = 1: 4.1 ms as launches of levels, 2.0 without chains, 1.59 now (three contexts in turn: 3.4,
+// 0.87, 0.63 ms a pool), this kernel 1.44 of it.  Its longest path, counted with links of 0.52 us in a chain and 1.5 to 1.9 from wave
+// to wave, is 1.2 to 1.47 ms: some 750 links through rows that have no wave of their own, 80 in a chain, 3 that hand a hub's row on.
+// 1.5*10^5 pairs drawn by degree on 10^5 nodes, exponent 2.5: 1.43 ms; 5*10^4 on 10^4 nodes, the hottest row in 4 % of them, 1.95, and
+// 5.03 at d = 256, K = 5 (2.57 and 6.48 with the slower chains that are named at flow_hub).
+// 1024 waves of 8 samples: 16 or more samples a wave wait for each other in the wave, and twice as many waves only poll more (3.4 ms
+// with 1024 waves of 64, 6.2 with 2048, before samples far from their turn were left alone).
 //
 // Every wait ends: the waves of the hubs are those of one workgroup, the first that runs, together with one that takes
 // samples as all others do; samples are taken in pool order, so the first sample of the pool that is not done is at
@@ -1220,10 +1221,13 @@ struct FlowRows {
 
 // The chain of hub h: its samples, except those that name a hub before it (the row is handed to the wave of that hub and
 // awaited back).  The row stays in registers y; the other rows of the next sample are on their way while one is computed,
-// and its stores are waited for after the next one's arithmetic.  What a link takes are the instructions of one wave (one every
-// five cycles or so, a branch more), so the samples that name the hub once and their other rows once, nearly all of them, have
-// a loop without branches on the rows, with the addresses that it needs worked out by the lanes, 64 samples at once: 2420 -> 1700
-// cycles a link at d = 128, K = 1.  false: gave up.
+// and its stores are waited for after the next one's arithmetic.  What a link takes are the loads of the next sample's other rows
+// and the instructions of one wave beside them (one every five cycles or so, a branch more), so the samples that name the hub once
+// and their other rows once have a loop without branches on the rows, with the addresses of the rows worked out by the lanes, 64
+// samples at once.  A link, in pools of 4*10^4 samples that all name one row and no other twice: d = 128, K = 1 0.90 us with one loop
+// for every kind of sample, 0.52 now; d = 96, K = 3 1.14 and 0.71; d = 128, K = 5 1.44 and 0.87; d = 256, K = 5 1.80 and 1.08.  The other
+// samples wait for their rows: 0.1 to 0.4 % of those that name a hub at K = 1, 1 to 2 % at K = 5, in pools that take this way.
+// false: gave up.
 template <int kV, int kK, bool kFull, bool kTrack>
 __device__ __forceinline__ bool flow_hub(const FlowArgs &a, const FlowHubs &hubs, uint32_t h, int lane, uint32_t &deepest,
                                          float &lane_loss) {
